@@ -44,7 +44,8 @@ constexpr int GROUP_M = 4;
 // workgroup covers 128 ffn columns and the epilogue applies SiLU(gate) * up in registers).
 // TEPI: 0 stores the fp32 product, 1 is the SwiGLU epilogue, 2 the q/k/v epilogue (the product never reaches memory:
 // bias, per-head RMSNorm of q and k, RoPE, q stored as half, k and v appended to the sequence's page; head_dim 128,
-// so a wave's 128 columns are exactly one head).
+// so a wave's 128 columns are exactly one head), 3 the scoring epilogue (per row the maximum and the sum of
+// exponentials over the tile's 256 columns, and the target column's product; no product reaches memory).
 template <int TEPI>
 __global__ __launch_bounds__(256) void gemm_tile_kernel(GemmArgs g, QkvPostArgs qa) {
     constexpr bool SWIGLU = TEPI == 1;
@@ -289,6 +290,46 @@ __global__ __launch_bounds__(256) void gemm_tile_kernel(GemmArgs g, QkvPostArgs 
             }
         }
         report_saturation(qa.sat_count, bad);
+    } else if (TEPI == 3) {
+        // A lane holds 64 of the 128 columns of four rows: it folds them to one (max, sum exp) pair, the lane halves
+        // and then the two column waves merge theirs, one pair per (row, tile) is written.  The exponentials (256 a lane)
+        // are 5 % of the tile's matrix time at K = 2560.  Bound by the matrix cores: 6,028 rows x 151,936 columns x 2560 take
+        // 4.4 ms (1.09 PFLOP/s); the streaming kernel with 128-row tiles, which fetches twice the bytes per product from L2
+        // and reads twice the LDS per MFMA, took 6.5.
+        float2* s_pair = (float2*)lds;                  // [2 column waves][256 rows]
+        const int c0 = n0 + wn * 128 + 4 * lh;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int row = wm * 128 + i * 32 + l32, m = m0 + row;
+            const int tgt = m < g.M ? g.targets[m] : -1;
+            float mx = -INFINITY;
+#pragma unroll
+            for (int j = 0; j < J; ++j)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const int col = c0 + 32 * j + 8 * (r >> 2) + (r & 3);
+                    if (col >= g.N) acc[j][i][r] = -INFINITY;         // padding of the last tile (clamped weight rows)
+                    if (col == tgt) g.tgt_logit[m] = acc[j][i][r];
+                    mx = fmaxf(mx, acc[j][i][r]);
+                }
+            mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+            const float ref = mx > -INFINITY ? mx : 0.f;              // a wave of padding columns: all terms are exp(-inf)
+            float sum = 0.f;
+#pragma unroll
+            for (int j = 0; j < J; ++j)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) sum += __expf(acc[j][i][r] - ref);
+            sum += __shfl_xor(sum, 32, 64);
+            if (lh == 0) s_pair[wn * 256 + row] = make_float2(mx, sum);
+        }
+        __syncthreads();
+        const int m = m0 + (int)threadIdx.x;
+        if (m < g.M) {
+            const float2 a = s_pair[threadIdx.x], b = s_pair[256 + threadIdx.x];
+            const float M = fmaxf(a.x, b.x);
+            const float S = (a.x > -INFINITY ? a.y * __expf(a.x - M) : 0.f) + (b.x > -INFINITY ? b.y * __expf(b.x - M) : 0.f);
+            g.s_part[(size_t)tile_n * g.M + m] = make_float2(M, S);
+        }
     } else if (!SWIGLU) {
         float* out = (float*)g.out;
         constexpr int TROW = 128 * 4 + 16;              // staged row: 128 floats + pad
@@ -369,6 +410,14 @@ hipError_t launch_gemm_tile(const GemmArgs& a, int epilogue, hipStream_t s) {
     if (!gemm_tile_usable(a) || (epilogue == EPI_SWIGLU && (a.N & 7))) return hipErrorInvalidValue;
     const QkvPostArgs none = {};
     return epilogue == EPI_SWIGLU ? launch_tile<1>(a, none, s) : launch_tile<0>(a, none, s);
+}
+
+// The LM head with the scoring epilogue: one (max, sum exp) pair per row and 256-column tile.
+int gemm_tile_score_tiles(int N) { return (N + BN - 1) / BN; }
+hipError_t launch_gemm_tile_score(const GemmArgs& a, hipStream_t s) {
+    if (!gemm_tile_usable(a) || !a.s_part || !a.targets || !a.tgt_logit || a.s_tiles != gemm_tile_score_tiles(a.N)) return hipErrorInvalidValue;
+    const QkvPostArgs none = {};
+    return launch_tile<3>(a, none, s);
 }
 
 // The q/k/v projection with the work of qkv_post_kernel in its epilogue (qa.qkv and qa.n_part are not used).

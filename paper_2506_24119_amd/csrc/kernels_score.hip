@@ -1,7 +1,10 @@
 // Learner-side scoring: log pi(target | context) for every row of a packed batch, without ever
 // writing the [rows, vocab] logits.
 //
-// score_lmhead_kernel is the LM-head GEMM of the decode path (32x32x16 MFMA, weights HBM/L2 ->
+// With fragment-ordered weights the LM head is the 256 x 256 tiled kernel with a scoring epilogue (gemm_tile_kernel<3>),
+// which leaves one (max, sum of exp) pair per row and tile for score_merge_tiles_kernel.
+//
+// Without them: score_lmhead_kernel is the LM-head GEMM of the decode path (32x32x16 MFMA, weights HBM/L2 ->
 // registers in operand layout, activations through LDS) with another epilogue: a workgroup owns 128
 // rows and a range of 128-column vocabulary tiles; after each tile every lane folds its 16 logits of
 // each row into a private running (max, sum of exp) pair and checks whether the row's target column
@@ -29,7 +32,6 @@ constexpr int PD = 2;
 
 }  // namespace
 
-template <bool FRAG>
 __global__ __launch_bounds__(256) void score_lmhead_kernel(ScoreArgs g) {
     extern __shared__ uint4 lds_raw[];
     char* lds = (char*)lds_raw;
@@ -71,8 +73,7 @@ __global__ __launch_bounds__(256) void score_lmhead_kernel(ScoreArgs g) {
     for (int nt = nt_begin; nt < nt_end; ++nt) {
         const int n_first = nt * 128 + wave * 32;
         int n = n_first + l32; if (n >= g.V) n = g.V - 1;
-        const uint16_t* wrow = FRAG ? (const uint16_t*)g.Wf + frag_block(min(nt * 4 + wave, (g.V + 31) / 32 - 1), 0, K) + lane * 8
-                                    : (const uint16_t*)g.W + (size_t)n * K + lh * 8;
+        const uint16_t* wrow = (const uint16_t*)g.W + (size_t)n * K + lh * 8;
 
         f32x16 acc[4];
 #pragma unroll
@@ -87,8 +88,7 @@ __global__ __launch_bounds__(256) void score_lmhead_kernel(ScoreArgs g) {
 #pragma unroll
             for (int i = 0; i < 8; ++i) S.a[i] = *(const u32x4*)(a_src[i] + off);
 #pragma unroll
-            for (int ks = 0; ks < 8; ++ks)
-                S.w[ks] = FRAG ? *(const u32x4*)(wrow + ((size_t)cc * 8 + ks) * 512) : *(const u32x4*)(wrow + off + ks * 16);
+            for (int ks = 0; ks < 8; ++ks) S.w[ks] = *(const u32x4*)(wrow + off + ks * 16);
         };
         auto iter = [&](St& S, int c) {
             char* buf = lds + (c & 1) * BUF;
@@ -105,7 +105,7 @@ __global__ __launch_bounds__(256) void score_lmhead_kernel(ScoreArgs g) {
                     for (int t = 0; t < 4; ++t)
                         af[(ks + 1) & 1][t] = *(const u32x4*)(buf + frag_off + t * 32 * ROWB + (ks + 1) * 32);
                 }
-                const u32x4 wp = FRAG ? S.w[ks] : prep_w(S.w[ks]);      // fragment-ordered copies are already widened
+                const u32x4 wp = prep_w(S.w[ks]);
 #pragma unroll
                 for (int t = 0; t < 4; ++t) acc[t] = mma32s(wp, af[ks & 1][t], acc[t]);
             }
@@ -189,6 +189,49 @@ __global__ __launch_bounds__(256) void score_merge_kernel(ScoreArgs g, float* ou
     out[m] = g.tgt_logit[m] - (M + logf(S));
 }
 
+// The same merge for the pairs of the tiled LM head, [s_tiles][M]: 32 rows a workgroup, eight threads to a row, so that
+// a load instruction reads two 256-byte runs (6000 rows x 594 tiles, 28 MB: one thread to a row takes 41 us).
+__global__ __launch_bounds__(256) void score_merge_tiles_kernel(GemmArgs g, float* out) {
+    __shared__ float2 s_pair[8][32];
+    const int r = threadIdx.x & 31, q = threadIdx.x >> 5;
+    const int m = blockIdx.x * 32 + r;
+    const int mc = m < g.M ? m : g.M - 1;
+    float M = -INFINITY, S = 0.f;
+    for (int t0 = q; t0 < g.s_tiles; t0 += 8 * 8) {              // eight loads in flight; past the end: the last pair, weight 0
+        float2 p[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) p[u] = g.s_part[(size_t)min(t0 + 8 * u, g.s_tiles - 1) * g.M + mc];
+        float mx = M;
+#pragma unroll
+        for (int u = 0; u < 8; ++u) mx = fmaxf(mx, p[u].x);
+        if (mx > -INFINITY) {
+            float sum = M > -INFINITY ? S * expf(M - mx) : 0.f;
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                if (t0 + 8 * u < g.s_tiles && p[u].x > -INFINITY) sum += p[u].y * expf(p[u].x - mx);
+            S = sum;
+            M = mx;
+        }
+    }
+    s_pair[q][r] = make_float2(M, S);
+    __syncthreads();
+    if (q != 0 || m >= g.M) return;
+    if (g.targets[m] < 0) { out[m] = 0.f; return; }
+    M = -INFINITY;
+#pragma unroll
+    for (int u = 0; u < 8; ++u) M = fmaxf(M, s_pair[u][r].x);
+    S = 0.f;
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+        if (s_pair[u][r].x > -INFINITY) S += s_pair[u][r].y * expf(s_pair[u][r].x - M);
+    out[m] = g.tgt_logit[m] - (M + logf(S));
+}
+
+hipError_t launch_score_merge_tiles(const GemmArgs& a, float* out, hipStream_t s) {
+    hipLaunchKernelGGL(score_merge_tiles_kernel, dim3((a.M + 31) / 32), dim3(256), 0, s, a, out);
+    return hipGetLastError();
+}
+
 // out[0] = sum mask * min(r * A, clip(r, 1 - eps, 1 + eps) * A), r = exp(new - old);  out[1] = sum mask * A * new
 __global__ __launch_bounds__(1024) void score_objective_kernel(const float* logp_new, const float* logp_old, const float* adv,
                                                                const int32_t* mask, long long n, float eps, double* out) {
@@ -215,8 +258,7 @@ hipError_t launch_score(const ScoreArgs& a, float* out, hipStream_t s) {
     if (a.M < 1 || a.V < 1 || (a.K & 127) || a.n_splits < 1 || a.tiles_per_split < 1) return hipErrorInvalidValue;
     ScoreArgs g = a;
     g.m_tiles = (a.M + 127) / 128;
-    if (g.Wf) hipLaunchKernelGGL(score_lmhead_kernel<true>, dim3(g.m_tiles * g.n_splits), dim3(256), (size_t)2 * BUF, s, g);
-    else hipLaunchKernelGGL(score_lmhead_kernel<false>, dim3(g.m_tiles * g.n_splits), dim3(256), (size_t)2 * BUF, s, g);
+    hipLaunchKernelGGL(score_lmhead_kernel, dim3(g.m_tiles * g.n_splits), dim3(256), (size_t)2 * BUF, s, g);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(score_merge_kernel, dim3((a.M + 255) / 256), dim3(256), 0, s, g, out);

@@ -52,6 +52,9 @@ struct GemmArgs {
     float2* s_part;
     float s_temperature;
     int32_t s_tiles;
+    // scoring: target column of each row (< 0: none) and where its product goes; (max, sum exp) pairs to s_part [s_tiles][M]
+    const int32_t* targets;
+    float* tgt_logit;
     int32_t* sat_count;   // or null: incremented when an activation left the half-precision range (SwiGLU output)
 };
 
@@ -148,13 +151,15 @@ hipError_t launch_repack(const void* src0, const void* src1, const void* src2, i
 struct ScoreArgs {
     const void* A;            // act [M][K]: final-normed hidden states
     const void* W;            // bf16 [V][K] LM head
-    const void* Wf;           // or null: the LM head in fragment order
     const int32_t* targets;   // [M] target token of each row, < 0: none
     float* part;              // [M][n_splits] (max, sum exp) pairs
     float* tgt_logit;         // [M]
     int32_t M, V, K, n_splits, tiles_per_split, m_tiles;
 };
 hipError_t launch_score(const ScoreArgs& a, float* out, hipStream_t s);
+hipError_t launch_gemm_tile_score(const GemmArgs& a, hipStream_t s);      // a.s_part: [gemm_tile_score_tiles(N)][M] pairs
+int gemm_tile_score_tiles(int N);
+hipError_t launch_score_merge_tiles(const GemmArgs& a, float* out, hipStream_t s);
 hipError_t launch_score_objective(const float* logp_new, const float* logp_old, const float* adv, const int32_t* mask,
                                   long long n, float eps, double* out, hipStream_t s);
 hipError_t launch_sample_truncated(const float* logits, int B, int V, float temperature, int top_k, float top_p,
