@@ -45,7 +45,7 @@ constexpr int GROUP_M = 4;
 // TEPI: 0 stores the fp32 product, 1 is the SwiGLU epilogue, 2 the q/k/v epilogue (the product never reaches memory:
 // bias, per-head RMSNorm of q and k, RoPE, q stored as half, k and v appended to the sequence's page; head_dim 128,
 // so a wave's 128 columns are exactly one head), 3 the scoring epilogue (per row the maximum and the sum of
-// exponentials over the tile's 256 columns, and the target column's product; no product reaches memory).
+// exponentials over each 128 columns, and the target column's product; no product reaches memory).
 template <int TEPI>
 __global__ __launch_bounds__(256) void gemm_tile_kernel(GemmArgs g, QkvPostArgs qa) {
     constexpr bool SWIGLU = TEPI == 1;
@@ -291,16 +291,16 @@ __global__ __launch_bounds__(256) void gemm_tile_kernel(GemmArgs g, QkvPostArgs 
         }
         report_saturation(qa.sat_count, bad);
     } else if (TEPI == 3) {
-        // A lane holds 64 of the 128 columns of four rows: it folds them to one (max, sum exp) pair, the lane halves
-        // and then the two column waves merge theirs, one pair per (row, tile) is written.  The exponentials (256 a lane)
-        // are 5 % of the tile's matrix time at K = 2560.  Bound by the matrix cores: 6,028 rows x 151,936 columns x 2560 take
-        // 4.4 ms (1.09 PFLOP/s); the streaming kernel with 128-row tiles, which fetches twice the bytes per product from L2
-        // and reads twice the LDS per MFMA, took 6.5.
-        float2* s_pair = (float2*)lds;                  // [2 column waves][256 rows]
-        const int c0 = n0 + wn * 128 + 4 * lh;
+        // A lane holds 64 of the 128 columns of four rows: it folds them, column tile by column tile, and the lane halves
+        // merge theirs: one (max, sum exp) pair per row and 128 columns.  The streaming kernel folds in the same order, so
+        // that repacked and row-major weights give the same bits.  The exponentials (256 a lane) are 5 % of the tile's
+        // matrix time at K = 2560.  Bound by the matrix cores: 6,028 rows x 151,936 columns x 2560 take 4.4 ms
+        // (1.09 PFLOP/s); the streaming kernel with 128-row tiles, which fetches twice the bytes per product from L2 and
+        // reads twice the LDS per MFMA, took 6.5.
+        const int c0 = n0 + wn * 128 + 4 * lh, pair = tile_n * 2 + wn;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            const int row = wm * 128 + i * 32 + l32, m = m0 + row;
+            const int m = m0 + wm * 128 + i * 32 + l32;
             const int tgt = m < g.M ? g.targets[m] : -1;
             float mx = -INFINITY;
 #pragma unroll
@@ -313,22 +313,17 @@ __global__ __launch_bounds__(256) void gemm_tile_kernel(GemmArgs g, QkvPostArgs 
                     mx = fmaxf(mx, acc[j][i][r]);
                 }
             mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-            const float ref = mx > -INFINITY ? mx : 0.f;              // a wave of padding columns: all terms are exp(-inf)
+            const float ref = mx > -INFINITY ? mx : 0.f;              // nothing but -inf: all terms are zero
             float sum = 0.f;
 #pragma unroll
-            for (int j = 0; j < J; ++j)
+            for (int j = 0; j < J; ++j) {
+                float sj = 0.f;
 #pragma unroll
-                for (int r = 0; r < 16; ++r) sum += __expf(acc[j][i][r] - ref);
+                for (int r = 0; r < 16; ++r) sj += __expf(acc[j][i][r] - ref);
+                sum = j == 0 ? sj : sum + sj;
+            }
             sum += __shfl_xor(sum, 32, 64);
-            if (lh == 0) s_pair[wn * 256 + row] = make_float2(mx, sum);
-        }
-        __syncthreads();
-        const int m = m0 + (int)threadIdx.x;
-        if (m < g.M) {
-            const float2 a = s_pair[threadIdx.x], b = s_pair[256 + threadIdx.x];
-            const float M = fmaxf(a.x, b.x);
-            const float S = (a.x > -INFINITY ? a.y * __expf(a.x - M) : 0.f) + (b.x > -INFINITY ? b.y * __expf(b.x - M) : 0.f);
-            g.s_part[(size_t)tile_n * g.M + m] = make_float2(M, S);
+            if (lh == 0 && m < g.M && pair < g.s_tiles) g.s_part[(size_t)pair * g.M + m] = make_float2(mx, sum);
         }
     } else if (!SWIGLU) {
         float* out = (float*)g.out;
@@ -412,10 +407,9 @@ hipError_t launch_gemm_tile(const GemmArgs& a, int epilogue, hipStream_t s) {
     return epilogue == EPI_SWIGLU ? launch_tile<1>(a, none, s) : launch_tile<0>(a, none, s);
 }
 
-// The LM head with the scoring epilogue: one (max, sum exp) pair per row and 256-column tile.
-int gemm_tile_score_tiles(int N) { return (N + BN - 1) / BN; }
+// The LM head with the scoring epilogue: one (max, sum exp) pair per row and 128 columns.
 hipError_t launch_gemm_tile_score(const GemmArgs& a, hipStream_t s) {
-    if (!gemm_tile_usable(a) || !a.s_part || !a.targets || !a.tgt_logit || a.s_tiles != gemm_tile_score_tiles(a.N)) return hipErrorInvalidValue;
+    if (!gemm_tile_usable(a) || !a.s_part || !a.targets || !a.tgt_logit || a.s_tiles != (a.N + 127) / 128) return hipErrorInvalidValue;
     const QkvPostArgs none = {};
     return launch_tile<3>(a, none, s);
 }

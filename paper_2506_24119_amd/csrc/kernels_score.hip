@@ -2,14 +2,15 @@
 // writing the [rows, vocab] logits.
 //
 // With fragment-ordered weights the LM head is the 256 x 256 tiled kernel with a scoring epilogue (gemm_tile_kernel<3>),
-// which leaves one (max, sum of exp) pair per row and tile for score_merge_tiles_kernel.
+// which leaves one (max, sum of exp) pair per row and 128 columns for score_merge_pairs_kernel.
 //
 // Without them: score_lmhead_kernel is the LM-head GEMM of the decode path (32x32x16 MFMA, weights HBM/L2 ->
 // registers in operand layout, activations through LDS) with another epilogue: a workgroup owns 128
-// rows and a range of 128-column vocabulary tiles; after each tile every lane folds its 16 logits of
-// each row into a private running (max, sum of exp) pair and checks whether the row's target column
-// is among them.  At the end of the range the pairs of a row (2 lanes x 4 waves) are merged through
-// LDS and written as one partial per (row, range); score_merge_kernel combines the ranges:
+// rows and a range of 128-column vocabulary tiles.  PAIRS: after each tile the four waves, 32 columns each, fold
+// their logits in the tiled kernel's order (same bits) and write its pair.  Otherwise (a vocabulary whose pairs do not fit
+// the workspace, with any weights): every lane folds its 16 logits of each row into a private running pair over the whole
+// range, the pairs of a row (2 lanes x 4 waves) are merged through LDS and written as one partial per (row, range);
+// score_merge_kernel combines the ranges:
 //     logp = logit[target] - (M + ln sum_i s_i * exp(m_i - M)).
 // score_objective_kernel evaluates the clipped importance-ratio surrogate and the REINFORCE sum in
 // float64 with a fixed reduction order.
@@ -32,6 +33,7 @@ constexpr int PD = 2;
 
 }  // namespace
 
+template <bool PAIRS>
 __global__ __launch_bounds__(256) void score_lmhead_kernel(ScoreArgs g) {
     extern __shared__ uint4 lds_raw[];
     char* lds = (char*)lds_raw;
@@ -124,6 +126,45 @@ __global__ __launch_bounds__(256) void score_lmhead_kernel(ScoreArgs g) {
         __syncthreads();                       // the next tile's first LDS write must not overtake a slow wave's reads
 
         // registers 4b..4b+3 of a tile hold columns n_first + 8b + 4*lh .. +3 of row l32
+        if (PAIRS) {
+            float* s_max = (float*)lds;                     // [4 waves][128 rows]
+            float* s_sum = s_max + 512;                     // [4 waves][4 batch tiles][64 lanes]
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                float mx = -INFINITY;
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const int col = n_first + 8 * (r >> 2) + 4 * lh + (r & 3);
+                    if (col >= g.V) acc[t][r] = -INFINITY;
+                    mx = fmaxf(mx, acc[t][r]);
+                    if (col == tgt[t]) g.tgt_logit[m0 + t * 32 + l32] = acc[t][r];
+                }
+                mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+                if (lh == 0) s_max[wave * 128 + t * 32 + l32] = mx;
+            }
+            __syncthreads();
+            float mine = -INFINITY;                         // the pair of batch tile `wave`: this wave writes it
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                const int row = t * 32 + l32;
+                const float mx = fmaxf(fmaxf(s_max[row], s_max[128 + row]), fmaxf(s_max[256 + row], s_max[384 + row]));
+                const float ref = mx > -INFINITY ? mx : 0.f;
+                float sj = 0.f;
+#pragma unroll
+                for (int r = 0; r < 16; ++r) sj += __expf(acc[t][r] - ref);
+                s_sum[(wave * 4 + t) * 64 + lane] = sj;
+                if (t == wave) mine = mx;
+            }
+            __syncthreads();
+            float sum = s_sum[wave * 64 + lane];
+#pragma unroll
+            for (int j = 1; j < 4; ++j) sum += s_sum[(j * 4 + wave) * 64 + lane];
+            sum += __shfl_xor(sum, 32, 64);
+            const int m = m0 + wave * 32 + l32;
+            if (lh == 0 && m < g.M) g.pairs[(size_t)nt * g.M + m] = make_float2(mine, sum);
+            __syncthreads();                                // the next tile's staging overwrites the exchange
+            continue;
+        }
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
             float mx = -INFINITY;
@@ -147,6 +188,7 @@ __global__ __launch_bounds__(256) void score_lmhead_kernel(ScoreArgs g) {
         }
     }
 
+    if (PAIRS) return;
     // ---- merge the 8 (max, sum) pairs of every row: the two lane halves, then the four waves
     float* s_m = (float*)lds;                  // [4 waves][128 rows]
     float* s_s = s_m + 512;
@@ -189,18 +231,18 @@ __global__ __launch_bounds__(256) void score_merge_kernel(ScoreArgs g, float* ou
     out[m] = g.tgt_logit[m] - (M + logf(S));
 }
 
-// The same merge for the pairs of the tiled LM head, [s_tiles][M]: 32 rows a workgroup, eight threads to a row, so that
-// a load instruction reads two 256-byte runs (6000 rows x 594 tiles, 28 MB: one thread to a row takes 41 us).
-__global__ __launch_bounds__(256) void score_merge_tiles_kernel(GemmArgs g, float* out) {
+// The same merge for one pair per 128 columns, [n_pairs][M]: 32 rows a workgroup, eight threads to a row, so that a load
+// instruction reads two 256-byte runs.
+__global__ __launch_bounds__(256) void score_merge_pairs_kernel(ScoreArgs g, int n_pairs, float* out) {
     __shared__ float2 s_pair[8][32];
     const int r = threadIdx.x & 31, q = threadIdx.x >> 5;
     const int m = blockIdx.x * 32 + r;
     const int mc = m < g.M ? m : g.M - 1;
     float M = -INFINITY, S = 0.f;
-    for (int t0 = q; t0 < g.s_tiles; t0 += 8 * 8) {              // eight loads in flight; past the end: the last pair, weight 0
+    for (int t0 = q; t0 < n_pairs; t0 += 8 * 8) {              // eight loads in flight; past the end: the last pair, weight 0
         float2 p[8];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) p[u] = g.s_part[(size_t)min(t0 + 8 * u, g.s_tiles - 1) * g.M + mc];
+        for (int u = 0; u < 8; ++u) p[u] = g.pairs[(size_t)min(t0 + 8 * u, n_pairs - 1) * g.M + mc];
         float mx = M;
 #pragma unroll
         for (int u = 0; u < 8; ++u) mx = fmaxf(mx, p[u].x);
@@ -208,7 +250,7 @@ __global__ __launch_bounds__(256) void score_merge_tiles_kernel(GemmArgs g, floa
             float sum = M > -INFINITY ? S * expf(M - mx) : 0.f;
 #pragma unroll
             for (int u = 0; u < 8; ++u)
-                if (t0 + 8 * u < g.s_tiles && p[u].x > -INFINITY) sum += p[u].y * expf(p[u].x - mx);
+                if (t0 + 8 * u < n_pairs && p[u].x > -INFINITY) sum += p[u].y * expf(p[u].x - mx);
             S = sum;
             M = mx;
         }
@@ -227,8 +269,9 @@ __global__ __launch_bounds__(256) void score_merge_tiles_kernel(GemmArgs g, floa
     out[m] = g.tgt_logit[m] - (M + logf(S));
 }
 
-hipError_t launch_score_merge_tiles(const GemmArgs& a, float* out, hipStream_t s) {
-    hipLaunchKernelGGL(score_merge_tiles_kernel, dim3((a.M + 31) / 32), dim3(256), 0, s, a, out);
+hipError_t launch_score_merge_pairs(const ScoreArgs& a, float* out, hipStream_t s) {
+    if (a.M < 1 || a.V < 1 || !a.pairs || !a.targets || !a.tgt_logit) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(score_merge_pairs_kernel, dim3((a.M + 31) / 32), dim3(256), 0, s, a, (a.V + 127) / 128, out);
     return hipGetLastError();
 }
 
@@ -258,9 +301,11 @@ hipError_t launch_score(const ScoreArgs& a, float* out, hipStream_t s) {
     if (a.M < 1 || a.V < 1 || (a.K & 127) || a.n_splits < 1 || a.tiles_per_split < 1) return hipErrorInvalidValue;
     ScoreArgs g = a;
     g.m_tiles = (a.M + 127) / 128;
-    hipLaunchKernelGGL(score_lmhead_kernel, dim3(g.m_tiles * g.n_splits), dim3(256), (size_t)2 * BUF, s, g);
+    if (g.pairs) hipLaunchKernelGGL(score_lmhead_kernel<true>, dim3(g.m_tiles * g.n_splits), dim3(256), (size_t)2 * BUF, s, g);
+    else hipLaunchKernelGGL(score_lmhead_kernel<false>, dim3(g.m_tiles * g.n_splits), dim3(256), (size_t)2 * BUF, s, g);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
+    if (g.pairs) return launch_score_merge_pairs(g, out, s);
     hipLaunchKernelGGL(score_merge_kernel, dim3((a.M + 255) / 256), dim3(256), 0, s, g, out);
     return hipGetLastError();
 }

@@ -693,25 +693,27 @@ static int run_layers(StepCtx& c) {
         // scoring pass: final norm on every row, then the LM head fused with log-softmax and the target gather
         NormArgs na = {c.w.x, c.w.proj, (const float*)m->w[1], c.w.h, nullptr, c.rows, c.rows, d, pending, cfg.rms_eps, sat};
         HIP_TRY(timed(m, SPIRAL_K_NORM, c.s, [&] { return launch_add_norm(na, act32, c.s); }));
-        // The tiled kernel's pairs go to the q/k/v products' memory, which nothing reads any more; a geometry whose
-        // vocabulary is so large against its heads that they do not fit keeps the streaming kernel.
-        GemmArgs gs = {};
-        gs.A = c.w.h; gs.wf = m->f_lm; gs.rows[0] = cfg.vocab; gs.M = c.rows; gs.N = cfg.vocab; gs.K = d; gs.splits = 1;
-        gs.s_tiles = gemm_tile_score_tiles(cfg.vocab);
-        gs.s_part = (float2*)c.w.qkv; gs.targets = c.score_targets; gs.tgt_logit = c.w.score_tgt;
-        if (gemm_tile_usable(gs) && (size_t)gs.s_tiles * sizeof(float2) <= (size_t)nqkv * sizeof(float)) {
-            HIP_TRY(timed(m, SPIRAL_K_GEMM_LM_HEAD, c.s, [&] {
-                const hipError_t e = launch_gemm_tile_score(gs, c.s);
-                return e != hipSuccess ? e : launch_score_merge_tiles(gs, c.score_out, c.s);
-            }));
-            return SPIRAL_OK;
-        }
         const int n_tiles = (cfg.vocab + 127) / 128;
         ScoreArgs sa = {};
         sa.A = c.w.h; sa.W = m->w[2]; sa.targets = c.score_targets; sa.part = c.w.score_part; sa.tgt_logit = c.w.score_tgt;
         sa.M = c.rows; sa.V = cfg.vocab; sa.K = d;
         sa.tiles_per_split = (n_tiles + kScoreSplits - 1) / kScoreSplits;
         sa.n_splits = (n_tiles + sa.tiles_per_split - 1) / sa.tiles_per_split;
+        // One pair per row and 128 columns, in the q/k/v products' memory, which nothing reads any more; a geometry whose
+        // vocabulary is so large against its heads that they do not fit keeps running pairs per vocabulary range.
+        if ((size_t)n_tiles * sizeof(float2) <= (size_t)nqkv * sizeof(float)) {
+            sa.pairs = (float2*)c.w.qkv;
+            GemmArgs gs = {};
+            gs.A = c.w.h; gs.wf = m->f_lm; gs.rows[0] = cfg.vocab; gs.M = c.rows; gs.N = cfg.vocab; gs.K = d; gs.splits = 1;
+            gs.s_tiles = n_tiles; gs.s_part = sa.pairs; gs.targets = c.score_targets; gs.tgt_logit = c.w.score_tgt;
+            if (gemm_tile_usable(gs)) {
+                HIP_TRY(timed(m, SPIRAL_K_GEMM_LM_HEAD, c.s, [&] {
+                    const hipError_t e = launch_gemm_tile_score(gs, c.s);
+                    return e != hipSuccess ? e : launch_score_merge_pairs(sa, c.score_out, c.s);
+                }));
+                return SPIRAL_OK;
+            }
+        }
         HIP_TRY(timed(m, SPIRAL_K_GEMM_LM_HEAD, c.s, [&] { return launch_score(sa, c.score_out, c.s); }));
         return SPIRAL_OK;
     }

@@ -155,11 +155,11 @@ struct ScoreArgs {
     float* part;              // [M][n_splits] (max, sum exp) pairs
     float* tgt_logit;         // [M]
     int32_t M, V, K, n_splits, tiles_per_split, m_tiles;
+    float2* pairs;            // or null: [ceil(V / 128)][M] (max, sum exp) pairs instead of `part`
 };
+hipError_t launch_score_merge_pairs(const ScoreArgs& a, float* out, hipStream_t s);        // a.pairs, a.targets, a.tgt_logit -> out
 hipError_t launch_score(const ScoreArgs& a, float* out, hipStream_t s);
-hipError_t launch_gemm_tile_score(const GemmArgs& a, hipStream_t s);      // a.s_part: [gemm_tile_score_tiles(N)][M] pairs
-int gemm_tile_score_tiles(int N);
-hipError_t launch_score_merge_tiles(const GemmArgs& a, float* out, hipStream_t s);
+hipError_t launch_gemm_tile_score(const GemmArgs& a, hipStream_t s);       // writes a.s_part: [ceil(N / 128)][M] pairs
 hipError_t launch_score_objective(const float* logp_new, const float* logp_old, const float* adv, const int32_t* mask,
                                   long long n, float eps, double* out, hipStream_t s);
 hipError_t launch_sample_truncated(const float* logits, int B, int V, float temperature, int top_k, float top_p,
@@ -211,12 +211,18 @@ template <> struct ActStore<true> {
     typedef float type;
     static __device__ __forceinline__ void put(void* base, size_t i, float v) { ((float*)base)[i] = v; }
     static __device__ __forceinline__ void put_noting(void* base, size_t i, float v, bool&) { ((float*)base)[i] = v; }
+    static __device__ __forceinline__ void put4(void* base, size_t i, float x, float y, float z, float w) {      // i % 4 == 0
+        *(float4*)((float*)base + i) = make_float4(x, y, z, w);
+    }
 };
 template <> struct ActStore<false> {
     typedef uint16_t type;
     static __device__ __forceinline__ void put(void* base, size_t i, float v) { ((uint16_t*)base)[i] = f32_to_act16(v); }
     static __device__ __forceinline__ void put_noting(void* base, size_t i, float v, bool& bad) {
         ((uint16_t*)base)[i] = f32_to_act16_noting(v, bad);
+    }
+    static __device__ __forceinline__ void put4(void* base, size_t i, float x, float y, float z, float w) {
+        *(ushort4*)((uint16_t*)base + i) = make_ushort4(f32_to_act16(x), f32_to_act16(y), f32_to_act16(z), f32_to_act16(w));
     }
 };
 
