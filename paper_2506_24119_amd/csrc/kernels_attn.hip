@@ -7,15 +7,14 @@
 //   O^T[d][row]    += sum_token V^T[d][token] * P^T[token][row]   v_mfma_f32_16x16x16_bf16, A = V page
 //                     (a lane reads 4 consecutive tokens of one d), B = P^T, which is exactly the
 //                     register layout S^T came out in, so probabilities never leave the lane.
-// A tile has 16 query rows.  Decode: the rows are the G = Hq/Hkv query heads that share one kv
-// head (padded to 16), so K and V are read once per group.  Prefill: the rows are 16 consecutive
-// positions of one query head, each with its own causal limit.
+// A decode tile has 16 query rows: the G = Hq/Hkv query heads that share one kv head (padded to
+// 16), so K and V are read once per group.
 //
 // Decode (attn_stream_kernel): the ordered stream of all (row, kv head, page) units of the batch is cut into equal
 // ranges, one per workgroup; inside a range the four waves take pages round-robin, each with a private online
 // softmax (running max m, sum l, unnormalised O), merged through LDS at the end of every (row, kv head) segment;
 // a second small kernel merges the partial (m, l, O) of a pair that spans workgroups.
-// Prefill (attn_prefill_kernel): one wave = one tile over all its pages, four heads per workgroup.
+// Prefill (attn_prefill_kernel): tiles of 32 positions of one head on the 32x32x16 MFMA, four a workgroup, pages in LDS.
 // Softmax is evaluated in base 2: scores are scaled by log2(e)/sqrt(hd) and v_exp_f32 is 2^x.
 #include "spiral_internal.h"
 
@@ -26,6 +25,7 @@ typedef __attribute__((ext_vector_type(8))) _Float16 f16x8;
 typedef __attribute__((ext_vector_type(4))) _Float16 f16x4;
 typedef __attribute__((ext_vector_type(4))) short s16x4;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
+typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
 
@@ -33,7 +33,7 @@ constexpr float kNegBig = -1.0e30f;
 
 // Decode reads every K/V byte once: non-temporal loads keep the stream from displacing q, the block
 // tables and the partial results in L2 (measured: 13 us less per launch at C3, -7 % step time).
-// Prefill re-reads pages across heads and position tiles and keeps ordinary cached loads.
+// Prefill re-reads pages across position tiles and keeps ordinary cached loads.
 #ifndef ATTN_NT
 #define ATTN_NT 1
 #endif
@@ -51,6 +51,9 @@ __device__ __forceinline__ f32x4 mma_qk(const u32x4& k, const u32x4& q, const f3
 __device__ __forceinline__ f32x4 mma_pv(const u32x2& v, const u32x2& p, const f32x4& c) {
     return __builtin_amdgcn_mfma_f32_16x16x16f16(__builtin_bit_cast(f16x4, v), __builtin_bit_cast(f16x4, p), c, 0, 0, 0);
 }
+__device__ __forceinline__ f32x16 mma32_f16(const u32x4& x, const u32x4& y, const f32x16& c) {
+    return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, x), __builtin_bit_cast(f16x8, y), c, 0, 0, 0);
+}
 
 // One (page, kv head) holds K then V, each 16 tokens x HD elements, stored in the order the MFMA
 // operand registers want them, so that every wave-wide 16-byte load reads 1 KB of consecutive memory:
@@ -62,93 +65,184 @@ struct PageFrag {
     u32x4 v[HD / 32];     // V: lane = (t/4)*16 + d%16; .xy = 4 tokens of d-tile 2m, .zw = of d-tile 2m+1
 };
 
-template <int HD, bool NT = true>
+template <int HD>
 __device__ __forceinline__ void load_page(PageFrag<HD>& f, const uint16_t* kp, int lane, bool real) {
     // !real: every lane reads the first 16 bytes of the page (a valid address, one cache line)
     const uint16_t* vp = kp + kPageTokens * HD;
     const int off = real ? lane * 8 : 0;
     const int step = real ? 512 : 0;
 #pragma unroll
-    for (int ks = 0; ks < HD / 32; ++ks) f.k[ks] = NT ? KVLOAD((const u32x4*)(kp + ks * step + off)) : *(const u32x4*)(kp + ks * step + off);
+    for (int ks = 0; ks < HD / 32; ++ks) f.k[ks] = KVLOAD((const u32x4*)(kp + ks * step + off));
 #pragma unroll
-    for (int mp = 0; mp < HD / 32; ++mp) f.v[mp] = NT ? KVLOAD((const u32x4*)((real ? vp : kp) + mp * step + off)) : *(const u32x4*)((real ? vp : kp) + mp * step + off);
+    for (int mp = 0; mp < HD / 32; ++mp) f.v[mp] = KVLOAD((const u32x4*)((real ? vp : kp) + mp * step + off));
 }
 
 // ---------------------------------------------------------------------------------------------
-// Causal prefill attention.  A tile is 16 consecutive positions of one query head, each row with its own
-// causal limit; a workgroup holds four tiles, the same 16 positions of four adjacent heads, one per wave.
-// Every wave walks all pages of its tile alone (no merge between waves); with G = 4 the four waves share
-// a kv head and read the same pages at the same time, so K/V come from HBM/L2 once per workgroup.
+// Causal prefill attention.  A wave's tile is 32 consecutive positions of one query head, each row with its own causal
+// limit; a workgroup holds four tiles that share a kv head: up to four heads of the group, or with groups of one or two
+// heads also two or four consecutive position tiles.  The pages of 64 tokens (K and V, in their memory order) are
+// copied to LDS by all four waves, double buffered, the next 64 tokens in flight in registers meanwhile; every wave
+// then takes its operands from there:
+//   S^T[token][row] = K q^T    v_mfma_f32_32x32x16, A = 32 tokens x 16 d of two pages, B = the query rows in registers;
+//   O^T[d][row]    += V^T P^T  v_mfma_f32_32x32x16 over the 16 tokens of a page.  In S^T a lane holds the tokens
+//                   4 lh .. + 3 and 8 + 4 lh .. + 3 of its row: they are the B operand as they are, and the A operand is
+//                   read with the same order of the contraction index (two 8-byte groups of 4 tokens).
+// Bound: the exponentials and the matrix pipe take about equally long (a 64-token step of a wave is 32 MFMAs = 1024
+// cycles and 32 exponentials plus 100 other vector operations a lane, ~900), so two workgroups per compute unit
+// interleave them.  Against 16-row tiles that walk single pages straight from L2 (16x16 MFMAs, no LDS), a layer of:
+// 15,272 rows of U[256, 1024] tokens, 32 heads 353 -> 184 us; 11,206 rows of U[2048, 4096], 16 heads 484 -> 203 us
+// (0.63 PFLOP/s); 788 rows appended to nine histories of U[400, 2000] 122 -> 66 us.
 // ---------------------------------------------------------------------------------------------
 template <int HD, bool ACT32>
-__global__ __launch_bounds__(256) void attn_prefill_kernel(AttnArgs a) {
-    constexpr int KS = HD / 32, MT = HD / 16;
+__global__ __launch_bounds__(256, 2) void attn_prefill_kernel(AttnArgs a, int qblocks, int pairs, int heads_wg, int head_groups) {
+    constexpr int KS = HD / 16, DT = HD / 32;
+    constexpr int PAGE_B = 2 * kPageTokens * HD * 2;          // bytes of one (page, kv head): K then V
+    constexpr int STAGE_B = 4 * PAGE_B;                       // 64 tokens
+    constexpr int LD = PAGE_B / 1024;                         // 16-byte loads of a lane per page
+    extern __shared__ float lds_f[];
+    char* lds = (char*)lds_f;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int li = lane & 15, lg = lane >> 4;
+    const int l32 = lane & 31, lh = lane >> 5;
     const int G = a.n_q_heads / a.n_kv_heads;
-    const int b = blockIdx.z, qb = blockIdx.x;
-    const int h = blockIdx.y * 4 + wave;
+
+    // blocks of one (sequence, kv head) run on one XCD (its L2 keeps the pages); the longest rows start first
+    const int k = blockIdx.x >> 3;
+    const int pair = (k / qblocks) * 8 + (blockIdx.x & 7);
+    if (pair >= pairs) return;
+    const int qb = qblocks - 1 - k % qblocks;
+    const int hg = pair % head_groups, kvh = (pair / head_groups) % a.n_kv_heads, b = pair / (head_groups * a.n_kv_heads);
+    const int tiles = 4 / heads_wg;                           // position tiles of the workgroup
     const int r_first = a.cu_rows[b];
     const int n_in_seq = a.cu_rows[b + 1] - r_first;
-    if (qb * 16 >= n_in_seq || h >= a.n_q_heads) return;          // no barriers below: waves are independent
-    const int n_valid_rows = min(16, n_in_seq - qb * 16);
-    const int row0 = r_first + qb * 16;
-    const int kvh = h / G;
-    const int seq = a.row_seq[row0];
-    const int pos0 = a.row_pos[row0];
-    const int limit = li < n_valid_rows ? pos0 + li : -1;
-    const int p_end = (pos0 + n_valid_rows - 1) / kPageTokens + 1;
+    const int first = qb * tiles * 32;                        // first position of the workgroup, counted from the run's start
+    if (first >= n_in_seq) return;
+    const int hw = wave % heads_wg, tile = wave / heads_wg;
+    const int my_first = first + tile * 32;
+    const int n_valid = min(32, n_in_seq - my_first);         // rows of this wave (<= 0: none)
+    const bool active = tile < tiles && hg * heads_wg + hw < G && n_valid > 0;
+    const int h = kvh * G + min(hg * heads_wg + hw, G - 1);
+    const int row0 = r_first + my_first;
+    const int pos_base = a.row_pos[r_first];                  // position of the run's first row
+    const int pos0 = pos_base + my_first;
+    const int limit = active && l32 < n_valid ? pos0 + l32 : -1;
+    const int my_last = active ? pos0 + n_valid - 1 : -1;     // last visible position of the wave
+    const int last = pos_base + min(first + tiles * 32, n_in_seq) - 1;       // ... of the workgroup
+    const int last_page = last / kPageTokens;
+    const int n_stages = last / 64 + 1;
+
+    const int32_t* bt = a.block_table + (size_t)a.row_seq[r_first] * a.max_blocks;
+    const size_t page_elems = (size_t)a.n_kv_heads * (2 * kPageTokens * HD);
+    const uint16_t* head_pages = a.pages + (size_t)kvh * (2 * kPageTokens * HD);
+
+    // staging: wave w copies page 4 * stage + w (past the end: the last page again)
+    u32x4 rg[LD];
+    auto load = [&](int stage) {
+        const int pg = min(stage * 4 + wave, last_page);
+        const uint16_t* src = head_pages + (size_t)bt[pg] * page_elems + lane * 8;
+#pragma unroll
+        for (int u = 0; u < LD; ++u) rg[u] = *(const u32x4*)(src + u * 512);
+    };
+    load(0);
 
     u32x4 qf[KS];
     {
-        const uint16_t* qptr = a.q + ((size_t)(row0 + (li < n_valid_rows ? li : 0)) * a.n_q_heads + h) * HD + lg * 8;
+        const bool real = active && l32 < n_valid;
+        const uint16_t* qptr = a.q + ((size_t)(real ? row0 + l32 : r_first) * a.n_q_heads + h) * HD + lh * 8;
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
-            const u32x4 v = *(const u32x4*)(qptr + ks * 32);
-            qf[ks] = li < n_valid_rows ? v : u32x4{0u, 0u, 0u, 0u};
+            const u32x4 v = *(const u32x4*)(qptr + ks * 16);
+            qf[ks] = real ? v : u32x4{0u, 0u, 0u, 0u};
         }
     }
-    f32x4 acc[MT];
+    f32x16 acc[DT];
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt) acc[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int d = 0; d < DT; ++d)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[d][r] = 0.f;
     float m_run = kNegBig, l_run = 0.f;
 
-    const int32_t* bt = a.block_table + (size_t)seq * a.max_blocks;
-    const size_t page_elems = (size_t)a.n_kv_heads * (2 * kPageTokens * HD);
-    const size_t head_off = (size_t)kvh * (2 * kPageTokens * HD);
-    auto step = [&](const PageFrag<HD>& f, int pi) {
-#include "attn_page_step.inc"
-    };
-    {
-        // the next page is in flight while one is consumed; the prefetch is unconditional (past the end it re-reads
-        // one valid 16-byte spot) so that the compiler's wait counts let it stay in flight during the arithmetic
-        PageFrag<HD> cur, nxt;
-        int pi = 0;
-        load_page<HD, false>(cur, a.pages + (size_t)bt[0] * page_elems + head_off, lane, true);
-        while (true) {
-            const int pn = pi + 1;
-            const bool more = pn < p_end;
-            load_page<HD, false>(nxt, a.pages + (size_t)bt[more ? pn : pi] * page_elems + head_off, lane, more);
-            step(cur, pi);
-            if (!more) break;
-            cur = nxt;
-            pi = pn;
+    // operand offsets: K of tokens 32 sub + l32 (two pages), V of d = 32 dt + l32 (4 tokens: 8 bytes)
+    const int k_off = (l32 >> 4) * PAGE_B + lh * 256 + (l32 & 15) * 16;
+    const int v_off = PAGE_B / 2 + lh * 256 + (l32 & 15) * 16 + (l32 >> 4) * 8;
+
+    for (int st = 0; st < n_stages; ++st) {
+        char* buf = lds + (st & 1) * STAGE_B;
+#pragma unroll
+        for (int u = 0; u < LD; ++u) *(u32x4*)(buf + wave * PAGE_B + u * 1024 + lane * 16) = rg[u];
+        __syncthreads();            // one barrier a step: the buffer written next was last read before this one
+        load(st + 1);
+        if (st * 64 > my_last) continue;                      // nothing visible to this wave any more
+        f32x16 s[2];
+#pragma unroll
+        for (int sub = 0; sub < 2; ++sub) {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) s[sub][r] = 0.f;
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) {
+                const u32x4 kf = *(const u32x4*)(buf + sub * 2 * PAGE_B + k_off + (ks >> 1) * 1024 + (ks & 1) * 512);
+                s[sub] = mma32_f16(kf, qf[ks], s[sub]);
+            }
         }
+        if (st * 64 + 63 > pos0) {                            // some row of the wave does not see all 64 tokens
+#pragma unroll
+            for (int sub = 0; sub < 2; ++sub)
+#pragma unroll
+                for (int r = 0; r < 16; ++r)
+                    if (st * 64 + sub * 32 + 8 * (r >> 2) + 4 * lh + (r & 3) > limit) s[sub][r] = -INFINITY;
+        }
+        float mx = s[0][0];
+#pragma unroll
+        for (int sub = 0; sub < 2; ++sub)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[sub][r]);
+        mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+        const float m_new = fmaxf(m_run, mx * a.scale_log2e);
+        float ps = 0.f;
+        u32x4 pb[4];                                          // P^T of the four pages
+#pragma unroll
+        for (int sub = 0; sub < 2; ++sub)
+#pragma unroll
+            for (int b2 = 0; b2 < 4; ++b2) {
+                f16x4 h4;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const float p = __builtin_amdgcn_exp2f(fmaf(s[sub][4 * b2 + e], a.scale_log2e, -m_new));
+                    ps += p;
+                    h4[e] = (_Float16)p;                      // in [0, 1]: no range to check
+                }
+                const u32x2 hb = __builtin_bit_cast(u32x2, h4);
+                pb[2 * sub + (b2 >> 1)][2 * (b2 & 1)] = hb.x;
+                pb[2 * sub + (b2 >> 1)][2 * (b2 & 1) + 1] = hb.y;
+            }
+        const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
+        l_run = l_run * alpha + ps;
+        if (__builtin_amdgcn_ballot_w64(m_new != m_run) != 0) {
+#pragma unroll
+            for (int d = 0; d < DT; ++d)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[d][r] *= alpha;
+        }
+        m_run = m_new;
+#pragma unroll
+        for (int pg = 0; pg < 4; ++pg)
+#pragma unroll
+            for (int d = 0; d < DT; ++d) {
+                const char* vp = buf + pg * PAGE_B + v_off + d * 1024;
+                const u32x2 lo = *(const u32x2*)vp, hi = *(const u32x2*)(vp + 512);
+                acc[d] = mma32_f16(u32x4{lo.x, lo.y, hi.x, hi.y}, pb[pg], acc[d]);
+            }
     }
 
-    // O^T[d][row]: lane (li, lg) holds d = mt * 16 + lg * 4 .. + 3 of row li; l is spread over the four lane groups
-    l_run += __shfl_xor(l_run, 16, 64);
+    // O^T[d][row]: lane (l32, lh) holds d = 32 dt + 8 b + 4 lh .. + 3 of row l32; l is spread over the two lane halves
     l_run += __shfl_xor(l_run, 32, 64);
-    if (li < n_valid_rows) {
+    if (active && l32 < n_valid) {
         const float inv = 1.0f / l_run;
-        const size_t o_idx = ((size_t)(row0 + li) * a.n_q_heads + h) * HD + lg * 4;
+        const size_t o_idx = ((size_t)(row0 + l32) * a.n_q_heads + h) * HD + lh * 4;
 #pragma unroll
-        for (int mt = 0; mt < MT; ++mt) {
-            ActStore<ACT32>::put(a.out, o_idx + mt * 16 + 0, acc[mt].x * inv);
-            ActStore<ACT32>::put(a.out, o_idx + mt * 16 + 1, acc[mt].y * inv);
-            ActStore<ACT32>::put(a.out, o_idx + mt * 16 + 2, acc[mt].z * inv);
-            ActStore<ACT32>::put(a.out, o_idx + mt * 16 + 3, acc[mt].w * inv);
-        }
+        for (int d = 0; d < DT; ++d)
+#pragma unroll
+            for (int b2 = 0; b2 < 4; ++b2) ActStore<ACT32>::put4(a.out, o_idx + d * 32 + b2 * 8, acc[d][4 * b2] * inv,
+                                                                 acc[d][4 * b2 + 1] * inv, acc[d][4 * b2 + 2] * inv, acc[d][4 * b2 + 3] * inv);
     }
 }
 
@@ -409,8 +503,18 @@ hipError_t launch_attn_stream_combine(const AttnArgs& a, int hd, bool act32, hip
 
 template <int HD, bool ACT32>
 static hipError_t prefill_impl(const AttnArgs& a, int B, int max_new, hipStream_t s) {
-    const int qblocks = (max_new + 15) / 16;
-    hipLaunchKernelGGL((attn_prefill_kernel<HD, ACT32>), dim3(qblocks, (a.n_q_heads + 3) / 4, B), dim3(256), 0, s, a);
+    const int G = a.n_q_heads / a.n_kv_heads;
+    const int head_groups = (G + 3) / 4, heads_wg = (G + head_groups - 1) / head_groups;      // at most four heads a workgroup
+    const int rows_wg = (4 / heads_wg) * 32;
+    const int qblocks = (max_new + rows_wg - 1) / rows_wg, pairs = B * a.n_kv_heads * head_groups;
+    const long long blocks = (long long)((pairs + 7) / 8) * 8 * qblocks;
+    if (blocks > 0x7FFFFFFFll) return hipErrorInvalidValue;
+    const size_t lds = (size_t)2 * 4 * (2 * kPageTokens * HD * 2);
+    if (lds > 65536) {
+        hipError_t e = hipFuncSetAttribute((const void*)attn_prefill_kernel<HD, ACT32>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL((attn_prefill_kernel<HD, ACT32>), dim3((unsigned)blocks), dim3(256), lds, s, a, qblocks, pairs, heads_wg, head_groups);
     return hipGetLastError();
 }
 
