@@ -16,6 +16,8 @@
 // a second small kernel merges the partial (m, l, O) of a pair that spans workgroups.
 // Prefill (attn_prefill_kernel): tiles of 32 positions of one head on the 32x32x16 MFMA, four a workgroup, pages in LDS.
 // Softmax is evaluated in base 2: scores are scaled by log2(e)/sqrt(hd) and v_exp_f32 is 2^x.
+#include <type_traits>
+
 #include "spiral_internal.h"
 
 namespace spiral {
@@ -122,7 +124,7 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(AttnArgs a, int qb
     const bool active = tile < tiles && hg * heads_wg + hw < G && n_valid > 0;
     const int h = kvh * G + min(hg * heads_wg + hw, G - 1);
     const int row0 = r_first + my_first;
-    const int pos_base = a.row_pos[r_first];                  // position of the run's first row
+    const int pos_base = a.base_pos[b];                       // position of the run's first row
     const int pos0 = pos_base + my_first;
     const int limit = active && l32 < n_valid ? pos0 + l32 : -1;
     const int my_last = active ? pos0 + n_valid - 1 : -1;     // last visible position of the wave
@@ -130,11 +132,11 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(AttnArgs a, int qb
     const int last_page = last / kPageTokens;
     const int n_stages = last / 64 + 1;
 
-    const int32_t* bt = a.block_table + (size_t)a.row_seq[r_first] * a.max_blocks;
+    const int32_t* bt = a.block_table + (size_t)a.seq_ids[b] * a.max_blocks;
     const size_t page_elems = (size_t)a.n_kv_heads * (2 * kPageTokens * HD);
     const uint16_t* head_pages = a.pages + (size_t)kvh * (2 * kPageTokens * HD);
 
-    // staging: wave w copies page 4 * stage + w (past the end: the last page again)
+    // staging: wave w copies page 4 * stage + w (past the last page: that one again)
     u32x4 rg[LD];
     auto load = [&](int stage) {
         const int pg = min(stage * 4 + wave, last_page);
@@ -165,16 +167,12 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(AttnArgs a, int qb
     const int k_off = (l32 >> 4) * PAGE_B + lh * 256 + (l32 & 15) * 16;
     const int v_off = PAGE_B / 2 + lh * 256 + (l32 & 15) * 16 + (l32 >> 4) * 8;
 
-    for (int st = 0; st < n_stages; ++st) {
-        char* buf = lds + (st & 1) * STAGE_B;
+    // one step of a wave over the first 32 * NS tokens of the staged 64
+    auto step = [&](const char* buf, int st, auto ns) {
+        constexpr int NS = decltype(ns)::value;
+        f32x16 s[NS];
 #pragma unroll
-        for (int u = 0; u < LD; ++u) *(u32x4*)(buf + wave * PAGE_B + u * 1024 + lane * 16) = rg[u];
-        __syncthreads();            // one barrier a step: the buffer written next was last read before this one
-        load(st + 1);
-        if (st * 64 > my_last) continue;                      // nothing visible to this wave any more
-        f32x16 s[2];
-#pragma unroll
-        for (int sub = 0; sub < 2; ++sub) {
+        for (int sub = 0; sub < NS; ++sub) {
 #pragma unroll
             for (int r = 0; r < 16; ++r) s[sub][r] = 0.f;
 #pragma unroll
@@ -185,22 +183,22 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(AttnArgs a, int qb
         }
         if (st * 64 + 63 > pos0) {                            // some row of the wave does not see all 64 tokens
 #pragma unroll
-            for (int sub = 0; sub < 2; ++sub)
+            for (int sub = 0; sub < NS; ++sub)
 #pragma unroll
                 for (int r = 0; r < 16; ++r)
                     if (st * 64 + sub * 32 + 8 * (r >> 2) + 4 * lh + (r & 3) > limit) s[sub][r] = -INFINITY;
         }
         float mx = s[0][0];
 #pragma unroll
-        for (int sub = 0; sub < 2; ++sub)
+        for (int sub = 0; sub < NS; ++sub)
 #pragma unroll
             for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[sub][r]);
         mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
         const float m_new = fmaxf(m_run, mx * a.scale_log2e);
         float ps = 0.f;
-        u32x4 pb[4];                                          // P^T of the four pages
+        u32x4 pb[2 * NS];                                          // P^T of the pages
 #pragma unroll
-        for (int sub = 0; sub < 2; ++sub)
+        for (int sub = 0; sub < NS; ++sub)
 #pragma unroll
             for (int b2 = 0; b2 < 4; ++b2) {
                 f16x4 h4;
@@ -224,13 +222,25 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(AttnArgs a, int qb
         }
         m_run = m_new;
 #pragma unroll
-        for (int pg = 0; pg < 4; ++pg)
+        for (int pg = 0; pg < 2 * NS; ++pg)
 #pragma unroll
             for (int d = 0; d < DT; ++d) {
                 const char* vp = buf + pg * PAGE_B + v_off + d * 1024;
                 const u32x2 lo = *(const u32x2*)vp, hi = *(const u32x2*)(vp + 512);
                 acc[d] = mma32_f16(u32x4{lo.x, lo.y, hi.x, hi.y}, pb[pg], acc[d]);
             }
+    };
+    for (int st = 0; st < n_stages; ++st) {
+        char* buf = lds + (st & 1) * STAGE_B;
+#pragma unroll
+        for (int u = 0; u < LD; ++u) *(u32x4*)(buf + wave * PAGE_B + u * 1024 + lane * 16) = rg[u];
+        __syncthreads();            // one barrier a step: the buffer written next was last read before this one
+        if (st + 1 < n_stages) load(st + 1);
+        if (st * 64 + 32 > my_last) {
+            if (st * 64 <= my_last) step(buf, st, std::integral_constant<int, 1>());      // nothing of the second 32 tokens is visible
+        } else {
+            step(buf, st, std::integral_constant<int, 2>());
+        }
     }
 
     // O^T[d][row]: lane (l32, lh) holds d = 32 dt + 8 b + 4 lh .. + 3 of row l32; l is spread over the two lane halves

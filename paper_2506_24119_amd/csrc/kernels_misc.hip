@@ -332,15 +332,14 @@ __global__ __launch_bounds__(256) void qkv_post_kernel(QkvPostArgs a) {
         if (bias) { lo += b_lo; hi += b_hi; }
         if (!act) { lo = 0.f; hi = 0.f; }
         if (gain) {       // hd <= 128: the whole head sits in one pass of the wave
-            const float ss = wave_sum(lo * lo + hi * hi);
+            const float ss = wave_sum(square_pair(lo, hi));
             const float rs = rsqrtf(ss / (float)hd + a.eps);
             lo = lo * rs * g_lo; hi = hi * rs * g_hi;
         }
         if (!act) continue;
         if (is_q || is_k) {
-            const float nlo = lo * cs.x - hi * cs.y;
-            const float nhi = hi * cs.x + lo * cs.y;
-            lo = nlo; hi = nhi;
+            const float2 r2 = rotate_pair(lo, hi, cs.x, cs.y);
+            lo = r2.x; hi = r2.y;
         }
         if (is_q) {
             uint16_t* q = a.q + ((size_t)r * a.n_q_heads + head) * hd;

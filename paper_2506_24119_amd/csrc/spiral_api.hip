@@ -596,6 +596,21 @@ struct StepCtx {
     int32_t* out_tokens = nullptr;
 };
 
+// K splits of a projection over more than 128 rows, and the streaming kernel's tile width: the pair for which the estimated
+// time of the launch plus that of the partial sums (written, and read by the norm kernel; 788 x 2560 of them cost 0.7 us
+// of the norm kernel each, and the writes about as much again) is least.  It depends on the shape alone, not on how the weights are
+// stored, so that repacked and row-major weights keep adding in the same order.
+static float wide_shape(int M, int N, int K, int most, int& bn, int& splits) {
+    float best = 1e30f;
+    for (int s = 1; s <= std::max(1, most) && (s == 1 || (K % 128 == 0 && K / s >= 512)); ++s) {
+        const float s128 = gemm_stream_us(M, N, K, s, 128), s64 = gemm_stream_us(M, N, K, s, 64);
+        const float launch = std::min({gemm_tile_us(M, N, K, s, 256, 256), gemm_tile_us(M, N, K, s, 256, 128), s128, s64});
+        const float us = launch + (float)(s - 1) * M * N * 4.f / 3.3e6f;
+        if (us < best) { best = us; splits = s; bn = s64 < s128 ? 64 : 128; }
+    }
+    return best;
+}
+
 static int run_layers(StepCtx& c) {
     spiral_model* m = c.m;
     const spiral_model_config& cfg = m->cfg;
@@ -620,15 +635,41 @@ static int run_layers(StepCtx& c) {
         if (wide) s = 1;
         return Shape{bn, std::max(1, std::min(s, K / 128))};
     };
-    const Shape sh_qkv = shape(t.bn_qkv, t.s_qkv, nqkv, d), sh_o = shape(t.bn_o, t.s_o, d, qw),
-                sh_down = shape(t.bn_down, t.s_down, d, cfg.ffn_dim);
+    Shape sh_qkv = shape(t.bn_qkv, t.s_qkv, nqkv, d);
+    Shape sh_o = shape(t.bn_o, t.s_o, d, qw), sh_down = shape(t.bn_down, t.s_down, d, cfg.ffn_dim);
+    // More than 128 rows: the row tiles of O and down still leave compute units idle up to a few thousand rows, so their K
+    // is split too.  The partial sums go where the layer's other products are dead by then (the workspace is carved in the
+    // order qkv, q, o, proj, mlp, hf): O has qkv and q, or proj and mlp; down has everything before mlp.
+    float *part_o = c.w.proj, *part_down = c.w.proj;
+    bool fuse_qkv = false;              // the q/k/v projection's epilogue does the post-processing, its product never reaches memory
+    if (c.rows > 128 && !act32) {
+        const size_t product = (size_t)c.rows * d * sizeof(float);
+        const size_t front = ((char*)c.w.o - (char*)c.w.qkv) / product, back = ((char*)c.w.hf - (char*)c.w.proj) / product;
+        if (front > back) part_o = c.w.qkv;
+        part_down = c.w.qkv;
+        wide_shape(c.rows, d, qw, (int)std::min<size_t>(std::max(front, back), kMaxSplit), sh_o.bn, sh_o.splits);
+        wide_shape(c.rows, d, cfg.ffn_dim, (int)std::min<size_t>(((char*)c.w.mlp - (char*)c.w.qkv) / product, kMaxSplit), sh_down.bn, sh_down.splits);
+    }
+    if (c.rows > 128 && !act32 && sh_qkv.bn != 1) {
+        // the fused form against a projection split along K (its partials fill the product's own memory, which holds at least
+        // 16 x 128 rows) with qkv_post_kernel behind it: 5 us and 2.55 ps a product (9 us at 200 rows of the 4B shape,
+        // 17 at 788).  By shape alone, as above; row-major weights take the unsplit projection where the others are fused.
+        const int most = (int)std::min<size_t>(((char*)c.w.q - (char*)c.w.qkv) / ((size_t)c.rows * nqkv * sizeof(float)), kMaxSplit);
+        QkvPostArgs qs = {};
+        qs.hd = hd; qs.n_q_heads = cfg.n_q_heads; qs.n_kv_heads = cfg.n_kv_heads;
+        int bn = 128, splits = 1;
+        const float split_us = wide_shape(c.rows, nqkv, d, most, bn, splits) + 5.f + 2.55e-6f * (float)c.rows * (float)nqkv;
+        if (t.fuse_qkv && gemm_tile_qkv_fits(nqkv, d, qs) && gemm_tile_qkv_us(c.rows, nqkv, d) <= split_us) fuse_qkv = true;
+        else { sh_qkv.bn = bn; sh_qkv.splits = splits; }
+    }
     const int s_qkv = sh_qkv.splits, s_o = sh_o.splits, s_down = sh_down.splits;
+    const float* part = c.w.proj;       // the partials waiting to be added to the residual
     int pending = 0;            // projection partials waiting to be added to the residual
     int32_t* sat = c.p->d_status;
 
     for (int l = 0; l < cfg.n_layers; ++l) {
         if (l > 0) {
-            NormArgs n = {c.w.x, c.w.proj, (const float*)m->lw(l, SPIRAL_W_ATTN_NORM), c.w.h, nullptr, c.rows, c.rows, d, pending, cfg.rms_eps, sat};
+            NormArgs n = {c.w.x, part, (const float*)m->lw(l, SPIRAL_W_ATTN_NORM), c.w.h, nullptr, c.rows, c.rows, d, pending, cfg.rms_eps, sat};
             HIP_TRY(timed(m, SPIRAL_K_NORM, c.s, [&] { return launch_add_norm(n, act32, c.s); }));
         }
         GemmArgs g = {};
@@ -641,9 +682,7 @@ static int run_layers(StepCtx& c) {
                           (const float*)m->lw(l, SPIRAL_W_Q_NORM), (const float*)m->lw(l, SPIRAL_W_K_NORM),
                           c.w.rope, c.w.row_page, c.w.q, pages,
                           c.rows, s_qkv, cfg.n_q_heads, cfg.n_kv_heads, hd, cfg.rms_eps, sat};
-        if (t.fuse_qkv && s_qkv == 1 && sh_qkv.bn != 1 && gemm_tile_qkv_usable(g, qa, m->w_bf16)) {
-            // thousands of rows (prefill, scoring): the projection's epilogue does the post-processing, the fp32 product
-            // never reaches memory
+        if (fuse_qkv && gemm_tile_usable(g)) {
             HIP_TRY(timed(m, SPIRAL_K_GEMM_QKV, c.s, [&] { return launch_gemm_tile_qkv(g, qa, c.s); }));
         } else {
             HIP_TRY(timed(m, SPIRAL_K_GEMM_QKV, c.s, [&] { return launch_gemm(g, EPI_STORE_F32, m->w_bf16, sh_qkv.bn, c.s); }));
@@ -652,7 +691,7 @@ static int run_layers(StepCtx& c) {
 
         AttnArgs aa = {};
         aa.q = c.w.q; aa.pages = pages; aa.block_table = c.p->d_block_table; aa.row_seq = c.w.row_seq;
-        aa.row_pos = c.w.row_pos; aa.cu_rows = c.w.cu_rows; aa.part = c.w.attn_part; aa.out = c.w.o;
+        aa.row_pos = c.w.row_pos; aa.cu_rows = c.w.cu_rows; aa.base_pos = c.w.base_pos; aa.seq_ids = c.w.seq_ids; aa.part = c.w.attn_part; aa.out = c.w.o;
         aa.n_rows = c.rows; aa.n_q_heads = cfg.n_q_heads; aa.n_kv_heads = cfg.n_kv_heads;
         aa.max_blocks = c.p->max_blocks; aa.chunk_pages = t.chunk_pages; aa.n_chunks = c.n_chunks;
         aa.scale_log2e = (float)(1.4426950408889634 / std::sqrt((double)hd));
@@ -667,11 +706,11 @@ static int run_layers(StepCtx& c) {
 
         GemmArgs go = {};
         go.A = c.w.o; go.w[0] = m->lw(l, SPIRAL_W_O); go.rows[0] = d;
-        go.M = c.rows; go.N = d; go.K = qw; go.out = c.w.proj; go.splits = s_o;
+        go.M = c.rows; go.N = d; go.K = qw; go.out = part_o; go.splits = s_o;
         go.wf = m->f_lm ? m->f_o[l] : nullptr;
         HIP_TRY(timed(m, SPIRAL_K_GEMM_O, c.s, [&] { return launch_gemm(go, EPI_STORE_F32, m->w_bf16, sh_o.bn, c.s); }));
 
-        NormArgs n2 = {c.w.x, c.w.proj, (const float*)m->lw(l, SPIRAL_W_MLP_NORM), c.w.h, nullptr, c.rows, c.rows, d, s_o, cfg.rms_eps, sat};
+        NormArgs n2 = {c.w.x, part_o, (const float*)m->lw(l, SPIRAL_W_MLP_NORM), c.w.h, nullptr, c.rows, c.rows, d, s_o, cfg.rms_eps, sat};
         HIP_TRY(timed(m, SPIRAL_K_NORM, c.s, [&] { return launch_add_norm(n2, act32, c.s); }));
 
         GemmArgs gu = {};
@@ -684,14 +723,15 @@ static int run_layers(StepCtx& c) {
 
         GemmArgs gd = {};
         gd.A = c.w.mlp; gd.w[0] = m->lw(l, SPIRAL_W_DOWN); gd.rows[0] = d;
-        gd.M = c.rows; gd.N = d; gd.K = cfg.ffn_dim; gd.out = c.w.proj; gd.splits = s_down;
+        gd.M = c.rows; gd.N = d; gd.K = cfg.ffn_dim; gd.out = part_down; gd.splits = s_down;
         gd.wf = m->f_lm ? m->f_down[l] : nullptr;
         HIP_TRY(timed(m, SPIRAL_K_GEMM_DOWN, c.s, [&] { return launch_gemm(gd, EPI_STORE_F32, m->w_bf16, sh_down.bn, c.s); }));
         pending = s_down;
+        part = part_down;
     }
     if (c.score_out) {
         // scoring pass: final norm on every row, then the LM head fused with log-softmax and the target gather
-        NormArgs na = {c.w.x, c.w.proj, (const float*)m->w[1], c.w.h, nullptr, c.rows, c.rows, d, pending, cfg.rms_eps, sat};
+        NormArgs na = {c.w.x, part, (const float*)m->w[1], c.w.h, nullptr, c.rows, c.rows, d, pending, cfg.rms_eps, sat};
         HIP_TRY(timed(m, SPIRAL_K_NORM, c.s, [&] { return launch_add_norm(na, act32, c.s); }));
         const int n_tiles = (cfg.vocab + 127) / 128;
         ScoreArgs sa = {};
@@ -718,7 +758,7 @@ static int run_layers(StepCtx& c) {
         return SPIRAL_OK;
     }
     // final norm on one row per sequence, then the LM head
-    NormArgs nf = {c.w.x, c.w.proj, (const float*)m->w[1], c.w.hf, c.decode ? nullptr : c.w.last_rows,
+    NormArgs nf = {c.w.x, part, (const float*)m->w[1], c.w.hf, c.decode ? nullptr : c.w.last_rows,
                    c.rows, c.B, d, pending, cfg.rms_eps, sat};
     HIP_TRY(timed(m, SPIRAL_K_NORM, c.s, [&] { return launch_add_norm(nf, act32, c.s); }));
     GemmArgs gl = {};

@@ -62,9 +62,11 @@ struct AttnArgs {
     const uint16_t* q;        // bf16 [rows][Hq][hd]
     const uint16_t* pages;    // this layer's pages: [page][Hkv]{K[16][hd], V[hd][16]}
     const int32_t* block_table;   // [max_seqs][max_blocks]
-    const int32_t* row_seq;   // [rows]
-    const int32_t* row_pos;   // [rows] position of the row's token
-    const int32_t* cu_rows;   // prefill: [B+1] first row of each sequence; decode: unused
+    const int32_t* row_seq;   // decode: [rows]
+    const int32_t* row_pos;   // decode: [rows] position of the row's token
+    const int32_t* cu_rows;   // prefill: [B+1] first row of each sequence, [B] its first position and its id; decode: unused
+    const int32_t* base_pos;
+    const int32_t* seq_ids;
     const int32_t* row_page_start;   // decode stream: [rows + 1] prefix sum of the rows' page counts
     float* part;              // decode: [rows][Hkv][chunks][G][hd + 2]
     void* out;                // act [rows][Hq*hd]
@@ -125,8 +127,12 @@ hipError_t launch_qkv_post(const QkvPostArgs& a, bool w_bf16, hipStream_t s);
 
 hipError_t launch_gemm(const GemmArgs& a, int epilogue, bool w_bf16, int bn, hipStream_t s);
 bool gemm_tile_usable(const GemmArgs& a);                                                  // fragment-ordered weights, K % 64 == 0, ...
-hipError_t launch_gemm_tile(const GemmArgs& a, int epilogue, hipStream_t s);
-bool gemm_tile_qkv_usable(const GemmArgs& a, const QkvPostArgs& qa, bool w_bf16);          // ... and head_dim 128, whole heads per tile
+int gemm_tile_rows(const GemmArgs& a, int epilogue, int bn);                               // tile height, 0: use the streaming kernel
+hipError_t launch_gemm_tile(const GemmArgs& a, int epilogue, int bm, hipStream_t s);
+float gemm_tile_us(int M, int N, int K, int splits, int cols, int bm);                     // cost estimates that choose between them
+float gemm_stream_us(int M, int N, int K, int splits, int bn);
+bool gemm_tile_qkv_fits(int N, int K, const QkvPostArgs& qa);                              // head_dim 128, whole heads per tile
+float gemm_tile_qkv_us(int M, int N, int K);
 hipError_t launch_gemm_tile_qkv(const GemmArgs& a, const QkvPostArgs& qa, hipStream_t s);  // q/k/v projection + qkv_post in one kernel
 hipError_t launch_gemm_stream(const GemmArgs& a, int epilogue, int bn, hipStream_t s);   // K % 128 == 0, N % 16 == 0
 hipError_t launch_attn_stream(const AttnArgs& a, int hd, bool act32, hipStream_t s);
@@ -240,6 +246,13 @@ __device__ __forceinline__ float gumbel_noise(uint64_t key, int v) {
 }
 // argmax order: larger score wins, equal scores go to the lower index
 __device__ __forceinline__ bool better(float v, int i, float bv, int bi) { return v > bv || (v == bv && i < bi); }
+
+// the q/k head arithmetic that two kernels share (a projection's epilogue and qkv_post_kernel): spelled out so that both
+// round alike whatever the compiler contracts
+__device__ __forceinline__ float square_pair(float lo, float hi) { return fmaf(lo, lo, hi * hi); }
+__device__ __forceinline__ float2 rotate_pair(float lo, float hi, float c, float s) {
+    return make_float2(fmaf(lo, c, -(hi * s)), fmaf(hi, c, lo * s));
+}
 
 __device__ __forceinline__ float wave_sum(float v) {
 #pragma unroll

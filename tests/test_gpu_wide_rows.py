@@ -1,0 +1,39 @@
+"""Projections over more than 128 rows: tiles of 256 x 256 or 128 x 256 or the streaming kernel, K split or not, q/k/v
+post-processing inside the projection or behind it - chosen from the shape.  Row counts around the tile heights, on a
+geometry whose O and down projections are split; repacked weights must give the bits that row-major ones give, and both
+the oracle's logits within the bar of every logit comparison (3e-2 x per-row logit std)."""
+import numpy as np
+import pytest
+
+from oracle import decoder as od
+from paper_2506_24119_amd import inputs as si
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("rows", [129, 255, 257, 520, 900])
+@pytest.mark.parametrize("head_dim,q_heads", [(128, 8), (64, 14)])
+def test_row_counts_around_the_tiles(rows, head_dim, q_heads):
+    import torch
+    from paper_2506_24119_amd import binding as sb
+    g = si.ModelGeometry("wide", 2, 1024, q_heads, 2, head_dim, 2048, 512, 1e6, qk_norm=head_dim == 128, qkv_bias=head_dim == 64)
+    host = si.make_weights(g, seed=11)
+    w = sb.weights_to_device(host)
+    rng = np.random.Generator(np.random.PCG64(rows))
+    lens = [rows - 2 * (rows // 3), rows // 3, rows // 3]
+    seqs = [rng.integers(0, g.vocab, n).astype(np.int32) for n in lens]
+    step = rng.integers(0, g.vocab, 3).astype(np.int32)
+    ids = np.arange(3, dtype=np.int32)
+    got = []
+    for repack in (True, False):
+        sess = sb.Session(g, w, 80, 3, 40, rows, 400, page_order=si.make_page_order(80, 4), repack=repack)
+        first = sess.prefill(ids, seqs).cpu().numpy()
+        second = sess.decode_step(ids, torch.from_numpy(step).cuda(), sess.new_logits(3)).cpu().numpy()      # reads the appended k, v
+        got.append((first, second))
+        sess.close()
+    assert np.array_equal(got[0][0], got[1][0]) and np.array_equal(got[0][1], got[1][1])
+    for b, s in enumerate(seqs):
+        want = od.forward_full(g, host, np.concatenate([s, step[b:b + 1]]), logits_at=np.array([len(s) - 1, len(s)]))
+        for k in range(2):
+            ratio = np.abs(got[0][k][b] - want[k]).max() / want[k].std()
+            assert ratio <= 3e-2, (b, k, ratio)
