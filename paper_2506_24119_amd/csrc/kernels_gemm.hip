@@ -14,6 +14,8 @@
 //
 // Weights are the MFMA "A" operand (rows i = output column n), activations the "B" operand
 // (columns j = batch row m), so that a lane ends up with 4 consecutive n of one m.
+#include <algorithm>
+
 #include "spiral_internal.h"
 #include "mfma_ops.h"
 
@@ -191,29 +193,67 @@ __global__ __launch_bounds__(256) void gemm_mfma_kernel(GemmArgs g) {
 }
 
 // ---------------------------------------------------------------------------------------------
-// fp32-weight models: one thread per output element, fp32 FMA.  Small correctness configuration only.
+// fp32-weight models (the small correctness configuration): a wave takes one output column of four rows, its lanes split K
+// (16 bytes each where rows are 16-byte aligned), plain fp32 FMAs and a tree over the lanes.  A call is a handful of
+// launches of a few microseconds; a thread per output that walks K alone takes 13 to 30 us a launch (K = 128 and 512,
+// four rows: every load is a cache line per lane and waits for the one before), this
+// 3 to 4, a decode step of the two-layer model 237 -> 83.
 // ---------------------------------------------------------------------------------------------
-template <int EPI>
-__global__ __launch_bounds__(64) void gemm_f32_kernel(GemmArgs g) {
-    const int n = blockIdx.x * 64 + threadIdx.x;
+template <int EPI, bool VEC>
+__global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs g) {
+    constexpr int R = 4;
+    const int lane = threadIdx.x & 63, n = blockIdx.x * 4 + (threadIdx.x >> 6);
     if (n >= g.N) return;
-    for (int m = blockIdx.y; m < g.M; m += gridDim.y) {
-        const float* a = (const float*)g.A + (size_t)m * g.K;
-        if (EPI == EPI_SWIGLU) {
-            const float* wg = (const float*)g.w[0] + (size_t)n * g.K;
-            const float* wu = (const float*)g.w[1] + (size_t)n * g.K;
-            float sg = 0.f, su = 0.f;
-            for (int k = 0; k < g.K; ++k) { sg = fmaf(a[k], wg[k], sg); su = fmaf(a[k], wu[k], su); }
-            ((float*)g.out)[(size_t)m * g.N + n] = (sg / (1.0f + expf(-sg))) * su;
-        } else {
-            const float* w;
-            if (n < g.rows[0]) w = (const float*)g.w[0] + (size_t)n * g.K;
-            else if (n < g.rows[0] + g.rows[1]) w = (const float*)g.w[1] + (size_t)(n - g.rows[0]) * g.K;
-            else w = (const float*)g.w[2] + (size_t)(n - g.rows[0] - g.rows[1]) * g.K;
-            float s = 0.f;
-            for (int k = 0; k < g.K; ++k) s = fmaf(a[k], w[k], s);
-            ((float*)g.out)[(size_t)m * g.N + n] = s;
+    const int K = g.K;
+    const float *w0, *w1 = nullptr;
+    if (EPI == EPI_SWIGLU) {
+        w0 = (const float*)g.w[0] + (size_t)n * K;
+        w1 = (const float*)g.w[1] + (size_t)n * K;
+    } else if (n < g.rows[0]) w0 = (const float*)g.w[0] + (size_t)n * K;
+    else if (n < g.rows[0] + g.rows[1]) w0 = (const float*)g.w[1] + (size_t)(n - g.rows[0]) * K;
+    else w0 = (const float*)g.w[2] + (size_t)(n - g.rows[0] - g.rows[1]) * K;
+    for (int m0 = blockIdx.y * R; m0 < g.M; m0 += gridDim.y * R) {
+        const float* a[R];
+        float s0[R], s1[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            a[r] = (const float*)g.A + (size_t)min(m0 + r, g.M - 1) * K;
+            s0[r] = s1[r] = 0.f;
         }
+        if (VEC) {
+            for (int k = lane * 4; k < K; k += 256) {
+                const float4 x0 = *(const float4*)(w0 + k);
+                const float4 x1 = EPI == EPI_SWIGLU ? *(const float4*)(w1 + k) : make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    const float4 y = *(const float4*)(a[r] + k);
+                    s0[r] = fmaf(y.w, x0.w, fmaf(y.z, x0.z, fmaf(y.y, x0.y, fmaf(y.x, x0.x, s0[r]))));
+                    if (EPI == EPI_SWIGLU) s1[r] = fmaf(y.w, x1.w, fmaf(y.z, x1.z, fmaf(y.y, x1.y, fmaf(y.x, x1.x, s1[r]))));
+                }
+            }
+        } else {
+            for (int k = lane; k < K; k += 64) {
+                const float x0 = w0[k], x1 = EPI == EPI_SWIGLU ? w1[k] : 0.f;
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    const float y = a[r][k];
+                    s0[r] = fmaf(y, x0, s0[r]);
+                    if (EPI == EPI_SWIGLU) s1[r] = fmaf(y, x1, s1[r]);
+                }
+            }
+        }
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            s0[r] = wave_sum(s0[r]);
+            if (EPI == EPI_SWIGLU) s1[r] = wave_sum(s1[r]);
+        }
+        float v = 0.f;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const float x = EPI == EPI_SWIGLU ? (s0[r] / (1.0f + expf(-s0[r]))) * s1[r] : s0[r];
+            if (lane == r) v = x;
+        }
+        if (lane < R && m0 + lane < g.M) ((float*)g.out)[(size_t)(m0 + lane) * g.N + n] = v;
     }
 }
 
@@ -241,9 +281,15 @@ hipError_t launch_gemm(const GemmArgs& a, int epilogue, bool w_bf16, int bn, hip
     if (a.M <= 0 || a.N <= 0 || a.K <= 0) return hipErrorInvalidValue;
     if (!w_bf16) {
         if (a.splits != 1) return hipErrorInvalidValue;
-        dim3 g((a.N + 63) / 64, a.M < 32768 ? a.M : 32768), b(64);
-        if (epilogue == EPI_SWIGLU) hipLaunchKernelGGL((gemm_f32_kernel<EPI_SWIGLU>), g, b, 0, s, a);
-        else hipLaunchKernelGGL((gemm_f32_kernel<EPI_STORE_F32>), g, b, 0, s, a);
+        const dim3 g((a.N + 3) / 4, std::min((a.M + 3) / 4, 32768)), b(256);
+        const bool vec = (a.K & 3) == 0;             // weights and activations are 16-byte aligned
+        if (epilogue == EPI_SWIGLU) {
+            if (vec) hipLaunchKernelGGL((gemm_f32_kernel<EPI_SWIGLU, true>), g, b, 0, s, a);
+            else hipLaunchKernelGGL((gemm_f32_kernel<EPI_SWIGLU, false>), g, b, 0, s, a);
+        } else {
+            if (vec) hipLaunchKernelGGL((gemm_f32_kernel<EPI_STORE_F32, true>), g, b, 0, s, a);
+            else hipLaunchKernelGGL((gemm_f32_kernel<EPI_STORE_F32, false>), g, b, 0, s, a);
+        }
         return hipGetLastError();
     }
     if ((a.K & 31) || (a.N & 3)) return hipErrorInvalidValue;
