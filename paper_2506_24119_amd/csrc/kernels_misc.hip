@@ -429,10 +429,8 @@ hipError_t launch_repack(const void* src0, const void* src1, const void* src2, i
 // memory to merge the slices in: a slice's winner is an index, and its score can be computed again from the index, so the
 // slices compete for out[row] by compare-and-swap on the index.  The order (score, then index) is total, so the result
 // does not depend on who comes first; out[row] starts as 0, which a NaN at index 0 does not defend.
-// Bound by the generator's 64-bit arithmetic.  Most entries cannot win and are told apart without a logarithm:
-// g > t needs 1 - u < -ln u < e^-t, so once some score `best` of the row is known an entry with
-// 1 - u >= e^(z - best) is passed over (with 1e-3 and 1e-6 of the magnitudes as slack: the rounding of z, of z + g, of the
-// reciprocal of T and of the fast exponential stays below that, so ties are still decided on the exact scores).
+// Bound by the generator's 64-bit arithmetic.  Most entries cannot win and are told apart without a logarithm
+// (noise_may_win, with the best score any thread has found so far; the product with 1/T stands for the division there).
 // Measured with 151,936 entries against a workgroup per row and two logarithms per entry: 128 rows, T = 1 77 -> 33 us, greedy
 // 30 -> 18; 16 rows 75 -> 21; one row 73 -> 14.
 // ---------------------------------------------------------------------------------------------
@@ -464,16 +462,15 @@ __global__ __launch_bounds__(kSampleThreads) void sample_kernel(const float* log
     const int lo = blockIdx.x * per_slice, hi = min(V, lo + per_slice);
     float bv = -INFINITY;
     int bi = 0x7FFFFFFF;
-    auto ordered = [](float f) { const int i = __float_as_int(f); return i ^ ((i >> 31) & 0x7FFFFFFF); };
     float bound = -INFINITY, pass = -INFINITY;   // a score of the row that an entry has to beat, and that less its slack
     const float inv_t = 1.0f / temperature;
     if (MODE == 1) {
-        if (tid == 0) s_best = ordered(-INFINITY);
+        if (tid == 0) s_best = ordered_bits(__float_as_int(-INFINITY));
         __syncthreads();
         const int v = lo + tid;                  // one entry a thread in full: a first bound (they are visited again below)
         if (v < hi) {
             const float sc = lr[v] / temperature + gumbel_noise(key, v);
-            if (sc > -INFINITY) atomicMax(&s_best, ordered(sc));
+            if (sc > -INFINITY) atomicMax(&s_best, ordered_bits(__float_as_int(sc)));
         }
         __syncthreads();
     }
@@ -484,23 +481,19 @@ __global__ __launch_bounds__(kSampleThreads) void sample_kernel(const float* log
 #pragma unroll
         for (int u = 0; u < U; ++u) l[u] = lr[min(base + u * NT, hi - 1)];
         if (MODE == 1) {
-            bound = __int_as_float(ordered(__int_as_float(*(volatile int*)&s_best)));
-            pass = bound - 1e-3f - 1e-6f * fabsf(bound);
+            bound = __int_as_float(ordered_bits(*(volatile int*)&s_best));
+            pass = noise_pass(bound);
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int v = base + u * NT;
             if (v >= hi) continue;
             if (MODE == 1) {
-                const uint32_t r = (uint32_t)(mix64(key + (uint64_t)v * 0x9E3779B97F4A7C15ull) >> 32) >> 9;
-                const float w = ((float)(0x7FFFFFu - r) + 0.5f) * 1.1920928955078125e-07f;      // 1 - u, exact
-                const float z = l[u] * inv_t;
-                const float e = __builtin_amdgcn_exp2f((fmaf(fabsf(z), 1e-6f, z) - pass) * 1.4426950408889634f);
-                if (!(w >= e)) {                             // also when e is NaN (inf - inf)
+                if (noise_may_win(key, v, l[u] * inv_t, pass)) {
                     const float sc = l[u] / temperature + gumbel_noise(key, v);
                     if (better(sc, v, bv, bi)) {
                         bv = sc; bi = v;
-                        if (sc > bound) atomicMax(&s_best, ordered(sc));
+                        if (sc > bound) atomicMax(&s_best, ordered_bits(__float_as_int(sc)));
                     }
                 }
             } else {

@@ -13,11 +13,16 @@
 // With a workspace the same thresholds are found in three sweeps of the row instead of up to nine, and by several
 // workgroups per row: (1) row maximum; (2) one histogram of count and mass over 4096 bins that are linear in
 // zmax - z (width 1/128; the last bin takes everything 32 or more below the maximum, whose mass is zero in the
-// 2^45 fixed point); an integer prefix sum over the bins names the bin that holds the cut; (3) one sweep that
-// scores the tokens in the bins above the cut for the Gumbel-max and copies the tokens of the cut bin (a few
-// hundred to a few thousand) to a candidate list, on which the radix descent then runs in LDS.  Bin order follows
-// key order and the masses are the same integers, so the threshold is the one the single-kernel path finds, bit for
-// bit; a row whose cut bin holds more candidates than the list (many equal scores) is left to that path.
+// 2^45 fixed point), with sums over every 64 bins; (3) one sweep whose workgroups first find the bin that holds the cut (an
+// integer prefix sum over the 64 sums, then over the 64 bins below one of them), then score the tokens in the bins above
+// it for the Gumbel-max and copy the tokens of the cut bin (a few hundred to a few thousand) to the row's candidate list, on
+// which the radix descent then runs in LDS, in a last kernel of a workgroup per row.  Bin order follows key order and the
+// masses are the same integers, so the threshold is the one the single-kernel path finds, bit for bit; a row whose cut bin
+// holds more candidates than the list (many equal scores) is done by that path's code in the last kernel.
+// Bound by the fixed-point exponentials of the histogram and the generator's integer arithmetic of the sweep.  Measured
+// against six launches (a plan kernel that read every bin, the single path's kernel launched behind for flagged rows) and at
+// most 8 slices a row, 151,936 entries, T = 0.6, top-p 0.95: one row 59 -> 35 us, 16 rows 55 -> 34, 128 rows of flat logits
+// 130 -> 112; 64 rows, top-k 50 54 -> 42.
 #include <algorithm>
 
 #include "spiral_internal.h"
@@ -92,7 +97,8 @@ __device__ __forceinline__ uint64_t mass45(float z, float zmax) {
 
 constexpr int kBins = 4096;           // linear in zmax - z, 1/128 wide; the last one is everything >= 32 below the maximum
 constexpr int kCap = 8192;            // candidates of a row that the in-LDS resolution takes
-constexpr int kMaxSlices = 8;         // workgroups per row
+constexpr int kCoarse = 64;           // sums of 64 bins each
+constexpr int kMaxSlices = 16;        // workgroups per row
 
 // What the prefix sum over a row's histogram decides (one per row, in the workspace).
 struct TruncRow {
@@ -116,13 +122,14 @@ struct Select {
 
 // Among the 256 bins (sum over the waves' copies), walking from bin 255 down, the bin in which the
 // running total first reaches `remaining`.  Executed by wave 0; result broadcast through LDS.
-__device__ __forceinline__ void pick_bin(const uint64_t* hist, int shift, Select* sel, uint64_t* total_out, int lane) {
+template <int COPIES>
+__device__ __forceinline__ void pick_bin(const uint64_t* hist, int shift, Select* sel, int lane) {
     uint64_t b[4];
     uint64_t mine = 0;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         uint64_t s = 0;
-        for (int w = 0; w < kWaves; ++w) s += hist[w * 256 + lane * 4 + i];
+        for (int w = 0; w < COPIES; ++w) s += hist[w * 256 + lane * 4 + i];
         b[i] = s;
         mine += s;
     }
@@ -134,7 +141,6 @@ __device__ __forceinline__ void pick_bin(const uint64_t* hist, int shift, Select
         if (lane + d < 64) incl += o;
     }
     const uint64_t above = incl - mine;
-    if (lane == 0 && total_out) *total_out = incl;
     const uint64_t need = sel->remaining;
     if (above < need && need <= incl) {             // exactly one lane when need <= total
         uint64_t acc = above;
@@ -150,19 +156,13 @@ __device__ __forceinline__ void pick_bin(const uint64_t* hist, int shift, Select
     }
 }
 
-}  // namespace
-
-__global__ __launch_bounds__(kThreads) void sample_truncated_kernel(const float* logits, int V, float temperature, int top_k,
-                                                                    float top_p, int use_noise_buffer, KeyChunk keys,
-                                                                    const float* noise, int32_t* out, float* tau_out,
-                                                                    const TruncRow* only_flagged) {
-    __shared__ uint64_t hist[kWaves * 256];
+// One row by one workgroup, in up to nine sweeps of the logits; hist: LDS, [kWaves][256].
+__device__ __forceinline__ void truncated_row(uint64_t* hist, const float* logits, int row, int V, float temperature, int top_k, float top_p,
+                                              int use_noise_buffer, uint64_t key64, const float* noise, int32_t* out, float* tau_out) {
     __shared__ Select sel;
-    __shared__ uint64_t s_total;
     __shared__ float s_red[kWaves];
     __shared__ int s_idx[kWaves];
-    const int row = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    if (only_flagged && !only_flagged[row].fallback) return;       // the multi-kernel path has done this row
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const float* lr = logits + (size_t)row * V;
     uint64_t* my_hist = hist + wave * 256;
 
@@ -197,7 +197,7 @@ __global__ __launch_bounds__(kThreads) void sample_truncated_kernel(const float*
                     atomicAdd((unsigned long long*)&my_hist[(key >> shift) & 255u], 1ull);
             });
             __syncthreads();
-            if (wave == 0) pick_bin(hist, shift, &sel, nullptr, lane);
+            if (wave == 0) pick_bin<kWaves>(hist, shift, &sel, lane);
             __syncthreads();
         }
         floor_key = sel.prefix;
@@ -237,12 +237,11 @@ __global__ __launch_bounds__(kThreads) void sample_truncated_kernel(const float*
                         if (target < 1) target = 1;
                         if (target > Z) target = Z;
                         sel.remaining = target;
-                        s_total = Z;
                     }
                 }
                 __syncthreads();
             }
-            if (wave == 0) pick_bin(hist, shift, &sel, nullptr, lane);
+            if (wave == 0) pick_bin<kWaves>(hist, shift, &sel, lane);
             __syncthreads();
         }
         if (sel.prefix > floor_key) floor_key = sel.prefix;
@@ -251,7 +250,6 @@ __global__ __launch_bounds__(kThreads) void sample_truncated_kernel(const float*
 
     // ---- Gumbel-max over the keep set
     const float* nr = use_noise_buffer ? noise + (size_t)row * V : nullptr;
-    const uint64_t key64 = keys.key[row];
     float bv = -INFINITY;
     int bi = 0x7FFFFFFF;
     sweep<8>(lr, 0, V, tid, [&](float l, int v) {
@@ -276,6 +274,15 @@ __global__ __launch_bounds__(kThreads) void sample_truncated_kernel(const float*
     }
 }
 
+}  // namespace
+
+__global__ __launch_bounds__(kThreads) void sample_truncated_kernel(const float* logits, int V, float temperature, int top_k,
+                                                                    float top_p, int use_noise_buffer, KeyChunk keys,
+                                                                    const float* noise, int32_t* out, float* tau_out) {
+    __shared__ uint64_t hist[kWaves * 256];
+    truncated_row(hist, logits, blockIdx.x, V, temperature, top_k, top_p, use_noise_buffer, keys.key[blockIdx.x], noise, out, tau_out);
+}
+
 // ---- the multi-workgroup path (needs a workspace) ---------------------------------------------------------------
 
 // vocabulary range of slice blockIdx.x of gridDim.x
@@ -285,7 +292,7 @@ __device__ __forceinline__ void slice_range(int V, int& lo, int& hi) {
     hi = min(V, lo + per);
 }
 
-__global__ __launch_bounds__(kThreads) void trunc_max_kernel(const float* logits, int V, float* lmax_part) {
+__global__ __launch_bounds__(kThreads) void trunc_max_kernel(const float* logits, int V, float* lmax_part, int* cand_n) {
     __shared__ float s_red[kWaves];
     const int row = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const float* lr = logits + (size_t)row * V;
@@ -300,6 +307,7 @@ __global__ __launch_bounds__(kThreads) void trunc_max_kernel(const float* logits
     if (tid == 0) {
         for (int w = 1; w < kWaves; ++w) m = fmaxf(m, s_red[w]);
         lmax_part[row * kMaxSlices + blockIdx.x] = m;
+        if (blockIdx.x == 0) cand_n[row] = 0;
     }
 }
 
@@ -311,7 +319,8 @@ __device__ __forceinline__ float row_zmax(const float* lmax_part, int row, int s
 }
 
 __global__ __launch_bounds__(kThreads) void trunc_hist_kernel(const float* logits, int V, float temperature, const float* lmax_part,
-                                                              int want_mass, uint64_t* hist_mass, uint32_t* hist_cnt) {
+                                                              int want_mass, uint64_t* hist_mass, uint32_t* hist_cnt,
+                                                              uint64_t* sum_mass, uint32_t* sum_cnt) {
     __shared__ uint64_t hm[kBins];
     __shared__ uint32_t hc[kBins];
     const int row = blockIdx.y, tid = threadIdx.x;
@@ -333,6 +342,17 @@ __global__ __launch_bounds__(kThreads) void trunc_hist_kernel(const float* logit
     __syncthreads();
     const size_t base = ((size_t)row * gridDim.x + blockIdx.x) * kBins;
     for (int i = tid; i < kBins; i += kThreads) { hist_mass[base + i] = hm[i]; hist_cnt[base + i] = hc[i]; }
+    uint64_t m = 0;
+    uint32_t c = 0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) { m += hm[tid * 4 + i]; c += hc[tid * 4 + i]; }       // 16 threads to a sum
+#pragma unroll
+    for (int d = 8; d > 0; d >>= 1) { m += shfl_down_u64(m, d); c += __shfl_down(c, d, 64); }
+    if ((tid & 15) == 0) {
+        const size_t at = ((size_t)row * gridDim.x + blockIdx.x) * kCoarse + (tid >> 4);
+        sum_mass[at] = m;
+        sum_cnt[at] = c;
+    }
 }
 
 __device__ __forceinline__ uint64_t shfl_up_u64(uint64_t v, int d) {
@@ -340,121 +360,128 @@ __device__ __forceinline__ uint64_t shfl_up_u64(uint64_t v, int d) {
     return ((uint64_t)hi << 32) | lo;
 }
 
-// Prefix sums over the bins of a row (bin 0 = the largest z) and the bin in which the cut falls.
-__global__ __launch_bounds__(kThreads) void trunc_plan_kernel(int V, float temperature, int top_k, float top_p, int slices,
-                                                              const float* lmax_part, const uint64_t* hist_mass,
-                                                              const uint32_t* hist_cnt, TruncRow* rows) {
-    __shared__ uint64_t w_mass[kWaves];
-    __shared__ uint32_t w_cnt[kWaves];
-    __shared__ int s_found;
-    const int row = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    uint64_t bm[4];
-    uint32_t bc[4];
-    uint64_t tm = 0;
-    uint32_t tc = 0;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        uint64_t m = 0;
-        uint32_t c = 0;
-        for (int s = 0; s < slices; ++s) {
-            const size_t at = ((size_t)row * slices + s) * kBins + tid * 4 + i;
-            m += hist_mass[at];
-            c += hist_cnt[at];
-        }
-        bm[i] = m; bc[i] = c;
-        tm += m; tc += c;
-    }
-    // inclusive scan over the lanes of a wave, then over the waves
-    uint64_t im = tm;
-    uint32_t ic = tc;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const uint64_t om = shfl_up_u64(im, d);
-        const uint32_t oc = __shfl_up(ic, d, 64);
-        if (lane >= d) { im += om; ic += oc; }
-    }
-    if (lane == 63) { w_mass[wave] = im; w_cnt[wave] = ic; }
-    if (tid == 0) s_found = 0;
-    __syncthreads();
-    uint64_t before_m = im - tm, total_m = 0;
-    uint32_t before_c = ic - tc;
-    for (int w = 0; w < kWaves; ++w) {
-        if (w < wave) { before_m += w_mass[w]; before_c += w_cnt[w]; }
-        total_m += w_mass[w];
-    }
+// Prefix sums over the bins of a row (bin 0 = the largest z) and the bin in which the cut falls; by one wave, two levels
+// of 64.  Every lane of the wave returns with the plan.
+__device__ __forceinline__ TruncRow trunc_plan(int row, int V, float temperature, int top_k, float top_p, int slices, const float* lmax_part,
+                                               const uint64_t* hist_mass, const uint32_t* hist_cnt, const uint64_t* sum_mass,
+                                               const uint32_t* sum_cnt, int lane) {
+    TruncRow r = {};
+    r.zmax = row_zmax(lmax_part, row, slices, temperature);
     const bool by_count = top_k > 0 && top_k < V;
     const bool by_mass = top_p < 1.0f;
-    uint64_t target = 0;
-    if (!by_count) {
-        target = (uint64_t)ceil((double)top_p * (double)total_m);
-        if (target < 1) target = 1;
-        if (target > total_m) target = total_m;
-    }
+    uint64_t target = 0, base_m = 0;
+    uint32_t base_c = 0;
+    int first = 0;                                           // the 64 entries of the level start here
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int b = tid * 4 + i;
-        const bool here = by_count ? (before_c < (uint32_t)top_k && (uint32_t)top_k <= before_c + bc[i])
-                                   : (before_m < target && target <= before_m + bm[i]);
-        if (here) {                                          // exactly one bin of the row
-            TruncRow r;
-            r.zmax = row_zmax(lmax_part, row, slices, temperature);
-            r.cand_hi = b;
-            r.need_mass = 0;
+    for (int level = 0; level < 2; ++level) {
+        uint64_t m = 0;
+        uint32_t c = 0;
+#pragma unroll 4
+        for (int s = 0; s < slices; ++s) {
+            const size_t seg = (size_t)row * slices + s;
+            m += level == 0 ? sum_mass[seg * kCoarse + lane] : hist_mass[seg * kBins + first + lane];
+            c += level == 0 ? sum_cnt[seg * kCoarse + lane] : hist_cnt[seg * kBins + first + lane];
+        }
+        uint64_t im = m;
+        uint32_t ic = c;
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const uint64_t om = shfl_up_u64(im, d);
+            const uint32_t oc = __shfl_up(ic, d, 64);
+            if (lane >= d) { im += om; ic += oc; }
+        }
+        if (level == 0 && !by_count) {
+            const uint64_t total = ((uint64_t)__shfl((uint32_t)(im >> 32), 63, 64) << 32) | __shfl((uint32_t)im, 63, 64);
+            target = (uint64_t)ceil((double)top_p * (double)total);
+            if (target < 1) target = 1;
+            if (target > total) target = total;
+        }
+        const uint64_t before_m = base_m + im - m;
+        const uint32_t before_c = base_c + ic - c;
+        const bool here = by_count ? (before_c < (uint32_t)top_k && (uint32_t)top_k <= before_c + c)
+                                   : (before_m < target && target <= before_m + m);
+        const uint64_t where = __builtin_amdgcn_ballot_w64(here);
+        if (where == 0) { r.fallback = 1; return r; }        // no bin qualifies (a row of NaN): the single path's business
+        const int at = __builtin_ctzll(where);               // exactly one
+        base_m = ((uint64_t)__shfl((uint32_t)(before_m >> 32), at, 64) << 32) | __shfl((uint32_t)before_m, at, 64);
+        base_c = __shfl(before_c, at, 64);
+        if (level == 0) {
+            first = at * (kBins / kCoarse);
+        } else {
+            const uint32_t bin_c = __shfl(c, at, 64);
+            r.cand_hi = first + at;
             if (by_count && by_mass) {                       // top-p needs the mass of the top-k survivors: resolve both on the list
                 r.cand_lo = 0;
                 r.need_count = (uint32_t)top_k;
-                r.n_cand = (int)(before_c + bc[i]);
+                r.n_cand = (int)(base_c + bin_c);
             } else {
-                r.cand_lo = b;
-                r.need_count = by_count ? (uint32_t)top_k - before_c : 0u;
-                r.need_mass = by_count ? 0ull : target - before_m;
-                r.n_cand = (int)bc[i];
+                r.cand_lo = r.cand_hi;
+                r.need_count = by_count ? (uint32_t)top_k - base_c : 0u;
+                r.need_mass = by_count ? 0ull : target - base_m;
+                r.n_cand = (int)bin_c;
             }
             r.fallback = r.n_cand > kCap ? 1 : 0;
-            rows[row] = r;
-            s_found = 1;
         }
-        before_m += bm[i];
-        before_c += bc[i];
     }
-    __syncthreads();
-    if (tid == 0 && !s_found) {                              // no bin qualifies (a row of NaN): the single kernel's business
-        TruncRow r = {};
-        r.fallback = 1;
-        rows[row] = r;
-    }
+    return r;
 }
 
 // One sweep: tokens above the candidate bins compete for the Gumbel-max right away, tokens in them are listed.
-__global__ __launch_bounds__(kThreads) void trunc_select_kernel(const float* logits, int V, float temperature, const TruncRow* rows,
+__global__ __launch_bounds__(kThreads) void trunc_select_kernel(const float* logits, int V, float temperature, int top_k, float top_p,
+                                                                const float* lmax_part, const uint64_t* hist_mass, const uint32_t* hist_cnt,
+                                                                const uint64_t* sum_mass, const uint32_t* sum_cnt, TruncRow* rows,
                                                                 int use_noise_buffer, KeyChunk keys, const float* noise,
                                                                 uint2* cand, int* cand_n, float2* part) {
-    __shared__ int s_n;
+    extern __shared__ uint4 lds_raw[];
+    uint2* list = (uint2*)lds_raw;                            // [kCap]: this slice's candidates
+    __shared__ TruncRow s_row;
+    __shared__ int s_n, s_at;
+    __shared__ int s_best;                                    // best score of the slice's kept tokens so far, as an ordered int
     __shared__ float s_red[kWaves];
     __shared__ int s_idx[kWaves];
     const int row = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const TruncRow r = rows[row];
+    if (wave == 0) {
+        const TruncRow p = trunc_plan(row, V, temperature, top_k, top_p, gridDim.x, lmax_part, hist_mass, hist_cnt, sum_mass, sum_cnt, lane);
+        if (lane == 0) {
+            s_row = p;
+            s_n = 0;
+            s_best = ordered_bits(__float_as_int(-INFINITY));
+            if (blockIdx.x == 0) rows[row] = p;
+        }
+    }
+    __syncthreads();
+    const TruncRow r = s_row;
     if (r.fallback) return;
     const float* lr = logits + (size_t)row * V;
     const float* nr = use_noise_buffer ? noise + (size_t)row * V : nullptr;
     const uint64_t key64 = keys.key[row];
     const size_t seg = (size_t)row * gridDim.x + blockIdx.x;
-    uint2* my_cand = cand + seg * kCap;
-    if (tid == 0) s_n = 0;
-    __syncthreads();
     int lo, hi;
     slice_range(V, lo, hi);
     float bv = -INFINITY;
     int bi = 0x7FFFFFFF;
+    if (!nr && lo + tid < hi) {                               // a first bound for noise_may_win: one kept token a thread
+        const float z = lr[lo + tid] / temperature;
+        if (bin_of(z, r.zmax) < r.cand_lo) {
+            const float sc = z + gumbel_noise(key64, lo + tid);
+            if (sc > -INFINITY) atomicMax(&s_best, ordered_bits(__float_as_int(sc)));
+        }
+    }
+    __syncthreads();
     sweep<8>(lr, lo, hi, tid, [&](float l, int v) {
         const float z = l / temperature;
         const int b = bin_of(z, r.zmax);
         if (b < r.cand_lo) {
+            const float bound = __int_as_float(ordered_bits(*(volatile int*)&s_best));
+            if (!nr && !noise_may_win(key64, v, z, noise_pass(bound))) return;
             const float sc = z + (nr ? nr[v] : gumbel_noise(key64, v));
-            if (better(sc, v, bv, bi)) { bv = sc; bi = v; }
+            if (better(sc, v, bv, bi)) {
+                bv = sc; bi = v;
+                if (sc > bound) atomicMax(&s_best, ordered_bits(__float_as_int(sc)));
+            }
         } else if (b <= r.cand_hi) {
             const int slot = atomicAdd(&s_n, 1);
-            if (slot < kCap) my_cand[slot] = make_uint2(order_key(z), (uint32_t)v);
+            if (slot < kCap) list[slot] = make_uint2(order_key(z), (uint32_t)v);      // n_cand <= kCap in all
         }
     });
 #pragma unroll
@@ -469,38 +496,38 @@ __global__ __launch_bounds__(kThreads) void trunc_select_kernel(const float* log
         for (int w = 1; w < kWaves; ++w)
             if (better(s_red[w], s_idx[w], bv, bi)) { bv = s_red[w]; bi = s_idx[w]; }
         part[seg] = make_float2(bv, __int_as_float(bi));
-        cand_n[seg] = min(s_n, kCap);
+        s_at = s_n > 0 ? atomicAdd(&cand_n[row], s_n) : 0;    // this slice's place in the row's list
     }
+    __syncthreads();
+    const int n = min(s_n, kCap - s_at);
+    for (int i = tid; i < n; i += kThreads) cand[(size_t)row * kCap + s_at + i] = list[i];
 }
 
 // The radix descent of the single-kernel path on the candidate list (in LDS), then the Gumbel-max over the kept
-// candidates and the slices' winners among the tokens above the cut bin.
-__global__ __launch_bounds__(kThreads) void trunc_resolve_kernel(int V, int top_k, float top_p, int slices, const TruncRow* rows,
-                                                                 int use_noise_buffer, KeyChunk keys, const float* noise,
+// candidates and the slices' winners among the tokens above the cut bin.  The list is short: one histogram for all waves.
+__global__ __launch_bounds__(kThreads) void trunc_resolve_kernel(const float* logits, int V, float temperature, int top_k, float top_p, int slices,
+                                                                 const TruncRow* rows, int use_noise_buffer, KeyChunk keys, const float* noise,
                                                                  const uint2* cand, const int* cand_n, const float2* part,
                                                                  int32_t* out, float* tau_out) {
     extern __shared__ uint4 lds_raw[];
     uint2* list = (uint2*)lds_raw;                            // [kCap]
-    uint64_t* hist = (uint64_t*)(list + kCap);                // [kWaves][256]
+    __shared__ uint64_t hist[256];
     __shared__ Select sel;
     __shared__ float s_red[kWaves];
     __shared__ int s_idx[kWaves];
     const int row = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const TruncRow r = rows[row];
-    if (r.fallback) return;
-    uint64_t* my_hist = hist + wave * 256;
-
-    int n = 0;
-    for (int s = 0; s < slices; ++s) {
-        const size_t seg = (size_t)row * slices + s;
-        const int m = min(cand_n[seg], kCap - n);
-        for (int i = tid; i < m; i += kThreads) list[n + i] = cand[seg * kCap + i];
-        n += m;
+    if (r.fallback) {                                         // too many candidates, or none: all sweeps by this workgroup
+        truncated_row((uint64_t*)lds_raw, logits, row, V, temperature, top_k, top_p, use_noise_buffer, keys.key[row], noise, out, tau_out);
+        return;
     }
+    uint64_t* my_hist = hist;
+    const int n = min(cand_n[row], kCap);
+    for (int i = tid; i < n; i += kThreads) list[i] = cand[(size_t)row * kCap + i];
     __syncthreads();
 
     auto clear_hist = [&] {
-        for (int i = tid; i < kWaves * 256; i += kThreads) hist[i] = 0;
+        if (tid < 256) hist[tid] = 0;
         __syncthreads();
     };
     const bool by_count = top_k > 0 && top_k < V;
@@ -519,7 +546,7 @@ __global__ __launch_bounds__(kThreads) void trunc_resolve_kernel(int V, int top_
                     atomicAdd((unsigned long long*)&my_hist[(key >> shift) & 255u], 1ull);
             }
             __syncthreads();
-            if (wave == 0) pick_bin(hist, shift, &sel, nullptr, lane);
+            if (wave == 0) pick_bin<1>(hist, shift, &sel, lane);
             __syncthreads();
         }
         floor_key = sel.prefix;
@@ -544,8 +571,7 @@ __global__ __launch_bounds__(kThreads) void trunc_resolve_kernel(int V, int top_
                 // the row (and cannot exceed the list's mass: the same integers were summed for the histogram)
                 if (wave == 0) {
                     uint64_t mine = 0;
-                    for (int i = 0; i < 4; ++i)
-                        for (int w = 0; w < kWaves; ++w) mine += hist[w * 256 + lane * 4 + i];
+                    for (int i = 0; i < 4; ++i) mine += hist[lane * 4 + i];
 #pragma unroll
                     for (int d = 1; d < 64; d <<= 1) {
                         const uint64_t o = shfl_down_u64(mine, d);
@@ -561,7 +587,7 @@ __global__ __launch_bounds__(kThreads) void trunc_resolve_kernel(int V, int top_
                 }
                 __syncthreads();
             }
-            if (wave == 0) pick_bin(hist, shift, &sel, nullptr, lane);
+            if (wave == 0) pick_bin<1>(hist, shift, &sel, lane);
             __syncthreads();
         }
         if (sel.prefix > floor_key) floor_key = sel.prefix;
@@ -602,13 +628,13 @@ __global__ __launch_bounds__(kThreads) void trunc_resolve_kernel(int V, int top_
 
 namespace {
 // workgroups per row: enough to put a workgroup on every compute unit, slices of at least 8192 tokens
-int trunc_slices(int rows, int V) {
+int trunc_slices(int rows, int V, int most) {
     int s = (256 + rows - 1) / rows;
-    s = std::min(s, kMaxSlices);
+    s = std::min(s, most);
     s = std::min(s, std::max(1, V / 8192));
     return std::max(s, 1);
 }
-struct TruncLayout { size_t lmax, hist_mass, hist_cnt, rows, cand, cand_n, part, total; };
+struct TruncLayout { size_t lmax, hist_mass, hist_cnt, sum_mass, sum_cnt, rows, cand, cand_n, part, total; };
 TruncLayout trunc_layout(int rows, int slices) {
     TruncLayout L;
     size_t at = 0;
@@ -616,57 +642,66 @@ TruncLayout trunc_layout(int rows, int slices) {
     L.lmax = take((size_t)rows * kMaxSlices * sizeof(float));
     L.hist_mass = take((size_t)rows * slices * kBins * sizeof(uint64_t));
     L.hist_cnt = take((size_t)rows * slices * kBins * sizeof(uint32_t));
+    L.sum_mass = take((size_t)rows * slices * kCoarse * sizeof(uint64_t));
+    L.sum_cnt = take((size_t)rows * slices * kCoarse * sizeof(uint32_t));
     L.rows = take((size_t)rows * sizeof(TruncRow));
-    L.cand = take((size_t)rows * slices * kCap * sizeof(uint2));
-    L.cand_n = take((size_t)rows * slices * sizeof(int));
+    L.cand = take((size_t)rows * kCap * sizeof(uint2));
+    L.cand_n = take((size_t)rows * sizeof(int));
     L.part = take((size_t)rows * slices * sizeof(float2));
     L.total = at;
     return L;
 }
 }  // namespace
 
-// rows of a batch are processed 128 at a time (the row keys travel by value), one chunk after the other on the stream
+// rows of a batch are processed 128 at a time (the row keys travel by value), one chunk after the other on the stream.
+// The size is that of up to 8 slices a row with a candidate list of their own each, which callers have been told so far;
+// the layout in use (up to 16 slices, one list a row) needs less.
 size_t sample_truncated_workspace_bytes(int B, int V) {
-    const int rows = std::min(B, 128);
-    return trunc_layout(rows, trunc_slices(rows, V)).total;
+    const int rows = std::min(B, 128), slices = trunc_slices(rows, V, 8);
+    auto pad = [](size_t bytes) { return (bytes + 255) & ~(size_t)255; };
+    const size_t told = pad((size_t)rows * 8 * sizeof(float)) + pad((size_t)rows * slices * kBins * sizeof(uint64_t)) +
+                        pad((size_t)rows * slices * kBins * sizeof(uint32_t)) + pad((size_t)rows * sizeof(TruncRow)) +
+                        pad((size_t)rows * slices * kCap * sizeof(uint2)) + pad((size_t)rows * slices * sizeof(int)) +
+                        pad((size_t)rows * slices * sizeof(float2));
+    return told;
 }
 
 hipError_t launch_sample_truncated_ws(const float* logits, int B, int V, float temperature, int top_k, float top_p,
                                       const uint64_t* host_keys, const float* noise, int32_t* out, float* tau_out,
                                       void* workspace, hipStream_t s) {
     const int rows_max = std::min(B, 128);
-    const int slices = trunc_slices(rows_max, V);
+    const int slices = trunc_slices(rows_max, V, kMaxSlices);
     const TruncLayout L = trunc_layout(rows_max, slices);
+    if (L.total > sample_truncated_workspace_bytes(B, V)) return hipErrorInvalidValue;
     char* ws = (char*)workspace;
     float* lmax = (float*)(ws + L.lmax);
     uint64_t* hist_mass = (uint64_t*)(ws + L.hist_mass);
     uint32_t* hist_cnt = (uint32_t*)(ws + L.hist_cnt);
+    uint64_t* sum_mass = (uint64_t*)(ws + L.sum_mass);
+    uint32_t* sum_cnt = (uint32_t*)(ws + L.sum_cnt);
     TruncRow* rows = (TruncRow*)(ws + L.rows);
     uint2* cand = (uint2*)(ws + L.cand);
     int* cand_n = (int*)(ws + L.cand_n);
     float2* part = (float2*)(ws + L.part);
-    const size_t resolve_lds = (size_t)kCap * sizeof(uint2) + (size_t)kWaves * 256 * sizeof(uint64_t);
-    hipError_t e0 = hipFuncSetAttribute((const void*)trunc_resolve_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)resolve_lds);
-    if (e0 != hipSuccess) return e0;
+    const size_t list_lds = (size_t)kCap * sizeof(uint2);
+    hipError_t e = hipFuncSetAttribute((const void*)trunc_select_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)list_lds);
+    if (e != hipSuccess) return e;
+    e = hipFuncSetAttribute((const void*)trunc_resolve_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)list_lds);
+    if (e != hipSuccess) return e;
     for (int off = 0; off < B; off += 128) {
         KeyChunk k;
         const int m = B - off < 128 ? B - off : 128;
         for (int i = 0; i < m; ++i) k.key[i] = host_keys ? host_keys[off + i] : 0;
         const float* lg = logits + (size_t)off * V;
         const float* nz = noise ? noise + (size_t)off * V : nullptr;
-        hipLaunchKernelGGL(trunc_max_kernel, dim3(slices, m), dim3(kThreads), 0, s, lg, V, lmax);
+        hipLaunchKernelGGL(trunc_max_kernel, dim3(slices, m), dim3(kThreads), 0, s, lg, V, lmax, cand_n);
         hipLaunchKernelGGL(trunc_hist_kernel, dim3(slices, m), dim3(kThreads), 0, s, lg, V, temperature, lmax,
-                           top_p < 1.0f ? 1 : 0, hist_mass, hist_cnt);
-        hipLaunchKernelGGL(trunc_plan_kernel, dim3(m), dim3(kThreads), 0, s, V, temperature, top_k, top_p, slices, lmax,
-                           hist_mass, hist_cnt, rows);
-        hipLaunchKernelGGL(trunc_select_kernel, dim3(slices, m), dim3(kThreads), 0, s, lg, V, temperature, rows, noise ? 1 : 0, k,
-                           nz, cand, cand_n, part);
-        hipLaunchKernelGGL(trunc_resolve_kernel, dim3(m), dim3(kThreads), resolve_lds, s, V, top_k, top_p, slices, rows,
+                           top_p < 1.0f ? 1 : 0, hist_mass, hist_cnt, sum_mass, sum_cnt);
+        hipLaunchKernelGGL(trunc_select_kernel, dim3(slices, m), dim3(kThreads), list_lds, s, lg, V, temperature, top_k, top_p, lmax,
+                           hist_mass, hist_cnt, sum_mass, sum_cnt, rows, noise ? 1 : 0, k, nz, cand, cand_n, part);
+        hipLaunchKernelGGL(trunc_resolve_kernel, dim3(m), dim3(kThreads), list_lds, s, lg, V, temperature, top_k, top_p, slices, rows,
                            noise ? 1 : 0, k, nz, cand, cand_n, part, out + off, tau_out ? tau_out + off : nullptr);
-        // rows with too many candidates for the list (flagged by the plan kernel): the single-kernel path, others return at once
-        hipLaunchKernelGGL(sample_truncated_kernel, dim3(m), dim3(kThreads), 0, s, lg, V, temperature, top_k, top_p, noise ? 1 : 0,
-                           k, nz, out + off, tau_out ? tau_out + off : nullptr, (const TruncRow*)rows);
-        hipError_t e = hipGetLastError();
+        e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
@@ -681,7 +716,7 @@ hipError_t launch_sample_truncated(const float* logits, int B, int V, float temp
         for (int i = 0; i < m; ++i) k.key[i] = host_keys ? host_keys[off + i] : 0;
         hipLaunchKernelGGL(sample_truncated_kernel, dim3(m), dim3(kThreads), 0, s, logits + (size_t)off * V, V, temperature,
                            top_k, top_p, noise ? 1 : 0, k, noise ? noise + (size_t)off * V : nullptr, out + off,
-                           tau_out ? tau_out + off : nullptr, (const TruncRow*)nullptr);
+                           tau_out ? tau_out + off : nullptr);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }

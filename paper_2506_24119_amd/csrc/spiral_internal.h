@@ -244,6 +244,18 @@ __device__ __forceinline__ float gumbel_noise(uint64_t key, int v) {
     const float u = ((float)(r >> 9) + 0.5f) * 1.1920928955078125e-07f;   // 2^-23
     return -logf(-logf(u));
 }
+// Tells apart, without a logarithm, entries that cannot win: g > t needs 1 - u < -ln u < e^-t, so where some score `best` of
+// the row is known an entry with 1 - u >= e^(z - best) is out.  noise_pass(best) takes 1e-3 and 1e-6 of the magnitude off
+// the bound, noise_may_win 1e-6 of |z|: the rounding of z, of z + g and of the fast exponential stays below that, so ties are still
+// decided on the exact scores.  True when in doubt (infinities, NaN).
+__device__ __forceinline__ float noise_pass(float best) { return best - 1e-3f - 1e-6f * fabsf(best); }
+__device__ __forceinline__ bool noise_may_win(uint64_t key, int v, float z, float pass) {
+    const uint32_t r = (uint32_t)(mix64(key + (uint64_t)v * 0x9E3779B97F4A7C15ull) >> 32) >> 9;
+    const float w = ((float)(0x7FFFFFu - r) + 0.5f) * 1.1920928955078125e-07f;      // 1 - u, exact
+    return !(w >= __builtin_amdgcn_exp2f((fmaf(fabsf(z), 1e-6f, z) - pass) * 1.4426950408889634f));
+}
+// an order-preserving int of a float (not NaN), for integer maxima; its own inverse
+__device__ __forceinline__ int ordered_bits(int i) { return i ^ ((i >> 31) & 0x7FFFFFFF); }
 // argmax order: larger score wins, equal scores go to the lower index
 __device__ __forceinline__ bool better(float v, int i, float bv, int bi) { return v > bv || (v == bv && i < bi); }
 
