@@ -429,8 +429,10 @@ __global__ __launch_bounds__(256) void attn_stream_kernel(AttnArgs a) {
     }
 }
 
-// merge the partial results of one (row, query head) written by attn_stream_kernel
-template <int HD, bool ACT32>
+// Merge the partial results of one (row, query head) written by attn_stream_kernel.  PRE parts are requested at once (past
+// the end: the last one again, not counted): a loop that waits for each costs 0.45 us a part (1,450 tokens in 4-page pieces
+// 10.8 us, eight at a time 3.4).  Four where no pair has more: further requests only repeat the last part.
+template <int HD, bool ACT32, int PRE>
 __global__ __launch_bounds__(HD) void attn_stream_combine_kernel(AttnArgs a) {
     const int r = blockIdx.x, h = blockIdx.y, i = threadIdx.x;
     const int G = a.n_q_heads / a.n_kv_heads, Hkv = a.n_kv_heads;
@@ -441,31 +443,31 @@ __global__ __launch_bounds__(HD) void attn_stream_combine_kernel(AttnArgs a) {
     const int n_parts = last - first + 1;
     const float* base = a.part + (((size_t)r * Hkv + kvh) * a.n_chunks * G + j) * (HD + 2);
     const size_t cstride = (size_t)G * (HD + 2);
-    // the first four parts (nearly always all of them) are requested at once instead of one after the other
-    constexpr int PRE = 4;
-    float pm[PRE], pl[PRE], po[PRE];
+    float M = kNegBig, L = 0.f, O = 0.f;
+    for (int c0 = 0; c0 < n_parts; c0 += PRE) {
+        float pm[PRE], pl[PRE], po[PRE];
 #pragma unroll
-    for (int c = 0; c < PRE; ++c) {
-        const float* src = base + (size_t)(c < n_parts ? c : n_parts - 1) * cstride;
-        pm[c] = src[HD]; pl[c] = src[HD + 1]; po[c] = src[i];
-    }
-    float M = kNegBig;
-#pragma unroll
-    for (int c = 0; c < PRE; ++c)
-        if (c < n_parts) M = fmaxf(M, pm[c]);
-    for (int c = PRE; c < n_parts; ++c) M = fmaxf(M, base[c * cstride + HD]);
-    float L = 0.f, O = 0.f;
-#pragma unroll
-    for (int c = 0; c < PRE; ++c)
-        if (c < n_parts) {
-            const float sc = __builtin_amdgcn_exp2f(pm[c] - M);
-            L += pl[c] * sc;
-            O += po[c] * sc;
+        for (int c = 0; c < PRE; ++c) {
+            const float* src = base + (size_t)min(c0 + c, n_parts - 1) * cstride;
+            pm[c] = src[HD]; pl[c] = src[HD + 1]; po[c] = src[i];
         }
-    for (int c = PRE; c < n_parts; ++c) {
-        const float sc = __builtin_amdgcn_exp2f(base[c * cstride + HD] - M);
-        L += base[c * cstride + HD + 1] * sc;
-        O += base[c * cstride + i] * sc;
+        float m_new = M;
+#pragma unroll
+        for (int c = 0; c < PRE; ++c)
+            if (c0 + c < n_parts) m_new = fmaxf(m_new, pm[c]);
+        if (c0 > 0) {
+            const float sc = __builtin_amdgcn_exp2f(M - m_new);
+            L *= sc;
+            O *= sc;
+        }
+        M = m_new;
+#pragma unroll
+        for (int c = 0; c < PRE; ++c)
+            if (c0 + c < n_parts) {
+                const float sc = __builtin_amdgcn_exp2f(pm[c] - M);
+                L += pl[c] * sc;
+                O += po[c] * sc;
+            }
     }
     ActStore<ACT32>::put(a.out, ((size_t)r * a.n_q_heads + h) * HD + i, O / L);
 }
@@ -481,7 +483,9 @@ static hipError_t stream_impl(const AttnArgs& a, hipStream_t s) {
 
 template <int HD, bool ACT32>
 static hipError_t stream_combine_impl(const AttnArgs& a, hipStream_t s) {
-    hipLaunchKernelGGL((attn_stream_combine_kernel<HD, ACT32>), dim3(a.n_rows, a.n_q_heads), dim3(HD), 0, s, a);
+    const dim3 g(a.n_rows, a.n_q_heads), b(HD);
+    if (a.n_chunks <= 4) hipLaunchKernelGGL((attn_stream_combine_kernel<HD, ACT32, 4>), g, b, 0, s, a);
+    else hipLaunchKernelGGL((attn_stream_combine_kernel<HD, ACT32, 8>), g, b, 0, s, a);
     return hipGetLastError();
 }
 

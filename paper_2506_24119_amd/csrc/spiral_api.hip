@@ -49,12 +49,14 @@ struct Tune {
     int bn_gu = 0;                 // 0: waves per workgroup chosen from the shape
     int bn_down = 0, s_down = 0;
     int bn_lm = 128;
-    int chunk_pages = 16;          // decode attention: least (row, kv head, page) units per workgroup
+    int chunk_pages = 16;          // decode attention: least (row, kv head, page) units per workgroup the partial results are sized for,
+    bool chunk_set = false;        // and used, when set; otherwise fewer where there are too few units to go round
     int attn_wgs = 0;              // workgroups of the decode attention; 0 = 3 per compute unit (its occupancy)
     int frag = 1;                  // 0: ignore spiral_model_repack (weights stay row-major; for A/B measurements)
     int fuse_qkv = 1;              // 0: large-M q/k/v projection and its post-processing as two kernels (for A/B measurements)
     int fail_after = 0;            // test hook: the n-th timed launch from now reports a launch failure instead of running
 };
+constexpr int kDecodePieces = 16;      // partial results of a (row, kv head) pair in a step with few units
 constexpr int kMaxSplit = 16;
 constexpr int kScoreSplits = 64;       // vocabulary ranges of the scoring pass (partial log-sum-exp pairs per row)
 
@@ -110,7 +112,7 @@ static void parse_tune(Tune& t, const char* e) {
                 else if (k == "gu") { t.bn_gu = a; }
                 else if (k == "down") { t.bn_down = a; if (n == 2) t.s_down = b; }
                 else if (k == "lm") { t.bn_lm = a; }
-                else if (k == "chunk") { t.chunk_pages = a; }
+                else if (k == "chunk") { t.chunk_pages = a; t.chunk_set = true; }
                 else if (k == "wgs") { t.attn_wgs = a; }
                 else if (k == "frag") { t.frag = a; }
                 else if (k == "fuse_qkv") { t.fuse_qkv = a; }
@@ -941,6 +943,21 @@ static int decode_impl(spiral_model* m, spiral_kv_pool* p, const int32_t* host_s
             c.total_units = start[B] * m->cfg.n_kv_heads;
             c.units_per_wg = std::max(m->tune.chunk_pages, (c.total_units + wgs - 1) / wgs);
             c.n_slots = decode_slots(m, max_ctx);
+            if (!m->tune.chunk_set && c.units_per_wg == m->tune.chunk_pages) {
+                // Few units (a small batch): as many workgroups as there are pages, up to 16 pieces to a pair.  A workgroup's time
+                // is its chain of dependent steps, of which 16 pages are four per wave: one row of 250 tokens, 4B shape, pieces of
+                // 16 / 8 / 4 / 2 pages 8.8 / 7.0 / 5.9 / 4.1 us; 1,450 tokens in 16 pieces 5.3 us, in 32 9.4.  The larger
+                // number of partial results goes to the q/k/v products' memory, dead by then.
+                const int pages = (max_ctx + kPageTokens - 1) / kPageTokens;
+                const int units = std::max((c.total_units + wgs - 1) / wgs, (pages + kDecodePieces - 1) / kDecodePieces);
+                const int slots = (pages + units - 1) / units + 2;
+                const size_t need = (size_t)B * m->cfg.n_q_heads * slots * (m->cfg.head_dim + 2) * sizeof(float);
+                if (units < c.units_per_wg && need <= (size_t)((char*)w.q - (char*)w.qkv)) {
+                    c.units_per_wg = units;
+                    c.n_slots = slots;
+                    c.w.attn_part = w.qkv;
+                }
+            }
         }
         if (sp) { c.sample = true; c.temperature = sp->temperature; c.out_tokens = sp->dev_out_tokens; }
         return run_layers(c);

@@ -1,0 +1,40 @@
+"""Decode attention of a few rows is cut into up to 16 pieces a (row, kv head) pair, down to single pages, with the partial
+results in borrowed memory.  Contexts around the page and piece boundaries, one row and a few ragged ones, against the oracle
+(bar 3e-2 x per-row logit std) and against the coarse cut (16 pages a workgroup at least): the two differ in the fp32
+merge of the pieces, so by roundings of the half-precision attention output - 2^-11 of a value, in two layers; 1e-2 x std is
+five times what that can add up to over one head's 128 values."""
+import numpy as np
+import pytest
+
+from oracle import decoder as od
+from paper_2506_24119_amd import inputs as si
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("lens", [[1], [15], [16], [17], [255], [256], [257], [272], [513], [1, 40, 300], [700, 3, 16, 129, 250]])
+@pytest.mark.parametrize("dtype", [si.WEIGHT_BF16, si.WEIGHT_FP32])
+def test_pieces_match_the_coarse_cut_and_the_oracle(lens, dtype):
+    import torch
+    from paper_2506_24119_amd import binding as sb
+    hd = 128 if dtype == si.WEIGHT_BF16 else 32
+    g = si.ModelGeometry("pieces", 2, 256, 8, 2, hd, 256, 512, 1e6, qk_norm=True, weight_dtype=dtype)
+    host = si.make_weights(g, seed=21)
+    w = sb.weights_to_device(host)
+    rng = np.random.Generator(np.random.PCG64(sum(lens)))
+    B = len(lens)
+    seqs = [rng.integers(0, g.vocab, n).astype(np.int32) for n in lens]
+    steps = rng.integers(0, g.vocab, (2, B)).astype(np.int32)
+    ids = np.arange(B, dtype=np.int32)
+    got = []
+    for tune in (None, "chunk=16"):
+        sess = sb.Session(g, w, 100, B, 48, max(B, sum(lens)), 720, page_order=si.make_page_order(100, 3), tune=tune)
+        sess.prefill(ids, seqs)
+        got.append([sess.decode_step(ids, torch.from_numpy(s).cuda(), sess.new_logits(B)).cpu().numpy() for s in steps])
+        sess.close()
+    for b, s in enumerate(seqs):
+        want = od.forward_full(g, host, np.concatenate([s, steps[:, b]]), logits_at=np.array([len(s), len(s) + 1]))
+        for k in range(2):
+            std = want[k].std()
+            assert np.abs(got[0][k][b] - want[k]).max() <= 3e-2 * std, (b, k)
+            assert np.abs(got[0][k][b] - got[1][k][b]).max() <= 1e-2 * std, (b, k)
