@@ -32,7 +32,6 @@ typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
 
 constexpr float kNegBig = -1.0e30f;
-constexpr int kShortContext = 64;      // tokens: attn_prefill_short_kernel up to here
 
 // Decode reads every K/V byte once: non-temporal loads keep the stream from displacing q, the block
 // tables and the partial results in L2 (measured: 13 us less per launch at C3, -7 % step time).
@@ -68,16 +67,16 @@ struct PageFrag {
     u32x4 v[HD / 32];     // V: lane = (t/4)*16 + d%16; .xy = 4 tokens of d-tile 2m, .zw = of d-tile 2m+1
 };
 
-template <int HD, bool NT = true>
+template <int HD>
 __device__ __forceinline__ void load_page(PageFrag<HD>& f, const uint16_t* kp, int lane, bool real) {
     // !real: every lane reads the first 16 bytes of the page (a valid address, one cache line)
     const uint16_t* vp = kp + kPageTokens * HD;
     const int off = real ? lane * 8 : 0;
     const int step = real ? 512 : 0;
 #pragma unroll
-    for (int ks = 0; ks < HD / 32; ++ks) f.k[ks] = NT ? KVLOAD((const u32x4*)(kp + ks * step + off)) : *(const u32x4*)(kp + ks * step + off);
+    for (int ks = 0; ks < HD / 32; ++ks) f.k[ks] = KVLOAD((const u32x4*)(kp + ks * step + off));
 #pragma unroll
-    for (int mp = 0; mp < HD / 32; ++mp) f.v[mp] = NT ? KVLOAD((const u32x4*)((real ? vp : kp) + mp * step + off)) : *(const u32x4*)((real ? vp : kp) + mp * step + off);
+    for (int mp = 0; mp < HD / 32; ++mp) f.v[mp] = KVLOAD((const u32x4*)((real ? vp : kp) + mp * step + off));
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -254,82 +253,6 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(AttnArgs a, int qb
 #pragma unroll
             for (int b2 = 0; b2 < 4; ++b2) ActStore<ACT32>::put4(a.out, o_idx + d * 32 + b2 * 8, acc[d][4 * b2] * inv,
                                                                  acc[d][4 * b2 + 1] * inv, acc[d][4 * b2 + 2] * inv, acc[d][4 * b2 + 3] * inv);
-    }
-}
-
-// Short contexts: a wave takes 16 positions of one head and walks the few pages alone, on the 16x16 MFMAs, every operand
-// straight from L2; four adjacent heads a workgroup.  A launch over single pages takes 3.5 us and a little more with every
-// page; the kernel above, with its longer code and its detour through LDS, starts at 5 to 7.  Measured, this / that, 14 runs of
-// 4, 32, 64 and 96 tokens: 0.6B shape 3.5 / 5.8, 5.0 / 6.0, 6.5 / 7.6, 9.7 / 8.2 us; 4B 3.6 / 7.6, 5.2 / 7.7, 8.9 / 8.6, 12.9 / 13.1.
-template <int HD, bool ACT32>
-__global__ __launch_bounds__(256) void attn_prefill_short_kernel(AttnArgs a) {
-    constexpr int KS = HD / 32, MT = HD / 16;
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int li = lane & 15, lg = lane >> 4;
-    const int G = a.n_q_heads / a.n_kv_heads;
-    const int b = blockIdx.z, qb = blockIdx.x;
-    const int h = blockIdx.y * 4 + wave;
-    const int r_first = a.cu_rows[b];
-    const int n_in_seq = a.cu_rows[b + 1] - r_first;
-    if (qb * 16 >= n_in_seq || h >= a.n_q_heads) return;          // no barriers below: waves are independent
-    const int n_valid_rows = min(16, n_in_seq - qb * 16);
-    const int row0 = r_first + qb * 16;
-    const int kvh = h / G;
-    const int seq = a.seq_ids[b];
-    const int pos0 = a.base_pos[b] + qb * 16;
-    const int limit = li < n_valid_rows ? pos0 + li : -1;
-    const int p_end = (pos0 + n_valid_rows - 1) / kPageTokens + 1;
-
-    u32x4 qf[KS];
-    {
-        const uint16_t* qptr = a.q + ((size_t)(row0 + (li < n_valid_rows ? li : 0)) * a.n_q_heads + h) * HD + lg * 8;
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-            const u32x4 v = *(const u32x4*)(qptr + ks * 32);
-            qf[ks] = li < n_valid_rows ? v : u32x4{0u, 0u, 0u, 0u};
-        }
-    }
-    f32x4 acc[MT];
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt) acc[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
-    float m_run = kNegBig, l_run = 0.f;
-
-    const int32_t* bt = a.block_table + (size_t)seq * a.max_blocks;
-    const size_t page_elems = (size_t)a.n_kv_heads * (2 * kPageTokens * HD);
-    const size_t head_off = (size_t)kvh * (2 * kPageTokens * HD);
-    auto step = [&](const PageFrag<HD>& f, int pi) {
-#include "attn_page_step.inc"
-    };
-    {
-        // the next page is in flight while one is consumed; the prefetch is unconditional (past the end it re-reads
-        // one valid 16-byte spot) so that the compiler's wait counts let it stay in flight during the arithmetic
-        PageFrag<HD> cur, nxt;
-        int pi = 0;
-        load_page<HD, false>(cur, a.pages + (size_t)bt[0] * page_elems + head_off, lane, true);
-        while (true) {
-            const int pn = pi + 1;
-            const bool more = pn < p_end;
-            load_page<HD, false>(nxt, a.pages + (size_t)bt[more ? pn : pi] * page_elems + head_off, lane, more);
-            step(cur, pi);
-            if (!more) break;
-            cur = nxt;
-            pi = pn;
-        }
-    }
-
-    // O^T[d][row]: lane (li, lg) holds d = mt * 16 + lg * 4 .. + 3 of row li; l is spread over the four lane groups
-    l_run += __shfl_xor(l_run, 16, 64);
-    l_run += __shfl_xor(l_run, 32, 64);
-    if (li < n_valid_rows) {
-        const float inv = 1.0f / l_run;
-        const size_t o_idx = ((size_t)(row0 + li) * a.n_q_heads + h) * HD + lg * 4;
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt) {
-            ActStore<ACT32>::put(a.out, o_idx + mt * 16 + 0, acc[mt].x * inv);
-            ActStore<ACT32>::put(a.out, o_idx + mt * 16 + 1, acc[mt].y * inv);
-            ActStore<ACT32>::put(a.out, o_idx + mt * 16 + 2, acc[mt].z * inv);
-            ActStore<ACT32>::put(a.out, o_idx + mt * 16 + 3, acc[mt].w * inv);
-        }
     }
 }
 
@@ -593,11 +516,7 @@ hipError_t launch_attn_stream_combine(const AttnArgs& a, int hd, bool act32, hip
 }
 
 template <int HD, bool ACT32>
-static hipError_t prefill_impl(const AttnArgs& a, int B, int max_new, int max_ctx, hipStream_t s) {
-    if (max_ctx <= kShortContext) {
-        hipLaunchKernelGGL((attn_prefill_short_kernel<HD, ACT32>), dim3((max_new + 15) / 16, (a.n_q_heads + 3) / 4, B), dim3(256), 0, s, a);
-        return hipGetLastError();
-    }
+static hipError_t prefill_impl(const AttnArgs& a, int B, int max_new, hipStream_t s) {
     const int G = a.n_q_heads / a.n_kv_heads;
     const int head_groups = (G + 3) / 4, heads_wg = (G + head_groups - 1) / head_groups;      // at most four heads a workgroup
     const int rows_wg = (4 / heads_wg) * 32;
@@ -613,12 +532,12 @@ static hipError_t prefill_impl(const AttnArgs& a, int B, int max_new, int max_ct
     return hipGetLastError();
 }
 
-hipError_t launch_attn_prefill(const AttnArgs& a, int hd, int B, int max_new, int max_ctx, bool act32, hipStream_t s) {
+hipError_t launch_attn_prefill(const AttnArgs& a, int hd, int B, int max_new, bool act32, hipStream_t s) {
     if (B <= 0 || max_new <= 0) return hipErrorInvalidValue;
     switch (hd) {
-        case 32:  return act32 ? prefill_impl<32, true>(a, B, max_new, max_ctx, s) : prefill_impl<32, false>(a, B, max_new, max_ctx, s);
-        case 64:  return act32 ? prefill_impl<64, true>(a, B, max_new, max_ctx, s) : prefill_impl<64, false>(a, B, max_new, max_ctx, s);
-        case 128: return act32 ? prefill_impl<128, true>(a, B, max_new, max_ctx, s) : prefill_impl<128, false>(a, B, max_new, max_ctx, s);
+        case 32:  return act32 ? prefill_impl<32, true>(a, B, max_new, s) : prefill_impl<32, false>(a, B, max_new, s);
+        case 64:  return act32 ? prefill_impl<64, true>(a, B, max_new, s) : prefill_impl<64, false>(a, B, max_new, s);
+        case 128: return act32 ? prefill_impl<128, true>(a, B, max_new, s) : prefill_impl<128, false>(a, B, max_new, s);
     }
     return hipErrorInvalidValue;
 }

@@ -587,7 +587,7 @@ struct StepCtx {
     int rows;            // activation rows
     int B;               // sequences
     bool decode;
-    int max_new, max_ctx;   // prefill: longest appended run, longest resulting context
+    int max_new;         // prefill: longest appended run
     int n_chunks;        // decode: context chunks
     float* logits;
     int total_units = 0, units_per_wg = 0, n_slots = 0;   // decode, stream kernel
@@ -703,7 +703,7 @@ static int run_layers(StepCtx& c) {
             HIP_TRY(timed(m, SPIRAL_K_ATTN_DECODE, c.s, [&] { return launch_attn_stream(aa, hd, act32, c.s); }));
             HIP_TRY(timed(m, SPIRAL_K_ATTN_COMBINE, c.s, [&] { return launch_attn_stream_combine(aa, hd, act32, c.s); }));
         } else {
-            HIP_TRY(timed(m, SPIRAL_K_ATTN_PREFILL, c.s, [&] { return launch_attn_prefill(aa, hd, c.B, c.max_new, c.max_ctx, act32, c.s); }));
+            HIP_TRY(timed(m, SPIRAL_K_ATTN_PREFILL, c.s, [&] { return launch_attn_prefill(aa, hd, c.B, c.max_new, act32, c.s); }));
         }
 
         GemmArgs go = {};
@@ -835,7 +835,7 @@ static int prefill_or_score(spiral_model* m, spiral_kv_pool* p, const int32_t* h
                        w.row_pos, w.rope, (int)rows, m->cfg.d_model, m->cfg.head_dim / 2, m->cfg.vocab, m->cfg.rms_eps,
                        w.row_seq, p->d_block_table, p->max_blocks, w.row_page};
         HIP_TRY(launch_embed_norm(e, m->freq, m->w_bf16, !m->w_bf16, s));
-        StepCtx c = {m, p, w, s, (int)rows, B, false, max_new, max_ctx, 1, dev_logits};
+        StepCtx c = {m, p, w, s, (int)rows, B, false, max_new, 1, dev_logits};
         c.score_targets = dev_targets;
         c.score_out = dev_logp;
         return run_layers(c);
@@ -937,7 +937,7 @@ static int decode_impl(spiral_model* m, spiral_kv_pool* p, const int32_t* host_s
                        w.row_pos, w.rope, B, m->cfg.d_model, m->cfg.head_dim / 2, m->cfg.vocab, m->cfg.rms_eps,
                        w.row_seq, p->d_block_table, p->max_blocks, w.row_page};
         HIP_TRY(launch_embed_norm(e, m->freq, m->w_bf16, !m->w_bf16, s));
-        StepCtx c = {m, p, w, s, B, B, true, 1, max_ctx, decode_chunks(m, max_ctx), dev_logits};
+        StepCtx c = {m, p, w, s, B, B, true, 1, decode_chunks(m, max_ctx), dev_logits};
         {
             const int wgs = m->tune.attn_wgs > 0 ? m->tune.attn_wgs : 3 * m->n_cus;
             c.total_units = start[B] * m->cfg.n_kv_heads;

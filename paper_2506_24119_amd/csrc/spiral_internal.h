@@ -137,7 +137,7 @@ hipError_t launch_gemm_tile_qkv(const GemmArgs& a, const QkvPostArgs& qa, hipStr
 hipError_t launch_gemm_stream(const GemmArgs& a, int epilogue, int bn, hipStream_t s);   // K % 128 == 0, N % 16 == 0
 hipError_t launch_attn_stream(const AttnArgs& a, int hd, bool act32, hipStream_t s);
 hipError_t launch_attn_stream_combine(const AttnArgs& a, int hd, bool act32, hipStream_t s);
-hipError_t launch_attn_prefill(const AttnArgs& a, int hd, int B, int max_new, int max_ctx, bool act32, hipStream_t s);   // max_ctx: longest resulting context
+hipError_t launch_attn_prefill(const AttnArgs& a, int hd, int B, int max_new, bool act32, hipStream_t s);
 
 hipError_t launch_stream_read(const void* p, size_t bytes, int workgroups, hipStream_t s);
 hipError_t launch_sample_pick(const float2* part, int B, int n_tiles, int32_t* out, hipStream_t s);
