@@ -167,9 +167,9 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(AttnArgs a, int qb
     const int k_off = (l32 >> 4) * PAGE_B + lh * 256 + (l32 & 15) * 16;
     const int v_off = PAGE_B / 2 + lh * 256 + (l32 & 15) * 16 + (l32 >> 4) * 8;
 
-    // one step of a wave over the first 32 * NS tokens of the staged 64
-    auto step = [&](const char* buf, int st, auto ns) {
-        constexpr int NS = decltype(ns)::value;
+    // one step of a wave over the first NP pages of the staged four
+    auto step = [&](const char* buf, int st, auto np) {
+        constexpr int NP = decltype(np)::value, NS = (NP + 1) / 2, NR = NP == 1 ? 8 : 16;      // NR: scores of a lane per 32 tokens
         f32x16 s[NS];
 #pragma unroll
         for (int sub = 0; sub < NS; ++sub) {
@@ -185,22 +185,22 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(AttnArgs a, int qb
 #pragma unroll
             for (int sub = 0; sub < NS; ++sub)
 #pragma unroll
-                for (int r = 0; r < 16; ++r)
+                for (int r = 0; r < NR; ++r)
                     if (st * 64 + sub * 32 + 8 * (r >> 2) + 4 * lh + (r & 3) > limit) s[sub][r] = -INFINITY;
         }
         float mx = s[0][0];
 #pragma unroll
         for (int sub = 0; sub < NS; ++sub)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[sub][r]);
+            for (int r = 0; r < NR; ++r) mx = fmaxf(mx, s[sub][r]);
         mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
         const float m_new = fmaxf(m_run, mx * a.scale_log2e);
         float ps = 0.f;
-        u32x4 pb[2 * NS];                                          // P^T of the pages
+        u32x4 pb[NP];                                              // P^T of the pages
 #pragma unroll
         for (int sub = 0; sub < NS; ++sub)
 #pragma unroll
-            for (int b2 = 0; b2 < 4; ++b2) {
+            for (int b2 = 0; b2 < NR / 4; ++b2) {
                 f16x4 h4;
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
@@ -222,7 +222,7 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(AttnArgs a, int qb
         }
         m_run = m_new;
 #pragma unroll
-        for (int pg = 0; pg < 2 * NS; ++pg)
+        for (int pg = 0; pg < NP; ++pg)
 #pragma unroll
             for (int d = 0; d < DT; ++d) {
                 const char* vp = buf + pg * PAGE_B + v_off + d * 1024;
@@ -236,11 +236,9 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(AttnArgs a, int qb
         for (int u = 0; u < LD; ++u) *(u32x4*)(buf + wave * PAGE_B + u * 1024 + lane * 16) = rg[u];
         __syncthreads();            // one barrier a step: the buffer written next was last read before this one
         if (st + 1 < n_stages) load(st + 1);
-        if (st * 64 + 32 > my_last) {
-            if (st * 64 <= my_last) step(buf, st, std::integral_constant<int, 1>());      // nothing of the second 32 tokens is visible
-        } else {
-            step(buf, st, std::integral_constant<int, 2>());
-        }
+        if (st * 64 + 32 <= my_last) step(buf, st, std::integral_constant<int, 4>());
+        else if (st * 64 + 16 <= my_last) step(buf, st, std::integral_constant<int, 2>());
+        else if (st * 64 <= my_last) step(buf, st, std::integral_constant<int, 1>());
     }
 
     // O^T[d][row]: lane (l32, lh) holds d = 32 dt + 8 b + 4 lh .. + 3 of row l32; l is spread over the two lane halves
