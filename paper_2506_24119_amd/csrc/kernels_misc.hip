@@ -487,17 +487,30 @@ hipError_t launch_repack(const void* src0, const void* src1, const void* src2, i
 
 // ---------------------------------------------------------------------------------------------
 // Gumbel-max sampler: token = argmax_v(logit_v / T + g_v), lowest index on ties; T == 0 => greedy.
-// A row is cut into slices of at least 8192 entries, one workgroup each, about one workgroup per compute unit in all (a
+// A long row is cut into slices of at least 8192 entries, one workgroup each, about one workgroup per compute unit in all (a
 // workgroup per row leaves half of them idle at 128 rows and 255 at one; two or four per unit took 37 and 42 us instead
-// of 33 at 128 rows; below 16384 entries the second launch costs more than the split gives).  There is no scratch
-// memory to merge the slices in: a slice's winner is an index, and its score can be computed again from the index, so the
-// slices compete for out[row] by compare-and-swap on the index.  The order (score, then index) is total, so the result
-// does not depend on who comes first; out[row] starts as 0, which a NaN at index 0 does not defend.
-// Bound by the generator's 64-bit arithmetic.  Most entries cannot win and are told apart without a logarithm
+// of 33 at 128 rows of 151,936).  There is no scratch memory to merge the slices in: a slice's winner is an index, and its score
+// can be computed again from the index, so the slices compete for out[row] by compare-and-swap on the index.  The order (score,
+// then index) is total, so the result does not depend on who comes first; out[row] starts as 0, which a NaN at index 0 does
+// not defend.
+// Bound by the generator's 64-bit arithmetic.  In a long slice most entries cannot win and are told apart without a logarithm
 // (noise_may_win, with the best score any thread has found so far; the product with 1/T stands for the division there).
-// Measured with 151,936 entries against a workgroup per row and two logarithms per entry: 128 rows, T = 1 77 -> 33 us, greedy
-// 30 -> 18; 16 rows 75 -> 21; one row 73 -> 14.
+// Measured with 151,936 entries against a workgroup per row and two logarithms per entry: 128 rows, T = 1 77 -> 34 us, greedy
+// 30 -> 19; 16 rows 75 -> 18 and 27 -> 14; one row 74 -> 14 and 27 -> 14.
 // ---------------------------------------------------------------------------------------------
+// Where a row is cut: the launch that sets out[row] costs 3 us.  One workgroup per row against slices (us, one and 128 rows; a
+// call does not get below 11 from the host): greedy 65,536 entries 10.6 / 10.3 against 13.3 / 13.3, 98,304 13.2 / 15.2
+// against 13.9 / 14.0; a noise buffer 40,000 10.7 / 17.7 against 13.6 / 15.8, 49,152 12.1 / 21.1 against 14.1 / 18.4;
+// generated noise 20,000 12.6 / 13.4 against 13.8 / 13.8, 28,000 16.3 / 17.0 against 13.8 / 14.4.
+int sample_slices(int rows, int V, int mode) {
+    const int from = mode == 0 ? 98304 : (mode == 2 ? 49152 : 24576);
+    return V < from ? 1 : std::max(1, std::min((256 + rows - 1) / rows, V / 8192));
+}
+// Where the screen pays for its first bound (one entry a thread in full, two barriers): slices of 4,000 entries 47 us without,
+// 70 with it (1,024 rows), 9,496 17.6 and 20.4 (16 rows), 16,384 15.2 and 16.7 (128 rows), 24,576 19.0 and 18.4, 75,968
+// 43.4 and 33.6.
+bool sample_screens(int per_slice) { return per_slice >= 20480; }
+
 constexpr int kSampleThreads = 1024;
 
 // mode 0: greedy; 1: generated noise; 2: noise buffer
@@ -512,7 +525,7 @@ __global__ void sample_begin_kernel(int32_t* out, int n) {
     if (i < n) out[i] = 0;
 }
 
-template <int MODE>
+template <int MODE, bool SCREEN>
 __global__ __launch_bounds__(kSampleThreads) void sample_kernel(const float* logits, int V, float temperature, int per_slice,
                                                                 KeyChunk keys, const float* noise, int32_t* out) {
     constexpr int NT = kSampleThreads, U = 8;
@@ -528,7 +541,7 @@ __global__ __launch_bounds__(kSampleThreads) void sample_kernel(const float* log
     int bi = 0x7FFFFFFF;
     float bound = -INFINITY, pass = -INFINITY;   // a score of the row that an entry has to beat, and that less its slack
     const float inv_t = 1.0f / temperature;
-    if (MODE == 1) {
+    if (SCREEN) {
         if (tid == 0) s_best = ordered_bits(__float_as_int(-INFINITY));
         __syncthreads();
         const int v = lo + tid;                  // one entry a thread in full: a first bound (they are visited again below)
@@ -544,7 +557,7 @@ __global__ __launch_bounds__(kSampleThreads) void sample_kernel(const float* log
         float l[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) l[u] = lr[min(base + u * NT, hi - 1)];
-        if (MODE == 1) {
+        if (SCREEN) {
             bound = __int_as_float(ordered_bits(*(volatile int*)&s_best));
             pass = noise_pass(bound);
         }
@@ -552,7 +565,7 @@ __global__ __launch_bounds__(kSampleThreads) void sample_kernel(const float* log
         for (int u = 0; u < U; ++u) {
             const int v = base + u * NT;
             if (v >= hi) continue;
-            if (MODE == 1) {
+            if (SCREEN) {
                 if (noise_may_win(key, v, l[u] * inv_t, pass)) {
                     const float sc = l[u] / temperature + gumbel_noise(key, v);
                     if (better(sc, v, bv, bi)) {
@@ -561,7 +574,8 @@ __global__ __launch_bounds__(kSampleThreads) void sample_kernel(const float* log
                     }
                 }
             } else {
-                const float sc = MODE == 0 ? l[u] : l[u] / temperature + nr[v];
+                float sc = l[u];
+                if (MODE != 0) sc = sc / temperature + (MODE == 2 ? nr[v] : gumbel_noise(key, v));
                 if (better(sc, v, bv, bi)) { bv = sc; bi = v; }
             }
         }
@@ -599,15 +613,16 @@ hipError_t launch_sample(const float* logits, int B, int V, float temperature, c
         KeyChunk k;
         const int m = B - off < 128 ? B - off : 128;
         for (int i = 0; i < m; ++i) k.key[i] = host_keys ? host_keys[off + i] : 0;
-        const int slices = std::max(1, std::min((256 + m - 1) / m, V / 8192));
+        const int slices = sample_slices(m, V, mode);
         const int per = (V + slices - 1) / slices;
         const dim3 g((V + per - 1) / per, m), b(kSampleThreads);
         const float* lg = logits + (size_t)off * V;
         const float* nz = noise ? noise + (size_t)off * V : nullptr;
         if (g.x > 1) hipLaunchKernelGGL(sample_begin_kernel, dim3((m + 255) / 256), dim3(256), 0, s, out + off, m);
-        if (mode == 0) hipLaunchKernelGGL(sample_kernel<0>, g, b, 0, s, lg, V, temperature, per, k, nz, out + off);
-        else if (mode == 1) hipLaunchKernelGGL(sample_kernel<1>, g, b, 0, s, lg, V, temperature, per, k, nz, out + off);
-        else hipLaunchKernelGGL(sample_kernel<2>, g, b, 0, s, lg, V, temperature, per, k, nz, out + off);
+        if (mode == 0) hipLaunchKernelGGL((sample_kernel<0, false>), g, b, 0, s, lg, V, temperature, per, k, nz, out + off);
+        else if (mode == 2) hipLaunchKernelGGL((sample_kernel<2, false>), g, b, 0, s, lg, V, temperature, per, k, nz, out + off);
+        else if (sample_screens(per)) hipLaunchKernelGGL((sample_kernel<1, true>), g, b, 0, s, lg, V, temperature, per, k, nz, out + off);
+        else hipLaunchKernelGGL((sample_kernel<1, false>), g, b, 0, s, lg, V, temperature, per, k, nz, out + off);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
     }

@@ -1,0 +1,37 @@
+"""The rules that choose a launch form from sizes, read from the library on the CPU (no GPU work): calls that one form serves
+faster must not be sent to another."""
+import ctypes as C
+
+import pytest
+
+
+@pytest.fixture(scope="module")
+def lib():
+    from paper_2506_24119_amd import binding
+    return binding.load_library()
+
+
+def rule(lib, mangled, restype, *argtypes):
+    f = lib[mangled]
+    f.restype, f.argtypes = restype, list(argtypes)
+    return f
+
+
+GREEDY, GENERATED, BUFFER = 0, 1, 2
+
+
+def test_short_rows_of_the_categorical_sampler_stay_in_one_workgroup(lib):
+    """Cutting a row costs a second launch (3 us): one workgroup a row is faster for greedy rows of 65,536 entries, buffered
+    noise of 40,000 and generated noise of 20,000, whatever the number of rows."""
+    slices = rule(lib, "_ZN6spiral13sample_slicesEiii", C.c_int, C.c_int, C.c_int, C.c_int)
+    for rows in (1, 16, 72, 128):
+        for mode, longest in ((GREEDY, 65536), (BUFFER, 40000), (GENERATED, 20000)):
+            assert all(slices(rows, V, mode) == 1 for V in (1, 500, 4000, 16384, 20000, longest) if V <= longest)
+        for mode in (GREEDY, GENERATED, BUFFER):
+            assert slices(rows, 151936, mode) > 1 and slices(rows, 151936, mode) * 8192 <= 151936
+
+
+def test_short_slices_are_not_screened(lib):
+    """The screen visits one entry a thread in full first: 1.5 times the time at 4,000 entries, a gain from 24,576 on."""
+    screens = rule(lib, "_ZN6spiral14sample_screensEi", C.c_bool, C.c_int)
+    assert not any(screens(n) for n in (1, 4000, 9496, 16384)) and all(screens(n) for n in (24576, 75968))
