@@ -4,13 +4,14 @@
 // With fragment-ordered weights the LM head is the 256 x 256 tiled kernel with a scoring epilogue (gemm_tile_kernel<3>),
 // which leaves one (max, sum of exp) pair per row and 128 columns for score_merge_pairs_kernel.
 //
-// Without them: score_lmhead_kernel is the LM-head GEMM of the decode path (32x32x16 MFMA, weights HBM/L2 ->
-// registers in operand layout, activations through LDS) with another epilogue: a workgroup owns 128
-// rows and a range of 128-column vocabulary tiles.  PAIRS: after each tile the four waves, 32 columns each, fold
-// their logits in the tiled kernel's order (same bits) and write its pair.  Otherwise (a vocabulary whose pairs do not fit
-// the workspace, with any weights): every lane folds its 16 logits of each row into a private running pair over the whole
-// range, the pairs of a row (2 lanes x 4 waves) are merged through LDS and written as one partial per (row, range);
-// score_merge_kernel combines the ranges:
+// Without them, or where that kernel's 32-bit offsets or the memory for its pairs do not suffice: score_lmhead_kernel is the
+// LM-head GEMM of the decode path (32x32x16 MFMA, weights HBM/L2 -> registers in operand layout, activations through LDS)
+// with another epilogue: a workgroup owns 128 rows and a range of 128-column vocabulary tiles.  FRAG: the weights come from
+// the fragment-ordered copy (rows of narrow-head models, 800 and 6,000 of them, score 8 to 11 % slower from the row-major one).
+// PAIRS: after each tile the four waves, 32 columns each, fold their logits in the tiled kernel's order (same bits) and
+// write its pair.  Otherwise (a vocabulary whose pairs do not fit the workspace, with any weights): every lane folds its 16
+// logits of each row into a private running pair over the whole range, the pairs of a row (2 lanes x 4 waves) are merged
+// through LDS and written as one partial per (row, range); score_merge_kernel combines the ranges:
 //     logp = logit[target] - (M + ln sum_i s_i * exp(m_i - M)).
 // score_objective_kernel evaluates the clipped importance-ratio surrogate and the REINFORCE sum in
 // float64 with a fixed reduction order.
@@ -33,7 +34,7 @@ constexpr int PD = 2;
 
 }  // namespace
 
-template <bool PAIRS>
+template <bool PAIRS, bool FRAG>
 __global__ __launch_bounds__(256) void score_lmhead_kernel(ScoreArgs g) {
     extern __shared__ uint4 lds_raw[];
     char* lds = (char*)lds_raw;
@@ -75,7 +76,8 @@ __global__ __launch_bounds__(256) void score_lmhead_kernel(ScoreArgs g) {
     for (int nt = nt_begin; nt < nt_end; ++nt) {
         const int n_first = nt * 128 + wave * 32;
         int n = n_first + l32; if (n >= g.V) n = g.V - 1;
-        const uint16_t* wrow = (const uint16_t*)g.W + (size_t)n * K + lh * 8;
+        const uint16_t* wrow = FRAG ? (const uint16_t*)g.Wf + frag_block(min(nt * 4 + wave, (g.V + 31) / 32 - 1), 0, K) + lane * 8
+                                    : (const uint16_t*)g.W + (size_t)n * K + lh * 8;
 
         f32x16 acc[4];
 #pragma unroll
@@ -90,7 +92,8 @@ __global__ __launch_bounds__(256) void score_lmhead_kernel(ScoreArgs g) {
 #pragma unroll
             for (int i = 0; i < 8; ++i) S.a[i] = *(const u32x4*)(a_src[i] + off);
 #pragma unroll
-            for (int ks = 0; ks < 8; ++ks) S.w[ks] = *(const u32x4*)(wrow + off + ks * 16);
+            for (int ks = 0; ks < 8; ++ks)
+                S.w[ks] = FRAG ? *(const u32x4*)(wrow + ((size_t)cc * 8 + ks) * 512) : *(const u32x4*)(wrow + off + ks * 16);
         };
         auto iter = [&](St& S, int c) {
             char* buf = lds + (c & 1) * BUF;
@@ -107,7 +110,7 @@ __global__ __launch_bounds__(256) void score_lmhead_kernel(ScoreArgs g) {
                     for (int t = 0; t < 4; ++t)
                         af[(ks + 1) & 1][t] = *(const u32x4*)(buf + frag_off + t * 32 * ROWB + (ks + 1) * 32);
                 }
-                const u32x4 wp = prep_w(S.w[ks]);
+                const u32x4 wp = FRAG ? S.w[ks] : prep_w(S.w[ks]);      // fragment-ordered copies are already widened
 #pragma unroll
                 for (int t = 0; t < 4; ++t) acc[t] = mma32s(wp, af[ks & 1][t], acc[t]);
             }
@@ -301,8 +304,12 @@ hipError_t launch_score(const ScoreArgs& a, float* out, hipStream_t s) {
     if (a.M < 1 || a.V < 1 || (a.K & 127) || a.n_splits < 1 || a.tiles_per_split < 1) return hipErrorInvalidValue;
     ScoreArgs g = a;
     g.m_tiles = (a.M + 127) / 128;
-    if (g.pairs) hipLaunchKernelGGL(score_lmhead_kernel<true>, dim3(g.m_tiles * g.n_splits), dim3(256), (size_t)2 * BUF, s, g);
-    else hipLaunchKernelGGL(score_lmhead_kernel<false>, dim3(g.m_tiles * g.n_splits), dim3(256), (size_t)2 * BUF, s, g);
+    const dim3 grid(g.m_tiles * g.n_splits), b(256);
+    const size_t lds = (size_t)2 * BUF;
+    if (g.pairs && g.Wf) hipLaunchKernelGGL((score_lmhead_kernel<true, true>), grid, b, lds, s, g);
+    else if (g.pairs) hipLaunchKernelGGL((score_lmhead_kernel<true, false>), grid, b, lds, s, g);
+    else if (g.Wf) hipLaunchKernelGGL((score_lmhead_kernel<false, true>), grid, b, lds, s, g);
+    else hipLaunchKernelGGL((score_lmhead_kernel<false, false>), grid, b, lds, s, g);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (g.pairs) return launch_score_merge_pairs(g, out, s);

@@ -613,6 +613,15 @@ static float wide_shape(int M, int N, int K, int most, int& bn, int& splits) {
     return best;
 }
 
+namespace spiral {
+// The scoring pass's pairs (one per row and 128 columns) go where every product of the layers is dead by then: from qkv to mlp
+// in carve()'s order.  By the bytes of a row, so that the choice does not depend on the number of rows.
+bool score_pairs_fit(int vocab, int d, int ffn, int q_width, int kv_width) {
+    const size_t row = (size_t)(q_width + 2 * kv_width) * 4 + (size_t)q_width * 2 + (size_t)q_width * 2 + (size_t)d * 4 + (size_t)ffn * 2;
+    return (size_t)((vocab + 127) / 128) * sizeof(float2) <= row;
+}
+}  // namespace spiral
+
 static int run_layers(StepCtx& c) {
     spiral_model* m = c.m;
     const spiral_model_config& cfg = m->cfg;
@@ -737,13 +746,13 @@ static int run_layers(StepCtx& c) {
         HIP_TRY(timed(m, SPIRAL_K_NORM, c.s, [&] { return launch_add_norm(na, act32, c.s); }));
         const int n_tiles = (cfg.vocab + 127) / 128;
         ScoreArgs sa = {};
-        sa.A = c.w.h; sa.W = m->w[2]; sa.targets = c.score_targets; sa.part = c.w.score_part; sa.tgt_logit = c.w.score_tgt;
+        sa.A = c.w.h; sa.W = m->w[2]; sa.Wf = m->f_lm; sa.targets = c.score_targets; sa.part = c.w.score_part; sa.tgt_logit = c.w.score_tgt;
         sa.M = c.rows; sa.V = cfg.vocab; sa.K = d;
         sa.tiles_per_split = (n_tiles + kScoreSplits - 1) / kScoreSplits;
         sa.n_splits = (n_tiles + sa.tiles_per_split - 1) / sa.tiles_per_split;
-        // One pair per row and 128 columns, in the q/k/v products' memory, which nothing reads any more; a geometry whose
-        // vocabulary is so large against its heads that they do not fit keeps running pairs per vocabulary range.
-        if ((size_t)n_tiles * sizeof(float2) <= (size_t)nqkv * sizeof(float)) {
+        // One pair per row and 128 columns, in the products' memory, which nothing reads any more; a geometry whose
+        // vocabulary is so large against its widths that they do not fit keeps running pairs per vocabulary range.
+        if (score_pairs_fit(cfg.vocab, d, cfg.ffn_dim, qw, kw)) {
             sa.pairs = (float2*)c.w.qkv;
             GemmArgs gs = {};
             gs.A = c.w.h; gs.wf = m->f_lm; gs.rows[0] = cfg.vocab; gs.M = c.rows; gs.N = cfg.vocab; gs.K = d; gs.splits = 1;

@@ -159,12 +159,14 @@ hipError_t launch_repack(const void* src0, const void* src1, const void* src2, i
 struct ScoreArgs {
     const void* A;            // act [M][K]: final-normed hidden states
     const void* W;            // bf16 [V][K] LM head
+    const void* Wf;           // or null: the LM head in fragment order
     const int32_t* targets;   // [M] target token of each row, < 0: none
     float* part;              // [M][n_splits] (max, sum exp) pairs
     float* tgt_logit;         // [M]
     int32_t M, V, K, n_splits, tiles_per_split, m_tiles;
     float2* pairs;            // or null: [ceil(V / 128)][M] (max, sum exp) pairs instead of `part`
 };
+bool score_pairs_fit(int vocab, int d, int ffn, int q_width, int kv_width);             // ... in the layers' dead products
 hipError_t launch_score_merge_pairs(const ScoreArgs& a, float* out, hipStream_t s);        // a.pairs, a.targets, a.tgt_logit -> out
 hipError_t launch_score(const ScoreArgs& a, float* out, hipStream_t s);
 hipError_t launch_gemm_tile_score(const GemmArgs& a, hipStream_t s);       // writes a.s_part: [ceil(N / 128)][M] pairs

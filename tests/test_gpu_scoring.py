@@ -150,11 +150,12 @@ def test_full_size_scoring_c3_shape(sb):
     sess.close()
 
 
-@pytest.mark.parametrize("rows,heads,vocab", [(1, 8, 1000), (255, 8, 1000), (257, 8, 1000), (300, 8, 1100), (70, 1, 30000)])
+@pytest.mark.parametrize("rows,heads,vocab", [(1, 8, 1000), (255, 8, 1000), (257, 8, 1000), (300, 8, 1100), (70, 1, 30000), (70, 1, 70000), (300, 1, 70000)])
 def test_tiled_and_streaming_lm_head_agree(sb, rows, heads, vocab):
     """The LM head on fragment-ordered weights (256 x 256 tiles) against the row-major one, around the edges of the row
     tile and with a last column tile that is partly padding: the same products folded in the same order, so the same
-    bits; and with a vocabulary whose pairs do not fit the workspace (the streaming kernel with either weights)."""
+    bits; and with a vocabulary of 70,000 against one head, whose pairs do not fit the products' memory (the streaming kernel
+    with running pairs, with either weights)."""
     g = si.ModelGeometry("edge", 1, 256, heads, min(heads, 2), 128, 384, vocab, 1e6, qk_norm=True)
     w = sb.weights_to_device(si.make_weights(g, seed=7))
     seq = [np.random.Generator(np.random.PCG64(rows)).integers(0, g.vocab, rows).astype(np.int32)]

@@ -35,3 +35,11 @@ def test_short_slices_are_not_screened(lib):
     """The screen visits one entry a thread in full first: 1.5 times the time at 4,000 entries, a gain from 24,576 on."""
     screens = rule(lib, "_ZN6spiral14sample_screensEi", C.c_bool, C.c_int)
     assert not any(screens(n) for n in (1, 4000, 9496, 16384)) and all(screens(n) for n in (24576, 75968))
+
+
+def test_scoring_pairs_of_narrow_head_models_fit(lib):
+    """The tiled LM head of the scoring pass needs a pair per row and 128 columns; a vocabulary of 151,936 on 12 + 2 + 2 heads of 128
+    or 14 + 2 + 2 of 64 leaves room for them in the layers' products.  70,000 entries on one head of a 256-wide model do not."""
+    fit = rule(lib, "_ZN6spiral15score_pairs_fitEiiiii", C.c_bool, *[C.c_int] * 5)
+    assert fit(151936, 1536, 8960, 12 * 128, 2 * 128) and fit(151936, 896, 4864, 14 * 64, 2 * 64)
+    assert fit(30000, 256, 384, 128, 128) and not fit(70000, 256, 384, 128, 128)
