@@ -115,7 +115,8 @@ int spiral_model_repack(spiral_model* m, void* dev_buffer, size_t bytes, void* s
 
 /* Measurement / test hook: overrides the launch decomposition the library would choose from the geometry.
  * spec is a comma-separated list of key=value items (unknown keys are ignored): "qkv=R:S", "o=R:S", "down=R:S"
- * (weight rows per workgroup : K splits of that projection), "gu=R", "lm=R", "chunk=P" (least pages per
+ * (weight rows per workgroup : K splits of that projection; above 128 rows as many splits as the workspace holds,
+ * one where S is not given), "gu=R", "lm=R", "chunk=P" (least pages per
  * decode-attention workgroup), "wgs=N" (workgroups of the decode attention), "frag=0|1" (use the repacked weights),
  * "fuse_qkv=0|1" (large row counts: q/k/v post-processing inside the projection kernel or as its own kernel),
  * "fail_after=N" (error-path tests: the N-th

@@ -650,7 +650,13 @@ static int run_layers(StepCtx& c) {
     Shape sh_o = shape(t.bn_o, t.s_o, d, qw), sh_down = shape(t.bn_down, t.s_down, d, cfg.ffn_dim);
     // More than 128 rows: the row tiles of O and down still leave compute units idle up to a few thousand rows, so their K
     // is split too.  The partial sums go where the layer's other products are dead by then (the workspace is carved in the
-    // order qkv, q, o, proj, mlp, hf): O has qkv and q, or proj and mlp; down has everything before mlp.
+    // order qkv, q, o, proj, mlp, hf): O has qkv and q, or proj and mlp; down has everything before mlp.  A projection whose
+    // rows or splits were set by spiral_model_tune keeps them, as far as the memory holds the partial sums.
+    auto wide_or_set = [&](int set_bn, int set_s, int N, int K, size_t most, Shape& sh) {
+        const int cap = (int)std::min<size_t>(most, kMaxSplit);
+        if (set_bn || set_s) sh.splits = std::max(1, std::min({set_s, cap, K / 128}));
+        else wide_shape(c.rows, N, K, cap, sh.bn, sh.splits);
+    };
     float *part_o = c.w.proj, *part_down = c.w.proj;
     bool fuse_qkv = false;              // the q/k/v projection's epilogue does the post-processing, its product never reaches memory
     if (c.rows > 128 && !act32) {
@@ -658,8 +664,8 @@ static int run_layers(StepCtx& c) {
         const size_t front = ((char*)c.w.o - (char*)c.w.qkv) / product, back = ((char*)c.w.hf - (char*)c.w.proj) / product;
         if (front > back) part_o = c.w.qkv;
         part_down = c.w.qkv;
-        wide_shape(c.rows, d, qw, (int)std::min<size_t>(std::max(front, back), kMaxSplit), sh_o.bn, sh_o.splits);
-        wide_shape(c.rows, d, cfg.ffn_dim, (int)std::min<size_t>(((char*)c.w.mlp - (char*)c.w.qkv) / product, kMaxSplit), sh_down.bn, sh_down.splits);
+        wide_or_set(t.bn_o, t.s_o, d, qw, std::max(front, back), sh_o);
+        wide_or_set(t.bn_down, t.s_down, d, cfg.ffn_dim, ((char*)c.w.mlp - (char*)c.w.qkv) / product, sh_down);
     }
     if (c.rows > 128 && !act32 && sh_qkv.bn != 1) {
         // the fused form against a projection split along K (its partials fill the product's own memory, which holds at least
@@ -668,10 +674,12 @@ static int run_layers(StepCtx& c) {
         const int most = (int)std::min<size_t>(((char*)c.w.q - (char*)c.w.qkv) / ((size_t)c.rows * nqkv * sizeof(float)), kMaxSplit);
         QkvPostArgs qs = {};
         qs.hd = hd; qs.n_q_heads = cfg.n_q_heads; qs.n_kv_heads = cfg.n_kv_heads;
-        int bn = 128, splits = 1;
-        const float split_us = wide_shape(c.rows, nqkv, d, most, bn, splits) + 5.f + 2.55e-6f * (float)c.rows * (float)nqkv;
-        if (t.fuse_qkv && gemm_tile_qkv_fits(nqkv, d, qs) && gemm_tile_qkv_us(c.rows, nqkv, d) <= split_us) fuse_qkv = true;
-        else { sh_qkv.bn = bn; sh_qkv.splits = splits; }
+        Shape sh = {128, 1};
+        const float split_us = wide_shape(c.rows, nqkv, d, most, sh.bn, sh.splits) + 5.f + 2.55e-6f * (float)c.rows * (float)nqkv;
+        const bool set = t.bn_qkv || t.s_qkv;
+        if (t.fuse_qkv && t.s_qkv <= 1 && gemm_tile_qkv_fits(nqkv, d, qs) && gemm_tile_qkv_us(c.rows, nqkv, d) <= split_us) fuse_qkv = true;
+        else if (set) sh_qkv.splits = std::max(1, std::min({t.s_qkv, most, d / 128}));
+        else sh_qkv = sh;
     }
     const int s_qkv = sh_qkv.splits, s_o = sh_o.splits, s_down = sh_down.splits;
     const float* part = c.w.proj;       // the partials waiting to be added to the residual

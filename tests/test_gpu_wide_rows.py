@@ -37,3 +37,25 @@ def test_row_counts_around_the_tiles(rows, head_dim, q_heads):
         for k in range(2):
             ratio = np.abs(got[0][k][b] - want[k]).max() / want[k].std()
             assert ratio <= 3e-2, (b, k, ratio)
+
+
+@pytest.mark.parametrize("key", ["o", "down", "qkv"])
+def test_tuned_splits_reach_calls_of_many_rows(key):
+    """spiral_model_tune "key=R:S" above 128 rows: one and three K splits of a projection add in different orders, so some
+    logit differs in its last bits (all of them would be equal if the setting were dropped), and both stay within the bar."""
+    from paper_2506_24119_amd import binding as sb
+    g = si.ModelGeometry("wide", 2, 1024, 8, 2, 64, 2048, 512, 1e6)
+    host = si.make_weights(g, seed=11)
+    w = sb.weights_to_device(host)
+    seqs = si.make_prompts(g.vocab, 3, 90, 120, seed=8)
+    ids = np.arange(3, dtype=np.int32)
+    got = []
+    for splits in (1, 3):
+        sess = sb.Session(g, w, 80, 3, 40, 400, 400, page_order=si.make_page_order(80, 4), tune=f"{key}=128:{splits}")
+        got.append(sess.prefill(ids, seqs).cpu().numpy())
+        sess.close()
+    assert not np.array_equal(got[0], got[1])
+    for b, s in enumerate(seqs):
+        want = od.forward_full(g, host, s, logits_at=np.array([len(s) - 1]))[0]
+        for k in range(2):
+            assert np.abs(got[k][b] - want).max() <= 3e-2 * want.std(), (b, k)
