@@ -677,7 +677,8 @@ static int run_layers(StepCtx& c) {
         Shape sh = {128, 1};
         const float split_us = wide_shape(c.rows, nqkv, d, most, sh.bn, sh.splits) + 5.f + 2.55e-6f * (float)c.rows * (float)nqkv;
         const bool set = t.bn_qkv || t.s_qkv;
-        if (t.fuse_qkv && t.s_qkv <= 1 && gemm_tile_qkv_fits(nqkv, d, qs) && gemm_tile_qkv_us(c.rows, nqkv, d) <= split_us) fuse_qkv = true;
+        const bool faster = d % 128 ? gemm_tile_qkv_fills(c.rows, nqkv) : gemm_tile_qkv_us(c.rows, nqkv, d) <= split_us;
+        if (t.fuse_qkv && t.s_qkv <= 1 && gemm_tile_qkv_fits(nqkv, d, qs) && faster) fuse_qkv = true;
         else if (set) sh_qkv.splits = std::max(1, std::min({t.s_qkv, most, d / 128}));
         else sh_qkv = sh;
     }

@@ -132,6 +132,7 @@ hipError_t launch_gemm_tile(const GemmArgs& a, int epilogue, int bm, hipStream_t
 float gemm_tile_us(int M, int N, int K, int splits, int cols, int bm);                     // cost estimates that choose between them
 float gemm_stream_us(int M, int N, int K, int splits, int bn);
 bool gemm_tile_qkv_fits(int N, int K, const QkvPostArgs& qa);                              // head_dim 128, whole heads per tile
+bool gemm_tile_qkv_fills(int M, int N);                                                    // for K % 128 == 64
 float gemm_tile_qkv_us(int M, int N, int K);
 hipError_t launch_gemm_tile_qkv(const GemmArgs& a, const QkvPostArgs& qa, hipStream_t s);  // q/k/v projection + qkv_post in one kernel
 hipError_t launch_gemm_stream(const GemmArgs& a, int epilogue, int bn, hipStream_t s);   // K % 128 == 0, N % 16 == 0

@@ -59,3 +59,29 @@ def test_tuned_splits_reach_calls_of_many_rows(key):
         want = od.forward_full(g, host, s, logits_at=np.array([len(s) - 1]))[0]
         for k in range(2):
             assert np.abs(got[k][b] - want).max() <= 3e-2 * want.std(), (b, k)
+
+
+def test_fused_qkv_epilogue_at_odd_multiples_of_64():
+    """d_model % 128 == 64 (the streaming kernel does not take it): the q/k/v projection does its post-processing itself once
+    its tiles fill the chip, an odd number of 64-wide chunks.  Against the two-kernel form: the same order of sums in
+    both, so the same bits; and against the oracle."""
+    from paper_2506_24119_amd import binding as sb
+    g = si.ModelGeometry("k64", 1, 192, 20, 5, 128, 256, 512, 1e6, qk_norm=True)
+    host = si.make_weights(g, seed=12)
+    w = sb.weights_to_device(host)
+    seqs = si.make_prompts(g.vocab, 9, 480, 520, seed=9)
+    seqs[0] = seqs[0][:61]
+    ids = np.arange(9, dtype=np.int32)
+    rows = sum(len(s) for s in seqs)
+    assert (rows + 255) // 256 * 15 >= 200 and rows % 128
+    got = []
+    for tune in ("fuse_qkv=1", "fuse_qkv=0"):
+        sess = sb.Session(g, w, 320, 9, 40, rows, 640, page_order=si.make_page_order(320, 4), tune=tune)
+        sb.spiral_profile_begin(sess.model, sb.KERNEL_CLASSES.index("qkv_post"), 10)
+        got.append(sess.prefill(ids, seqs).cpu().numpy())
+        _, n_post = sb.spiral_profile_end(sess.model)
+        assert n_post == (0 if tune == "fuse_qkv=1" else 1)
+        sess.close()
+    assert np.array_equal(got[0], got[1])
+    want = od.forward_full(g, host, seqs[0], logits_at=np.array([len(seqs[0]) - 1]))[0]
+    assert np.abs(got[0][0] - want).max() <= 3e-2 * want.std()
