@@ -96,7 +96,7 @@ __device__ __forceinline__ void load_page(PageFrag<HD>& f, const uint16_t* kp, i
 // (0.63 PFLOP/s); 788 rows appended to nine histories of U[400, 2000] 122 -> 66 us.
 // ---------------------------------------------------------------------------------------------
 template <int HD, bool ACT32>
-__global__ __launch_bounds__(256, 2) void attn_prefill_kernel(AttnArgs a, int qblocks, int pairs, int heads_wg, int head_groups) {
+__global__ __launch_bounds__(256, 2) void attn_prefill_kernel(AttnArgs a, int pairs, int heads_wg, int head_groups) {
     constexpr int KS = HD / 16, DT = HD / 32;
     constexpr int PAGE_B = 2 * kPageTokens * HD * 2;          // bytes of one (page, kv head): K then V
     constexpr int STAGE_B = 4 * PAGE_B;                       // 64 tokens
@@ -108,10 +108,9 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(AttnArgs a, int qb
     const int G = a.n_q_heads / a.n_kv_heads;
 
     // blocks of one (sequence, kv head) run on one XCD (its L2 keeps the pages); the longest rows start first
-    const int k = blockIdx.x >> 3;
-    const int pair = (k / qblocks) * 8 + (blockIdx.x & 7);
+    const int pair = blockIdx.y * 8 + (blockIdx.x & 7);
     if (pair >= pairs) return;
-    const int qb = qblocks - 1 - k % qblocks;
+    const int qb = (int)((gridDim.x - 1 - blockIdx.x) >> 3);
     const int hg = pair % head_groups, kvh = (pair / head_groups) % a.n_kv_heads, b = pair / (head_groups * a.n_kv_heads);
     const int tiles = 4 / heads_wg;                           // position tiles of the workgroup
     const int r_first = a.cu_rows[b];
@@ -519,14 +518,15 @@ static hipError_t prefill_impl(const AttnArgs& a, int B, int max_new, hipStream_
     const int head_groups = (G + 3) / 4, heads_wg = (G + head_groups - 1) / head_groups;      // at most four heads a workgroup
     const int rows_wg = (4 / heads_wg) * 32;
     const int qblocks = (max_new + rows_wg - 1) / rows_wg, pairs = B * a.n_kv_heads * head_groups;
-    const long long blocks = (long long)((pairs + 7) / 8) * 8 * qblocks;
-    if (blocks > 0x7FFFFFFFll) return hipErrorInvalidValue;
+    // x: position blocks of eight pairs, y: groups of eight pairs (in one dimension a thousand sequences beside one of 65,600
+    // tokens would pass the 2^32 threads that a dimension of a launch may have)
+    const dim3 grid(8 * qblocks, (pairs + 7) / 8);
     const size_t lds = (size_t)2 * 4 * (2 * kPageTokens * HD * 2);
     if (lds > 65536) {
         hipError_t e = hipFuncSetAttribute((const void*)attn_prefill_kernel<HD, ACT32>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL((attn_prefill_kernel<HD, ACT32>), dim3((unsigned)blocks), dim3(256), lds, s, a, qblocks, pairs, heads_wg, head_groups);
+    hipLaunchKernelGGL((attn_prefill_kernel<HD, ACT32>), grid, dim3(256), lds, s, a, pairs, heads_wg, head_groups);
     return hipGetLastError();
 }
 

@@ -34,3 +34,26 @@ def test_ragged_runs_and_histories(q_heads, kv_heads, head_dim, dtype):
         for k in range(2):
             ratio = np.abs(got[k][b] - want[k]).max() / want[k].std()
             assert ratio <= 3e-2, (b, k, ratio)
+
+
+def test_one_very_long_run_beside_a_thousand_short_ones():
+    """1,023 runs of one token beside one of 65,632: 8,192 (sequence, kv head) pairs x 2,051 blocks of 32 positions are more
+    workgroups than one dimension of a launch may have threads for.  Every sequence must get the logits that it gets without the
+    others (fp32 weights: nothing but attention sees more than one row), bit for bit."""
+    import torch
+    from paper_2506_24119_amd import binding as sb
+    g = si.ModelGeometry("long", 1, 64, 32, 8, 32, 64, 64, 1e4, weight_dtype=si.WEIGHT_FP32)
+    w = sb.weights_to_device(si.make_weights(g, seed=4))
+    rng = np.random.Generator(np.random.PCG64(6))
+    B, n = 1024, 65632
+    seqs = [rng.integers(0, g.vocab, n if b == 5 else 1).astype(np.int32) for b in range(B)]
+    assert (n + 31) // 32 * B * g.n_kv_heads * 256 > 1 << 32
+    ids = np.arange(B, dtype=np.int32)
+    sess = sb.Session(g, w, 4103 + B, B, 4103, n + B, n + 1, page_order=None)
+    together = sess.prefill(ids, seqs).cpu().numpy()
+    sb.spiral_seq_reset(sess.pool, ids)
+    assert np.array_equal(together[5:6], sess.prefill(ids[5:6], seqs[5:6]).cpu().numpy())
+    rest = np.delete(ids, 5)
+    assert np.array_equal(together[rest], sess.prefill(rest, [seqs[b] for b in rest]).cpu().numpy())
+    torch.cuda.synchronize()
+    sess.close()
