@@ -79,6 +79,57 @@ __device__ __forceinline__ void load_page(PageFrag<HD>& f, const uint16_t* kp, i
     for (int mp = 0; mp < HD / 32; ++mp) f.v[mp] = KVLOAD((const u32x4*)((real ? vp : kp) + mp * step + off));
 }
 
+// One (row, query head) by one wave, token by token, nothing read of a token that the row does not see: a lane scores one token
+// of 64, then holds one dimension (of 128: two).  For rows whose sums met a NaN only; speed does not matter.
+template <int HD, bool ACT32>
+__device__ __forceinline__ void prefill_row_alone(const AttnArgs& a, const int32_t* bt, const uint16_t* head_pages, size_t page_elems, size_t out_row,
+                                                  int last, int lane) {
+    constexpr int DL = (HD + 63) / 64;
+    const uint16_t* q = a.q + out_row * HD;
+    float m_run = kNegBig, l_run = 0.f, o[DL];
+#pragma unroll
+    for (int j = 0; j < DL; ++j) o[j] = 0.f;
+    for (int t0 = 0; t0 <= last; t0 += 64) {
+        const int t = t0 + lane;
+        float sc = -INFINITY;
+        if (t <= last) {
+            const uint16_t* kp = head_pages + (size_t)bt[t >> 4] * page_elems + (t & 15) * 8;
+            sc = 0.f;
+#pragma unroll 1
+            for (int d = 0; d < HD; d += 8) {
+                const f16x8 kv = *(const f16x8*)(kp + (d >> 5) * 512 + ((d & 31) >> 3) * 128), qv = *(const f16x8*)(q + d);
+#pragma unroll
+                for (int e = 0; e < 8; ++e) sc = fmaf((float)kv[e], (float)qv[e], sc);
+            }
+            sc *= a.scale_log2e;
+        }
+        float mx = sc;
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 64));
+        const float m_new = fmaxf(m_run, mx), alpha = __builtin_amdgcn_exp2f(m_run - m_new);
+        const float p = __builtin_amdgcn_exp2f(sc - m_new), ph = (float)(_Float16)p;
+        l_run = l_run * alpha + wave_sum(p);
+        m_run = m_new;
+#pragma unroll
+        for (int j = 0; j < DL; ++j) o[j] *= alpha;
+#pragma unroll 1
+        for (int i = 0; i < 64 && t0 + i <= last; ++i) {
+            const int ti = t0 + i;
+            const uint16_t* vp = head_pages + (size_t)bt[ti >> 4] * page_elems + kPageTokens * HD + ((ti & 15) >> 2) * 128 + (ti & 3);
+            const float pi = __shfl(ph, i, 64);
+#pragma unroll
+            for (int j = 0; j < DL; ++j) {
+                const int d = (lane + 64 * j) & (HD - 1);
+                o[j] = fmaf(pi, (float)__builtin_bit_cast(_Float16, vp[(d >> 5) * 512 + (d & 15) * 8 + ((d >> 4) & 1) * 4]), o[j]);
+            }
+        }
+    }
+    const float inv = 1.0f / l_run;
+#pragma unroll
+    for (int j = 0; j < DL; ++j)
+        if (lane + 64 * j < HD) ActStore<ACT32>::put(a.out, out_row * HD + lane + 64 * j, o[j] * inv);
+}
+
 // ---------------------------------------------------------------------------------------------
 // Causal prefill attention.  A wave's tile is 32 consecutive positions of one query head, each row with its own causal
 // limit; a workgroup holds four tiles that share a kv head: up to four heads of the group, or with groups of one or two
@@ -242,14 +293,26 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(AttnArgs a, int pa
 
     // O^T[d][row]: lane (l32, lh) holds d = 32 dt + 8 b + 4 lh .. + 3 of row l32; l is spread over the two lane halves
     l_run += __shfl_xor(l_run, 32, 64);
+    bool nan = false;
     if (active && l32 < n_valid) {
         const float inv = 1.0f / l_run;
+#pragma unroll
+        for (int d = 0; d < DT; ++d)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) nan = nan || acc[d][r] != acc[d][r];
         const size_t o_idx = ((size_t)(row0 + l32) * a.n_q_heads + h) * HD + lh * 4;
 #pragma unroll
         for (int d = 0; d < DT; ++d)
 #pragma unroll
             for (int b2 = 0; b2 < 4; ++b2) ActStore<ACT32>::put4(a.out, o_idx + d * 32 + b2 * 8, acc[d][4 * b2] * inv,
                                                                  acc[d][4 * b2 + 1] * inv, acc[d][4 * b2 + 2] * inv, acc[d][4 * b2 + 3] * inv);
+    }
+    // A weight of zero does not stop a NaN: one in the V of a token that a row does not see (up to 63 further on in the row's
+    // last 64) has reached its sums.  Such rows, and rows with a NaN of their own, are done again over their visible tokens only.
+    const uint64_t lanes = __builtin_amdgcn_ballot_w64(nan);
+    for (uint32_t rows = (uint32_t)lanes | (uint32_t)(lanes >> 32); rows; rows &= rows - 1) {
+        const int row = __builtin_ctz(rows);
+        prefill_row_alone<HD, ACT32>(a, bt, head_pages, page_elems, (size_t)(row0 + row) * a.n_q_heads + h, pos0 + row, lane);
     }
 }
 

@@ -57,3 +57,34 @@ def test_one_very_long_run_beside_a_thousand_short_ones():
     assert np.array_equal(together[rest], sess.prefill(rest, [seqs[b] for b in rest]).cpu().numpy())
     torch.cuda.synchronize()
     sess.close()
+
+
+@pytest.mark.parametrize("q_heads,kv_heads,head_dim", [(4, 2, 128), (6, 2, 64), (8, 1, 32)])
+@pytest.mark.parametrize("at", [16, 40, 63, 64, 90, 149])
+def test_a_nan_stays_out_of_earlier_positions(q_heads, kv_heads, head_dim, at):
+    """A token whose embedding is NaN leaves NaN in its K and V.  No earlier position sees it, so their log-probabilities must
+    stay what they are with an ordinary token there; the position itself and the later ones are NaN.  Rows that share a
+    64-token step with it are summed by another routine (fp32 sums in another order, the same half-precision weights): bound as
+    for every log-probability, 6e-2 x logit std, here 1e-2 absolute at a logit std of about 0.3."""
+    import torch
+    from paper_2506_24119_amd import binding as sb
+    g = si.ModelGeometry("nan", 2, 128, q_heads, kv_heads, head_dim, 256, 256, 1e4, tie_lm_head=False)
+    w = si.make_weights(g, seed=13)
+    w["embed"][7] = 0x7FC0                                  # bf16 NaN
+    wd = sb.weights_to_device(w)
+    rng = np.random.Generator(np.random.PCG64(7))
+    seqs = [rng.integers(8, g.vocab, n).astype(np.int32) for n in (150, 33)]
+    got = []
+    for tok in (7, 9):
+        seqs[0][at] = tok
+        sess = sb.Session(g, wd, 40, 2, 16, 256, 200, page_order=si.make_page_order(40, 2))
+        toks = torch.from_numpy(np.concatenate(seqs)).cuda()
+        tg = torch.from_numpy(rng.permutation(183).astype(np.int32)).cuda() % g.vocab if not got else tg
+        out = torch.empty(183, dtype=torch.float32, device="cuda")
+        sb.spiral_score(sess.model, sess.pool, [0, 1], [150, 33], toks, tg, sess.ws, out)
+        got.append(out.cpu().numpy())
+        sess.close()
+    assert np.isnan(got[0][at:150]).all() and not np.isnan(got[1]).any()
+    assert not np.isnan(got[0][:at]).any() and not np.isnan(got[0][150:]).any()
+    assert np.abs(got[0][:at] - got[1][:at]).max() <= 1e-2 and np.array_equal(got[0][150:], got[1][150:])
+    assert np.array_equal(got[0][:max(0, at - 63)], got[1][:max(0, at - 63)])      # out of reach: not summed again
