@@ -130,6 +130,21 @@ __device__ __forceinline__ void prefill_row_alone(const AttnArgs& a, const int32
         if (lane + 64 * j < HD) ActStore<ACT32>::put(a.out, out_row * HD + lane + 64 * j, o[j] * inv);
 }
 
+// Grid of the prefill kernel: x = position blocks of eight pairs, y = groups of eight (sequence, kv head, head group) pairs.
+// Everything a workgroup would divide for comes from the host, as a whole number or as a reciprocal: seven integer divisions in a
+// row, and four look-ups one after the other, were half a microsecond of a launch before its first load.  Runs of 5 tokens without a
+// history, 16 heads: 5.9 -> 5.2 us a launch (1.5 of it empty, 0.4 the look-ups, 1.2 the pages and q, 0.8 the step, 1.3 the output: few
+// instructions, all of them fetched for the first time); 65 tokens, 32 heads 11.7 -> 10.1 with the events around it.
+struct Reciprocal {
+    uint32_t m;                                               // ceil(2^32 / d), 0 for d = 1
+    __device__ __forceinline__ int of(int n) const { return m ? (int)__umulhi((uint32_t)n, m) : n; }      // n / d where n * d < 2^32
+};
+static Reciprocal reciprocal(int d) { return Reciprocal{d > 1 ? (uint32_t)(((1ull << 32) + d - 1) / d) : 0u}; }
+struct PrefillGrid {
+    int32_t pairs, group, heads_wg, head_groups, tiles;       // group: query heads per kv head; tiles: position tiles of a workgroup
+    Reciprocal by_groups, by_kv_heads;                        // 1 / head_groups, 1 / n_kv_heads
+};
+
 // ---------------------------------------------------------------------------------------------
 // Causal prefill attention.  A wave's tile is 32 consecutive positions of one query head, each row with its own causal
 // limit; a workgroup holds four tiles that share a kv head: up to four heads of the group, or with groups of one or two
@@ -147,7 +162,7 @@ __device__ __forceinline__ void prefill_row_alone(const AttnArgs& a, const int32
 // (0.63 PFLOP/s); 788 rows appended to nine histories of U[400, 2000] 122 -> 66 us.
 // ---------------------------------------------------------------------------------------------
 template <int HD, bool ACT32>
-__global__ __launch_bounds__(256, 2) void attn_prefill_kernel(AttnArgs a, int pairs, int heads_wg, int head_groups) {
+__global__ __launch_bounds__(256, 2) void attn_prefill_kernel(AttnArgs a, PrefillGrid gr) {
     constexpr int KS = HD / 16, DT = HD / 32;
     constexpr int PAGE_B = 2 * kPageTokens * HD * 2;          // bytes of one (page, kv head): K then V
     constexpr int STAGE_B = 4 * PAGE_B;                       // 64 tokens
@@ -156,25 +171,25 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(AttnArgs a, int pa
     char* lds = (char*)lds_f;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int l32 = lane & 31, lh = lane >> 5;
-    const int G = a.n_q_heads / a.n_kv_heads;
 
     // blocks of one (sequence, kv head) run on one XCD (its L2 keeps the pages); the longest rows start first
     const int pair = blockIdx.y * 8 + (blockIdx.x & 7);
-    if (pair >= pairs) return;
+    if (pair >= gr.pairs) return;
     const int qb = (int)((gridDim.x - 1 - blockIdx.x) >> 3);
-    const int hg = pair % head_groups, kvh = (pair / head_groups) % a.n_kv_heads, b = pair / (head_groups * a.n_kv_heads);
-    const int tiles = 4 / heads_wg;                           // position tiles of the workgroup
-    const int r_first = a.cu_rows[b];
-    const int n_in_seq = a.cu_rows[b + 1] - r_first;
+    const int seq_head = gr.by_groups.of(pair), hg = pair - seq_head * gr.head_groups;
+    const int b = gr.by_kv_heads.of(seq_head), kvh = seq_head - b * a.n_kv_heads;
+    const int r_first = a.cu_rows[b], r_end = a.cu_rows[b + 1];
+    const int pos_base = a.base_pos[b], seq = a.seq_ids[b];   // position of the run's first row; requested together
+    const int tiles = gr.tiles;                               // position tiles of the workgroup
+    const int n_in_seq = r_end - r_first;
     const int first = qb * tiles * 32;                        // first position of the workgroup, counted from the run's start
     if (first >= n_in_seq) return;
-    const int hw = wave % heads_wg, tile = wave / heads_wg;
+    const int hw = tiles == 4 ? 0 : (tiles == 2 ? wave & 1 : wave), tile = tiles == 4 ? wave : (tiles == 2 ? wave >> 1 : 0);
     const int my_first = first + tile * 32;
     const int n_valid = min(32, n_in_seq - my_first);         // rows of this wave (<= 0: none)
-    const bool active = tile < tiles && hg * heads_wg + hw < G && n_valid > 0;
-    const int h = kvh * G + min(hg * heads_wg + hw, G - 1);
+    const bool active = hw < gr.heads_wg && hg * gr.heads_wg + hw < gr.group && n_valid > 0;
+    const int h = kvh * gr.group + min(hg * gr.heads_wg + hw, gr.group - 1);
     const int row0 = r_first + my_first;
-    const int pos_base = a.base_pos[b];                       // position of the run's first row
     const int pos0 = pos_base + my_first;
     const int limit = active && l32 < n_valid ? pos0 + l32 : -1;
     const int my_last = active ? pos0 + n_valid - 1 : -1;     // last visible position of the wave
@@ -182,7 +197,7 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(AttnArgs a, int pa
     const int last_page = last / kPageTokens;
     const int n_stages = last / 64 + 1;
 
-    const int32_t* bt = a.block_table + (size_t)a.seq_ids[b] * a.max_blocks;
+    const int32_t* bt = a.block_table + (size_t)seq * a.max_blocks;
     const size_t page_elems = (size_t)a.n_kv_heads * (2 * kPageTokens * HD);
     const uint16_t* head_pages = a.pages + (size_t)kvh * (2 * kPageTokens * HD);
 
@@ -296,16 +311,29 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(AttnArgs a, int pa
     bool nan = false;
     if (active && l32 < n_valid) {
         const float inv = 1.0f / l_run;
+        f32x16 sum = acc[0];                                  // NaN where one is among its terms; far from overflow
 #pragma unroll
-        for (int d = 0; d < DT; ++d)
+        for (int d = 1; d < DT; ++d) sum += acc[d];
+        float s1 = sum[0];
 #pragma unroll
-            for (int r = 0; r < 16; ++r) nan = nan || acc[d][r] != acc[d][r];
+        for (int r = 1; r < 16; ++r) s1 += sum[r];
+        nan = s1 != s1;
         const size_t o_idx = ((size_t)(row0 + l32) * a.n_q_heads + h) * HD + lh * 4;
 #pragma unroll
         for (int d = 0; d < DT; ++d)
 #pragma unroll
-            for (int b2 = 0; b2 < 4; ++b2) ActStore<ACT32>::put4(a.out, o_idx + d * 32 + b2 * 8, acc[d][4 * b2] * inv,
-                                                                 acc[d][4 * b2 + 1] * inv, acc[d][4 * b2 + 2] * inv, acc[d][4 * b2 + 3] * inv);
+            for (int b2 = 0; b2 < 4; ++b2) {
+                float o[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) o[e] = acc[d][4 * b2 + e] * inv;
+                if (ACT32) *(float4*)((float*)a.out + o_idx + d * 32 + b2 * 8) = make_float4(o[0], o[1], o[2], o[3]);
+                else {                                        // the range as f32_to_act16 has it; a NaN is stored again below
+                    f16x4 o4;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) o4[e] = (_Float16)__builtin_amdgcn_fmed3f(o[e], -65504.0f, 65504.0f);
+                    *(f16x4*)((uint16_t*)a.out + o_idx + d * 32 + b2 * 8) = o4;
+                }
+            }
     }
     // A weight of zero does not stop a NaN: one in the V of a token that a row does not see (up to 63 further on in the row's
     // last 64) has reached its sums.  Such rows, and rows with a NaN of their own, are done again over their visible tokens only.
@@ -577,19 +605,25 @@ hipError_t launch_attn_stream_combine(const AttnArgs& a, int hd, bool act32, hip
 
 template <int HD, bool ACT32>
 static hipError_t prefill_impl(const AttnArgs& a, int B, int max_new, hipStream_t s) {
-    const int G = a.n_q_heads / a.n_kv_heads;
-    const int head_groups = (G + 3) / 4, heads_wg = (G + head_groups - 1) / head_groups;      // at most four heads a workgroup
-    const int rows_wg = (4 / heads_wg) * 32;
-    const int qblocks = (max_new + rows_wg - 1) / rows_wg, pairs = B * a.n_kv_heads * head_groups;
-    // x: position blocks of eight pairs, y: groups of eight pairs (in one dimension a thousand sequences beside one of 65,600
-    // tokens would pass the 2^32 threads that a dimension of a launch may have)
-    const dim3 grid(8 * qblocks, (pairs + 7) / 8);
+    PrefillGrid gr;
+    gr.group = a.n_q_heads / a.n_kv_heads;
+    gr.head_groups = (gr.group + 3) / 4;
+    gr.heads_wg = (gr.group + gr.head_groups - 1) / gr.head_groups;       // at most four heads a workgroup
+    gr.tiles = 4 / gr.heads_wg;
+    gr.pairs = B * a.n_kv_heads * gr.head_groups;
+    gr.by_groups = reciprocal(gr.head_groups);
+    gr.by_kv_heads = reciprocal(a.n_kv_heads);
+    if ((unsigned long long)gr.pairs * a.n_kv_heads >> 32) return hipErrorInvalidValue;       // no model: 2,000 kv heads in 1,024 sequences
+    const int qblocks = (max_new + gr.tiles * 32 - 1) / (gr.tiles * 32);
+    // (in one dimension a thousand sequences beside one of 65,600 tokens would pass the 2^32 threads that a dimension of a
+    // launch may have)
+    const dim3 grid(8 * qblocks, (gr.pairs + 7) / 8);
     const size_t lds = (size_t)2 * 4 * (2 * kPageTokens * HD * 2);
     if (lds > 65536) {
         hipError_t e = hipFuncSetAttribute((const void*)attn_prefill_kernel<HD, ACT32>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL((attn_prefill_kernel<HD, ACT32>), grid, dim3(256), lds, s, a, pairs, heads_wg, head_groups);
+    hipLaunchKernelGGL((attn_prefill_kernel<HD, ACT32>), grid, dim3(256), lds, s, a, gr);
     return hipGetLastError();
 }
 

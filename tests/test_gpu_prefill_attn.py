@@ -88,3 +88,21 @@ def test_a_nan_stays_out_of_earlier_positions(q_heads, kv_heads, head_dim, at):
     assert not np.isnan(got[0][:at]).any() and not np.isnan(got[0][150:]).any()
     assert np.abs(got[0][:at] - got[1][:at]).max() <= 1e-2 and np.array_equal(got[0][150:], got[1][150:])
     assert np.array_equal(got[0][:max(0, at - 63)], got[1][:max(0, at - 63)])      # out of reach: not summed again
+
+
+@pytest.mark.parametrize("q_heads,kv_heads", [(12, 12), (18, 6), (15, 3), (32, 2), (64, 4), (11, 11)])
+def test_head_groups_and_sequence_counts(q_heads, kv_heads):
+    """Workgroups find their sequence, kv head and head group by multiplication with reciprocals: group sizes 1 to 16 over kv
+    head counts that are and are not powers of two, 1 and 37 sequences, against the oracle."""
+    from paper_2506_24119_amd import binding as sb
+    g = si.ModelGeometry("groups", 1, 64, q_heads, kv_heads, 32, 64, 128, 1e4, weight_dtype=si.WEIGHT_FP32)
+    host = si.make_weights(g, seed=5)
+    w = sb.weights_to_device(host)
+    for n_seqs in (1, 37):
+        seqs = si.make_prompts(g.vocab, n_seqs, 1, 90, seed=n_seqs)
+        sess = sb.Session(g, w, 7 * n_seqs, n_seqs, 7, 90 * n_seqs, 100, page_order=si.make_page_order(7 * n_seqs, 2))
+        got = sess.prefill(np.arange(n_seqs, dtype=np.int32), seqs).cpu().numpy()
+        sess.close()
+        for b, s in enumerate(seqs):
+            want = od.forward_full(g, host, s, logits_at=np.array([len(s) - 1]))[0]
+            assert np.abs(got[b] - want).max() <= 3e-2 * want.std(), (n_seqs, b)
