@@ -490,18 +490,33 @@ float gemm_stream_us(int M, int N, int K, int splits, int bn) {
 // The tile height for a launch: the cheaper of the two, 0 where the streaming kernel is cheaper still.  All three add
 // the products of an output in the same order, so the choice never changes a result.  Shapes that the streaming kernel does not
 // take (row-major weights go to a kernel with another order there) are tiled only where 256 x 256 tiles fill the chip.
-static int tile_rows(const GemmArgs& a, int cols, int bn) {
-    if ((a.K & 127) || (a.N & 15))
-        return a.M >= 512 && (long)((a.M + 255) / 256) * ((a.N + cols - 1) / cols) >= 200 ? 256 : 0;
-    const float t256 = gemm_tile_us(a.M, a.N, a.K, a.splits, cols, 256), t128 = gemm_tile_us(a.M, a.N, a.K, a.splits, cols, 128);
-    const float ts = gemm_stream_us(a.M, cols == 128 ? 2 * a.N : a.N, a.K, a.splits, bn == 64 ? 64 : 128);
-    if (a.M <= 128 || ts < std::min(t256, t128)) return 0;
+int gemm_tile_height(int M, int N, int K, int splits, int cols, int bn) {
+    if ((K & 127) || (N & 15))
+        return M >= 512 && (long)((M + 255) / 256) * ((N + cols - 1) / cols) >= 200 ? 256 : 0;
+    const float t256 = gemm_tile_us(M, N, K, splits, cols, 256), t128 = gemm_tile_us(M, N, K, splits, cols, 128);
+    const float ts = gemm_stream_us(M, cols == 128 ? 2 * N : N, K, splits, bn == 64 ? 64 : 128);
+    if (M <= 128 || ts < std::min(t256, t128)) return 0;
     return t128 < t256 ? 128 : 256;
 }
 
 int gemm_tile_rows(const GemmArgs& a, int epilogue, int bn) {
     if (!gemm_tile_usable(a) || (epilogue == EPI_SWIGLU && ((a.N & 7) || a.splits != 1))) return 0;     // SwiGLU rows are stored 8 halves at a time
-    return tile_rows(a, epilogue == EPI_SWIGLU ? 128 : 256, bn);
+    return gemm_tile_height(a.M, a.N, a.K, a.splits, epilogue == EPI_SWIGLU ? 128 : 256, bn);
+}
+
+// K splits of a projection over more than 128 rows, and the streaming kernel's tile width: the pair for which the estimated
+// time of the launch plus that of the partial sums (written, and read by the norm kernel; 788 x 2560 of them cost 0.7 us
+// of the norm kernel each, and the writes about as much again) is least.  It depends on the shape alone, not on how the weights are
+// stored, so that repacked and row-major weights keep adding in the same order.
+float gemm_wide_shape(int M, int N, int K, int most, int& bn, int& splits) {
+    float best = 1e30f;
+    for (int s = 1; s <= std::max(1, most) && (s == 1 || (K % 128 == 0 && K / s >= 512)); ++s) {
+        const float s128 = gemm_stream_us(M, N, K, s, 128), s64 = gemm_stream_us(M, N, K, s, 64);
+        const float launch = std::min({gemm_tile_us(M, N, K, s, 256, 256), gemm_tile_us(M, N, K, s, 256, 128), s128, s64});
+        const float us = launch + (float)(s - 1) * M * N * 4.f / 3.3e6f;
+        if (us < best) { best = us; splits = s; bn = s64 < s128 ? 64 : 128; }
+    }
+    return best;
 }
 
 hipError_t launch_gemm_tile(const GemmArgs& a, int epilogue, int bm, hipStream_t s) {
@@ -511,12 +526,12 @@ hipError_t launch_gemm_tile(const GemmArgs& a, int epilogue, int bm, hipStream_t
     return epilogue == EPI_SWIGLU ? launch_tile<1>(a, none, bm, s) : launch_tile<0>(a, none, bm, s);
 }
 
+int gemm_tile_score_height(int M, int N, int K) { return gemm_tile_us(M, N, K, 1, 256, 128) < gemm_tile_us(M, N, K, 1, 256, 256) ? 128 : 256; }
 // The LM head with the scoring epilogue: one (max, sum exp) pair per row and 128 columns.
 hipError_t launch_gemm_tile_score(const GemmArgs& a, hipStream_t s) {
     if (!gemm_tile_usable(a) || a.splits != 1 || !a.s_part || !a.targets || !a.tgt_logit || a.s_tiles != (a.N + 127) / 128) return hipErrorInvalidValue;
     const QkvPostArgs none = {};
-    const bool small = gemm_tile_us(a.M, a.N, a.K, 1, 256, 128) < gemm_tile_us(a.M, a.N, a.K, 1, 256, 256);
-    return launch_tile<3>(a, none, small ? 128 : 256, s);
+    return launch_tile<3>(a, none, gemm_tile_score_height(a.M, a.N, a.K), s);
 }
 
 // The q/k/v projection with the work of qkv_post_kernel in its epilogue (qa.qkv and qa.n_part are not used).

@@ -598,21 +598,6 @@ struct StepCtx {
     int32_t* out_tokens = nullptr;
 };
 
-// K splits of a projection over more than 128 rows, and the streaming kernel's tile width: the pair for which the estimated
-// time of the launch plus that of the partial sums (written, and read by the norm kernel; 788 x 2560 of them cost 0.7 us
-// of the norm kernel each, and the writes about as much again) is least.  It depends on the shape alone, not on how the weights are
-// stored, so that repacked and row-major weights keep adding in the same order.
-static float wide_shape(int M, int N, int K, int most, int& bn, int& splits) {
-    float best = 1e30f;
-    for (int s = 1; s <= std::max(1, most) && (s == 1 || (K % 128 == 0 && K / s >= 512)); ++s) {
-        const float s128 = gemm_stream_us(M, N, K, s, 128), s64 = gemm_stream_us(M, N, K, s, 64);
-        const float launch = std::min({gemm_tile_us(M, N, K, s, 256, 256), gemm_tile_us(M, N, K, s, 256, 128), s128, s64});
-        const float us = launch + (float)(s - 1) * M * N * 4.f / 3.3e6f;
-        if (us < best) { best = us; splits = s; bn = s64 < s128 ? 64 : 128; }
-    }
-    return best;
-}
-
 namespace spiral {
 // The scoring pass's pairs (one per row and 128 columns) go where every product of the layers is dead by then: from qkv to mlp
 // in carve()'s order.  By the bytes of a row, so that the choice does not depend on the number of rows.
@@ -655,7 +640,7 @@ static int run_layers(StepCtx& c) {
     auto wide_or_set = [&](int set_bn, int set_s, int N, int K, size_t most, Shape& sh) {
         const int cap = (int)std::min<size_t>(most, kMaxSplit);
         if (set_bn || set_s) sh.splits = std::max(1, std::min({set_s, cap, K / 128}));
-        else wide_shape(c.rows, N, K, cap, sh.bn, sh.splits);
+        else gemm_wide_shape(c.rows, N, K, cap, sh.bn, sh.splits);
     };
     float *part_o = c.w.proj, *part_down = c.w.proj;
     bool fuse_qkv = false;              // the q/k/v projection's epilogue does the post-processing, its product never reaches memory
@@ -675,7 +660,7 @@ static int run_layers(StepCtx& c) {
         QkvPostArgs qs = {};
         qs.hd = hd; qs.n_q_heads = cfg.n_q_heads; qs.n_kv_heads = cfg.n_kv_heads;
         Shape sh = {128, 1};
-        const float split_us = wide_shape(c.rows, nqkv, d, most, sh.bn, sh.splits) + 5.f + 2.55e-6f * (float)c.rows * (float)nqkv;
+        const float split_us = gemm_wide_shape(c.rows, nqkv, d, most, sh.bn, sh.splits) + 5.f + 2.55e-6f * (float)c.rows * (float)nqkv;
         const bool set = t.bn_qkv || t.s_qkv;
         const bool faster = d % 128 ? gemm_tile_qkv_fills(c.rows, nqkv) : gemm_tile_qkv_us(c.rows, nqkv, d) <= split_us;
         if (t.fuse_qkv && t.s_qkv <= 1 && gemm_tile_qkv_fits(nqkv, d, qs) && faster) fuse_qkv = true;

@@ -1,7 +1,10 @@
 """Projections over more than 128 rows: tiles of 256 x 256 or 128 x 256 or the streaming kernel, K split or not, q/k/v
-post-processing inside the projection or behind it - chosen from the shape.  Row counts around the tile heights, on a
-geometry whose O and down projections are split; repacked weights must give the bits that row-major ones give, and both
-the oracle's logits within the bar of every logit comparison (3e-2 x per-row logit std)."""
+post-processing inside the projection or behind it - chosen from the shape.  Repacked weights must give the bits that
+row-major ones (always the streaming kernel) give, and both the oracle's logits within the bar of every logit comparison
+(3e-2 x per-row logit std).  test_row_counts_around_the_tiles is the streaming kernel with either weights, its O and down
+projections split; the tests behind it name the tile that their shapes reach and check the rule for it."""
+import ctypes as C
+
 import numpy as np
 import pytest
 
@@ -9,6 +12,14 @@ from oracle import decoder as od
 from paper_2506_24119_amd import inputs as si
 
 pytestmark = pytest.mark.gpu
+
+
+def tile_height(M, N, K, splits, cols=256):
+    """Rows of the tiles that a projection with fragment-ordered weights takes, 0 for the streaming kernel."""
+    from paper_2506_24119_amd import binding as sb
+    f = sb.load_library()["_ZN6spiral16gemm_tile_heightEiiiiii"]
+    f.restype, f.argtypes = C.c_int, [C.c_int] * 6
+    return f(M, N, K, splits, cols, 128)
 
 
 @pytest.mark.parametrize("rows", [129, 255, 257, 520, 900])
@@ -85,3 +96,91 @@ def test_fused_qkv_epilogue_at_odd_multiples_of_64():
     assert np.array_equal(got[0], got[1])
     want = od.forward_full(g, host, seqs[0], logits_at=np.array([len(seqs[0]) - 1]))[0]
     assert np.abs(got[0][0] - want).max() <= 3e-2 * want.std()
+
+
+TILED = dict(d_model=1024, n_q_heads=16, n_kv_heads=4, head_dim=128, ffn_dim=8192, vocab=512, rope_theta=1e6)
+
+
+def _prefill_and_step(g, w, rows, tune, repack):
+    import torch
+    from paper_2506_24119_amd import binding as sb
+    rng = np.random.Generator(np.random.PCG64(rows))
+    lens = [rows - 2 * (rows // 3), rows // 3, rows // 3]
+    seqs = [rng.integers(0, g.vocab, n).astype(np.int32) for n in lens]
+    step = rng.integers(0, g.vocab, 3).astype(np.int32)
+    ids = np.arange(3, dtype=np.int32)
+    sess = sb.Session(g, w, 150, 3, 50, rows, 600, page_order=si.make_page_order(150, 4), repack=repack, tune=tune)
+    out = [sess.prefill(ids, seqs).cpu().numpy()]
+    sb.spiral_model_tune(sess.model, "qkv=0:0,o=0:0,down=0:0")                # the step that reads the appended k, v: as it comes
+    out.append(sess.decode_step(ids, torch.from_numpy(step).cuda(), sess.new_logits(3)).cpu().numpy())
+    sess.close()
+    return seqs, step, out
+
+
+# rows; K splits of O, down, q/k/v; tile heights of O, down, q/k/v and gate/up that these reach
+@pytest.mark.parametrize("rows,splits,heights", [
+    (129, (1, 3, 1), (128, 128, 0, 0)), (255, (1, 2, 1), (128, 128, 0, 0)), (257, (1, 2, 5), (128, 128, 128, 128)),
+    (520, (1, 1, 3), (0, 128, 128, 256)), (1000, (5, 5, 2), (128, 128, 128, 256)), (1300, (3, 3, 1), (128, 128, 128, 128)),
+    (1600, (5, 5, 1), (256, 256, 128, 256))])
+def test_tiles_against_the_streaming_kernel(rows, splits, heights):
+    """Both tile heights, split (64 and 8 chunks of K in 3 and 5 uneven parts) and whole, with and without SwiGLU, at row counts
+    that leave remainders of 1, 127 and more rows in the last tile."""
+    g = si.ModelGeometry("tiles", 1, qk_norm=True, **TILED)
+    d, qw, nqkv, ffn = 1024, 2048, 3072, 8192
+    assert (tile_height(rows, d, qw, splits[0]), tile_height(rows, d, ffn, splits[1]), tile_height(rows, nqkv, d, splits[2]),
+            tile_height(rows, ffn, d, 1, 128)) == heights
+    from paper_2506_24119_amd import binding as sb
+    host = si.make_weights(g, seed=14)
+    w = sb.weights_to_device(host)
+    tune = "fuse_qkv=0,o=128:%d,down=128:%d,qkv=128:%d" % splits
+    seqs, step, tiled = _prefill_and_step(g, w, rows, tune, True)
+    _, _, streamed = _prefill_and_step(g, w, rows, tune, False)
+    assert np.array_equal(tiled[0], streamed[0]) and np.array_equal(tiled[1], streamed[1])
+    want = od.forward_full(g, host, np.concatenate([seqs[2], step[2:]]), logits_at=np.array([len(seqs[2]) - 1, len(seqs[2])]))
+    for k in range(2):
+        assert np.abs(tiled[k][2] - want[k]).max() <= 3e-2 * want[k].std()
+
+
+@pytest.mark.parametrize("rows", [900, 1281])
+@pytest.mark.parametrize("variant", ["qk_norm", "qkv_bias"])
+def test_fused_qkv_epilogue_rounds_like_the_post_kernel(rows, variant):
+    """The q/k/v projection's own epilogue, qkv_post_kernel behind the tiled projection and qkv_post_kernel behind the streaming
+    one (row-major weights): the same bits in the logits, and in the k and v that a decode step reads."""
+    from paper_2506_24119_amd import binding as sb
+    g = si.ModelGeometry("tiles", 2, qk_norm=variant == "qk_norm", qkv_bias=variant == "qkv_bias", **dict(TILED, ffn_dim=1024))
+    host = si.make_weights(g, seed=15)
+    w = sb.weights_to_device(host)
+    got = []
+    for tune, repack in ((None, True), ("fuse_qkv=0,qkv=128:1", True), (None, False)):
+        got.append(_prefill_and_step(g, w, rows, tune, repack)[2])
+    for other in got[1:]:
+        assert np.array_equal(got[0][0], other[0]) and np.array_equal(got[0][1], other[1])
+    # the default form is the fused one here: no post-processing launches in a prefill
+    sess = sb.Session(g, w, 150, 3, 100, rows, 1500, page_order=si.make_page_order(150, 4))
+    sb.spiral_profile_begin(sess.model, sb.KERNEL_CLASSES.index("qkv_post"), 10)
+    sess.prefill([0], [np.zeros(rows, dtype=np.int32)])
+    assert sb.spiral_profile_end(sess.model)[1] == 0
+    sess.close()
+
+
+def test_a_sequence_among_others_stays_close_to_itself_alone():
+    """Above 128 rows the K splits, and so the order of fp32 sums, follow from the rows of the whole call: a sequence of 300
+    tokens alone (300 rows) and among others (1,600) differs by roundings of half-precision activations, 2^-11 of a
+    value, in two layers: 1e-2 x std, the bound of the decode-attention pieces, which differ for the same reason."""
+    import torch
+    from paper_2506_24119_amd import binding as sb
+    g = si.ModelGeometry("tiles", 2, qk_norm=True, **TILED)
+    w = sb.weights_to_device(si.make_weights(g, seed=16))
+    seqs = si.make_prompts(g.vocab, 4, 433, 434, seed=10)
+    seqs[1] = seqs[1][:300]
+    step = torch.arange(4, dtype=torch.int32, device="cuda")
+    got = []
+    for batch in ([0, 1, 2, 3], [1]):
+        sess = sb.Session(g, w, 120, 4, 30, 1700, 480, page_order=si.make_page_order(120, 4))
+        at = batch.index(1)
+        out = [sess.prefill(batch, [seqs[b] for b in batch]).cpu().numpy()[at]]
+        out.append(sess.decode_step(batch, step[torch.tensor(batch, device="cuda")].contiguous(), sess.new_logits(len(batch))).cpu().numpy()[at])
+        got.append(out)
+        sess.close()
+    for k in range(2):
+        assert np.abs(got[0][k] - got[1][k]).max() <= 1e-2 * got[1][k].std(), k
