@@ -170,6 +170,10 @@ int    spiral_kv_free_pages(const spiral_kv_pool* p);
  * dev_tokens_packed: int32 [sum(host_lens)], the sequences' tokens back to back, ids in [0, vocab).
  * dev_logits: fp32 [B, vocab].  dev_ws/ws_bytes: workspace of at least
  * spiral_workspace_bytes(m, sum(host_lens), longest resulting context), 256-byte aligned.
+ * Repeating a call repeats its bits.  A sequence's bits are not independent of the rest of its call: above 128 rows the
+ * K splits of the projections, and so the order of their fp32 sums, follow from sum(host_lens) (in a decode step the cut of
+ * the attention follows from all contexts); logits differ by the rounding of half-precision activations then, about 1e-3
+ * of their standard deviation a layer.
  * Errors: INVALID_ARG, OOM_KV (pages, block-table slots or workspace too small), HIP. */
 int spiral_prefill(spiral_model* m, spiral_kv_pool* p, const int32_t* host_seq_ids,
                    const int32_t* host_lens, int B, const int32_t* dev_tokens_packed,

@@ -506,8 +506,13 @@ int gemm_tile_rows(const GemmArgs& a, int epilogue, int bn) {
 
 // K splits of a projection over more than 128 rows, and the streaming kernel's tile width: the pair for which the estimated
 // time of the launch plus that of the partial sums (written, and read by the norm kernel; 788 x 2560 of them cost 0.7 us
-// of the norm kernel each, and the writes about as much again) is least.  It depends on the shape alone, not on how the weights are
-// stored, so that repacked and row-major weights keep adding in the same order.
+// of the norm kernel each, and the writes about as much again) is least.  It depends on the shape - the rows of the whole call
+// among it - and not on how the weights are stored, so that repacked and row-major weights keep adding in the same order.
+// The estimates err by 5 to 9 %, so splits that they prefer by less may go either way; measured (launch unsplit -> as chosen, and
+// what the partial sums add to the norm kernel): down, 15,272 rows of the 4B shape (estimated gain 2.8 %) 712 -> 686 us and 21,
+// 8,000 rows (3.1 %) 398 -> 399 and 10; down of the 7B shape, 15,272 rows (4.2 %) 1972 -> 1803 and 20, 11,000 (7.2 %)
+// 1344 -> 1285 and 10; O of the 0.6B shape, 1,500 rows (3.0 %) 30.6 -> 21.5 and 0.8.  Asking for a gain of 8 % would lose all of
+// these but the second.
 float gemm_wide_shape(int M, int N, int K, int most, int& bn, int& splits) {
     float best = 1e30f;
     for (int s = 1; s <= std::max(1, most) && (s == 1 || (K % 128 == 0 && K / s >= 512)); ++s) {
