@@ -618,11 +618,8 @@ static hipError_t prefill_impl(const AttnArgs& a, int B, int max_new, hipStream_
     // (in one dimension a thousand sequences beside one of 65,600 tokens would pass the 2^32 threads that a dimension of a
     // launch may have)
     const dim3 grid(8 * qblocks, (gr.pairs + 7) / 8);
-    const size_t lds = (size_t)2 * 4 * (2 * kPageTokens * HD * 2);
-    if (lds > 65536) {
-        hipError_t e = hipFuncSetAttribute((const void*)attn_prefill_kernel<HD, ACT32>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        if (e != hipSuccess) return e;
-    }
+    constexpr size_t lds = (size_t)2 * 4 * (2 * kPageTokens * HD * 2);
+    static_assert(lds <= 65536, "more needs hipFuncAttributeMaxDynamicSharedMemorySize");
     hipLaunchKernelGGL((attn_prefill_kernel<HD, ACT32>), grid, dim3(256), lds, s, a, gr);
     return hipGetLastError();
 }

@@ -162,35 +162,31 @@ __global__ __launch_bounds__(256) void embed_norm_kernel(EmbedArgs a, RopeFreq f
         ActStore<ACT32>::put(a.h, (size_t)r * a.d + i, x[i] * rs * a.gain[i]);
 }
 
-// bf16 embedding, d % 8 == 0, d <= 8192: 16 bytes of the embedding row a thread (at most two such groups), the widened values stay
-// in registers between the reduction and the normalised store, and one sincos gives the rotation pair.  Bound by its stores;
-// 15,272 rows of the 4B shape 126 -> 66 us (2.5 -> 4.8 TB/s) against two-byte loads, a re-read of x and separate sine and cosine.
+// bf16 embedding, d % 8 == 0, d <= 8192: 16 bytes of the embedding row a thread, the widened values stay in registers between
+// the reduction and the normalised store, and one sincos gives the rotation pair.  Bound by its stores; 15,272 rows of the 4B
+// shape 126 -> 64 us (2.5 -> 4.9 TB/s) against two-byte loads, a re-read of x and separate sine and cosine.
 __global__ __launch_bounds__(1024) void embed_norm_wide_kernel(EmbedArgs a, RopeFreq f) {
     __shared__ float red[16];
     const int r = blockIdx.x, tid = threadIdx.x;
     const int pos = a.row_pos[r];
     int tok = a.tokens[r];
     tok = tok < 0 ? 0 : (tok >= a.vocab ? a.vocab - 1 : tok);   // ids are validated by the caller; stay in bounds regardless
-    const int groups = a.d >> 3;
-    float v[2][8];
+    const bool mine = tid < (a.d >> 3);
+    float v[8];
     float ss = 0.f;
+    if (mine) {
+        const u32x4 w = *(const u32x4*)((const uint16_t*)a.embed + (size_t)tok * a.d + tid * 8);
+        const uint32_t u[4] = {w.x, w.y, w.z, w.w};
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-        const int g = tid + j * blockDim.x;
-        if (g < groups) {
-            const u32x4 w = *(const u32x4*)((const uint16_t*)a.embed + (size_t)tok * a.d + g * 8);
-            const uint32_t u[4] = {w.x, w.y, w.z, w.w};
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                v[j][2 * i] = __uint_as_float(u[i] << 16);
-                v[j][2 * i + 1] = __uint_as_float(u[i] & 0xFFFF0000u);
-            }
-            float4* x = (float4*)(a.x + (size_t)r * a.d + g * 8);
-            x[0] = make_float4(v[j][0], v[j][1], v[j][2], v[j][3]);
-            x[1] = make_float4(v[j][4], v[j][5], v[j][6], v[j][7]);
-#pragma unroll
-            for (int i = 0; i < 8; ++i) ss += v[j][i] * v[j][i];
+        for (int i = 0; i < 4; ++i) {
+            v[2 * i] = __uint_as_float(u[i] << 16);
+            v[2 * i + 1] = __uint_as_float(u[i] & 0xFFFF0000u);
         }
+        float4* x = (float4*)(a.x + (size_t)r * a.d + tid * 8);
+        x[0] = make_float4(v[0], v[1], v[2], v[3]);
+        x[1] = make_float4(v[4], v[5], v[6], v[7]);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) ss += v[i] * v[i];
     }
     if (tid < a.half_hd) {
         double sn, cs;
@@ -206,24 +202,20 @@ __global__ __launch_bounds__(1024) void embed_norm_wide_kernel(EmbedArgs a, Rope
     float tot = 0.f;
     for (int w = 0; w < n_waves; ++w) tot += red[w];
     const float rs = rsqrtf(tot / (float)a.d + a.eps);
+    if (mine) {
+        const float4 g0 = *(const float4*)(a.gain + tid * 8), g1 = *(const float4*)(a.gain + tid * 8 + 4);
+        const float gn[8] = {g0.x, g0.y, g0.z, g0.w, g1.x, g1.y, g1.z, g1.w};
+        uint32_t o[4];
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-        const int g = tid + j * blockDim.x;
-        if (g < groups) {
-            const float4 g0 = *(const float4*)(a.gain + g * 8), g1 = *(const float4*)(a.gain + g * 8 + 4);
-            const float gn[8] = {g0.x, g0.y, g0.z, g0.w, g1.x, g1.y, g1.z, g1.w};
-            uint32_t o[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-                o[i] = (uint32_t)f32_to_act16(v[j][2 * i] * rs * gn[2 * i]) | ((uint32_t)f32_to_act16(v[j][2 * i + 1] * rs * gn[2 * i + 1]) << 16);
-            *(u32x4*)((uint16_t*)a.h + (size_t)r * a.d + g * 8) = u32x4{o[0], o[1], o[2], o[3]};
-        }
+        for (int i = 0; i < 4; ++i)
+            o[i] = (uint32_t)f32_to_act16(v[2 * i] * rs * gn[2 * i]) | ((uint32_t)f32_to_act16(v[2 * i + 1] * rs * gn[2 * i + 1]) << 16);
+        *(u32x4*)((uint16_t*)a.h + (size_t)r * a.d + tid * 8) = u32x4{o[0], o[1], o[2], o[3]};
     }
 }
 
 hipError_t launch_embed_norm(const EmbedArgs& a, const RopeFreq& f, bool w_bf16, bool act32, hipStream_t s) {
     if (w_bf16 && !act32 && (a.d & 7) == 0 && a.d <= 8192) {
-        const int threads = std::max(64, std::min(1024, ((a.d >> 3) + 63) & ~63));      // half_hd <= 64 of them make the rotations
+        const int threads = ((a.d >> 3) + 63) & ~63;      // one a group of 8; half_hd <= 64 of them make the rotations
         hipLaunchKernelGGL(embed_norm_wide_kernel, dim3(a.n_rows), dim3(threads), 0, s, a, f);
         return hipGetLastError();
     }
