@@ -28,3 +28,35 @@ def test_decode_attention_fits_three_waves_per_simd(tmp_path):
     assert len(stream) >= 6, sorted(found)                      # head_dim 32 / 64 / 128 x two activation types
     for name, (vgprs, spills) in stream.items():
         assert vgprs <= 168 and spills == 0, (name, vgprs, spills)
+
+
+def _resources(tmp_path, source):
+    """{kernel: (vector registers, vector spills)} as the compiler reports them"""
+    from paper_2506_24119_amd import build as B
+    if not (os.path.exists(B.HIPCC) or shutil.which(B.HIPCC)):
+        pytest.skip("hipcc not available")
+    src = os.path.join(B.CSRC, source)
+    cmd = [B.HIPCC] + B._flags() + ["-x", "hip", "--cuda-device-only", "-S", src, "-o", str(tmp_path / "k.s")]
+    r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    assert r.returncode == 0, r.stdout[-2000:]
+    asm = open(tmp_path / "k.s").read()
+    found = {}
+    for m in re.finditer(r"\.name:\s+(\S+)\n(?:.*\n)*?\s+\.vgpr_count:\s+(\d+)\n\s+\.vgpr_spill_count:\s+(\d+)", asm):
+        found[m.group(1)] = (int(m.group(2)), int(m.group(3)))
+    return found
+
+
+def test_prefill_attention_fits_two_waves_per_simd(tmp_path):
+    prefill = {k: v for k, v in _resources(tmp_path, "kernels_attn.hip").items() if "attn_prefill_kernel" in k}
+    assert len(prefill) == 6, sorted(prefill)                   # head_dim 32 / 64 / 128 x two activation types
+    for name, (vgprs, spills) in prefill.items():
+        assert vgprs <= 256 and spills == 0, (name, vgprs, spills)
+
+
+def test_tiled_projections_keep_their_accumulators_in_registers(tmp_path):
+    """One wave per SIMD has 512 registers, a 256-row tile's accumulators take half of them.  The scoring epilogue on such a
+    tile (gemm_tile_kernel<3, 256>) puts one register aside, outside the loop over K; nothing else spills."""
+    tile = {k: v for k, v in _resources(tmp_path, "kernels_gemm_tile.hip").items() if "gemm_tile_kernel" in k}
+    assert len(tile) == 7, sorted(tile)
+    for name, (vgprs, spills) in tile.items():
+        assert vgprs <= 512 and spills <= (1 if "ILi3ELi256E" in name else 0), (name, vgprs, spills)
