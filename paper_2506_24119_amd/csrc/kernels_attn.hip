@@ -158,8 +158,8 @@ struct PrefillGrid {
 // Bound: the exponentials and the matrix pipe take about equally long (a 64-token step of a wave is 32 MFMAs = 1024
 // cycles and 32 exponentials plus 100 other vector operations a lane, ~900), so two workgroups per compute unit
 // interleave them.  Against 16-row tiles that walk single pages straight from L2 (16x16 MFMAs, no LDS), a layer of:
-// 15,272 rows of U[256, 1024] tokens, 32 heads 353 -> 184 us; 11,206 rows of U[2048, 4096], 16 heads 484 -> 203 us
-// (0.63 PFLOP/s); 788 rows appended to nine histories of U[400, 2000] 122 -> 66 us.
+// 15,272 rows of U[256, 1024] tokens, 32 heads 353 -> 178 us; 11,206 rows of U[2048, 4096], 16 heads 484 -> 214 us
+// (0.60 PFLOP/s); 788 rows appended to nine histories of U[400, 2000] 122 -> 74 us.
 // ---------------------------------------------------------------------------------------------
 template <int HD, bool ACT32>
 __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(AttnArgs a, PrefillGrid gr) {

@@ -22,7 +22,7 @@
 // A second form has tiles of 128 x 256 (a wave 64 x 128, 128 accumulator registers), and K may be split over workgroups:
 // at 788 rows of the 4B shape 256-row tiles leave O and down 40 workgroups.  A layer's projections there, before (streaming
 // kernel for q/k/v, O and down, 256-row tiles for gate/up) and with the form and the split chosen by estimated time:
-// q/k/v 67 + 17 (its post-processing) -> 42 us, O 51 -> 25, gate/up 133 -> 110, down 113 -> 46.
+// q/k/v 67 + 17 (its post-processing) -> 50 us, O 51 -> 26, gate/up 133 -> 115, down 113 -> 50.
 
 #include <algorithm>
 

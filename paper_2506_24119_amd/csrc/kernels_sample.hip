@@ -22,7 +22,7 @@
 // Bound by the fixed-point exponentials of the histogram and the generator's integer arithmetic of the sweep.  Measured
 // against six launches (a plan kernel that read every bin, the single path's kernel launched behind for flagged rows) and at
 // most 8 slices a row, 151,936 entries, T = 0.6, top-p 0.95: one row 59 -> 35 us, 16 rows 55 -> 34, 128 rows of flat logits
-// 130 -> 112; 64 rows, top-k 50 54 -> 42.
+// 130 -> 111 (a call; 117 traced); 64 rows, top-k 50 54 -> 42.
 #include <algorithm>
 
 #include "spiral_internal.h"

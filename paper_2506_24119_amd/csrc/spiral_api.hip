@@ -614,7 +614,7 @@ static int run_layers(StepCtx& c) {
     const Tune& t = m->tune;
     const int d = cfg.d_model, hd = cfg.head_dim;
     const int qw = cfg.n_q_heads * hd, kw = cfg.n_kv_heads * hd, nqkv = qw + 2 * kw;
-    const bool wide = c.rows > 128 || act32;      // many row tiles already fill the GPU: no K split
+    const bool wide = c.rows > 128 || act32;      // shape() leaves K whole there
     // A narrow projection is split along K until its workgroups fill the 256 compute units in one
     // round (at least two 128-wide k chunks per split); 64-row workgroups when 128-row ones cannot.
     struct Shape { int bn, splits; };
