@@ -106,3 +106,25 @@ def test_head_groups_and_sequence_counts(q_heads, kv_heads):
         for b, s in enumerate(seqs):
             want = od.forward_full(g, host, s, logits_at=np.array([len(s) - 1]))[0]
             assert np.abs(got[b] - want).max() <= 3e-2 * want.std(), (n_seqs, b)
+
+
+@pytest.mark.parametrize("head_dim,dtype", [(32, si.WEIGHT_FP32), (128, si.WEIGHT_FP32), (64, si.WEIGHT_BF16)])
+def test_a_nan_token_can_be_dropped(head_dim, dtype):
+    """A run with a NaN token in it, cut back to the tokens before it and continued: the kept K and V of the second layer, which
+    earlier positions' attention produced, hold no NaN.  Bound as for a sequence among others: 1e-2 x std."""
+    from paper_2506_24119_amd import binding as sb
+    g = si.ModelGeometry("nan", 2, 64, 8, 2, head_dim, 128, 256, 1e4, tie_lm_head=False, weight_dtype=dtype)
+    w = si.make_weights(g, seed=17)
+    w["embed"][7] = 0x7FC0 if dtype == si.WEIGHT_BF16 else np.nan
+    wd = sb.weights_to_device(w)
+    rng = np.random.Generator(np.random.PCG64(8))
+    seq, more = rng.integers(8, g.vocab, 100).astype(np.int32), rng.integers(8, g.vocab, 3).astype(np.int32)
+    seq[70] = 7
+    got = []
+    for run in (seq, seq[:70]):
+        sess = sb.Session(g, wd, 16, 1, 16, 128, 200, page_order=si.make_page_order(16, 2))
+        sess.prefill([0], [run])
+        sb.spiral_seq_truncate(sess.pool, [0], [70])
+        got.append(sess.prefill([0], [more]).cpu().numpy()[0])
+        sess.close()
+    assert np.abs(got[0] - got[1]).max() <= 1e-2 * got[1].std()
