@@ -553,7 +553,7 @@ float gemm_tile_qkv_us(int M, int N, int K) {
     return gemm_tile_us(M, N, K, 1, 256, 128) + 8.f * (float)((tiles + 255) / 256);
 }
 hipError_t launch_gemm_tile_qkv(const GemmArgs& a, const QkvPostArgs& qa, hipStream_t s) {
-    if (!gemm_tile_usable(a) || a.splits != 1 || !gemm_tile_qkv_fits(a.N, a.K, qa)) return hipErrorInvalidValue;
+    if (!gemm_tile_usable(a) || a.splits != 1 || qa.row_map || !gemm_tile_qkv_fits(a.N, a.K, qa)) return hipErrorInvalidValue;
     return launch_tile_bm<2, 128>(a, qa, s);
 }
 

@@ -261,7 +261,8 @@ __global__ __launch_bounds__(1024) void add_norm_wide_kernel(NormArgs a) {
                 const float4 q = *(const float4*)(prow + p * pstride + i);
                 acc.x += q.x; acc.y += q.y; acc.z += q.z; acc.w += q.w;
             }
-            if (a.n_part > 0) *(float4*)(x + i) = acc;
+            if (a.x_out) *(float4*)(a.x_out + (size_t)ro * a.d + i) = acc;
+            else if (a.n_part > 0) *(float4*)(x + i) = acc;
             v[j] = acc;
             ss += acc.x * acc.x + acc.y * acc.y + acc.z * acc.z + acc.w * acc.w;
         }
@@ -294,21 +295,22 @@ __global__ __launch_bounds__(256) void add_norm_kernel(NormArgs a) {
     __shared__ float red[4];
     const int ro = blockIdx.x;
     const int ri = a.row_map ? a.row_map[ro] : ro;
-    float* x = a.x + (size_t)ri * a.d;
+    const float* x = a.x + (size_t)ri * a.d;
+    float* xo = a.x_out ? a.x_out + (size_t)ro * a.d : a.x + (size_t)ri * a.d;
     const size_t pstride = (size_t)a.rows_in * a.d;
     const float* prow = a.part + (size_t)ri * a.d;
     float ss = 0.f;
     for (int i = threadIdx.x; i < a.d; i += 256) {
         float v = x[i];
         for (int p = 0; p < a.n_part; ++p) v += prow[p * pstride + i];
-        if (a.n_part > 0) x[i] = v;
+        if (a.n_part > 0 || a.x_out) xo[i] = v;
         ss += v * v;
     }
     ss = block_sum_256(ss, red);
     const float rs = rsqrtf(ss / (float)a.d + a.eps);
     bool bad = false;
     for (int i = threadIdx.x; i < a.d; i += 256)
-        ActStore<ACT32>::put_noting(a.h, (size_t)ro * a.d + i, x[i] * rs * a.gain[i], bad);
+        ActStore<ACT32>::put_noting(a.h, (size_t)ro * a.d + i, xo[i] * rs * a.gain[i], bad);
     report_saturation(a.sat_count, bad);
 }
 
@@ -353,7 +355,8 @@ __global__ __launch_bounds__(256) void qkv_post_kernel(QkvPostArgs a) {
     const int bias_off = (is_q ? head : kvh) * hd;
     const float* gain = is_q ? a.q_gain : (is_k ? a.k_gain : nullptr);
 
-    const int2 pp = a.row_page[r];                       // (page, position): q heads read it too and ignore it
+    const int rr = a.row_map ? a.row_map[r] : r;
+    const int2 pp = a.row_page[rr];                      // (page, position): q heads read it too and ignore it
     const int slot = pp.y & (kPageTokens - 1);
     const size_t page_base = ((size_t)pp.x * a.n_kv_heads + kvh) * (size_t)(2 * kPageTokens * hd);
 
@@ -380,7 +383,7 @@ __global__ __launch_bounds__(256) void qkv_post_kernel(QkvPostArgs a) {
             }
         }
         if (gain) { g_lo = gain[pc]; g_hi = gain[pc + half]; }
-        const float2 cs = a.rope[(size_t)r * half + pc];
+        const float2 cs = a.rope[(size_t)rr * half + pc];
         float lo = 0.f, hi = 0.f;
 #pragma unroll
         for (int s = 0; s < NP; ++s)

@@ -54,6 +54,7 @@ struct Tune {
     int attn_wgs = 0;              // workgroups of the decode attention; 0 = 3 per compute unit (its occupancy)
     int frag = 1;                  // 0: ignore spiral_model_repack (weights stay row-major; for A/B measurements)
     int fuse_qkv = 1;              // 0: large-M q/k/v projection and its post-processing as two kernels (for A/B measurements)
+    int trim = 1;                  // 0: a prefill's last layer computes every row (for A/B measurements)
     int fail_after = 0;            // test hook: the n-th timed launch from now reports a launch failure instead of running
 };
 constexpr int kDecodePieces = 16;      // partial results of a (row, kv head) pair in a step with few units
@@ -116,6 +117,7 @@ static void parse_tune(Tune& t, const char* e) {
                 else if (k == "wgs") { t.attn_wgs = a; }
                 else if (k == "frag") { t.frag = a; }
                 else if (k == "fuse_qkv") { t.fuse_qkv = a; }
+                else if (k == "trim") { t.trim = a; }
                 else if (k == "fail_after") { t.fail_after = a; }
             }
         }
@@ -596,7 +598,34 @@ struct StepCtx {
     bool sample = false;                                   // fused LM head + sampler (no logits written)
     float temperature = 0.f;
     int32_t* out_tokens = nullptr;
-};
+    const int32_t *host_ids = nullptr, *host_pos = nullptr;   // prefill: sequences and the positions of their last tokens
+    int first_layer = 0;
+    const int32_t* q_rows = nullptr;                       // set: first_layer's k and v are in the pages and h is normed; q's rows of the
+};                                                         // rotation table
+
+// Pieces and partial results of the decode attention over c.rows rows; `pages`: the sum of the rows' page counts.
+static void plan_decode_attention(StepCtx& c, int pages_all, int max_ctx) {
+    const spiral_model* m = c.m;
+    const int wgs = m->tune.attn_wgs > 0 ? m->tune.attn_wgs : 3 * m->n_cus;
+    c.total_units = pages_all * m->cfg.n_kv_heads;
+    c.units_per_wg = std::max(m->tune.chunk_pages, (c.total_units + wgs - 1) / wgs);
+    c.n_slots = decode_slots(m, max_ctx);
+    if (!m->tune.chunk_set && c.units_per_wg == m->tune.chunk_pages) {
+        // Few units (a small batch): as many workgroups as there are pages, up to 16 pieces to a pair.  A workgroup's time
+        // is its chain of dependent steps, of which 16 pages are four per wave: one row of 250 tokens, 4B shape, pieces of
+        // 16 / 8 / 4 / 2 pages 8.8 / 7.0 / 5.9 / 4.1 us; 1,450 tokens in 16 pieces 5.3 us, in 32 9.4.  The larger
+        // number of partial results goes to the q/k/v products' memory, dead by then.
+        const int pages = (max_ctx + kPageTokens - 1) / kPageTokens;
+        const int units = std::max((c.total_units + wgs - 1) / wgs, (pages + kDecodePieces - 1) / kDecodePieces);
+        const int slots = (pages + units - 1) / units + 2;
+        const size_t need = (size_t)c.rows * m->cfg.n_q_heads * slots * (m->cfg.head_dim + 2) * sizeof(float);
+        if (units < c.units_per_wg && need <= (size_t)((char*)c.w.q - (char*)c.w.qkv)) {
+            c.units_per_wg = units;
+            c.n_slots = slots;
+            c.w.attn_part = c.w.qkv;
+        }
+    }
+}
 
 namespace spiral {
 // The scoring pass's pairs (one per row and 128 columns) go where every product of the layers is dead by then: from qkv to mlp
@@ -631,7 +660,6 @@ static int run_layers(StepCtx& c) {
         if (wide) s = 1;
         return Shape{bn, std::max(1, std::min(s, K / 128))};
     };
-    Shape sh_qkv = shape(t.bn_qkv, t.s_qkv, nqkv, d);
     Shape sh_o = shape(t.bn_o, t.s_o, d, qw), sh_down = shape(t.bn_down, t.s_down, d, cfg.ffn_dim);
     // More than 128 rows: the row tiles of O and down still leave compute units idle up to a few thousand rows, so their K
     // is split too.  The partial sums go where the layer's other products are dead by then (the workspace is carved in the
@@ -643,7 +671,6 @@ static int run_layers(StepCtx& c) {
         else gemm_wide_shape(c.rows, N, K, cap, sh.bn, sh.splits);
     };
     float *part_o = c.w.proj, *part_down = c.w.proj;
-    bool fuse_qkv = false;              // the q/k/v projection's epilogue does the post-processing, its product never reaches memory
     if (c.rows > 128 && !act32) {
         const size_t product = (size_t)c.rows * d * sizeof(float);
         const size_t front = ((char*)c.w.o - (char*)c.w.qkv) / product, back = ((char*)c.w.hf - (char*)c.w.proj) / product;
@@ -652,47 +679,110 @@ static int run_layers(StepCtx& c) {
         wide_or_set(t.bn_o, t.s_o, d, qw, std::max(front, back), sh_o);
         wide_or_set(t.bn_down, t.s_down, d, cfg.ffn_dim, ((char*)c.w.mlp - (char*)c.w.qkv) / product, sh_down);
     }
-    if (c.rows > 128 && !act32 && sh_qkv.bn != 1) {
+    // The projection onto q, k and v heads (the last layer of a prefill has k and v, then q, by themselves) and what follows it.
+    struct QkvPlan { Shape sh; bool fuse; int hq, hkv; };       // fuse: its epilogue does the post-processing, no product reaches memory
+    auto plan_qkv = [&](int hq, int hkv) {
+        const int N = (hq + 2 * hkv) * hd;
+        const int set_bn = hkv ? t.bn_qkv : 0, set_s = hkv ? t.s_qkv : 0;
+        QkvPlan pl = {shape(set_bn, set_s, N, d), false, hq, hkv};
+        if (c.rows <= 128 || act32 || pl.sh.bn == 1) return pl;
         // the fused form against a projection split along K (its partials fill the product's own memory, which holds at least
         // 16 x 128 rows) with qkv_post_kernel behind it: 5 us and 2.55 ps a product (9 us at 200 rows of the 4B shape,
         // 17 at 788).  By shape alone, as above; row-major weights take the unsplit projection where the others are fused.
-        const int most = (int)std::min<size_t>(((char*)c.w.q - (char*)c.w.qkv) / ((size_t)c.rows * nqkv * sizeof(float)), kMaxSplit);
+        const int most = (int)std::min<size_t>(((char*)c.w.q - (char*)c.w.qkv) / ((size_t)c.rows * N * sizeof(float)), kMaxSplit);
         QkvPostArgs qs = {};
-        qs.hd = hd; qs.n_q_heads = cfg.n_q_heads; qs.n_kv_heads = cfg.n_kv_heads;
+        qs.hd = hd; qs.n_q_heads = hq; qs.n_kv_heads = hkv;
         Shape sh = {128, 1};
-        const float split_us = gemm_wide_shape(c.rows, nqkv, d, most, sh.bn, sh.splits) + 5.f + 2.55e-6f * (float)c.rows * (float)nqkv;
-        const bool set = t.bn_qkv || t.s_qkv;
-        const bool faster = d % 128 ? gemm_tile_qkv_fills(c.rows, nqkv) : gemm_tile_qkv_us(c.rows, nqkv, d) <= split_us;
-        if (t.fuse_qkv && t.s_qkv <= 1 && gemm_tile_qkv_fits(nqkv, d, qs) && faster) fuse_qkv = true;
-        else if (set) sh_qkv.splits = std::max(1, std::min({t.s_qkv, most, d / 128}));
-        else sh_qkv = sh;
-    }
-    const int s_qkv = sh_qkv.splits, s_o = sh_o.splits, s_down = sh_down.splits;
+        const float split_us = gemm_wide_shape(c.rows, N, d, most, sh.bn, sh.splits) + 5.f + 2.55e-6f * (float)c.rows * (float)N;
+        const bool set = set_bn || set_s;
+        const bool faster = d % 128 ? gemm_tile_qkv_fills(c.rows, N) : gemm_tile_qkv_us(c.rows, N, d) <= split_us;
+        if (t.fuse_qkv && set_s <= 1 && hkv && gemm_tile_qkv_fits(N, d, qs) && faster) pl.fuse = true;
+        else if (set) pl.sh.splits = std::max(1, std::min({set_s, most, d / 128}));
+        else pl.sh = sh;
+        return pl;
+    };
+    // A prefill returns the logits of every sequence's last token, so its last layer needs k and v of all rows and the rest - q,
+    // attention, O, the MLP - for one row a sequence: what a decode step does, on the decode step's kernels.  The other rows' work
+    // reaches no output.  From 129 rows and four to a sequence on: below 129 the projections stream the same weights for one row as
+    // for all, and with three rows to a sequence the extra launches (about 20 us) cost what they save on the smallest shape.  Whole
+    // calls of four 0.6B or 4B layers and two 7B layers, all rows / last rows, us: 1 x 129 tokens 259 / 253, 488 / 454, 390 / 341;
+    // 24 x 10 265 / 262, 526 / 491, 423 / 362; 64 x 4 at 1,000 463 / 458, 734 / 705, 505 / 434; 64 x 3 at 100 268 / 275 (0.6B).
+    // Two 4B layers, 15,272 rows: 6755 / 3798; four, 788 rows on histories: 1364 / 1162; four 0.6B layers, 11,206 rows: 3028 / 2447.
+    // (The last layer's share: of a 36-layer model's prefill it is 2.3 %.)
+    const int last = cfg.n_layers - 1;
+    const bool trim = t.trim && !c.decode && !c.score_out && !act32 && c.rows > 128 && c.rows >= 4 * c.B &&
+                      !(t.bn_o || t.s_o || t.bn_down || t.s_down) &&                // set for the rows of the call
+                      d % 128 == 0 && qw % 128 == 0 && cfg.ffn_dim % 128 == 0;      // the widths that the streaming kernels take
+    const QkvPlan whole = plan_qkv(cfg.n_q_heads, cfg.n_kv_heads);
+    const int s_o = sh_o.splits, s_down = sh_down.splits;
     const float* part = c.w.proj;       // the partials waiting to be added to the residual
     int pending = 0;            // projection partials waiting to be added to the residual
     int32_t* sat = c.p->d_status;
 
-    for (int l = 0; l < cfg.n_layers; ++l) {
-        if (l > 0) {
+    auto project = [&](int l, const QkvPlan& pl, const int32_t* row_map) -> int {
+        GemmArgs g = {};
+        int blocks = 0;
+        if (pl.hq) { g.w[blocks] = m->lw(l, SPIRAL_W_Q); g.rows[blocks++] = qw; }
+        if (pl.hkv) {
+            g.w[blocks] = m->lw(l, SPIRAL_W_K); g.rows[blocks++] = kw;
+            g.w[blocks] = m->lw(l, SPIRAL_W_V); g.rows[blocks++] = kw;
+        }
+        g.A = c.w.h; g.M = c.rows; g.N = (pl.hq + 2 * pl.hkv) * hd; g.K = d; g.out = c.w.qkv; g.splits = pl.sh.splits;
+        g.wf = m->f_lm ? (const uint16_t*)m->f_qkv[l] + (pl.hq ? 0 : frag_block(qw / 32, 0, d)) : nullptr;
+        QkvPostArgs qa = {c.w.qkv, m->lw(l, SPIRAL_W_BQ), m->lw(l, SPIRAL_W_BK), m->lw(l, SPIRAL_W_BV),
+                          (const float*)m->lw(l, SPIRAL_W_Q_NORM), (const float*)m->lw(l, SPIRAL_W_K_NORM),
+                          c.w.rope, c.w.row_page, c.w.q, c.p->d_pages + (size_t)l * c.p->layer_elems,
+                          c.rows, pl.sh.splits, pl.hq, pl.hkv, hd, cfg.rms_eps, sat, row_map};
+        if (pl.fuse && gemm_tile_usable(g)) {
+            HIP_TRY(timed(m, SPIRAL_K_GEMM_QKV, c.s, [&] { return launch_gemm_tile_qkv(g, qa, c.s); }));
+        } else if (row_map) {               // the last rows' queries: one class, the post-processing counts a layer's k and v
+            HIP_TRY(timed(m, SPIRAL_K_GEMM_QKV, c.s, [&] {
+                const hipError_t e = launch_gemm(g, EPI_STORE_F32, m->w_bf16, pl.sh.bn, c.s);
+                return e != hipSuccess ? e : launch_qkv_post(qa, m->w_bf16, c.s);
+            }));
+        } else {
+            HIP_TRY(timed(m, SPIRAL_K_GEMM_QKV, c.s, [&] { return launch_gemm(g, EPI_STORE_F32, m->w_bf16, pl.sh.bn, c.s); }));
+            HIP_TRY(timed(m, SPIRAL_K_QKV_POST, c.s, [&] { return launch_qkv_post(qa, m->w_bf16, c.s); }));
+        }
+        return SPIRAL_OK;
+    };
+
+    for (int l = c.first_layer; l < cfg.n_layers; ++l) {
+        const bool q_only = c.q_rows && l == c.first_layer;
+        if (l > 0 && !q_only) {
             NormArgs n = {c.w.x, part, (const float*)m->lw(l, SPIRAL_W_ATTN_NORM), c.w.h, nullptr, c.rows, c.rows, d, pending, cfg.rms_eps, sat};
             HIP_TRY(timed(m, SPIRAL_K_NORM, c.s, [&] { return launch_add_norm(n, act32, c.s); }));
         }
-        GemmArgs g = {};
-        g.A = c.w.h; g.w[0] = m->lw(l, SPIRAL_W_Q); g.w[1] = m->lw(l, SPIRAL_W_K); g.w[2] = m->lw(l, SPIRAL_W_V);
-        g.rows[0] = qw; g.rows[1] = kw; g.rows[2] = kw;
-        g.M = c.rows; g.N = nqkv; g.K = d; g.out = c.w.qkv; g.splits = s_qkv;
-        g.wf = m->f_lm ? m->f_qkv[l] : nullptr;
-        uint16_t* pages = c.p->d_pages + (size_t)l * c.p->layer_elems;
-        QkvPostArgs qa = {c.w.qkv, m->lw(l, SPIRAL_W_BQ), m->lw(l, SPIRAL_W_BK), m->lw(l, SPIRAL_W_BV),
-                          (const float*)m->lw(l, SPIRAL_W_Q_NORM), (const float*)m->lw(l, SPIRAL_W_K_NORM),
-                          c.w.rope, c.w.row_page, c.w.q, pages,
-                          c.rows, s_qkv, cfg.n_q_heads, cfg.n_kv_heads, hd, cfg.rms_eps, sat};
-        if (fuse_qkv && gemm_tile_usable(g)) {
-            HIP_TRY(timed(m, SPIRAL_K_GEMM_QKV, c.s, [&] { return launch_gemm_tile_qkv(g, qa, c.s); }));
-        } else {
-            HIP_TRY(timed(m, SPIRAL_K_GEMM_QKV, c.s, [&] { return launch_gemm(g, EPI_STORE_F32, m->w_bf16, sh_qkv.bn, c.s); }));
-            HIP_TRY(timed(m, SPIRAL_K_QKV_POST, c.s, [&] { return launch_qkv_post(qa, m->w_bf16, c.s); }));
+        if (trim && l == last) {
+            QkvPlan kv = plan_qkv(0, cfg.n_kv_heads);
+            if (whole.fuse) kv.fuse = true, kv.sh = whole.sh;     // as in the layers before: the same order of sums
+            int rc = project(l, kv, nullptr);
+            if (rc) return rc;
+            // the last rows: residual to h's memory (h has been read), normed to hf
+            NormArgs n = {c.w.x, nullptr, (const float*)m->lw(l, SPIRAL_W_ATTN_NORM), c.w.hf, c.w.last_rows, c.rows, c.B, d, 0, cfg.rms_eps,
+                          nullptr, (float*)c.w.h};
+            HIP_TRY(timed(m, SPIRAL_K_NORM, c.s, [&] { return launch_add_norm(n, act32, c.s); }));
+            std::vector<int32_t> start(c.B + 1, 0);
+            int max_ctx = 0;
+            for (int i = 0; i < c.B; ++i) {
+                start[i + 1] = start[i] + c.host_pos[i] / kPageTokens + 1;
+                max_ctx = std::max(max_ctx, c.host_pos[i] + 1);
+            }
+            int32_t* dst[3] = {c.w.row_seq, c.w.row_pos, c.w.page_start};
+            const int32_t* src[3] = {c.host_ids, c.host_pos, start.data()};
+            const int cnt[3] = {c.B, c.B, c.B + 1};
+            HIP_TRY(launch_upload_multi(dst, src, cnt, 3, c.s));
+            StepCtx r = c;
+            r.decode = true; r.rows = c.B; r.first_layer = l; r.q_rows = c.w.last_rows;
+            r.w.x = (float*)c.w.h; r.w.h = c.w.hf;
+            plan_decode_attention(r, start[c.B], max_ctx);
+            return run_layers(r);
         }
+        {
+            int rc = project(l, q_only ? plan_qkv(cfg.n_q_heads, 0) : whole, c.q_rows);
+            if (rc) return rc;
+        }
+        uint16_t* pages = c.p->d_pages + (size_t)l * c.p->layer_elems;
 
         AttnArgs aa = {};
         aa.q = c.w.q; aa.pages = pages; aa.block_table = c.p->d_block_table; aa.row_seq = c.w.row_seq;
@@ -820,12 +910,13 @@ static int prefill_or_score(spiral_model* m, spiral_kv_pool* p, const int32_t* h
     if (rc) return rc;
 
     Workspace w = carve(m, (char*)dev_ws, (int)rows, max_ctx);
-    std::vector<int32_t> cu(B + 1), base(B), last(B), ids(host_seq_ids, host_seq_ids + B);
+    std::vector<int32_t> cu(B + 1), base(B), last(B), last_pos(B), ids(host_seq_ids, host_seq_ids + B);
     cu[0] = 0;
     for (int i = 0; i < B; ++i) {
         cu[i + 1] = cu[i] + host_lens[i];
         base[i] = p->h_lens[ids[i]];
         last[i] = cu[i + 1] - 1;
+        last_pos[i] = base[i] + host_lens[i] - 1;
     }
     // everything that can fail runs before the lengths advance; on failure the pages go back
     auto enqueue = [&]() -> int {
@@ -841,6 +932,7 @@ static int prefill_or_score(spiral_model* m, spiral_kv_pool* p, const int32_t* h
         StepCtx c = {m, p, w, s, (int)rows, B, false, max_new, 1, dev_logits};
         c.score_targets = dev_targets;
         c.score_out = dev_logp;
+        c.host_ids = ids.data(); c.host_pos = last_pos.data();
         return run_layers(c);
     };
     rc = enqueue();
@@ -941,27 +1033,7 @@ static int decode_impl(spiral_model* m, spiral_kv_pool* p, const int32_t* host_s
                        w.row_seq, p->d_block_table, p->max_blocks, w.row_page};
         HIP_TRY(launch_embed_norm(e, m->freq, m->w_bf16, !m->w_bf16, s));
         StepCtx c = {m, p, w, s, B, B, true, 1, decode_chunks(m, max_ctx), dev_logits};
-        {
-            const int wgs = m->tune.attn_wgs > 0 ? m->tune.attn_wgs : 3 * m->n_cus;
-            c.total_units = start[B] * m->cfg.n_kv_heads;
-            c.units_per_wg = std::max(m->tune.chunk_pages, (c.total_units + wgs - 1) / wgs);
-            c.n_slots = decode_slots(m, max_ctx);
-            if (!m->tune.chunk_set && c.units_per_wg == m->tune.chunk_pages) {
-                // Few units (a small batch): as many workgroups as there are pages, up to 16 pieces to a pair.  A workgroup's time
-                // is its chain of dependent steps, of which 16 pages are four per wave: one row of 250 tokens, 4B shape, pieces of
-                // 16 / 8 / 4 / 2 pages 8.8 / 7.0 / 5.9 / 4.1 us; 1,450 tokens in 16 pieces 5.3 us, in 32 9.4.  The larger
-                // number of partial results goes to the q/k/v products' memory, dead by then.
-                const int pages = (max_ctx + kPageTokens - 1) / kPageTokens;
-                const int units = std::max((c.total_units + wgs - 1) / wgs, (pages + kDecodePieces - 1) / kDecodePieces);
-                const int slots = (pages + units - 1) / units + 2;
-                const size_t need = (size_t)B * m->cfg.n_q_heads * slots * (m->cfg.head_dim + 2) * sizeof(float);
-                if (units < c.units_per_wg && need <= (size_t)((char*)w.q - (char*)w.qkv)) {
-                    c.units_per_wg = units;
-                    c.n_slots = slots;
-                    c.w.attn_part = w.qkv;
-                }
-            }
-        }
+        plan_decode_attention(c, start[B], max_ctx);
         if (sp) { c.sample = true; c.temperature = sp->temperature; c.out_tokens = sp->dev_out_tokens; }
         return run_layers(c);
     };

@@ -108,6 +108,7 @@ struct NormArgs {
     int32_t rows_in, rows_out, d, n_part;
     float eps;
     int32_t* sat_count;       // or null
+    float* x_out;             // or null: the residual rows go here, [rows_out][d], instead of back to x
 };
 hipError_t launch_add_norm(const NormArgs& a, bool act32, hipStream_t s);
 
@@ -122,6 +123,7 @@ struct QkvPostArgs {
     int32_t n_rows, n_part, n_q_heads, n_kv_heads, hd;
     float eps;
     int32_t* sat_count;       // or null
+    const int32_t* row_map;   // or null: row r's rotation (and page) are those of row row_map[r]
 };
 hipError_t launch_qkv_post(const QkvPostArgs& a, bool w_bf16, hipStream_t s);
 
