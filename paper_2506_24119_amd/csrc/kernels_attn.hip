@@ -517,27 +517,37 @@ __global__ __launch_bounds__(256) void attn_stream_kernel(AttnArgs a) {
     }
 }
 
-// Merge the partial results of one (row, query head) written by attn_stream_kernel.  PRE parts are requested at once (past
-// the end: the last one again, not counted): a loop that waits for each costs 0.45 us a part (1,450 tokens in 4-page pieces
-// 10.8 us, eight at a time 3.4).  Four where no pair has more: further requests only repeat the last part.
+// Merge the partial results of one (row, query head) written by attn_stream_kernel: one wave, a lane holds VEC neighbouring
+// dimensions.  PRE parts are requested at once (past the end: the last one again, not counted): a loop that waits for each costs
+// 0.45 us a part (1,450 tokens in 4-page pieces 10.8 us, eight at a time 3.4).  Four where no pair has more: further requests only
+// repeat the last part.
 template <int HD, bool ACT32, int PRE>
-__global__ __launch_bounds__(HD) void attn_stream_combine_kernel(AttnArgs a) {
-    const int r = blockIdx.x, h = blockIdx.y, i = threadIdx.x;
+__global__ __launch_bounds__(64) void attn_stream_combine_kernel(AttnArgs a) {
+    constexpr int VEC = HD >= 128 ? 2 : 1;
+    const int r = blockIdx.x, h = blockIdx.y, i = threadIdx.x * VEC;
+    if (i >= HD) return;
     const int G = a.n_q_heads / a.n_kv_heads, Hkv = a.n_kv_heads;
     const int kvh = h / G, j = h % G;
     const int rs = a.row_page_start[r], np = a.row_page_start[r + 1] - rs;
     const int first = (rs * Hkv + kvh * np) / a.units_per_wg;
     const int last = (rs * Hkv + kvh * np + np - 1) / a.units_per_wg;
     const int n_parts = last - first + 1;
-    const float* base = a.part + (((size_t)r * Hkv + kvh) * a.n_chunks * G + j) * (HD + 2);
+    const float* base = a.part + (((size_t)r * Hkv + kvh) * a.n_chunks * G + j) * (HD + 2);       // a part is HD + 2 floats: 8-byte aligned
     const size_t cstride = (size_t)G * (HD + 2);
-    float M = kNegBig, L = 0.f, O = 0.f;
+    float M = kNegBig, L = 0.f, O[VEC];
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) O[e] = 0.f;
     for (int c0 = 0; c0 < n_parts; c0 += PRE) {
-        float pm[PRE], pl[PRE], po[PRE];
+        float pm[PRE], pl[PRE], po[PRE][VEC];
 #pragma unroll
         for (int c = 0; c < PRE; ++c) {
             const float* src = base + (size_t)min(c0 + c, n_parts - 1) * cstride;
-            pm[c] = src[HD]; pl[c] = src[HD + 1]; po[c] = src[i];
+            const float2 ml = *(const float2*)(src + HD);
+            pm[c] = ml.x; pl[c] = ml.y;
+            if (VEC == 2) {
+                const float2 o = *(const float2*)(src + i);
+                po[c][0] = o.x; po[c][VEC - 1] = o.y;
+            } else po[c][0] = src[i];
         }
         float m_new = M;
 #pragma unroll
@@ -546,7 +556,8 @@ __global__ __launch_bounds__(HD) void attn_stream_combine_kernel(AttnArgs a) {
         if (c0 > 0) {
             const float sc = __builtin_amdgcn_exp2f(M - m_new);
             L *= sc;
-            O *= sc;
+#pragma unroll
+            for (int e = 0; e < VEC; ++e) O[e] *= sc;
         }
         M = m_new;
 #pragma unroll
@@ -554,10 +565,18 @@ __global__ __launch_bounds__(HD) void attn_stream_combine_kernel(AttnArgs a) {
             if (c0 + c < n_parts) {
                 const float sc = __builtin_amdgcn_exp2f(pm[c] - M);
                 L += pl[c] * sc;
-                O += po[c] * sc;
+#pragma unroll
+                for (int e = 0; e < VEC; ++e) O[e] += po[c][e] * sc;
             }
     }
-    ActStore<ACT32>::put(a.out, ((size_t)r * a.n_q_heads + h) * HD + i, O / L);
+    const size_t at = a.out_frag ? act_frag(r, h * HD + i, a.n_rows, a.n_q_heads * HD) : ((size_t)r * a.n_q_heads + h) * HD + i;
+    if (ACT32) {
+        if (VEC == 2) *(float2*)((float*)a.out + at) = make_float2(O[0] / L, O[VEC - 1] / L);
+        else ((float*)a.out)[at] = O[0] / L;
+    } else {
+        if (VEC == 2) *(uint32_t*)((uint16_t*)a.out + at) = (uint32_t)f32_to_act16(O[0] / L) | ((uint32_t)f32_to_act16(O[VEC - 1] / L) << 16);
+        else ((uint16_t*)a.out)[at] = f32_to_act16(O[0] / L);
+    }
 }
 
 template <int HD, bool ACT32>
@@ -571,7 +590,7 @@ static hipError_t stream_impl(const AttnArgs& a, hipStream_t s) {
 
 template <int HD, bool ACT32>
 static hipError_t stream_combine_impl(const AttnArgs& a, hipStream_t s) {
-    const dim3 g(a.n_rows, a.n_q_heads), b(HD);
+    const dim3 g(a.n_rows, a.n_q_heads), b(64);
     if (a.n_chunks <= 4) hipLaunchKernelGGL((attn_stream_combine_kernel<HD, ACT32, 4>), g, b, 0, s, a);
     else hipLaunchKernelGGL((attn_stream_combine_kernel<HD, ACT32, 8>), g, b, 0, s, a);
     return hipGetLastError();

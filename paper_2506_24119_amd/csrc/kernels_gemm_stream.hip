@@ -1,4 +1,5 @@
-// Weight-streaming projection kernel for the decode step (K a multiple of 128).
+// Weight-streaming projection kernel for row tiles of 128 (K a multiple of 128): the LM head above 32 rows, gate/up of more than
+// 12,288 ffn columns, and above 128 rows row-major weights and what gemm_tile_kernel does not take.
 //
 // out[m][n] = sum_k A[m][k] * W[n][k], M <= 128 rows per tile.  Every weight byte is used once, so
 // the kernel is a stream over W; at M = 128 it also needs ~40 % of the matrix-core peak while
@@ -425,8 +426,10 @@ static hipError_t launch_one(const GemmArgs& a, hipStream_t s, bool sample = fal
 
 template <bool SWIGLU>
 static hipError_t launch_shape(const GemmArgs& a, int bn, hipStream_t s, bool sample = false) {
-    // bn = weight rows per workgroup (128 or 64); narrower workgroups split the batch between waves
-    if (a.M <= 32) return launch_one<1, 4, SWIGLU, 4>(a, s, sample);
+    // bn = weight rows per workgroup (128 or 64); narrower workgroups split the batch between waves.  Up to 32 rows only gate/up
+    // projections come here.
+    if constexpr (SWIGLU)
+        if (a.M <= 32) return launch_one<1, 4, SWIGLU, 4>(a, s, sample);
     if (a.M <= 64) return bn >= 128 ? launch_one<2, 4, SWIGLU, 3>(a, s, sample) : launch_one<2, 2, SWIGLU, 3>(a, s, sample);
 #ifndef STREAM_PD
 #define STREAM_PD 2
@@ -437,8 +440,9 @@ static hipError_t launch_shape(const GemmArgs& a, int bn, hipStream_t s, bool sa
     return bn >= 128 ? launch_one<4, 4, SWIGLU, STREAM_PD>(a, s, sample) : launch_one<4, 2, SWIGLU, 3>(a, s, sample);
 }
 
-// columns of the LM head that one workgroup of the sampling epilogue covers (host code sizes s_part with it)
-int gemm_sample_tile_cols(int M, int bn) { return (M > 32 && bn < 128) ? 64 : 128; }
+// columns of the LM head that one workgroup of the sampling epilogue covers (host code sizes s_part with it): up to 32 rows two
+// tiles of gemm_decode_kernel
+int gemm_sample_tile_cols(int M, int bn) { return (M <= 32 || bn < 128) ? 64 : 128; }
 
 hipError_t launch_gemm_stream(const GemmArgs& a, int epilogue, int bn, hipStream_t s) {
     if ((a.K & 127) || (a.N & 15) || a.splits < 1 || a.splits > (a.K >> 7)) return hipErrorInvalidValue;

@@ -159,7 +159,7 @@ __global__ __launch_bounds__(256) void embed_norm_kernel(EmbedArgs a, RopeFreq f
     ss = block_sum_256(ss, red);
     const float rs = rsqrtf(ss / (float)a.d + a.eps);
     for (int i = threadIdx.x; i < a.d; i += 256)
-        ActStore<ACT32>::put(a.h, (size_t)r * a.d + i, x[i] * rs * a.gain[i]);
+        ActStore<ACT32>::put(a.h, a.h_frag ? act_frag(r, i, a.n_rows, a.d) : (size_t)r * a.d + i, x[i] * rs * a.gain[i]);
 }
 
 // bf16 embedding, d % 8 == 0, d <= 8192: 16 bytes of the embedding row a thread, the widened values stay in registers between
@@ -209,7 +209,7 @@ __global__ __launch_bounds__(1024) void embed_norm_wide_kernel(EmbedArgs a, Rope
 #pragma unroll
         for (int i = 0; i < 4; ++i)
             o[i] = (uint32_t)f32_to_act16(v[2 * i] * rs * gn[2 * i]) | ((uint32_t)f32_to_act16(v[2 * i + 1] * rs * gn[2 * i + 1]) << 16);
-        *(u32x4*)((uint16_t*)a.h + (size_t)r * a.d + tid * 8) = u32x4{o[0], o[1], o[2], o[3]};
+        *(u32x4*)((uint16_t*)a.h + (a.h_frag ? act_frag(r, tid * 8, a.n_rows, a.d) : (size_t)r * a.d + tid * 8)) = u32x4{o[0], o[1], o[2], o[3]};
     }
 }
 
@@ -280,7 +280,7 @@ __global__ __launch_bounds__(1024) void add_norm_wide_kernel(NormArgs a) {
         const int gidx = threadIdx.x + j * blockDim.x;
         if (gidx < groups) {
             const int i = gidx * 4;
-            const size_t o = (size_t)ro * a.d + i;
+            const size_t o = a.h_frag ? act_frag(ro, i, a.rows_out, a.d) : (size_t)ro * a.d + i;
             ActStore<ACT32>::put_noting(a.h, o, v[j].x * rs * gn[j].x, bad);
             ActStore<ACT32>::put_noting(a.h, o + 1, v[j].y * rs * gn[j].y, bad);
             ActStore<ACT32>::put_noting(a.h, o + 2, v[j].z * rs * gn[j].z, bad);
@@ -310,7 +310,7 @@ __global__ __launch_bounds__(256) void add_norm_kernel(NormArgs a) {
     const float rs = rsqrtf(ss / (float)a.d + a.eps);
     bool bad = false;
     for (int i = threadIdx.x; i < a.d; i += 256)
-        ActStore<ACT32>::put_noting(a.h, (size_t)ro * a.d + i, xo[i] * rs * a.gain[i], bad);
+        ActStore<ACT32>::put_noting(a.h, a.h_frag ? act_frag(ro, i, a.rows_out, a.d) : (size_t)ro * a.d + i, xo[i] * rs * a.gain[i], bad);
     report_saturation(a.sat_count, bad);
 }
 

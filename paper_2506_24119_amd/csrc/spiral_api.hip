@@ -636,6 +636,12 @@ bool score_pairs_fit(int vocab, int d, int ffn, int q_width, int kv_width) {
 }
 }  // namespace spiral
 
+// Whether the q/k/v projection of a call with that many rows reads act_frag() order.
+static int qkv_in_frag(const spiral_model* m, int rows) {
+    const spiral_model_config& c = m->cfg;
+    return m->w_bf16 && gemm_decode_takes(rows, c.n_kv_heads * c.head_dim, c.d_model, EPI_STORE_F32, false);
+}
+
 static int run_layers(StepCtx& c) {
     spiral_model* m = c.m;
     const spiral_model_config& cfg = m->cfg;
@@ -648,6 +654,10 @@ static int run_layers(StepCtx& c) {
     // round (at least two 128-wide k chunks per split); 64-row workgroups when 128-row ones cannot.
     struct Shape { int bn, splits; };
     auto shape = [&](int bn, int s, int N, int K) {
+        if (!act32 && gemm_decode_takes(c.rows, N, K, EPI_STORE_F32, false)) {
+            const int splits = s ? std::max(1, std::min(s, K / 128)) : gemm_decode_splits(N, K, kMaxSplit);
+            return Shape{bn ? std::max(32, bn) : 32 * gemm_decode_tiles(c.rows, N, K, EPI_STORE_F32, splits), splits};
+        }
         auto fit = [&](int rows) {
             const int tiles = (N + rows - 1) / rows;
             return std::max(1, std::min({256 / std::max(tiles, 1), kMaxSplit, K / 256}));
@@ -718,6 +728,13 @@ static int run_layers(StepCtx& c) {
     const float* part = c.w.proj;       // the partials waiting to be added to the residual
     int pending = 0;            // projection partials waiting to be added to the residual
     int32_t* sat = c.p->d_status;
+    // At most 128 rows: activations go from kernel to kernel in the order of the projections' operands where both ends know it (the
+    // output of the prefill attention is in rows).  qkv_in_frag() is what the embedding kernel of the call went by.
+    const int h_frag = qkv_in_frag(m, c.rows);
+    const int h2_frag = !act32 && gemm_decode_takes(c.rows, cfg.ffn_dim, d, EPI_SWIGLU, false);
+    const int o_frag = c.decode && !act32 && gemm_decode_takes(c.rows, d, qw, EPI_STORE_F32, false);
+    const int mlp_frag = h2_frag && gemm_decode_takes(c.rows, d, cfg.ffn_dim, EPI_STORE_F32, false);
+    const int hf_frag = !act32 && gemm_decode_takes(c.B, cfg.vocab, d, EPI_STORE_F32, true);
 
     auto project = [&](int l, const QkvPlan& pl, const int32_t* row_map) -> int {
         GemmArgs g = {};
@@ -727,7 +744,7 @@ static int run_layers(StepCtx& c) {
             g.w[blocks] = m->lw(l, SPIRAL_W_K); g.rows[blocks++] = kw;
             g.w[blocks] = m->lw(l, SPIRAL_W_V); g.rows[blocks++] = kw;
         }
-        g.A = c.w.h; g.M = c.rows; g.N = (pl.hq + 2 * pl.hkv) * hd; g.K = d; g.out = c.w.qkv; g.splits = pl.sh.splits;
+        g.A = c.w.h; g.M = c.rows; g.N = (pl.hq + 2 * pl.hkv) * hd; g.K = d; g.out = c.w.qkv; g.splits = pl.sh.splits; g.a_frag = h_frag;
         g.wf = m->f_lm ? (const uint16_t*)m->f_qkv[l] + (pl.hq ? 0 : frag_block(qw / 32, 0, d)) : nullptr;
         QkvPostArgs qa = {c.w.qkv, m->lw(l, SPIRAL_W_BQ), m->lw(l, SPIRAL_W_BK), m->lw(l, SPIRAL_W_BV),
                           (const float*)m->lw(l, SPIRAL_W_Q_NORM), (const float*)m->lw(l, SPIRAL_W_K_NORM),
@@ -750,7 +767,8 @@ static int run_layers(StepCtx& c) {
     for (int l = c.first_layer; l < cfg.n_layers; ++l) {
         const bool q_only = c.q_rows && l == c.first_layer;
         if (l > 0 && !q_only) {
-            NormArgs n = {c.w.x, part, (const float*)m->lw(l, SPIRAL_W_ATTN_NORM), c.w.h, nullptr, c.rows, c.rows, d, pending, cfg.rms_eps, sat};
+            NormArgs n = {c.w.x, part, (const float*)m->lw(l, SPIRAL_W_ATTN_NORM), c.w.h, nullptr, c.rows, c.rows, d, pending, cfg.rms_eps, sat,
+                          nullptr, h_frag};
             HIP_TRY(timed(m, SPIRAL_K_NORM, c.s, [&] { return launch_add_norm(n, act32, c.s); }));
         }
         if (trim && l == last) {
@@ -760,7 +778,7 @@ static int run_layers(StepCtx& c) {
             if (rc) return rc;
             // the last rows: residual to h's memory (h has been read), normed to hf
             NormArgs n = {c.w.x, nullptr, (const float*)m->lw(l, SPIRAL_W_ATTN_NORM), c.w.hf, c.w.last_rows, c.rows, c.B, d, 0, cfg.rms_eps,
-                          nullptr, (float*)c.w.h};
+                          nullptr, (float*)c.w.h, qkv_in_frag(m, c.B)};
             HIP_TRY(timed(m, SPIRAL_K_NORM, c.s, [&] { return launch_add_norm(n, act32, c.s); }));
             std::vector<int32_t> start(c.B + 1, 0);
             int max_ctx = 0;
@@ -792,7 +810,7 @@ static int run_layers(StepCtx& c) {
         aa.scale_log2e = (float)(1.4426950408889634 / std::sqrt((double)hd));
         if (c.decode) {
             aa.row_page_start = c.w.page_start; aa.units_per_wg = c.units_per_wg; aa.total_units = c.total_units;
-            aa.n_chunks = c.n_slots;
+            aa.n_chunks = c.n_slots; aa.out_frag = o_frag;
             HIP_TRY(timed(m, SPIRAL_K_ATTN_DECODE, c.s, [&] { return launch_attn_stream(aa, hd, act32, c.s); }));
             HIP_TRY(timed(m, SPIRAL_K_ATTN_COMBINE, c.s, [&] { return launch_attn_stream_combine(aa, hd, act32, c.s); }));
         } else {
@@ -801,11 +819,11 @@ static int run_layers(StepCtx& c) {
 
         GemmArgs go = {};
         go.A = c.w.o; go.w[0] = m->lw(l, SPIRAL_W_O); go.rows[0] = d;
-        go.M = c.rows; go.N = d; go.K = qw; go.out = part_o; go.splits = s_o;
+        go.M = c.rows; go.N = d; go.K = qw; go.out = part_o; go.splits = s_o; go.a_frag = o_frag;
         go.wf = m->f_lm ? m->f_o[l] : nullptr;
         HIP_TRY(timed(m, SPIRAL_K_GEMM_O, c.s, [&] { return launch_gemm(go, EPI_STORE_F32, m->w_bf16, sh_o.bn, c.s); }));
 
-        NormArgs n2 = {c.w.x, part_o, (const float*)m->lw(l, SPIRAL_W_MLP_NORM), c.w.h, nullptr, c.rows, c.rows, d, s_o, cfg.rms_eps, sat};
+        NormArgs n2 = {c.w.x, part_o, (const float*)m->lw(l, SPIRAL_W_MLP_NORM), c.w.h, nullptr, c.rows, c.rows, d, s_o, cfg.rms_eps, sat, nullptr, h2_frag};
         HIP_TRY(timed(m, SPIRAL_K_NORM, c.s, [&] { return launch_add_norm(n2, act32, c.s); }));
 
         GemmArgs gu = {};
@@ -813,12 +831,12 @@ static int run_layers(StepCtx& c) {
         gu.rows[0] = cfg.ffn_dim; gu.rows[1] = cfg.ffn_dim;
         gu.M = c.rows; gu.N = cfg.ffn_dim; gu.K = d; gu.out = c.w.mlp; gu.splits = 1;
         gu.wf = m->f_lm ? m->f_gu[l] : nullptr;
-        gu.sat_count = sat;
+        gu.sat_count = sat; gu.a_frag = h2_frag; gu.out_frag = mlp_frag;
         HIP_TRY(timed(m, SPIRAL_K_GEMM_GATE_UP, c.s, [&] { return launch_gemm(gu, EPI_SWIGLU, m->w_bf16, t.bn_gu, c.s); }));
 
         GemmArgs gd = {};
         gd.A = c.w.mlp; gd.w[0] = m->lw(l, SPIRAL_W_DOWN); gd.rows[0] = d;
-        gd.M = c.rows; gd.N = d; gd.K = cfg.ffn_dim; gd.out = part_down; gd.splits = s_down;
+        gd.M = c.rows; gd.N = d; gd.K = cfg.ffn_dim; gd.out = part_down; gd.splits = s_down; gd.a_frag = mlp_frag;
         gd.wf = m->f_lm ? m->f_down[l] : nullptr;
         HIP_TRY(timed(m, SPIRAL_K_GEMM_DOWN, c.s, [&] { return launch_gemm(gd, EPI_STORE_F32, m->w_bf16, sh_down.bn, c.s); }));
         pending = s_down;
@@ -854,12 +872,12 @@ static int run_layers(StepCtx& c) {
     }
     // final norm on one row per sequence, then the LM head
     NormArgs nf = {c.w.x, part, (const float*)m->w[1], c.w.hf, c.decode ? nullptr : c.w.last_rows,
-                   c.rows, c.B, d, pending, cfg.rms_eps, sat};
+                   c.rows, c.B, d, pending, cfg.rms_eps, sat, nullptr, hf_frag};
     HIP_TRY(timed(m, SPIRAL_K_NORM, c.s, [&] { return launch_add_norm(nf, act32, c.s); }));
     GemmArgs gl = {};
     gl.A = c.w.hf; gl.w[0] = m->w[2]; gl.rows[0] = cfg.vocab;
     gl.M = c.B; gl.N = cfg.vocab; gl.K = d; gl.out = c.logits; gl.splits = 1;
-    gl.wf = m->f_lm;
+    gl.wf = m->f_lm; gl.a_frag = hf_frag; gl.head = 1;
     if (c.sample) {
         // the LM head keeps the best (score, index) of each 128-column tile per row; a small kernel picks the winner
         const int cols = gemm_sample_tile_cols(c.B, t.bn_lm);
@@ -927,7 +945,7 @@ static int prefill_or_score(spiral_model* m, spiral_kv_pool* p, const int32_t* h
         HIP_TRY(launch_prefill_meta(w.cu_rows, w.base_pos, w.seq_ids, B, (int)rows, w.row_seq, w.row_pos, s));
         EmbedArgs e = {dev_tokens_packed, m->w[0], (const float*)m->lw(0, SPIRAL_W_ATTN_NORM), w.x, w.h,
                        w.row_pos, w.rope, (int)rows, m->cfg.d_model, m->cfg.head_dim / 2, m->cfg.vocab, m->cfg.rms_eps,
-                       w.row_seq, p->d_block_table, p->max_blocks, w.row_page};
+                       w.row_seq, p->d_block_table, p->max_blocks, w.row_page, qkv_in_frag(m, (int)rows)};
         HIP_TRY(launch_embed_norm(e, m->freq, m->w_bf16, !m->w_bf16, s));
         StepCtx c = {m, p, w, s, (int)rows, B, false, max_new, 1, dev_logits};
         c.score_targets = dev_targets;
@@ -1030,7 +1048,7 @@ static int decode_impl(spiral_model* m, spiral_kv_pool* p, const int32_t* host_s
         HIP_TRY(launch_upload_multi(dst, src, cnt, keys.empty() ? 3 : 4, s));
         EmbedArgs e = {dev_in_tokens, m->w[0], (const float*)m->lw(0, SPIRAL_W_ATTN_NORM), w.x, w.h,
                        w.row_pos, w.rope, B, m->cfg.d_model, m->cfg.head_dim / 2, m->cfg.vocab, m->cfg.rms_eps,
-                       w.row_seq, p->d_block_table, p->max_blocks, w.row_page};
+                       w.row_seq, p->d_block_table, p->max_blocks, w.row_page, qkv_in_frag(m, B)};
         HIP_TRY(launch_embed_norm(e, m->freq, m->w_bf16, !m->w_bf16, s));
         StepCtx c = {m, p, w, s, B, B, true, 1, decode_chunks(m, max_ctx), dev_logits};
         plan_decode_attention(c, start[B], max_ctx);

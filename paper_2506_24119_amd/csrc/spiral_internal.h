@@ -56,6 +56,8 @@ struct GemmArgs {
     const int32_t* targets;
     float* tgt_logit;
     int32_t* sat_count;   // or null: incremented when an activation left the half-precision range (SwiGLU output)
+    int32_t a_frag, out_frag;    // at most 128 rows: A, and the SwiGLU output, lie in act_frag() order
+    int32_t head;         // the LM head
 };
 
 struct AttnArgs {
@@ -73,6 +75,7 @@ struct AttnArgs {
     int32_t n_rows, n_q_heads, n_kv_heads, max_blocks, chunk_pages, n_chunks;
     int32_t units_per_wg, total_units;   // decode stream: (row, kv head, page) units per workgroup, and in all
     float scale_log2e;        // log2(e) / sqrt(hd)
+    int32_t out_frag;         // decode: out in act_frag() order
 };
 
 // Launchers (defined in the kernel translation units).  All enqueue on `s` and return the launch status.
@@ -96,6 +99,7 @@ struct EmbedArgs {
     // the page that takes each row's k and v, looked up here once for all layers: row_page[r] = (page, position)
     const int32_t* row_seq; const int32_t* block_table; int32_t max_blocks;
     int2* row_page;           // [rows], written
+    int32_t h_frag;           // h in act_frag() order
 };
 hipError_t launch_embed_norm(const EmbedArgs& a, const RopeFreq& f, bool w_bf16, bool act32, hipStream_t s);
 
@@ -109,6 +113,7 @@ struct NormArgs {
     float eps;
     int32_t* sat_count;       // or null
     float* x_out;             // or null: the residual rows go here, [rows_out][d], instead of back to x
+    int32_t h_frag;           // h in act_frag() order
 };
 hipError_t launch_add_norm(const NormArgs& a, bool act32, hipStream_t s);
 
@@ -141,6 +146,10 @@ bool gemm_tile_qkv_fills(int M, int N);                                         
 float gemm_tile_qkv_us(int M, int N, int K);
 hipError_t launch_gemm_tile_qkv(const GemmArgs& a, const QkvPostArgs& qa, hipStream_t s);  // q/k/v projection + qkv_post in one kernel
 hipError_t launch_gemm_stream(const GemmArgs& a, int epilogue, int bn, hipStream_t s);   // K % 128 == 0, N % 16 == 0
+bool gemm_decode_takes(int M, int N, int K, int epilogue, bool head);                     // at most 128 rows, K % 128 == 0, N % 16 == 0
+int gemm_decode_splits(int N, int K, int most);                                          // K splits, whatever the rows
+int gemm_decode_tiles(int M, int N, int K, int epilogue, int splits);                    // 32-row weight tiles of a workgroup
+hipError_t launch_gemm_decode(const GemmArgs& a, int epilogue, int nt, hipStream_t s);
 hipError_t launch_attn_stream(const AttnArgs& a, int hd, bool act32, hipStream_t s);
 hipError_t launch_attn_stream_combine(const AttnArgs& a, int hd, bool act32, hipStream_t s);
 hipError_t launch_attn_prefill(const AttnArgs& a, int hd, int B, int max_new, bool act32, hipStream_t s);
@@ -158,6 +167,13 @@ hipError_t launch_sample(const float* logits, int B, int V, float temperature, c
 // v_mfma_f32_32x32x16 step, so a wave's load instruction reads one contiguous block (8 cache lines
 // instead of 32 half-used ones).
 __host__ __device__ inline size_t frag_block(int t, int ks, int K) { return ((size_t)t * (K >> 4) + ks) * 512; }
+// Order of 16-bit activations [M][K] between the kernels of at most 128 rows: tiles of 32 rows, in a tile blocks of 16 k, in a block
+// [2][rows of the tile][8 k], the matrix instruction's operand again, without room for rows that are not there: a wave's load is one
+// contiguous piece, and the matrix takes no more memory than in rows.
+__host__ __device__ inline size_t act_frag(int m, int k, int M, int K) {
+    const int m0 = m & ~31, rows = M - m0 < 32 ? M - m0 : 32;
+    return (size_t)m0 * K + ((size_t)(k >> 3) * rows + (m - m0)) * 8 + (k & 7);
+}
 hipError_t launch_repack(const void* src0, const void* src1, const void* src2, int rows0, int rows1, int rows2, int K,
                          bool interleave16, void* dst, hipStream_t s);
 

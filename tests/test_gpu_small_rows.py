@@ -1,0 +1,94 @@
+"""The projections of at most 128 rows (gemm_decode_kernel): a decode step and a short prefill at the edges of its row tiles, weight
+tiles and K splits, against the oracle; repacked and row-major weights give the same bits, a sequence's logits do not depend on
+how many others are in the call, and the fused sampler draws what the stored logits give on either side of 32 rows."""
+import ctypes
+
+import numpy as np
+import pytest
+
+from oracle import decoder as od
+from paper_2506_24119_amd import inputs as si
+
+LOGIT_TOL = 3e-2          # the bar of every logit comparison: half-precision activations
+
+# K = 128 (the least, no split to make), widths that leave a remainder in the last weight tile (176 q/k/v heads x 32; ffn 416 and
+# vocabulary 2,512 are 26 and 78.5 tiles), and a wide one whose projections split K
+NARROW = si.ModelGeometry("narrow", 2, 128, 4, 1, 32, 384, 2512, 1e4, qkv_bias=True, tie_lm_head=False)
+WIDE = si.ModelGeometry("wide", 2, 640, 10, 2, 128, 1408, 2512, 1e6, qk_norm=True)
+
+
+def _run(g, w, B, repack, ids=None, sample=False):
+    import torch
+    from paper_2506_24119_amd import binding as sb
+    rng = np.random.Generator(np.random.PCG64(7))
+    lens = rng.integers(1, 20, 128)
+    prompts = [rng.integers(0, g.vocab, int(n)).astype(np.int32) for n in lens]
+    step = rng.integers(0, g.vocab, 128).astype(np.int32)
+    ids = np.arange(B) if ids is None else np.array(ids)
+    n = len(ids)
+    sess = sb.Session(g, w, 3 * n + 2, n, 3, 128, 40, page_order=si.make_page_order(3 * n + 2, 3), repack=repack)
+    seqs = np.arange(n, dtype=np.int32)
+    for i in range(0, n, 6):                               # at most 6 x 19 rows: every projection of the prompts is a small one, too
+        sess.prefill(seqs[i:i + 6], [prompts[b] for b in ids[i:i + 6]])
+    tin = torch.from_numpy(step[ids]).cuda()
+    out = sess.decode_step(seqs, tin, sess.new_logits(n)).cpu().numpy()
+    if sample:
+        at = np.full(n, 4, dtype=np.int32)
+        a, b = torch.empty(n, dtype=torch.int32, device="cuda"), torch.empty(n, dtype=torch.int32, device="cuda")
+        sess.sample(torch.from_numpy(out).cuda(), 1.0, 5, seqs, at, a)
+        sb.spiral_seq_truncate(sess.pool, seqs, np.array([len(prompts[b]) for b in ids], dtype=np.int32))
+        sess.decode_sample_step(seqs, tin, 1.0, 5, at, b)
+        assert torch.equal(a, b)
+    assert sess.saturation_count() == 0
+    sess.close()
+    return out, prompts, step
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("g", [NARROW, WIDE], ids=["narrow", "wide"])
+@pytest.mark.parametrize("B", [1, 7, 31, 32, 33, 64, 65, 96, 97, 128])
+def test_rows_against_oracle_and_row_major(g, B):
+    from paper_2506_24119_amd import binding as sb
+    host = si.make_weights(g, seed=71)
+    w = sb.weights_to_device(host)
+    got, prompts, step = _run(g, w, B, True, sample=B in (32, 33))
+    assert np.array_equal(got, _run(g, w, B, False)[0])
+    for b in {0, B // 2, B - 1}:
+        toks = np.concatenate([prompts[b], step[b:b + 1]]).astype(np.int64)
+        want = od.forward_full(g, host, toks, logits_at=np.array([len(toks) - 1]))[0]
+        assert np.abs(got[b] - want).max() <= LOGIT_TOL * want.std(), b
+
+
+@pytest.mark.gpu
+def test_a_sequence_does_not_depend_on_the_rows_of_its_step():
+    """The same K splits and order of sums at every row count up to 128: only the LM head changes kernels (at 33 rows), and nothing
+    rounds its fp32 sums, so logits differ by a few units in the last place of a sum of 640 products (1e-6 of their size)."""
+    from paper_2506_24119_amd import binding as sb
+    w = sb.weights_to_device(si.make_weights(WIDE, seed=72))
+    full = _run(WIDE, w, 128, True)[0]
+    for ids in ([5], list(range(3, 33)), list(range(40)), list(range(30, 100))):
+        got = _run(WIDE, w, None, True, ids=ids)[0]
+        assert np.abs(got - full[ids]).max() <= 1e-5 * np.abs(full[ids]).max(), len(ids)
+
+
+def test_which_projections_are_small():
+    from paper_2506_24119_amd import binding
+    takes = binding.load_library()._ZN6spiral17gemm_decode_takesEiiiib
+    takes.argtypes = [ctypes.c_int] * 4 + [ctypes.c_bool]
+    takes.restype = ctypes.c_bool
+    assert takes(1, 16, 128, 0, False) and takes(128, 16, 128, 0, False) and not takes(129, 16, 128, 0, False) and not takes(0, 16, 128, 0, False)
+    assert not takes(8, 24, 128, 0, False) and not takes(8, 32, 192, 0, False)
+    assert takes(128, 12288, 128, 1, False) and not takes(128, 12304, 128, 1, False)          # gate/up of at most three tiles a unit
+    assert takes(32, 151936, 1024, 0, True) and not takes(33, 151936, 1024, 0, True)
+
+
+def test_splits_are_those_of_the_shape():
+    """The K splits by the projection alone, at least 128 k each; measured choices of three shapes."""
+    from paper_2506_24119_amd import binding
+    splits = binding.load_library()._ZN6spiral18gemm_decode_splitsEiii
+    assert [splits(n, k, 16) for n, k in ((4096, 1024), (1024, 2048), (1024, 3072))] == [2, 8, 8]
+    assert [splits(n, k, 16) for n, k in ((6144, 2560), (2560, 4096), (2560, 9728))] == [4, 3, 6]
+    assert [splits(n, k, 16) for n, k in ((4608, 3584), (3584, 3584), (3584, 18944))] == [3, 4, 6]
+    for n in (16, 48, 640, 6144):
+        for k in (128, 256, 1408, 9728):
+            assert 1 <= splits(n, k, 16) <= k // 128
