@@ -155,11 +155,16 @@ struct PrefillGrid {
 //   O^T[d][row]    += V^T P^T  v_mfma_f32_32x32x16 over the 16 tokens of a page.  In S^T a lane holds the tokens
 //                   4 lh .. + 3 and 8 + 4 lh .. + 3 of its row: they are the B operand as they are, and the A operand is
 //                   read with the same order of the contraction index (two 8-byte groups of 4 tokens).
-// Bound: the exponentials and the matrix pipe take about equally long (a 64-token step of a wave is 32 MFMAs = 1024
-// cycles and 32 exponentials plus 100 other vector operations a lane, ~900), so two workgroups per compute unit
-// interleave them.  Against 16-row tiles that walk single pages straight from L2 (16x16 MFMAs, no LDS), a layer of:
-// 15,272 rows of U[256, 1024] tokens, 32 heads 353 -> 178 us; 11,206 rows of U[2048, 4096], 16 heads 484 -> 214 us
-// (0.60 PFLOP/s); 788 rows appended to nine histories of U[400, 2000] 122 -> 74 us.
+// Bound: a wave's own chain.  A 64-token step is 32 MFMAs (1024 cycles) and about 200 vector operations a lane (~1000, the
+// exponentials half of them), in series but for the exponentials of a page under the products of the one before, then a barrier; two
+// workgroups per compute unit hide half of it (matrix pipe busy 35 %, at 1.95 GHz; with zeros for q, k and v 15 % less time).
+// Against 16-row tiles that walk single pages straight from L2 (16x16 MFMAs, no LDS), a layer of: 15,272 rows of U[256, 1024]
+// tokens, 32 heads 353 -> 143 us; 11,206 rows of U[2048, 4096], 16 heads 484 -> 189 us (0.68 PFLOP/s); 788 rows appended to nine
+// histories of U[400, 2000] 122 -> 61 us.  Of that, 175 -> 143, 213 -> 189 and 73 -> 61 came with unmasked steps in a loop of their
+// own, K operands four reads ahead, rescaling only after a growth of 2^8, V reads without bank conflicts (a third of the LDS
+// cycles; 4-byte stores to go with them cost more than they gave on short runs, 175 -> 208) and whole rows written through LDS.
+// Without effect: the two score chains interleaved, sequences sorted by length, s_setprio around the scores (199 -> 204), two
+// stages of pages in flight in registers (spills, 213 -> 233).
 // ---------------------------------------------------------------------------------------------
 template <int HD, bool ACT32>
 __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(AttnArgs a, PrefillGrid gr) {
@@ -201,15 +206,21 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(AttnArgs a, Prefil
     const size_t page_elems = (size_t)a.n_kv_heads * (2 * kPageTokens * HD);
     const uint16_t* head_pages = a.pages + (size_t)kvh * (2 * kPageTokens * HD);
 
-    // staging: wave w copies page 4 * stage + w (past the last page: that one again)
+    // staging: wave w copies page 4 * stage + w (past the last page: that one again); pages are looked up a stage ahead of their load (a
+    // scalar load and the LDS reads share a counter)
     u32x4 rg[LD];
-    auto load = [&](int stage) {
-        const int pg = min(stage * 4 + wave, last_page);
-        const uint16_t* src = head_pages + (size_t)bt[pg] * page_elems + lane * 8;
+    auto page_of = [&](int stage) { return bt[min(stage * 4 + wave, last_page)]; };
+    auto load = [&](int page) {
+        const uint16_t* src = head_pages + (size_t)page * page_elems + lane * 8;
 #pragma unroll
         for (int u = 0; u < LD; ++u) rg[u] = *(const u32x4*)(src + u * 512);
     };
-    load(0);
+    auto park = [&](char* buf) {
+#pragma unroll
+        for (int u = 0; u < LD; ++u) *(u32x4*)(buf + wave * PAGE_B + u * 1024 + lane * 16) = rg[u];
+    };
+    load(page_of(0));
+    int next_page = page_of(1);
 
     u32x4 qf[KS];
     {
@@ -228,9 +239,10 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(AttnArgs a, Prefil
         for (int r = 0; r < 16; ++r) acc[d][r] = 0.f;
     float m_run = kNegBig, l_run = 0.f;
 
-    // operand offsets: K of tokens 32 sub + l32 (two pages), V of d = 32 dt + l32 (4 tokens: 8 bytes)
+    // operand offsets: K of tokens 32 sub + l32 (two pages), V of d = 32 dt + l32 / 2 + 16 (l32 % 2) (4 tokens: 8 bytes).  With d in
+    // the lanes' order sixteen lanes would read every other 8 bytes of 256, two to a bank.
     const int k_off = (l32 >> 4) * PAGE_B + lh * 256 + (l32 & 15) * 16;
-    const int v_off = PAGE_B / 2 + lh * 256 + (l32 & 15) * 16 + (l32 >> 4) * 8;
+    const int v_off = PAGE_B / 2 + lh * 256 + l32 * 8;
 
     // one step of a wave over the first NP pages of the staged four
     auto step = [&](const char* buf, int st, auto np) {
@@ -295,20 +307,110 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(AttnArgs a, Prefil
                 acc[d] = mma32_f16(u32x4{lo.x, lo.y, hi.x, hi.y}, pb[pg], acc[d]);
             }
     };
-    for (int st = 0; st < n_stages; ++st) {
-        char* buf = lds + (st & 1) * STAGE_B;
+    // the same over all four pages, none of whose tokens is hidden from a row of the wave
+    auto whole_step = [&](const char* buf) {
+        constexpr int KD = 4;                                 // K operands ahead
+        f32x16 s[2];
+        u32x4 kf[KD];
+        auto read_k = [&](int i) { return *(const u32x4*)(buf + (i / KS) * 2 * PAGE_B + k_off + ((i % KS) >> 1) * 1024 + (i & 1) * 512); };
+        auto read_v = [&](int i) {
+            const char* vp = buf + (i / DT) * PAGE_B + v_off + (i % DT) * 1024;
+            const u32x2 lo = *(const u32x2*)vp, hi = *(const u32x2*)(vp + 512);
+            return u32x4{lo.x, lo.y, hi.x, hi.y};
+        };
 #pragma unroll
-        for (int u = 0; u < LD; ++u) *(u32x4*)(buf + wave * PAGE_B + u * 1024 + lane * 16) = rg[u];
+        for (int i = 0; i < KD; ++i) kf[i] = read_k(i);
+#pragma unroll
+        for (int sub = 0; sub < 2; ++sub)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) s[sub][r] = 0.f;
+        __builtin_amdgcn_sched_barrier(0);                    // left alone, the scheduler puts every read right before its use
+#pragma unroll
+        for (int i = 0; i < 2 * KS; ++i) {
+            s[i / KS] = mma32_f16(kf[i % KD], qf[i % KS], s[i / KS]);
+            if (i + KD < 2 * KS) kf[i % KD] = read_k(i + KD);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        u32x4 vf[DT];                                         // the first page's V arrives under the exponentials
+#pragma unroll
+        for (int i = 0; i < DT; ++i) vf[i] = read_v(i);
+        float mx = s[0][0];
+#pragma unroll
+        for (int sub = 0; sub < 2; ++sub)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[sub][r]);
+        mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+        // The weights are relative to m_run, which follows the row's maximum only when that has left it behind by 2^8: 32 rows raise
+        // their maxima in most steps, and the accumulators' 64 products are a quarter of the vector operations.  A weight of up
+        // to 256 is as exact in half as one of up to 1.
+        const float m_new = fmaxf(m_run, mx * a.scale_log2e);
+        if (__builtin_amdgcn_ballot_w64(m_new > m_run + 8.0f) != 0) {
+            const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
+#pragma unroll
+            for (int d = 0; d < DT; ++d)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[d][r] *= alpha;
+            l_run *= alpha;
+            m_run = m_new;
+        }
+        float ps = 0.f;
+#pragma unroll
+        for (int pg = 0; pg < 4; ++pg) {
+            u32x4 pb;                                         // P^T of the page
+#pragma unroll
+            for (int b2 = 0; b2 < 2; ++b2) {
+                f16x4 h4;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const float p = __builtin_amdgcn_exp2f(fmaf(s[pg >> 1][8 * (pg & 1) + 4 * b2 + e], a.scale_log2e, -m_run));
+                    ps += p;
+                    h4[e] = (_Float16)p;
+                }
+                const u32x2 hb = __builtin_bit_cast(u32x2, h4);
+                pb[2 * b2] = hb.x;
+                pb[2 * b2 + 1] = hb.y;
+            }
+#pragma unroll
+            for (int d = 0; d < DT; ++d) {
+                acc[d] = mma32_f16(vf[d], pb, acc[d]);
+                if (pg < 3) vf[d] = read_v((pg + 1) * DT + d);
+            }
+        }
+        l_run += ps;
+    };
+    // Stages that every row of the workgroup sees in full: a step without a mask, in a loop of its own.  (With the three forms of a
+    // step in one loop the accumulators were copied twice a step, and the registers of the copies left two operand reads in flight.)
+    // Waves without rows multiply zeros along.
+    const int n_whole = min((pos_base + first + 1) / 64, n_stages);
+    int st = 0;
+    for (; st < n_whole; ++st) {
+        char* buf = lds + (st & 1) * STAGE_B;
+        park(buf);
         __syncthreads();            // one barrier a step: the buffer written next was last read before this one
-        if (st + 1 < n_stages) load(st + 1);
+        load(next_page);            // past the last stage: its last page again
+        whole_step(buf);
+        next_page = page_of(st + 2);
+    }
+    for (; st < n_stages; ++st) {
+        char* buf = lds + (st & 1) * STAGE_B;
+        park(buf);
+        __syncthreads();
+        if (st + 1 < n_stages) {
+            load(next_page);
+            next_page = page_of(st + 2);
+        }
         if (st * 64 + 32 <= my_last) step(buf, st, std::integral_constant<int, 4>());
         else if (st * 64 + 16 <= my_last) step(buf, st, std::integral_constant<int, 2>());
         else if (st * 64 <= my_last) step(buf, st, std::integral_constant<int, 1>());
     }
 
-    // O^T[d][row]: lane (l32, lh) holds d = 32 dt + 8 b + 4 lh .. + 3 of row l32; l is spread over the two lane halves
+    // O^T[d][row]: lane (l32, lh) holds rows 8 b + 4 lh .. + 3 of each tile of 32 d; l is spread over the two lane halves
     l_run += __shfl_xor(l_run, 32, 64);
     bool nan = false;
+    constexpr int OROW = HD * 2 + 16;
+    static_assert(4 * 32 * OROW <= 2 * STAGE_B, "the output rows of four waves take the staged pages' place");
+    char* rows_out = lds + wave * (32 * OROW);
+    __syncthreads();                                          // every wave is done with the staged pages
     if (active && l32 < n_valid) {
         const float inv = 1.0f / l_run;
         f32x16 sum = acc[0];                                  // NaN where one is among its terms; far from overflow
@@ -318,7 +420,10 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(AttnArgs a, Prefil
 #pragma unroll
         for (int r = 1; r < 16; ++r) s1 += sum[r];
         nan = s1 != s1;
-        const size_t o_idx = ((size_t)(row0 + l32) * a.n_q_heads + h) * HD + lh * 4;
+        // Row i = 8 b2 + 4 lh + e of a tile is d = i / 2 + 16 (i % 2): a lane has two neighbours at 4 b2 + 2 lh and two 16 on.  Half
+        // precision: the lane halves swap, so that one has four from 4 b2 on and the other the four 16 on, and the rows go out
+        // through LDS, whole.
+        const size_t o_idx = ((size_t)(row0 + l32) * a.n_q_heads + h) * HD;
 #pragma unroll
         for (int d = 0; d < DT; ++d)
 #pragma unroll
@@ -326,14 +431,31 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(AttnArgs a, Prefil
                 float o[4];
 #pragma unroll
                 for (int e = 0; e < 4; ++e) o[e] = acc[d][4 * b2 + e] * inv;
-                if (ACT32) *(float4*)((float*)a.out + o_idx + d * 32 + b2 * 8) = make_float4(o[0], o[1], o[2], o[3]);
-                else {                                        // the range as f32_to_act16 has it; a NaN is stored again below
-                    f16x4 o4;
+                if (ACT32) {
+                    float* at = (float*)a.out + o_idx + d * 32 + b2 * 4 + lh * 2;
+                    *(float2*)at = make_float2(o[0], o[2]);
+                    *(float2*)(at + 16) = make_float2(o[1], o[3]);
+                } else {                                      // the range as f32_to_act16 has it; a NaN is stored again below
+                    typedef __attribute__((ext_vector_type(2))) _Float16 f16x2;
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) o4[e] = (_Float16)__builtin_amdgcn_fmed3f(o[e], -65504.0f, 65504.0f);
-                    *(f16x4*)((uint16_t*)a.out + o_idx + d * 32 + b2 * 8) = o4;
+                    for (int e = 0; e < 4; ++e) o[e] = __builtin_amdgcn_fmed3f(o[e], -65504.0f, 65504.0f);
+                    const uint32_t even = __builtin_bit_cast(uint32_t, f16x2{(_Float16)o[0], (_Float16)o[2]});
+                    const uint32_t odd = __builtin_bit_cast(uint32_t, f16x2{(_Float16)o[1], (_Float16)o[3]});
+                    const auto both = __builtin_amdgcn_permlane32_swap(even, odd, false, false);
+                    *(u32x2*)(rows_out + l32 * OROW + (d * 32 + b2 * 4 + lh * 16) * 2) = u32x2{both[0], both[1]};
                 }
             }
+    }
+    if (!ACT32) {
+        constexpr int LPR = HD / 8;                           // lanes of 16 bytes to a row
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int ps = 0; ps < 32 * LPR / 64; ++ps) {
+            const int row = ps * (64 / LPR) + lane / LPR;
+            if (active && row < n_valid)
+                *(u32x4*)((uint16_t*)a.out + ((size_t)(row0 + row) * a.n_q_heads + h) * HD + (lane % LPR) * 8) =
+                    *(const u32x4*)(rows_out + row * OROW + (lane % LPR) * 16);
+        }
     }
     // A weight of zero does not stop a NaN: one in the V of a token that a row does not see (up to 63 further on in the row's
     // last 64) has reached its sums.  Such rows, and rows with a NaN of their own, are done again over their visible tokens only.

@@ -128,3 +128,26 @@ def test_a_nan_token_can_be_dropped(head_dim, dtype):
         got.append(sess.prefill([0], [more]).cpu().numpy()[0])
         sess.close()
     assert np.abs(got[0] - got[1]).max() <= 1e-2 * got[1].std()
+
+
+@pytest.mark.parametrize("gain", [0.25, 3.0, 6.0])
+def test_maxima_that_rise_by_less_and_by_more_than_the_rescale_threshold(gain):
+    """Unmasked steps keep a row's weights relative to a maximum that they follow only when it has risen by 2^8: scores of a
+    standard deviation of 0.4, 4 and 9 (in powers of two) over 13 steps, so that rows never rescale after the first step, do so
+    now and then, and do so often; runs that end in a step, on its edge and one token behind it.  Bar as above."""
+    from paper_2506_24119_amd import binding as sb
+    g = si.ModelGeometry("rise", 1, 128, 4, 2, 128, 128, 256, 1e4, qk_norm=True)
+    w = si.make_weights(g, seed=17)
+    w["layers"][0]["q_norm"] = (w["layers"][0]["q_norm"] * gain).astype(np.float32)
+    rng = np.random.Generator(np.random.PCG64(18))
+    lens, hist = [832, 833, 700, 64, 127], [0, 300, 64, 63, 1]
+    seqs = [rng.integers(0, g.vocab, n).astype(np.int32) for n in lens]
+    ids = np.arange(len(seqs), dtype=np.int32)
+    sess = sb.Session(g, sb.weights_to_device(w), 180, len(seqs), 56, 3000, 860, page_order=si.make_page_order(180, 2), tune="trim=0")
+    old = [b for b in range(len(seqs)) if hist[b]]
+    sess.prefill(ids[old], [seqs[b][:hist[b]] for b in old])
+    got = sess.prefill(ids, [s[h:] for s, h in zip(seqs, hist)]).cpu().numpy()
+    sess.close()
+    for b, s in enumerate(seqs):
+        want = od.forward_full(g, w, s, logits_at=np.array([len(s) - 1]))[0]
+        assert np.abs(got[b] - want).max() <= 3e-2 * want.std(), b
