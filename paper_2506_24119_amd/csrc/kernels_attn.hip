@@ -480,7 +480,10 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(AttnArgs a, Prefil
 // page stream does not stop at segment boundaries (a workgroup per chunk pays a start-up and a
 // drain for every 16 pages: 5.2 vs 5.9 TB/s measured).
 // ---------------------------------------------------------------------------------------------
-template <int HD, bool ACT32>
+// DIRECT: short contexts (the host's rule): a workgroup has one pair to itself and writes the output: no search, no partial
+// results, no merging launch.  27 rows of 400 tokens, 0.6B shape: 6 us a layer less of 51.  A parameter of the template, since the test
+// at run time costs the other form 8 registers and with them a workgroup of three a CU (128 rows of 1,280 tokens: 7 % of a step).
+template <int HD, bool ACT32, bool DIRECT>
 __global__ __launch_bounds__(256) void attn_stream_kernel(AttnArgs a) {
     constexpr int KS = HD / 32, MT = HD / 16, OSTRIDE = HD + 4;
     extern __shared__ float lds_f[];
@@ -496,14 +499,15 @@ __global__ __launch_bounds__(256) void attn_stream_kernel(AttnArgs a) {
     const int32_t* rps = a.row_page_start;
     const int T = rps[a.n_rows] * Hkv;
     int u = blockIdx.x * U;
-    if (u >= T) return;
-    const int u_end = min(u + U, T);
+    if (!DIRECT && u >= T) return;
+    int u_end = min(u + U, T);
 
     // the row that holds unit u: the largest r with row_page_start[r] * Hkv <= u.  The prefix sums
     // increase strictly, so r + 1 is the number of entries that satisfy it: the lanes test 64 entries
     // at a time (one round of independent loads instead of a chain of dependent ones).
     int below = 0;
-    for (int base = 0; base < a.n_rows; base += 64) {
+    if (DIRECT) below = blockIdx.x / Hkv + 1;
+    else for (int base = 0; base < a.n_rows; base += 64) {
         const int j = min(base + lane, a.n_rows - 1);
         const bool hit = base + lane < a.n_rows && rps[j] * Hkv <= u;
         below += __builtin_popcountll(__builtin_amdgcn_ballot_w64(hit));
@@ -514,8 +518,12 @@ __global__ __launch_bounds__(256) void attn_stream_kernel(AttnArgs a) {
     cur.r = lo;
     cur.rs = rps[lo];
     cur.np = rps[lo + 1] - cur.rs;
-    cur.kvh = (u - cur.rs * Hkv) / cur.np;
-    cur.p0 = (u - cur.rs * Hkv) % cur.np;
+    if (DIRECT) {
+        cur.kvh = blockIdx.x % Hkv;
+        u = cur.rs * Hkv + cur.kvh * cur.np;
+        u_end = u + cur.np;
+    } else cur.kvh = (u - cur.rs * Hkv) / cur.np;
+    cur.p0 = DIRECT ? 0 : (u - cur.rs * Hkv) % cur.np;
     cur.p1 = min(cur.np, cur.p0 + (u_end - u));
     cur.pos = a.row_pos[lo];
     cur.bt = a.block_table + (size_t)a.row_seq[lo] * a.max_blocks;
@@ -556,7 +564,7 @@ __global__ __launch_bounds__(256) void attn_stream_kernel(AttnArgs a) {
     while (true) {
         // ---- where the next segment starts (if this workgroup has one)
         const int u_next = u + (cur.p1 - cur.p0);
-        const bool has_next = u_next < u_end;
+        const bool has_next = !DIRECT && u_next < u_end;
         Seg nxt = cur;
         if (has_next) {                          // cur ended at the last page of its pair
             if (cur.kvh + 1 < Hkv) {
@@ -626,6 +634,12 @@ __global__ __launch_bounds__(256) void attn_stream_kernel(AttnArgs a) {
                     const float sc = __builtin_amdgcn_exp2f(s_m[w * 16 + j] - M);
                     L += s_l[w * 16 + j] * sc;
                     O += s_o[(w * G + j) * OSTRIDE + i] * sc;
+                }
+                if (DIRECT) {
+                    const int h = cur.kvh * G + j;
+                    ActStore<ACT32>::put(a.out, a.out_frag ? act_frag(cur.r, h * HD + i, a.n_rows, a.n_q_heads * HD)
+                                                           : ((size_t)cur.r * a.n_q_heads + h) * HD + i, O / L);
+                    continue;
                 }
                 float* dst = dst0 + (size_t)j * (HD + 2);
                 dst[i] = O;
@@ -705,8 +719,9 @@ template <int HD, bool ACT32>
 static hipError_t stream_impl(const AttnArgs& a, hipStream_t s) {
     const int G = a.n_q_heads / a.n_kv_heads;
     const size_t lds = (size_t)(4 * G * (HD + 4) + 128) * sizeof(float);
-    const int wgs = (a.total_units + a.units_per_wg - 1) / a.units_per_wg;
-    hipLaunchKernelGGL((attn_stream_kernel<HD, ACT32>), dim3(wgs), dim3(256), lds, s, a);
+    const int wgs = a.direct ? a.n_rows * a.n_kv_heads : (a.total_units + a.units_per_wg - 1) / a.units_per_wg;
+    if (a.direct) hipLaunchKernelGGL((attn_stream_kernel<HD, ACT32, true>), dim3(wgs), dim3(256), lds, s, a);
+    else hipLaunchKernelGGL((attn_stream_kernel<HD, ACT32, false>), dim3(wgs), dim3(256), lds, s, a);
     return hipGetLastError();
 }
 

@@ -593,6 +593,7 @@ struct StepCtx {
     int n_chunks;        // decode: context chunks
     float* logits;
     int total_units = 0, units_per_wg = 0, n_slots = 0;   // decode, stream kernel
+    bool direct = false;                                   // ... a workgroup to a (row, kv head) pair
     const int32_t* score_targets = nullptr;                // scoring pass: per-row targets and output
     float* score_out = nullptr;
     bool sample = false;                                   // fused LM head + sampler (no logits written)
@@ -610,6 +611,15 @@ static void plan_decode_attention(StepCtx& c, int pages_all, int max_ctx) {
     c.total_units = pages_all * m->cfg.n_kv_heads;
     c.units_per_wg = std::max(m->tune.chunk_pages, (c.total_units + wgs - 1) / wgs);
     c.n_slots = decode_slots(m, max_ctx);
+    // Short contexts: a workgroup to a pair, which needs no search for its first page, writes no partial results and needs no second
+    // launch.  Its price is that the longest pair is not shared out.  Four layers, us a step, stream -> workgroup to a pair: 0.6B
+    // shape, 1 row of 250 tokens 158 -> 143, of 400 153 -> 157, of 800 159 -> 176; 27 rows of 100 184 -> 160, of 400 205 -> 181, of
+    // 200..1,000 216 -> 207; 128 rows of 250 315 -> 294, of 200..1,000 431 -> 435; 4B, 3 rows of 250 265 -> 251, 8 (64 pairs) of 400
+    // 272 -> 265, of 800 282 -> 283; 128 of 100..400 532 -> 509; 7B, 27 of 400 486 -> 468.  So up to 256 tokens always, up to 512
+    // once a quarter of the CUs has a pair.
+    const int pairs = c.rows * m->cfg.n_kv_heads;
+    c.direct = !m->tune.chunk_set && !m->tune.attn_wgs && max_ctx <= (4 * pairs >= m->n_cus ? 32 : 16) * kPageTokens;
+    if (c.direct) return;
     if (!m->tune.chunk_set && c.units_per_wg == m->tune.chunk_pages) {
         // Few units (a small batch): as many workgroups as there are pages, up to 16 pieces to a pair.  A workgroup's time
         // is its chain of dependent steps, of which 16 pages are four per wave: one row of 250 tokens, 4B shape, pieces of
@@ -810,9 +820,9 @@ static int run_layers(StepCtx& c) {
         aa.scale_log2e = (float)(1.4426950408889634 / std::sqrt((double)hd));
         if (c.decode) {
             aa.row_page_start = c.w.page_start; aa.units_per_wg = c.units_per_wg; aa.total_units = c.total_units;
-            aa.n_chunks = c.n_slots; aa.out_frag = o_frag;
+            aa.n_chunks = c.n_slots; aa.out_frag = o_frag; aa.direct = c.direct;
             HIP_TRY(timed(m, SPIRAL_K_ATTN_DECODE, c.s, [&] { return launch_attn_stream(aa, hd, act32, c.s); }));
-            HIP_TRY(timed(m, SPIRAL_K_ATTN_COMBINE, c.s, [&] { return launch_attn_stream_combine(aa, hd, act32, c.s); }));
+            if (!c.direct) HIP_TRY(timed(m, SPIRAL_K_ATTN_COMBINE, c.s, [&] { return launch_attn_stream_combine(aa, hd, act32, c.s); }));
         } else {
             HIP_TRY(timed(m, SPIRAL_K_ATTN_PREFILL, c.s, [&] { return launch_attn_prefill(aa, hd, c.B, c.max_new, act32, c.s); }));
         }

@@ -80,6 +80,7 @@ struct AttnArgs {
 
 // Launchers (defined in the kernel translation units).  All enqueue on `s` and return the launch status.
 hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t s);
+    int32_t direct;           // decode: a workgroup has one (row, kv head) pair and writes `out`, no partial results
 hipError_t launch_upload(int32_t* dev_dst, const int32_t* host_src, int n, hipStream_t s);
 hipError_t launch_upload_multi(int32_t* const* dev_dst, const int32_t* const* host_src, const int* n, int n_seg, hipStream_t s);
 hipError_t launch_scatter(int32_t* dev_base, const int32_t* host_idx, const int32_t* host_val, int n, hipStream_t s);

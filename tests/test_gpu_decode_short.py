@@ -1,0 +1,60 @@
+"""Decode steps on short contexts: a workgroup to a (row, kv head) pair up to 16 or 32 pages, against the balanced stream (forced by
+spiral_model_tune "chunk=") on either side of the rule, and against the oracle."""
+import numpy as np
+import pytest
+
+from oracle import decoder as od
+from paper_2506_24119_amd import inputs as si
+
+pytestmark = pytest.mark.gpu
+
+
+def _step(g, w, lens, tune):
+    import torch
+    from paper_2506_24119_amd import binding as sb
+    rng = np.random.Generator(np.random.PCG64(sum(lens)))
+    B = len(lens)
+    seqs = [rng.integers(0, g.vocab, n + 1).astype(np.int32) for n in lens]
+    ids = np.arange(B, dtype=np.int32)
+    sess = sb.Session(g, w, 34 * B + 2, B, 34, max(sum(lens), B), max(lens) + 4,
+                      page_order=si.make_page_order(34 * B + 2, 3), tune=tune)
+    sess.prefill(ids, [s[:-1] for s in seqs])
+    sb.spiral_profile_begin(sess.model, sb.KERNEL_CLASSES.index("attn_combine"), 8)
+    out = sess.decode_step(ids, torch.from_numpy(np.array([s[-1] for s in seqs])).cuda(), sess.new_logits(B)).cpu().numpy()
+    merges = sb.spiral_profile_end(sess.model)[1]
+    sess.close()
+    return out, seqs, merges
+
+
+def _compare(g, host, lens, direct, rows):
+    from paper_2506_24119_amd import binding as sb
+    w = sb.weights_to_device(host)
+    got, seqs, merges = _step(g, w, lens, None)
+    assert merges == (0 if direct else g.n_layers)
+    stream, _, merges = _step(g, w, lens, "chunk=4")
+    assert merges == g.n_layers
+    for b in rows:
+        want = od.forward_full(g, host, seqs[b], logits_at=np.array([len(seqs[b]) - 1]))[0]
+        assert np.abs(got[b] - want).max() <= 3e-2 * want.std(), b
+    scale = stream.std(axis=1, keepdims=True)
+    assert (np.abs(got - stream) <= 1e-2 * scale).all()
+
+
+@pytest.mark.parametrize("q_heads,kv_heads,head_dim,dtype", [
+    (8, 2, 128, si.WEIGHT_BF16), (7, 1, 64, si.WEIGHT_BF16), (4, 4, 32, si.WEIGHT_BF16), (16, 1, 32, si.WEIGHT_FP32), (6, 2, 128, si.WEIGHT_FP32)])
+@pytest.mark.parametrize("longest", [1, 16, 100, 255, 256])
+def test_a_workgroup_to_a_pair(q_heads, kv_heads, head_dim, dtype, longest):
+    """Contexts of two tokens to 256 (with the step's own; 16 pages), and 257, which few pairs leave to the balanced stream.  The two differ in the
+    fp32 merge of the partial results, so by roundings of the half-precision attention output: 2^-11 of a value, in two layers; 1e-2 of the logits'
+    deviation is five times what that can add up to over a head's 128 values.  The oracle's bar is the 3e-2 of every logits test."""
+    g = si.ModelGeometry("short", 2, 128, q_heads, kv_heads, head_dim, 128, 256, 1e4, weight_dtype=dtype)
+    lens = sorted({1, 15, 16, 17, 63, 64, 65, longest} & set(range(1, longest + 1)))
+    _compare(g, si.make_weights(g, seed=81), lens, longest <= 255, range(len(lens)))
+
+
+@pytest.mark.parametrize("longest", [256, 511, 512])
+def test_many_pairs(longest):
+    """130 pairs: the longest context may have 512 tokens (with the step's own)"""
+    g = si.ModelGeometry("short", 2, 128, 4, 2, 64, 128, 256, 1e4)
+    lens = [1 + (37 * b) % 90 for b in range(64)] + [longest]
+    _compare(g, si.make_weights(g, seed=84), lens, longest <= 511, (0, 31, 64))
