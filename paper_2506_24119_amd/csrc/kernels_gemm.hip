@@ -199,7 +199,11 @@ __global__ __launch_bounds__(256) void gemm_mfma_kernel(GemmArgs g) {
 // four rows: every load is a cache line per lane and waits for the one before), this
 // 3 to 4, a decode step of the two-layer model 237 -> 83.
 // ---------------------------------------------------------------------------------------------
-template <int EPI, bool VEC>
+// NORM: the rows of A are residual rows, whose RMSNorm each wave does by itself: the sum of squares beside the products, the factor
+// on the sums.  ADD: the product goes onto the residual.  Both save a launch each time in a decode step, which is nothing
+// but launches: two layers, four rows 148 -> 120 us with the attention's merge gone too (4 + 1 launches of 3 us a layer
+// less, and the last norm).
+template <int EPI, bool VEC, bool NORM = false, bool ADD = false>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs g) {
     constexpr int R = 4;
     const int lane = threadIdx.x & 63, n = blockIdx.x * 4 + (threadIdx.x >> 6);
@@ -214,19 +218,24 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs g) {
     else w0 = (const float*)g.w[2] + (size_t)(n - g.rows[0] - g.rows[1]) * K;
     for (int m0 = blockIdx.y * R; m0 < g.M; m0 += gridDim.y * R) {
         const float* a[R];
-        float s0[R], s1[R];
+        float s0[R], s1[R], sq[R];
 #pragma unroll
         for (int r = 0; r < R; ++r) {
             a[r] = (const float*)g.A + (size_t)min(m0 + r, g.M - 1) * K;
-            s0[r] = s1[r] = 0.f;
+            s0[r] = s1[r] = sq[r] = 0.f;
         }
         if (VEC) {
             for (int k = lane * 4; k < K; k += 256) {
                 const float4 x0 = *(const float4*)(w0 + k);
                 const float4 x1 = EPI == EPI_SWIGLU ? *(const float4*)(w1 + k) : make_float4(0.f, 0.f, 0.f, 0.f);
+                const float4 gn = NORM ? *(const float4*)(g.norm_gain + k) : make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
                 for (int r = 0; r < R; ++r) {
-                    const float4 y = *(const float4*)(a[r] + k);
+                    float4 y = *(const float4*)(a[r] + k);
+                    if (NORM) {
+                        sq[r] = fmaf(y.w, y.w, fmaf(y.z, y.z, fmaf(y.y, y.y, fmaf(y.x, y.x, sq[r]))));
+                        y.x *= gn.x; y.y *= gn.y; y.z *= gn.z; y.w *= gn.w;
+                    }
                     s0[r] = fmaf(y.w, x0.w, fmaf(y.z, x0.z, fmaf(y.y, x0.y, fmaf(y.x, x0.x, s0[r]))));
                     if (EPI == EPI_SWIGLU) s1[r] = fmaf(y.w, x1.w, fmaf(y.z, x1.z, fmaf(y.y, x1.y, fmaf(y.x, x1.x, s1[r]))));
                 }
@@ -246,6 +255,11 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs g) {
         for (int r = 0; r < R; ++r) {
             s0[r] = wave_sum(s0[r]);
             if (EPI == EPI_SWIGLU) s1[r] = wave_sum(s1[r]);
+            if (NORM) {
+                const float rs = rsqrtf(wave_sum(sq[r]) / (float)K + g.norm_eps);
+                s0[r] *= rs;
+                if (EPI == EPI_SWIGLU) s1[r] *= rs;
+            }
         }
         float v = 0.f;
 #pragma unroll
@@ -253,7 +267,10 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs g) {
             const float x = EPI == EPI_SWIGLU ? (s0[r] / (1.0f + expf(-s0[r]))) * s1[r] : s0[r];
             if (lane == r) v = x;
         }
-        if (lane < R && m0 + lane < g.M) ((float*)g.out)[(size_t)(m0 + lane) * g.N + n] = v;
+        if (lane < R && m0 + lane < g.M) {
+            float* out = (float*)g.out + (size_t)(m0 + lane) * g.N + n;
+            *out = ADD ? *out + v : v;
+        }
     }
 }
 
@@ -283,6 +300,13 @@ hipError_t launch_gemm(const GemmArgs& a, int epilogue, bool w_bf16, int bn, hip
         if (a.splits != 1) return hipErrorInvalidValue;
         const dim3 g((a.N + 3) / 4, std::min((a.M + 3) / 4, 32768)), b(256);
         const bool vec = (a.K & 3) == 0;             // weights and activations are 16-byte aligned
+        if (a.norm_gain || a.add) {                  // the decode step's forms: the host asks for them where K % 4 == 0
+            if (!vec || (a.norm_gain && a.add) || (a.add && epilogue != EPI_STORE_F32)) return hipErrorInvalidValue;
+            if (a.add) hipLaunchKernelGGL((gemm_f32_kernel<EPI_STORE_F32, true, false, true>), g, b, 0, s, a);
+            else if (epilogue == EPI_SWIGLU) hipLaunchKernelGGL((gemm_f32_kernel<EPI_SWIGLU, true, true>), g, b, 0, s, a);
+            else hipLaunchKernelGGL((gemm_f32_kernel<EPI_STORE_F32, true, true>), g, b, 0, s, a);
+            return hipGetLastError();
+        }
         if (epilogue == EPI_SWIGLU) {
             if (vec) hipLaunchKernelGGL((gemm_f32_kernel<EPI_SWIGLU, true>), g, b, 0, s, a);
             else hipLaunchKernelGGL((gemm_f32_kernel<EPI_SWIGLU, false>), g, b, 0, s, a);

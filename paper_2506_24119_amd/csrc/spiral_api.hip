@@ -746,6 +746,14 @@ static int run_layers(StepCtx& c) {
     const int mlp_frag = h2_frag && gemm_decode_takes(c.rows, d, cfg.ffn_dim, EPI_STORE_F32, false);
     const int hf_frag = !act32 && gemm_decode_takes(c.B, cfg.vocab, d, EPI_STORE_F32, true);
 
+    // fp32 weights, a few rows: the norms and the residual's sums are done by the projections.  Each wave norms the rows for itself,
+    // four at a time, so the rows and d must be few.  Four layers, us a step, separate kernels -> this: d 128, 1 row 135 -> 109, 8
+    // 148 -> 102, 32 146 -> 120; d 256, 16 rows 116 -> 111, 32 131 -> 132; d 512, 16 147 -> 151; d 1,024, 1 row 212 -> 179, 8
+    // 214 -> 208, 12 232 -> 239; d 2,048, 4 rows 354 -> 365.
+    const bool lean = act32 && c.decode && d <= 1024 && (c.rows <= 8 || (c.rows <= 32 && c.rows * d <= 4096)) && d % 4 == 0 &&
+                      qw % 4 == 0 && cfg.ffn_dim % 4 == 0;
+    if (lean) part_o = part_down = c.w.x;
+
     auto project = [&](int l, const QkvPlan& pl, const int32_t* row_map) -> int {
         GemmArgs g = {};
         int blocks = 0;
@@ -755,6 +763,7 @@ static int run_layers(StepCtx& c) {
             g.w[blocks] = m->lw(l, SPIRAL_W_V); g.rows[blocks++] = kw;
         }
         g.A = c.w.h; g.M = c.rows; g.N = (pl.hq + 2 * pl.hkv) * hd; g.K = d; g.out = c.w.qkv; g.splits = pl.sh.splits; g.a_frag = h_frag;
+        if (lean) { g.A = c.w.x; g.norm_gain = (const float*)m->lw(l, SPIRAL_W_ATTN_NORM); g.norm_eps = cfg.rms_eps; }
         g.wf = m->f_lm ? (const uint16_t*)m->f_qkv[l] + (pl.hq ? 0 : frag_block(qw / 32, 0, d)) : nullptr;
         QkvPostArgs qa = {c.w.qkv, m->lw(l, SPIRAL_W_BQ), m->lw(l, SPIRAL_W_BK), m->lw(l, SPIRAL_W_BV),
                           (const float*)m->lw(l, SPIRAL_W_Q_NORM), (const float*)m->lw(l, SPIRAL_W_K_NORM),
@@ -776,7 +785,7 @@ static int run_layers(StepCtx& c) {
 
     for (int l = c.first_layer; l < cfg.n_layers; ++l) {
         const bool q_only = c.q_rows && l == c.first_layer;
-        if (l > 0 && !q_only) {
+        if (l > 0 && !q_only && !lean) {
             NormArgs n = {c.w.x, part, (const float*)m->lw(l, SPIRAL_W_ATTN_NORM), c.w.h, nullptr, c.rows, c.rows, d, pending, cfg.rms_eps, sat,
                           nullptr, h_frag};
             HIP_TRY(timed(m, SPIRAL_K_NORM, c.s, [&] { return launch_add_norm(n, act32, c.s); }));
@@ -829,12 +838,12 @@ static int run_layers(StepCtx& c) {
 
         GemmArgs go = {};
         go.A = c.w.o; go.w[0] = m->lw(l, SPIRAL_W_O); go.rows[0] = d;
-        go.M = c.rows; go.N = d; go.K = qw; go.out = part_o; go.splits = s_o; go.a_frag = o_frag;
+        go.M = c.rows; go.N = d; go.K = qw; go.out = part_o; go.splits = s_o; go.a_frag = o_frag; go.add = lean;
         go.wf = m->f_lm ? m->f_o[l] : nullptr;
         HIP_TRY(timed(m, SPIRAL_K_GEMM_O, c.s, [&] { return launch_gemm(go, EPI_STORE_F32, m->w_bf16, sh_o.bn, c.s); }));
 
         NormArgs n2 = {c.w.x, part_o, (const float*)m->lw(l, SPIRAL_W_MLP_NORM), c.w.h, nullptr, c.rows, c.rows, d, s_o, cfg.rms_eps, sat, nullptr, h2_frag};
-        HIP_TRY(timed(m, SPIRAL_K_NORM, c.s, [&] { return launch_add_norm(n2, act32, c.s); }));
+        if (!lean) HIP_TRY(timed(m, SPIRAL_K_NORM, c.s, [&] { return launch_add_norm(n2, act32, c.s); }));
 
         GemmArgs gu = {};
         gu.A = c.w.h; gu.w[0] = m->lw(l, SPIRAL_W_GATE); gu.w[1] = m->lw(l, SPIRAL_W_UP);
@@ -842,11 +851,12 @@ static int run_layers(StepCtx& c) {
         gu.M = c.rows; gu.N = cfg.ffn_dim; gu.K = d; gu.out = c.w.mlp; gu.splits = 1;
         gu.wf = m->f_lm ? m->f_gu[l] : nullptr;
         gu.sat_count = sat; gu.a_frag = h2_frag; gu.out_frag = mlp_frag;
+        if (lean) { gu.A = c.w.x; gu.norm_gain = (const float*)m->lw(l, SPIRAL_W_MLP_NORM); gu.norm_eps = cfg.rms_eps; }
         HIP_TRY(timed(m, SPIRAL_K_GEMM_GATE_UP, c.s, [&] { return launch_gemm(gu, EPI_SWIGLU, m->w_bf16, t.bn_gu, c.s); }));
 
         GemmArgs gd = {};
         gd.A = c.w.mlp; gd.w[0] = m->lw(l, SPIRAL_W_DOWN); gd.rows[0] = d;
-        gd.M = c.rows; gd.N = d; gd.K = cfg.ffn_dim; gd.out = part_down; gd.splits = s_down; gd.a_frag = mlp_frag;
+        gd.M = c.rows; gd.N = d; gd.K = cfg.ffn_dim; gd.out = part_down; gd.splits = s_down; gd.a_frag = mlp_frag; gd.add = lean;
         gd.wf = m->f_lm ? m->f_down[l] : nullptr;
         HIP_TRY(timed(m, SPIRAL_K_GEMM_DOWN, c.s, [&] { return launch_gemm(gd, EPI_STORE_F32, m->w_bf16, sh_down.bn, c.s); }));
         pending = s_down;
@@ -883,11 +893,12 @@ static int run_layers(StepCtx& c) {
     // final norm on one row per sequence, then the LM head
     NormArgs nf = {c.w.x, part, (const float*)m->w[1], c.w.hf, c.decode ? nullptr : c.w.last_rows,
                    c.rows, c.B, d, pending, cfg.rms_eps, sat, nullptr, hf_frag};
-    HIP_TRY(timed(m, SPIRAL_K_NORM, c.s, [&] { return launch_add_norm(nf, act32, c.s); }));
+    if (!lean) HIP_TRY(timed(m, SPIRAL_K_NORM, c.s, [&] { return launch_add_norm(nf, act32, c.s); }));
     GemmArgs gl = {};
     gl.A = c.w.hf; gl.w[0] = m->w[2]; gl.rows[0] = cfg.vocab;
     gl.M = c.B; gl.N = cfg.vocab; gl.K = d; gl.out = c.logits; gl.splits = 1;
     gl.wf = m->f_lm; gl.a_frag = hf_frag; gl.head = 1;
+    if (lean) { gl.A = c.w.x; gl.norm_gain = (const float*)m->w[1]; gl.norm_eps = cfg.rms_eps; }
     if (c.sample) {
         // the LM head keeps the best (score, index) of each 128-column tile per row; a small kernel picks the winner
         const int cols = gemm_sample_tile_cols(c.B, t.bn_lm);

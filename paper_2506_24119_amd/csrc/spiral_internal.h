@@ -58,6 +58,10 @@ struct GemmArgs {
     int32_t* sat_count;   // or null: incremented when an activation left the half-precision range (SwiGLU output)
     int32_t a_frag, out_frag;    // at most 128 rows: A, and the SwiGLU output, lie in act_frag() order
     int32_t head;         // the LM head
+    // fp32 weights: A holds residual rows, normed by this gain while they are read (null: A as it is); add: the product is added to `out`
+    const float* norm_gain;
+    float norm_eps;
+    int32_t add;
 };
 
 struct AttnArgs {
@@ -76,11 +80,11 @@ struct AttnArgs {
     int32_t units_per_wg, total_units;   // decode stream: (row, kv head, page) units per workgroup, and in all
     float scale_log2e;        // log2(e) / sqrt(hd)
     int32_t out_frag;         // decode: out in act_frag() order
+    int32_t direct;           // decode: a workgroup has one (row, kv head) pair and writes `out`, no partial results
 };
 
 // Launchers (defined in the kernel translation units).  All enqueue on `s` and return the launch status.
 hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t s);
-    int32_t direct;           // decode: a workgroup has one (row, kv head) pair and writes `out`, no partial results
 hipError_t launch_upload(int32_t* dev_dst, const int32_t* host_src, int n, hipStream_t s);
 hipError_t launch_upload_multi(int32_t* const* dev_dst, const int32_t* const* host_src, const int* n, int n_seg, hipStream_t s);
 hipError_t launch_scatter(int32_t* dev_base, const int32_t* host_idx, const int32_t* host_val, int n, hipStream_t s);

@@ -1,5 +1,6 @@
 """Decode steps on short contexts: a workgroup to a (row, kv head) pair up to 16 or 32 pages, against the balanced stream (forced by
-spiral_model_tune "chunk=") on either side of the rule, and against the oracle."""
+spiral_model_tune "chunk=") on either side of the rule, and the fp32 step of a few rows whose projections do the norms and the
+residual's sums, against the oracle and at the edges of its rows."""
 import numpy as np
 import pytest
 
@@ -58,3 +59,22 @@ def test_many_pairs(longest):
     g = si.ModelGeometry("short", 2, 128, 4, 2, 64, 128, 256, 1e4)
     lens = [1 + (37 * b) % 90 for b in range(64)] + [longest]
     _compare(g, si.make_weights(g, seed=84), lens, longest <= 511, (0, 31, 64))
+
+
+@pytest.mark.parametrize("d,ffn,norm,B", [(128, 512, False, 1), (128, 512, False, 4), (128, 512, False, 5), (128, 512, False, 32), (128, 512, False, 33),
+                                          (132, 200, True, 8), (132, 200, True, 31), (132, 200, True, 32), (1024, 96, False, 8), (1024, 96, False, 9)])
+def test_fp32_projections_that_norm(d, ffn, norm, B):
+    """The last batch the rule takes and the first it leaves, remainders of four rows, widths that are and are not multiples of the 256 elements a
+    wave reads at once.  Bar: q, k, v and the attention output round to half, 2^-11 each; all four in the same direction in two layers are 4e-3."""
+    from paper_2506_24119_amd import binding as sb
+    g = si.ModelGeometry("lean", 2, d, 4, 2, 32, ffn, 260, 1e4, qk_norm=norm, qkv_bias=not norm, weight_dtype=si.WEIGHT_FP32)
+    host = si.make_weights(g, seed=82)
+    rng = np.random.Generator(np.random.PCG64(83))
+    for lw in host["layers"]:
+        for k in ("attn_norm", "mlp_norm"):
+            lw[k] = rng.normal(1.0, 0.2, d).astype(np.float32)
+    host["final_norm"] = rng.normal(1.0, 0.2, d).astype(np.float32)
+    got, seqs, _ = _step(g, sb.weights_to_device(host), [3 + 7 * (b % 9) for b in range(B)], None)
+    for b, s in enumerate(seqs):
+        want = od.forward_full(g, host, s, logits_at=np.array([len(s) - 1]))[0]
+        assert np.abs(got[b] - want).max() <= 4e-3 * want.std(), b
