@@ -616,9 +616,13 @@ static void plan_decode_attention(StepCtx& c, int pages_all, int max_ctx) {
     // shape, 1 row of 250 tokens 158 -> 143, of 400 153 -> 157, of 800 159 -> 176; 27 rows of 100 184 -> 160, of 400 205 -> 181, of
     // 200..1,000 216 -> 207; 128 rows of 250 315 -> 294, of 200..1,000 431 -> 435; 4B, 3 rows of 250 265 -> 251, 8 (64 pairs) of 400
     // 272 -> 265, of 800 282 -> 283; 128 of 100..400 532 -> 509; 7B, 27 of 400 486 -> 468.  So up to 256 tokens always, up to 512
-    // once a quarter of the CUs has a pair.
-    const int pairs = c.rows * m->cfg.n_kv_heads;
-    c.direct = !m->tune.chunk_set && !m->tune.attn_wgs && max_ctx <= (4 * pairs >= m->n_cus ? 32 : 16) * kPageTokens;
+    // once a quarter of the CUs has a pair.  Up to 1,536 once every CU has one and the mean is at least half of
+    // the longest: 0.6B, 32 rows of 300..1,500 245 -> 236, 128 of 250..1,250 476 -> 481, of 300..1,500 528 -> 525; 4B, 64 of 200..900
+    // 430 -> 411, 128 of 300..1,500 745 -> 735, of 1,200..1,500 893 -> 868; 7B, 128 of 300..1,500 891 -> 871.  Beyond: 4B, 128 rows of
+    // 400..2,000 859 -> 866, of 1,024..5,120 1471 -> 1510.
+    const int pairs = c.rows * m->cfg.n_kv_heads, longest = (max_ctx + kPageTokens - 1) / kPageTokens;
+    const bool even = (long)longest * pairs <= 2L * c.total_units;
+    c.direct = !m->tune.chunk_set && !m->tune.attn_wgs && longest <= (pairs >= m->n_cus && even ? 96 : 4 * pairs >= m->n_cus ? 32 : 16);
     if (c.direct) return;
     if (!m->tune.chunk_set && c.units_per_wg == m->tune.chunk_pages) {
         // Few units (a small batch): as many workgroups as there are pages, up to 16 pieces to a pair.  A workgroup's time

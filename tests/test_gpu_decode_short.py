@@ -1,4 +1,4 @@
-"""Decode steps on short contexts: a workgroup to a (row, kv head) pair up to 16 or 32 pages, against the balanced stream (forced by
+"""Decode steps on short contexts: a workgroup to a (row, kv head) pair up to 16, 32 or 96 pages, against the balanced stream (forced by
 spiral_model_tune "chunk=") on either side of the rule, and the fp32 step of a few rows whose projections do the norms and the
 residual's sums, against the oracle and at the edges of its rows."""
 import numpy as np
@@ -17,8 +17,9 @@ def _step(g, w, lens, tune):
     B = len(lens)
     seqs = [rng.integers(0, g.vocab, n + 1).astype(np.int32) for n in lens]
     ids = np.arange(B, dtype=np.int32)
-    sess = sb.Session(g, w, 34 * B + 2, B, 34, max(sum(lens), B), max(lens) + 4,
-                      page_order=si.make_page_order(34 * B + 2, 3), tune=tune)
+    nb = max(lens) // 16 + 2
+    sess = sb.Session(g, w, nb * B + 2, B, nb, max(sum(lens), B), max(lens) + 4,
+                      page_order=si.make_page_order(nb * B + 2, 3), tune=tune)
     sess.prefill(ids, [s[:-1] for s in seqs])
     sb.spiral_profile_begin(sess.model, sb.KERNEL_CLASSES.index("attn_combine"), 8)
     out = sess.decode_step(ids, torch.from_numpy(np.array([s[-1] for s in seqs])).cuda(), sess.new_logits(B)).cpu().numpy()
@@ -59,6 +60,14 @@ def test_many_pairs(longest):
     g = si.ModelGeometry("short", 2, 128, 4, 2, 64, 128, 256, 1e4)
     lens = [1 + (37 * b) % 90 for b in range(64)] + [longest]
     _compare(g, si.make_weights(g, seed=84), lens, longest <= 511, (0, 31, 64))
+
+
+@pytest.mark.parametrize("shortest,longest,direct", [(850, 1535, True), (850, 1536, False), (60, 1535, False)])
+def test_a_pair_for_every_cu(shortest, longest, direct):
+    """264 pairs: 1,536 tokens, where the mean is at least half of the longest"""
+    g = si.ModelGeometry("short", 2, 128, 8, 8, 32, 128, 256, 1e4)
+    lens = [shortest + (29 * b) % 300 for b in range(32)] + [longest]
+    _compare(g, si.make_weights(g, seed=85), lens, direct, (0, 32))
 
 
 @pytest.mark.parametrize("d,ffn,norm,B", [(128, 512, False, 1), (128, 512, False, 4), (128, 512, False, 5), (128, 512, False, 32), (128, 512, False, 33),
