@@ -480,12 +480,16 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(AttnArgs a, Prefil
 // page stream does not stop at segment boundaries (a workgroup per chunk pays a start-up and a
 // drain for every 16 pages: 5.2 vs 5.9 TB/s measured).
 // ---------------------------------------------------------------------------------------------
-// DIRECT: short contexts (the host's rule): a workgroup has one pair to itself and writes the output: no search, no partial
-// results, no merging launch.  27 rows of 400 tokens, 0.6B shape: 6 us a layer less of 51.  A parameter of the template, since the test
-// at run time costs the other form 8 registers and with them a workgroup of three a CU (128 rows of 1,280 tokens: 7 % of a step).
-template <int HD, bool ACT32, bool DIRECT>
+// FORM (a parameter of the template, since the test at run time costs the stream 8 registers and with them a workgroup of three a CU:
+// 128 rows of 1,280 tokens, 7 % of a step):
+//   DECODE_PAIR: short contexts (the host's rule): a workgroup has one pair to itself and writes the output: no search, no partial
+//   results, no merging launch.  27 rows of 400 tokens, 0.6B shape: 6 us a layer less of 51.
+//   DECODE_PIECES: the last rows of a prefill: workgroup (x, y) has pages y * U to (y + 1) * U of pair x, if there are any, and writes the
+//   pair's part y.  Where a pair is cut, and with it the order of its sums, follows from its own context, not from the call's others.
+template <int HD, bool ACT32, int FORM>
 __global__ __launch_bounds__(256) void attn_stream_kernel(AttnArgs a) {
     constexpr int KS = HD / 32, MT = HD / 16, OSTRIDE = HD + 4;
+    constexpr bool STREAM = FORM == DECODE_STREAM;
     extern __shared__ float lds_f[];
     const int G = a.n_q_heads / a.n_kv_heads;
     const int Hkv = a.n_kv_heads;
@@ -499,14 +503,14 @@ __global__ __launch_bounds__(256) void attn_stream_kernel(AttnArgs a) {
     const int32_t* rps = a.row_page_start;
     const int T = rps[a.n_rows] * Hkv;
     int u = blockIdx.x * U;
-    if (!DIRECT && u >= T) return;
+    if (STREAM && u >= T) return;
     int u_end = min(u + U, T);
 
     // the row that holds unit u: the largest r with row_page_start[r] * Hkv <= u.  The prefix sums
     // increase strictly, so r + 1 is the number of entries that satisfy it: the lanes test 64 entries
     // at a time (one round of independent loads instead of a chain of dependent ones).
     int below = 0;
-    if (DIRECT) below = blockIdx.x / Hkv + 1;
+    if (!STREAM) below = blockIdx.x / Hkv + 1;
     else for (int base = 0; base < a.n_rows; base += 64) {
         const int j = min(base + lane, a.n_rows - 1);
         const bool hit = base + lane < a.n_rows && rps[j] * Hkv <= u;
@@ -518,12 +522,16 @@ __global__ __launch_bounds__(256) void attn_stream_kernel(AttnArgs a) {
     cur.r = lo;
     cur.rs = rps[lo];
     cur.np = rps[lo + 1] - cur.rs;
-    if (DIRECT) {
+    if (STREAM) {
+        cur.kvh = (u - cur.rs * Hkv) / cur.np;
+        cur.p0 = (u - cur.rs * Hkv) % cur.np;
+    } else {
         cur.kvh = blockIdx.x % Hkv;
-        u = cur.rs * Hkv + cur.kvh * cur.np;
-        u_end = u + cur.np;
-    } else cur.kvh = (u - cur.rs * Hkv) / cur.np;
-    cur.p0 = DIRECT ? 0 : (u - cur.rs * Hkv) % cur.np;
+        cur.p0 = FORM == DECODE_PIECES ? blockIdx.y * U : 0;
+        if (cur.p0 >= cur.np) return;            // the longest pair has more pieces
+        u = cur.rs * Hkv + cur.kvh * cur.np + cur.p0;
+        u_end = u + (FORM == DECODE_PIECES ? U : cur.np);
+    }
     cur.p1 = min(cur.np, cur.p0 + (u_end - u));
     cur.pos = a.row_pos[lo];
     cur.bt = a.block_table + (size_t)a.row_seq[lo] * a.max_blocks;
@@ -564,7 +572,7 @@ __global__ __launch_bounds__(256) void attn_stream_kernel(AttnArgs a) {
     while (true) {
         // ---- where the next segment starts (if this workgroup has one)
         const int u_next = u + (cur.p1 - cur.p0);
-        const bool has_next = !DIRECT && u_next < u_end;
+        const bool has_next = STREAM && u_next < u_end;
         Seg nxt = cur;
         if (has_next) {                          // cur ended at the last page of its pair
             if (cur.kvh + 1 < Hkv) {
@@ -623,7 +631,7 @@ __global__ __launch_bounds__(256) void attn_stream_kernel(AttnArgs a) {
         __syncthreads();
         {
             const int pair_start = cur.rs * Hkv + cur.kvh * cur.np;
-            const int slot = blockIdx.x - pair_start / U;
+            const int slot = FORM == DECODE_PIECES ? blockIdx.y : blockIdx.x - pair_start / U;
             float* dst0 = a.part + (((size_t)cur.r * Hkv + cur.kvh) * a.n_chunks + slot) * G * (HD + 2);
             for (int e = threadIdx.x; e < G * HD; e += 256) {
                 const int j = e / HD, i = e % HD;
@@ -635,7 +643,7 @@ __global__ __launch_bounds__(256) void attn_stream_kernel(AttnArgs a) {
                     L += s_l[w * 16 + j] * sc;
                     O += s_o[(w * G + j) * OSTRIDE + i] * sc;
                 }
-                if (DIRECT) {
+                if (FORM == DECODE_PAIR) {
                     const int h = cur.kvh * G + j;
                     ActStore<ACT32>::put(a.out, a.out_frag ? act_frag(cur.r, h * HD + i, a.n_rows, a.n_q_heads * HD)
                                                            : ((size_t)cur.r * a.n_q_heads + h) * HD + i, O / L);
@@ -665,8 +673,9 @@ __global__ __launch_bounds__(64) void attn_stream_combine_kernel(AttnArgs a) {
     const int G = a.n_q_heads / a.n_kv_heads, Hkv = a.n_kv_heads;
     const int kvh = h / G, j = h % G;
     const int rs = a.row_page_start[r], np = a.row_page_start[r + 1] - rs;
-    const int first = (rs * Hkv + kvh * np) / a.units_per_wg;
-    const int last = (rs * Hkv + kvh * np + np - 1) / a.units_per_wg;
+    const int start = a.form == DECODE_PIECES ? 0 : rs * Hkv + kvh * np;           // pieces are counted from the pair's own start
+    const int first = start / a.units_per_wg;
+    const int last = (start + np - 1) / a.units_per_wg;
     const int n_parts = last - first + 1;
     const float* base = a.part + (((size_t)r * Hkv + kvh) * a.n_chunks * G + j) * (HD + 2);       // a part is HD + 2 floats: 8-byte aligned
     const size_t cstride = (size_t)G * (HD + 2);
@@ -719,9 +728,11 @@ template <int HD, bool ACT32>
 static hipError_t stream_impl(const AttnArgs& a, hipStream_t s) {
     const int G = a.n_q_heads / a.n_kv_heads;
     const size_t lds = (size_t)(4 * G * (HD + 4) + 128) * sizeof(float);
-    const int wgs = a.direct ? a.n_rows * a.n_kv_heads : (a.total_units + a.units_per_wg - 1) / a.units_per_wg;
-    if (a.direct) hipLaunchKernelGGL((attn_stream_kernel<HD, ACT32, true>), dim3(wgs), dim3(256), lds, s, a);
-    else hipLaunchKernelGGL((attn_stream_kernel<HD, ACT32, false>), dim3(wgs), dim3(256), lds, s, a);
+    const int pairs = a.n_rows * a.n_kv_heads, wgs = (a.total_units + a.units_per_wg - 1) / a.units_per_wg;
+    if (a.form == DECODE_PAIR) hipLaunchKernelGGL((attn_stream_kernel<HD, ACT32, DECODE_PAIR>), dim3(pairs), dim3(256), lds, s, a);
+    else if (a.form == DECODE_STREAM) hipLaunchKernelGGL((attn_stream_kernel<HD, ACT32, DECODE_STREAM>), dim3(wgs), dim3(256), lds, s, a);
+    else if constexpr (!ACT32) hipLaunchKernelGGL((attn_stream_kernel<HD, ACT32, DECODE_PIECES>), dim3(pairs, a.n_chunks), dim3(256), lds, s, a);
+    else return hipErrorInvalidValue;            // only prefills with 16-bit weights have such rows
     return hipGetLastError();
 }
 

@@ -58,6 +58,7 @@ struct Tune {
     int fail_after = 0;            // test hook: the n-th timed launch from now reports a launch failure instead of running
 };
 constexpr int kDecodePieces = 16;      // partial results of a (row, kv head) pair in a step with few units
+constexpr int kLastRowsPages = 16;     // pages of a workgroup in the attention of a prefill's last rows
 constexpr int kMaxSplit = 16;
 constexpr int kScoreSplits = 64;       // vocabulary ranges of the scoring pass (partial log-sum-exp pairs per row)
 
@@ -593,7 +594,7 @@ struct StepCtx {
     int n_chunks;        // decode: context chunks
     float* logits;
     int total_units = 0, units_per_wg = 0, n_slots = 0;   // decode, stream kernel
-    bool direct = false;                                   // ... a workgroup to a (row, kv head) pair
+    int form = DECODE_STREAM;                              // ... a DecodeForm
     const int32_t* score_targets = nullptr;                // scoring pass: per-row targets and output
     float* score_out = nullptr;
     bool sample = false;                                   // fused LM head + sampler (no logits written)
@@ -622,8 +623,10 @@ static void plan_decode_attention(StepCtx& c, int pages_all, int max_ctx) {
     // 400..2,000 859 -> 866, of 1,024..5,120 1471 -> 1510.
     const int pairs = c.rows * m->cfg.n_kv_heads, longest = (max_ctx + kPageTokens - 1) / kPageTokens;
     const bool even = (long)longest * pairs <= 2L * c.total_units;
-    c.direct = !m->tune.chunk_set && !m->tune.attn_wgs && longest <= (pairs >= m->n_cus && even ? 96 : 4 * pairs >= m->n_cus ? 32 : 16);
-    if (c.direct) return;
+    if (!m->tune.chunk_set && !m->tune.attn_wgs && longest <= (pairs >= m->n_cus && even ? 96 : 4 * pairs >= m->n_cus ? 32 : 16)) {
+        c.form = DECODE_PAIR;
+        return;
+    }
     if (!m->tune.chunk_set && c.units_per_wg == m->tune.chunk_pages) {
         // Few units (a small batch): as many workgroups as there are pages, up to 16 pieces to a pair.  A workgroup's time
         // is its chain of dependent steps, of which 16 pages are four per wave: one row of 250 tokens, 4B shape, pieces of
@@ -639,6 +642,19 @@ static void plan_decode_attention(StepCtx& c, int pages_all, int max_ctx) {
             c.w.attn_part = c.w.qkv;
         }
     }
+}
+
+// The same for the last rows of a prefill: pieces of a fixed number of pages from each pair's first on, so that a sequence's sums do not
+// follow from the contexts of its call (contexts of one piece: no parts to merge, the same bits).  Calls of two or four layers, us, the
+// decode step's cut -> this: 4B, 15,272 rows 3647 -> 3665 (runs differ by 50), 788 rows on histories 1069 -> 1068, 64 runs of 4 on 1,000
+// tokens 340 -> 346, 130 tokens on 8,000 350 -> 348; 0.6B, 11,206 rows 2184 -> 2181.
+static void plan_last_rows_attention(StepCtx& c, int pages_all, int max_ctx) {
+    const spiral_model* m = c.m;
+    c.total_units = pages_all * m->cfg.n_kv_heads;
+    c.units_per_wg = std::max(kLastRowsPages, m->tune.chunk_pages);       // the partial results have room for pieces of chunk_pages
+    const int longest = (max_ctx + kPageTokens - 1) / kPageTokens;
+    c.n_slots = (longest + c.units_per_wg - 1) / c.units_per_wg;
+    c.form = c.n_slots == 1 ? DECODE_PAIR : DECODE_PIECES;
 }
 
 namespace spiral {
@@ -816,7 +832,7 @@ static int run_layers(StepCtx& c) {
             StepCtx r = c;
             r.decode = true; r.rows = c.B; r.first_layer = l; r.q_rows = c.w.last_rows;
             r.w.x = (float*)c.w.h; r.w.h = c.w.hf;
-            plan_decode_attention(r, start[c.B], max_ctx);
+            plan_last_rows_attention(r, start[c.B], max_ctx);
             return run_layers(r);
         }
         {
@@ -833,9 +849,9 @@ static int run_layers(StepCtx& c) {
         aa.scale_log2e = (float)(1.4426950408889634 / std::sqrt((double)hd));
         if (c.decode) {
             aa.row_page_start = c.w.page_start; aa.units_per_wg = c.units_per_wg; aa.total_units = c.total_units;
-            aa.n_chunks = c.n_slots; aa.out_frag = o_frag; aa.direct = c.direct;
+            aa.n_chunks = c.n_slots; aa.out_frag = o_frag; aa.form = c.form;
             HIP_TRY(timed(m, SPIRAL_K_ATTN_DECODE, c.s, [&] { return launch_attn_stream(aa, hd, act32, c.s); }));
-            if (!c.direct) HIP_TRY(timed(m, SPIRAL_K_ATTN_COMBINE, c.s, [&] { return launch_attn_stream_combine(aa, hd, act32, c.s); }));
+            if (c.form != DECODE_PAIR) HIP_TRY(timed(m, SPIRAL_K_ATTN_COMBINE, c.s, [&] { return launch_attn_stream_combine(aa, hd, act32, c.s); }));
         } else {
             HIP_TRY(timed(m, SPIRAL_K_ATTN_PREFILL, c.s, [&] { return launch_attn_prefill(aa, hd, c.B, c.max_new, act32, c.s); }));
         }

@@ -64,6 +64,10 @@ struct GemmArgs {
     int32_t add;
 };
 
+// How the decode attention shares out its pages: the whole batch in equal ranges, a workgroup to a (row, kv head) pair, which writes `out`
+// (no partial results), or pieces of units_per_wg pages counted from each pair's first (n_chunks: as many as the longest pair has).
+enum DecodeForm { DECODE_STREAM = 0, DECODE_PAIR = 1, DECODE_PIECES = 2 };
+
 struct AttnArgs {
     const uint16_t* q;        // bf16 [rows][Hq][hd]
     const uint16_t* pages;    // this layer's pages: [page][Hkv]{K[16][hd], V[hd][16]}
@@ -80,7 +84,7 @@ struct AttnArgs {
     int32_t units_per_wg, total_units;   // decode stream: (row, kv head, page) units per workgroup, and in all
     float scale_log2e;        // log2(e) / sqrt(hd)
     int32_t out_frag;         // decode: out in act_frag() order
-    int32_t direct;           // decode: a workgroup has one (row, kv head) pair and writes `out`, no partial results
+    int32_t form;             // decode: DecodeForm
 };
 
 // Launchers (defined in the kernel translation units).  All enqueue on `s` and return the launch status.

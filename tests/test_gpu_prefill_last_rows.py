@@ -81,3 +81,34 @@ def test_every_row_below_the_rule(rows, B):
     sess.prefill(np.arange(B, dtype=np.int32), new)
     assert sb.spiral_profile_end(sess.model)[1] == 2
     sess.close()
+
+
+@pytest.mark.parametrize("repack", [True, False])
+def test_a_sequence_does_not_depend_on_the_contexts_of_its_call(repack):
+    """Copies of a run at several places of a call, and the same run among other lengths and histories (the same sum of rows, from which
+    the projections' K splits follow): the last layer's attention is cut from the pair's own first page, so all get the same bits.  By
+    contexts of one piece of 16 pages (250 tokens) and of three (700)."""
+    from paper_2506_24119_amd import binding as sb
+    g = si.ModelGeometry("last", 2, 256, 4, 2, 128, 384, 512, 1e6, qk_norm=True)
+    w = sb.weights_to_device(si.make_weights(g, seed=63))
+    rng = np.random.Generator(np.random.PCG64(64))
+    probes = {n: rng.integers(0, g.vocab, n).astype(np.int32) for n in (250, 700)}
+    want = {}
+    # lengths of the runs of a call, and of the histories in front of them; all calls append 4,000 tokens
+    for lens, hist in (([250, 700, 333, 250, 700, 417, 650, 700], [0] * 8),
+                       ([700, 601, 250, 10, 700, 700, 38, 250, 700, 51], [0] * 10),
+                       ([1100, 250, 700, 700, 250, 1000], [500, 0, 0, 0, 0, 1400]), ([250] * 16, [0] * 16)):
+        assert sum(lens) == 4000
+        B = len(lens)
+        ids = rng.permutation(B).astype(np.int32)
+        old = [rng.integers(0, g.vocab, n).astype(np.int32) for n in hist]
+        new = [probes[n] if n in probes and not h else rng.integers(0, g.vocab, n).astype(np.int32) for n, h in zip(lens, hist)]
+        sess = sb.Session(g, w, 600, B, 152, 4000, 2500, page_order=si.make_page_order(600, B), repack=repack)
+        kept = [b for b in range(B) if hist[b]]
+        if kept:
+            sess.prefill(ids[kept], [old[b] for b in kept])
+        got = sess.prefill(ids, new).cpu().numpy()
+        sess.close()
+        for b in range(B):
+            if lens[b] in probes and not hist[b]:
+                assert np.array_equal(got[b], want.setdefault(lens[b], got[b])), (lens, b)
