@@ -151,3 +151,34 @@ def test_maxima_that_rise_by_less_and_by_more_than_the_rescale_threshold(gain):
     for b, s in enumerate(seqs):
         want = od.forward_full(g, w, s, logits_at=np.array([len(s) - 1]))[0]
         assert np.abs(got[b] - want).max() <= 3e-2 * want.std(), b
+
+
+@pytest.mark.parametrize("head_dim,dtype", [(32, si.WEIGHT_FP32), (128, si.WEIGHT_BF16), (64, si.WEIGHT_BF16)])
+@pytest.mark.parametrize("run,at,keep,more,tune", [
+    (200, 186, 30, 150, None), (300, 286, 100, 185, None), (300, 286, 100, 185, "trim=0"),
+    (60, 46, 40, 1, None), (300, 286, 280, 1, None), (300, 286, 280, 1, "chunk=16"), (300, 286, 285, 1, "wgs=768")])
+def test_a_nan_behind_the_last_token(head_dim, dtype, run, at, keep, more, tune):
+    """A run with a NaN token, cut back to before it and continued up to the same page, by a prefill whose last layer has one row and by a decode
+    step, in every form of their attention: pages are not cleared, and a weight of zero does not stop a NaN.  Bound as above."""
+    import torch
+    from paper_2506_24119_amd import binding as sb
+    assert at < run and keep <= at and keep + more <= at and (keep + more - 1) // 16 == at // 16
+    g = si.ModelGeometry("nan", 2, 128, 256 // head_dim, 2, head_dim, 128, 256, 1e4, tie_lm_head=False, weight_dtype=dtype)
+    w = si.make_weights(g, seed=17)
+    w["embed"][7] = 0x7FC0 if dtype == si.WEIGHT_BF16 else np.nan
+    wd = sb.weights_to_device(w)
+    rng = np.random.Generator(np.random.PCG64(run + more))
+    seq, new = rng.integers(8, g.vocab, run).astype(np.int32), rng.integers(8, g.vocab, more).astype(np.int32)
+    got = []
+    for tok in (7, 9):
+        seq[at] = tok
+        sess = sb.Session(g, wd, 24, 1, 24, 320, 320, page_order=si.make_page_order(24, 2), tune=tune)
+        sess.prefill([0], [seq])
+        sb.spiral_seq_truncate(sess.pool, [0], [keep])
+        if more > 1:
+            got.append(sess.prefill([0], [new]).cpu().numpy()[0])
+        else:
+            got.append(sess.decode_step(np.zeros(1, dtype=np.int32), torch.from_numpy(new).cuda(), sess.new_logits(1)).cpu().numpy()[0])
+        sess.close()
+    assert np.isfinite(got[0]).all()
+    assert np.abs(got[0] - got[1]).max() <= 1e-2 * got[1].std()
