@@ -271,6 +271,12 @@ bool gemm_decode_takes(int M, int N, int K, int epilogue, bool head) {
     return epilogue != EPI_SWIGLU || (N + 15) / 16 <= 768;
 }
 
+// Whether the down projection reads act_frag() order: whenever it comes here, as gate/up (d columns in, ffn out) writes that order from
+// either kernel.  In rows the 7B shape's down takes, at 32, 64 and 128 rows, 34, 45 and 64 us for 29, 30 and 37 on the streaming kernel.
+bool gemm_mlp_in_frag(int M, int d, int ffn) {
+    return gemm_decode_takes(M, d, ffn, EPI_STORE_F32, false) && (d & 127) == 0;
+}
+
 // K splits of a projection, by its shape alone: the least sum of rounds over the 256 compute units x k steps of a wave x operand blocks
 // of a step at 32 rows, and of the partial sums (in the same unit, 0.1 us, N / 640 each), over 1 to 3 weight tiles a workgroup.  Against
 // a sweep of 1 to 4 tiles x 1 to 16 splits on the q/k/v, O and down projections of three shapes at 3, 32, 64 and 128 rows the

@@ -257,7 +257,7 @@ __global__ __launch_bounds__(256) void gemm_stream_kernel(GemmArgs g) {
                     o.y = f32_to_act16_noting(silu_f(acc[t][4 * b + 1]) * u.y, bad);
                     o.z = f32_to_act16_noting(silu_f(acc[t][4 * b + 2]) * u.z, bad);
                     o.w = f32_to_act16_noting(silu_f(acc[t][4 * b + 3]) * u.w, bad);
-                    *(ushort4*)((uint16_t*)g.out + (size_t)m * g.N + f) = o;
+                    *(ushort4*)((uint16_t*)g.out + (g.out_frag ? act_frag(m, f, g.M, g.N) : (size_t)m * g.N + f)) = o;
                 }
             }
         }
@@ -371,7 +371,7 @@ __global__ __launch_bounds__(64 * NW) void swiglu_stream_kernel(GemmArgs g) {
                 o.y = f32_to_act16_noting(silu_f(acc[t][4 * b + 1]) * acc[t][4 * b + 9], bad);
                 o.z = f32_to_act16_noting(silu_f(acc[t][4 * b + 2]) * acc[t][4 * b + 10], bad);
                 o.w = f32_to_act16_noting(silu_f(acc[t][4 * b + 3]) * acc[t][4 * b + 11], bad);
-                *(ushort4*)((uint16_t*)g.out + (size_t)m * g.N + fo) = o;
+                *(ushort4*)((uint16_t*)g.out + (g.out_frag ? act_frag(m, fo, g.M, g.N) : (size_t)m * g.N + fo)) = o;
             }
         }
     }
@@ -446,6 +446,7 @@ int gemm_sample_tile_cols(int M, int bn) { return (M <= 32 || bn < 128) ? 64 : 1
 
 hipError_t launch_gemm_stream(const GemmArgs& a, int epilogue, int bn, hipStream_t s) {
     if ((a.K & 127) || (a.N & 15) || a.splits < 1 || a.splits > (a.K >> 7)) return hipErrorInvalidValue;
+    if (a.a_frag || (a.out_frag && (epilogue != EPI_SWIGLU || a.M > 128))) return hipErrorInvalidValue;
     if (epilogue == EPI_SWIGLU) {
         if (a.splits != 1) return hipErrorInvalidValue;
         if (bn != 64) {

@@ -156,6 +156,7 @@ float gemm_tile_qkv_us(int M, int N, int K);
 hipError_t launch_gemm_tile_qkv(const GemmArgs& a, const QkvPostArgs& qa, hipStream_t s);  // q/k/v projection + qkv_post in one kernel
 hipError_t launch_gemm_stream(const GemmArgs& a, int epilogue, int bn, hipStream_t s);   // K % 128 == 0, N % 16 == 0
 bool gemm_decode_takes(int M, int N, int K, int epilogue, bool head);                     // at most 128 rows, K % 128 == 0, N % 16 == 0
+bool gemm_mlp_in_frag(int M, int d, int ffn);                                            // gate/up hands its output on in act_frag() order
 int gemm_decode_splits(int N, int K, int most);                                          // K splits, whatever the rows
 int gemm_decode_tiles(int M, int N, int K, int epilogue, int splits);                    // 32-row weight tiles of a workgroup
 hipError_t launch_gemm_decode(const GemmArgs& a, int epilogue, int nt, hipStream_t s);

@@ -15,9 +15,11 @@ LOGIT_TOL = 3e-2          # the bar of every logit comparison: half-precision ac
 # vocabulary 2,512 are 26 and 78.5 tiles), and a wide one whose projections split K
 NARROW = si.ModelGeometry("narrow", 2, 128, 4, 1, 32, 384, 2512, 1e4, qkv_bias=True, tie_lm_head=False)
 WIDE = si.ModelGeometry("wide", 2, 640, 10, 2, 128, 1408, 2512, 1e6, qk_norm=True)
+# gate/up on the streaming kernel (776 tiles of 16 columns), which writes what the down projection reads
+FFN = si.ModelGeometry("ffn", 2, 128, 4, 2, 32, 12416, 512, 1e4)
 
 
-def _run(g, w, B, repack, ids=None, sample=False):
+def _run(g, w, B, repack, ids=None, sample=False, tune=None):
     import torch
     from paper_2506_24119_amd import binding as sb
     rng = np.random.Generator(np.random.PCG64(7))
@@ -26,7 +28,7 @@ def _run(g, w, B, repack, ids=None, sample=False):
     step = rng.integers(0, g.vocab, 128).astype(np.int32)
     ids = np.arange(B) if ids is None else np.array(ids)
     n = len(ids)
-    sess = sb.Session(g, w, 3 * n + 2, n, 3, 128, 40, page_order=si.make_page_order(3 * n + 2, 3), repack=repack)
+    sess = sb.Session(g, w, 3 * n + 2, n, 3, 128, 40, page_order=si.make_page_order(3 * n + 2, 3), repack=repack, tune=tune)
     seqs = np.arange(n, dtype=np.int32)
     for i in range(0, n, 6):                               # at most 6 x 19 rows: every projection of the prompts is a small one, too
         sess.prefill(seqs[i:i + 6], [prompts[b] for b in ids[i:i + 6]])
@@ -45,7 +47,7 @@ def _run(g, w, B, repack, ids=None, sample=False):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("g", [NARROW, WIDE], ids=["narrow", "wide"])
+@pytest.mark.parametrize("g", [NARROW, WIDE, FFN], ids=["narrow", "wide", "ffn"])
 @pytest.mark.parametrize("B", [1, 7, 31, 32, 33, 64, 65, 96, 97, 128])
 def test_rows_against_oracle_and_row_major(g, B):
     from paper_2506_24119_amd import binding as sb
@@ -69,6 +71,31 @@ def test_a_sequence_does_not_depend_on_the_rows_of_its_step():
     for ids in ([5], list(range(3, 33)), list(range(40)), list(range(30, 100))):
         got = _run(WIDE, w, None, True, ids=ids)[0]
         assert np.abs(got - full[ids]).max() <= 1e-5 * np.abs(full[ids]).max(), len(ids)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("tune", ["gu=64", "gu=96", "gu=160"])
+def test_every_form_of_a_wide_gate_up(tune):
+    """The streaming kernel's other workgroups hand the down projection the same bits."""
+    from paper_2506_24119_amd import binding as sb
+    w = sb.weights_to_device(si.make_weights(FFN, seed=73))
+    for B in (7, 64, 128):
+        for repack in (True, False):
+            assert np.array_equal(_run(FFN, w, B, repack, tune=tune)[0], _run(FFN, w, B, repack)[0]), B
+
+
+def test_gate_up_and_down_agree_on_the_order_between_them():
+    """Down projections that read rows where they could read the operands' order take up to 1.7 times as long."""
+    from paper_2506_24119_amd import binding
+    lib = binding.load_library()
+    frag, takes = lib._ZN6spiral16gemm_mlp_in_fragEiii, lib._ZN6spiral17gemm_decode_takesEiiiib
+    for f, args in ((frag, [ctypes.c_int] * 3), (takes, [ctypes.c_int] * 4 + [ctypes.c_bool])):
+        f.argtypes, f.restype = args, ctypes.c_bool
+    for d, ffn in ((1024, 3072), (2560, 9728), (3584, 18944)):
+        for M in (1, 32, 33, 128):
+            assert takes(M, d, ffn, 0, False) and frag(M, d, ffn)
+        assert not frag(129, d, ffn)
+    assert not frag(8, 1088, 2176) and not frag(8, 1024, 1088)          # gate/up, down on another kernel
 
 
 def test_which_projections_are_small():
