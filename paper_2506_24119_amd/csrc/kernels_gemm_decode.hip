@@ -262,17 +262,27 @@ static hipError_t launch_tiles(const GemmArgs& a, int nt, hipStream_t s) {
 }
 
 // Which projections launch_gemm_decode takes (A in act_frag() order or in rows).  All row counts up to 128 take the same kernel and
-// the same K splits, so that a sequence's sums do not follow from how many others are in the call.  Gate/up of more than 768 tiles
-// (three to a compute unit) stays on the streaming kernel: the 7B shape's 1,184 take 42.5 us on 1,184 workgroups of one tile
-// against 44.1 at 3 rows, but 46 to 50 against 44.4 to 44.8 from 27 rows on and 71 against 56 at 128.  The LM head does up to 32 rows
-// (above, 128 rows: 186 us against 180 on the 4B shape, 85 and 83 on the 0.6B); its sums are rounded by nothing that follows.
+// the same K splits, so that a sequence's sums do not follow from how many others are in the call; repacked and row-major weights too, so
+// that they give the same bits.  Row-major weights draw the lines for large projections, which is where they are slow here: a load has 32
+// bytes of each of 32 rows, the four waves share every line of 128 bytes, and the lines in flight leave the L1 before the last of them has come.
+// Gate/up of more than 512 tiles (two to a compute unit) stays on the streaming kernel.  Streaming kernel -> this, us between events at
+// 1, 32 and 128 rows, d 2,048: 512 tiles row-major 23.6 -> 23.7, 25.7 -> 23.6, 32.4 -> 30.8, repacked 17.1 -> 16.8, 18.9 -> 17.1,
+// 26.4 -> 24.1; 688 tiles row-major 24.7 -> 31.6, 25.7 -> 32.3, 34.0 -> 37.8, repacked 20.4 -> 20.6, 21.0 -> 20.5, 28.3 -> 28.6; the 4B
+// shape's 608 tiles row-major 31.8 -> 39.2, 34.8 -> 41.6, 41.7 -> 51.8, repacked 21.4 -> 21.9, 23.1 -> 22.3, 32.5 -> 33.9.
+// The others stay there from 64 MB of weights on: the 7B shape's down (136 MB) row-major 31.8 -> 47.4, 35.1 -> 49.8, 44.0 -> 58.0, repacked 27.0
+// -> 26.2, 28.8 -> 28, 37.0 -> 37; 2,560 x 12,288 (63 MB) row-major 19.8 -> 20.9, 21.0 -> 21.9, 26.4 -> 30.8, repacked 16.1 -> 14.9,
+// 18.6 -> 16.2, 23.4 -> 24.7.
+// The LM head does up to 32 rows (above, 128 rows: 186 us against 180 on the 4B shape, 85 and 83 on the 0.6B); its sums are rounded by
+// nothing that follows.  One layer and a row-major head, 1, 16 and 32 rows: 0.6B 119 -> 107, 129 -> 115, 136 -> 122; 4B 252 -> 229,
+// 267 -> 264, 283 -> 287; 7B 337 -> 333, 364 -> 370, 382 -> 402.
 bool gemm_decode_takes(int M, int N, int K, int epilogue, bool head) {
     if (M < 1 || M > (head ? 32 : 128) || (K & 127) || (N & 15)) return false;
-    return epilogue != EPI_SWIGLU || (N + 15) / 16 <= 768;
+    if (epilogue == EPI_SWIGLU) return (N + 15) / 16 <= 512;
+    return head || (long long)N * K <= 1 << 25;
 }
 
 // Whether the down projection reads act_frag() order: whenever it comes here, as gate/up (d columns in, ffn out) writes that order from
-// either kernel.  In rows the 7B shape's down takes, at 32, 64 and 128 rows, 34, 45 and 64 us for 29, 30 and 37 on the streaming kernel.
+// either kernel.  (In rows the 7B shape's down took, at 32, 64 and 128 rows, 34, 45 and 64 us for 29, 30 and 37 on the streaming kernel.)
 bool gemm_mlp_in_frag(int M, int d, int ffn) {
     return gemm_decode_takes(M, d, ffn, EPI_STORE_F32, false) && (d & 127) == 0;
 }

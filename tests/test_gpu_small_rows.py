@@ -15,7 +15,7 @@ LOGIT_TOL = 3e-2          # the bar of every logit comparison: half-precision ac
 # vocabulary 2,512 are 26 and 78.5 tiles), and a wide one whose projections split K
 NARROW = si.ModelGeometry("narrow", 2, 128, 4, 1, 32, 384, 2512, 1e4, qkv_bias=True, tie_lm_head=False)
 WIDE = si.ModelGeometry("wide", 2, 640, 10, 2, 128, 1408, 2512, 1e6, qk_norm=True)
-# gate/up on the streaming kernel (776 tiles of 16 columns), which writes what the down projection reads
+# gate/up on the streaming kernel (776 tiles of 16 columns; up to 512 do not go there), which writes what the down projection reads
 FFN = si.ModelGeometry("ffn", 2, 128, 4, 2, 32, 12416, 512, 1e4)
 
 
@@ -91,11 +91,11 @@ def test_gate_up_and_down_agree_on_the_order_between_them():
     frag, takes = lib._ZN6spiral16gemm_mlp_in_fragEiii, lib._ZN6spiral17gemm_decode_takesEiiiib
     for f, args in ((frag, [ctypes.c_int] * 3), (takes, [ctypes.c_int] * 4 + [ctypes.c_bool])):
         f.argtypes, f.restype = args, ctypes.c_bool
-    for d, ffn in ((1024, 3072), (2560, 9728), (3584, 18944)):
+    for d, ffn in ((1024, 3072), (2560, 9728), (2048, 11008)):
         for M in (1, 32, 33, 128):
             assert takes(M, d, ffn, 0, False) and frag(M, d, ffn)
         assert not frag(129, d, ffn)
-    assert not frag(8, 1088, 2176) and not frag(8, 1024, 1088)          # gate/up, down on another kernel
+    assert not frag(8, 1088, 2176) and not frag(8, 1024, 1088) and not frag(8, 3584, 18944)          # gate/up, down on another kernel
 
 
 def test_which_projections_are_small():
@@ -105,7 +105,9 @@ def test_which_projections_are_small():
     takes.restype = ctypes.c_bool
     assert takes(1, 16, 128, 0, False) and takes(128, 16, 128, 0, False) and not takes(129, 16, 128, 0, False) and not takes(0, 16, 128, 0, False)
     assert not takes(8, 24, 128, 0, False) and not takes(8, 32, 192, 0, False)
-    assert takes(128, 12288, 128, 1, False) and not takes(128, 12304, 128, 1, False)          # gate/up of at most three tiles a unit
+    # where row-major weights, which take the same kernel as repacked ones, are slow on it: gate/up of more than two tiles a unit, 64 MB
+    assert takes(128, 8192, 128, 1, False) and not takes(128, 8208, 128, 1, False) and not takes(1, 9728, 2560, 1, False)
+    assert takes(128, 8192, 4096, 0, False) and not takes(1, 8208, 4096, 0, False) and not takes(1, 3584, 18944, 0, False)
     assert takes(32, 151936, 1024, 0, True) and not takes(33, 151936, 1024, 0, True)
 
 
