@@ -127,7 +127,10 @@ __device__ __forceinline__ void prefill_row_alone(const AttnArgs& a, const int32
     const float inv = 1.0f / l_run;
 #pragma unroll
     for (int j = 0; j < DL; ++j)
-        if (lane + 64 * j < HD) ActStore<ACT32>::put(a.out, out_row * HD + lane + 64 * j, o[j] * inv);
+        if (lane + 64 * j < HD) {
+            const int r = (int)(out_row / a.n_q_heads), col = (int)(out_row % a.n_q_heads) * HD + lane + 64 * j;
+            ActStore<ACT32>::put(a.out, a.out_frag ? act_frag(r, col, a.n_rows, a.n_q_heads * HD) : out_row * HD + lane + 64 * j, o[j] * inv);
+        }
 }
 
 // Grid of the prefill kernel: x = position blocks of eight pairs, y = groups of eight (sequence, kv head, head group) pairs.
@@ -452,9 +455,11 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(AttnArgs a, Prefil
 #pragma unroll
         for (int ps = 0; ps < 32 * LPR / 64; ++ps) {
             const int row = ps * (64 / LPR) + lane / LPR;
-            if (active && row < n_valid)
-                *(u32x4*)((uint16_t*)a.out + ((size_t)(row0 + row) * a.n_q_heads + h) * HD + (lane % LPR) * 8) =
-                    *(const u32x4*)(rows_out + row * OROW + (lane % LPR) * 16);
+            if (active && row < n_valid) {
+                const size_t at = a.out_frag ? act_frag(row0 + row, h * HD + (lane % LPR) * 8, a.n_rows, a.n_q_heads * HD)
+                                             : ((size_t)(row0 + row) * a.n_q_heads + h) * HD + (lane % LPR) * 8;
+                *(u32x4*)((uint16_t*)a.out + at) = *(const u32x4*)(rows_out + row * OROW + (lane % LPR) * 16);
+            }
         }
     }
     // A weight of zero does not stop a NaN: one in the V of a token that a row does not see (up to 63 further on in the row's

@@ -758,11 +758,11 @@ static int run_layers(StepCtx& c) {
     const float* part = c.w.proj;       // the partials waiting to be added to the residual
     int pending = 0;            // projection partials waiting to be added to the residual
     int32_t* sat = c.p->d_status;
-    // At most 128 rows: activations go from kernel to kernel in the order of the projections' operands where both ends know it (the
-    // output of the prefill attention is in rows).  qkv_in_frag() is what the embedding kernel of the call went by.
+    // At most 128 rows: activations go from kernel to kernel in the order of the projections' operands where the reader is
+    // gemm_decode_kernel.  qkv_in_frag() is what the embedding kernel of the call went by.
     const int h_frag = qkv_in_frag(m, c.rows);
     const int h2_frag = !act32 && gemm_decode_takes(c.rows, cfg.ffn_dim, d, EPI_SWIGLU, false);
-    const int o_frag = c.decode && !act32 && gemm_decode_takes(c.rows, d, qw, EPI_STORE_F32, false);
+    const int o_frag = !act32 && gemm_decode_takes(c.rows, d, qw, EPI_STORE_F32, false);
     const int mlp_frag = !act32 && gemm_mlp_in_frag(c.rows, d, cfg.ffn_dim);
     const int hf_frag = !act32 && gemm_decode_takes(c.B, cfg.vocab, d, EPI_STORE_F32, true);
 
@@ -853,6 +853,7 @@ static int run_layers(StepCtx& c) {
             HIP_TRY(timed(m, SPIRAL_K_ATTN_DECODE, c.s, [&] { return launch_attn_stream(aa, hd, act32, c.s); }));
             if (c.form != DECODE_PAIR) HIP_TRY(timed(m, SPIRAL_K_ATTN_COMBINE, c.s, [&] { return launch_attn_stream_combine(aa, hd, act32, c.s); }));
         } else {
+            aa.out_frag = o_frag;
             HIP_TRY(timed(m, SPIRAL_K_ATTN_PREFILL, c.s, [&] { return launch_attn_prefill(aa, hd, c.B, c.max_new, act32, c.s); }));
         }
 

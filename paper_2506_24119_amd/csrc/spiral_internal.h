@@ -83,7 +83,7 @@ struct AttnArgs {
     int32_t n_rows, n_q_heads, n_kv_heads, max_blocks, chunk_pages, n_chunks;
     int32_t units_per_wg, total_units;   // decode stream: (row, kv head, page) units per workgroup, and in all
     float scale_log2e;        // log2(e) / sqrt(hd)
-    int32_t out_frag;         // decode: out in act_frag() order
+    int32_t out_frag;         // 16-bit out, at most 128 rows: in act_frag() order
     int32_t form;             // decode: DecodeForm
 };
 

@@ -121,3 +121,47 @@ def test_splits_are_those_of_the_shape():
     for n in (16, 48, 640, 6144):
         for k in (128, 256, 1408, 9728):
             assert 1 <= splits(n, k, 16) <= k // 128
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("rows", [31, 33, 97, 128])
+@pytest.mark.parametrize("repack", [True, False])
+def test_prefill_attention_writes_what_the_projection_reads(rows, repack):
+    """Prefills of at most 128 rows: the attention's output goes to O in the operands' order, at row counts that leave remainders of
+    a tile of 32, with runs that start inside a tile; against the oracle, and the same bits with either order of the weights."""
+    from paper_2506_24119_amd import binding as sb
+    host = si.make_weights(WIDE, seed=74)
+    w = sb.weights_to_device(host)
+    rng = np.random.Generator(np.random.PCG64(rows))
+    seqs = [rng.integers(0, WIDE.vocab, n).astype(np.int32) for n in (5, rows - 22, 17)]
+    sess = sb.Session(WIDE, w, 30, 3, 10, 128, 140, page_order=si.make_page_order(30, 3), repack=repack)
+    got = sess.prefill(np.arange(3, dtype=np.int32), seqs).cpu().numpy()
+    sess.close()
+    for b, s in enumerate(seqs):
+        want = od.forward_full(WIDE, host, s, logits_at=np.array([len(s) - 1]))[0]
+        assert np.abs(got[b] - want).max() <= LOGIT_TOL * want.std(), b
+
+
+@pytest.mark.gpu
+def test_output_projection_of_a_prefill_takes_as_long_as_that_of_a_step():
+    """The same projection of 128 rows on the 4B shape, in a prefill and in a decode step: 1.75 times as long when the prefill's
+    attention left its output in rows.  The shortest of 20 launches each, between events."""
+    import torch
+    from paper_2506_24119_amd import binding as sb
+    g = si.scaled_geometry("qwen3-4b", n_layers=1, vocab=512)
+    sess = sb.Session(g, si.make_weights_torch(g, 1, "cuda:0"), 2 * 128 + 8, 128, 2, 128, 32, page_order=si.make_page_order(264, 3))
+    ids = np.arange(128, dtype=np.int32)
+    tok = torch.zeros(128, dtype=torch.int32, device="cuda")
+    logits = sess.new_logits(128)
+    runs = {"prefill": lambda: sb.spiral_prefill(sess.model, sess.pool, ids, np.ones(128, dtype=np.int32), tok, sess.ws, logits),
+            "step": lambda: sess.decode_step(ids, tok, logits)}
+    best = {}
+    for name, run in runs.items():
+        for _ in range(20):
+            sb.spiral_seq_reset(sess.pool, ids)
+            runs["prefill"]()
+            sb.spiral_profile_begin(sess.model, sb.KERNEL_CLASSES.index("gemm_o"), 1)
+            run()
+            best[name] = min(best.get(name, 1e9), sb.spiral_profile_end(sess.model)[0])
+    sess.close()
+    assert best["prefill"] <= 1.35 * best["step"], best
