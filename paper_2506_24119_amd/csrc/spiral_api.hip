@@ -767,10 +767,11 @@ static int run_layers(StepCtx& c) {
     const int hf_frag = !act32 && gemm_decode_takes(c.B, cfg.vocab, d, EPI_STORE_F32, true);
 
     // fp32 weights, a few rows: the norms and the residual's sums are done by the projections.  Each wave norms the rows for itself,
-    // four at a time, so the rows and d must be few.  Four layers, us a step, separate kernels -> this: d 128, 1 row 135 -> 109, 8
-    // 148 -> 102, 32 146 -> 120; d 256, 16 rows 116 -> 111, 32 131 -> 132; d 512, 16 147 -> 151; d 1,024, 1 row 212 -> 179, 8
-    // 214 -> 208, 12 232 -> 239; d 2,048, 4 rows 354 -> 365.
-    const bool lean = act32 && c.decode && d <= 1024 && (c.rows <= 8 || (c.rows <= 32 && c.rows * d <= 4096)) && d % 4 == 0 &&
+    // four at a time, so the rows and d must be few.  Four layers, us a step, separate kernels -> this, contexts of 64 tokens: d 256, 16
+    // rows 116 -> 111, 32 131 -> 132; d 512, 1 row 126 -> 114, 4 127 -> 121, 8 132 -> 129, 16 147 -> 151; d 640, 4 137 -> 135, 8
+    // 146 -> 146; d 768, 1 136 -> 133, 4 142 -> 142, 8 153 -> 156; d 1,024, 1 154 -> 154, 4 158 -> 160, 8 176 -> 183.  Of 700: d 512, 8
+    // rows 150 -> 146; d 768, 1 154 -> 149, 4 158 -> 157, 8 169 -> 172; d 1,024, 1 170 -> 170, 4 175 -> 177, 8 192 -> 200.
+    const bool lean = act32 && c.decode && d <= 768 && c.rows <= 32 && c.rows * d <= 4096 && d % 4 == 0 &&
                       qw % 4 == 0 && cfg.ffn_dim % 4 == 0;
     if (lean) part_o = part_down = c.w.x;
 

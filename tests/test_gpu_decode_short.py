@@ -71,7 +71,7 @@ def test_a_pair_for_every_cu(shortest, longest, direct):
 
 
 @pytest.mark.parametrize("d,ffn,norm,B", [(128, 512, False, 1), (128, 512, False, 4), (128, 512, False, 5), (128, 512, False, 32), (128, 512, False, 33),
-                                          (132, 200, True, 8), (132, 200, True, 31), (132, 200, True, 32), (1024, 96, False, 8), (1024, 96, False, 9)])
+                                          (132, 200, True, 8), (132, 200, True, 31), (132, 200, True, 32), (512, 96, False, 8), (768, 96, False, 5), (1024, 96, False, 8), (1024, 96, False, 9)])
 def test_fp32_projections_that_norm(d, ffn, norm, B):
     """The last batch the rule takes and the first it leaves, remainders of four rows, widths that are and are not multiples of the 256 elements a
     wave reads at once.  Bar: q, k, v and the attention output round to half, 2^-11 each; all four in the same direction in two layers are 4e-3."""
@@ -87,3 +87,19 @@ def test_fp32_projections_that_norm(d, ffn, norm, B):
     for b, s in enumerate(seqs):
         want = od.forward_full(g, host, s, logits_at=np.array([len(s) - 1]))[0]
         assert np.abs(got[b] - want).max() <= 4e-3 * want.std(), b
+
+
+@pytest.mark.parametrize("d,B,norms", [(128, 32, False), (128, 33, True), (132, 31, False), (132, 32, True), (512, 8, False), (512, 9, True), (768, 1, False),
+                                       (768, 5, False), (768, 6, True), (772, 1, True), (1024, 1, True), (1024, 8, True)])
+def test_which_fp32_steps_keep_their_norms(d, B, norms):
+    """By the launches of a step: wider models and more rows are slower without them (d 1,024, 8 rows 176 -> 183 us, d 768 153 -> 156)."""
+    import torch
+    from paper_2506_24119_amd import binding as sb
+    g = si.ModelGeometry("lean", 2, d, 4, 2, 32, 96, 260, 1e4, weight_dtype=si.WEIGHT_FP32)
+    ids = np.arange(B, dtype=np.int32)
+    sess = sb.Session(g, sb.weights_to_device(si.make_weights(g, seed=82)), B, B, 1, B, 16)
+    sess.prefill(ids, [np.zeros(1, dtype=np.int32)] * B)
+    sb.spiral_profile_begin(sess.model, sb.KERNEL_CLASSES.index("norm"), 16)
+    sess.decode_step(ids, torch.zeros(B, dtype=torch.int32, device="cuda"), sess.new_logits(B))
+    assert (sb.spiral_profile_end(sess.model)[1] > 0) == norms
+    sess.close()
