@@ -618,12 +618,16 @@ static void plan_decode_attention(StepCtx& c, int pages_all, int max_ctx) {
     // 200..1,000 216 -> 207; 128 rows of 250 315 -> 294, of 200..1,000 431 -> 435; 4B, 3 rows of 250 265 -> 251, 8 (64 pairs) of 400
     // 272 -> 265, of 800 282 -> 283; 128 of 100..400 532 -> 509; 7B, 27 of 400 486 -> 468.  So up to 256 tokens always, up to 512
     // once a quarter of the CUs has a pair.  Up to 1,536 once every CU has one and the mean is at least half of
-    // the longest: 0.6B, 32 rows of 300..1,500 245 -> 236, 128 of 250..1,250 476 -> 481, of 300..1,500 528 -> 525; 4B, 64 of 200..900
-    // 430 -> 411, 128 of 300..1,500 745 -> 735, of 1,200..1,500 893 -> 868; 7B, 128 of 300..1,500 891 -> 871.  Beyond: 4B, 128 rows of
-    // 400..2,000 859 -> 866, of 1,024..5,120 1471 -> 1510.
+    // the longest: 0.6B, 32 rows of 300..1,480 236 -> 230, 64 323 -> 315, 192 763 -> 758; 4B, 64 rows 470 -> 456, 128 743 -> 735 (of
+    // 1,200..1,480 879 -> 865); 7B, 128 788 -> 768.  Beyond: 4B, 128 rows of 400..2,000 859 -> 866, of 1,024..5,120 1471 -> 1510.
+    // Only up to 1,024 where the pairs are just above two to a CU (7B, 144 rows of 300..1,480 1017 -> 1038; 0.6B, 80 of 256..1,250
+    // 354 -> 364; of 200..1,000 965 -> 967 and 331 -> 333), and with fewer than four query heads a pair, whose partial results are
+    // small, up to six (0.6B, 112 rows of 300..1,480 475 -> 485, 128 525 -> 529, 160 644 -> 652; 4B 685 -> 685, 743 -> 735, 919 -> 911).
     const int pairs = c.rows * m->cfg.n_kv_heads, longest = (max_ctx + kPageTokens - 1) / kPageTokens;
     const bool even = (long)longest * pairs <= 2L * c.total_units;
-    if (!m->tune.chunk_set && !m->tune.attn_wgs && longest <= (pairs >= m->n_cus && even ? 96 : 4 * pairs >= m->n_cus ? 32 : 16)) {
+    const int cus = m->n_cus, group = m->cfg.n_q_heads / m->cfg.n_kv_heads;
+    const bool uneven_rounds = pairs > 2 * cus && (2 * pairs < 5 * cus || (group < 4 && pairs < 6 * cus));
+    if (!m->tune.chunk_set && !m->tune.attn_wgs && longest <= (pairs >= cus && even ? (uneven_rounds ? 64 : 96) : 4 * pairs >= cus ? 32 : 16)) {
         c.form = DECODE_PAIR;
         return;
     }
