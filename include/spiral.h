@@ -116,12 +116,17 @@ int spiral_model_repack(spiral_model* m, void* dev_buffer, size_t bytes, void* s
 /* Measurement / test hook: overrides the launch decomposition the library would choose from the geometry.
  * spec is a comma-separated list of key=value items (unknown keys are ignored): "qkv=R:S", "o=R:S", "down=R:S"
  * (weight rows per workgroup : K splits of that projection; above 128 rows as many splits as the workspace holds,
- * one where S is not given), "gu=R", "lm=R", "chunk=P" (least pages per
- * decode-attention workgroup), "wgs=N" (workgroups of the decode attention), "frag=0|1" (use the repacked weights),
+ * one where S is not given), "gu=R", "lm=R" (from 33 sequences on), "chunk=P" (least pages per decode-attention workgroup, from 16 on
+ * also of a prefill's last rows), "wgs=N" (workgroups of the decode attention; with either of the two set, no (row, kv head) pair gets
+ * a workgroup to itself), "frag=0|1" (use the repacked weights),
  * "fuse_qkv=0|1" (large row counts: q/k/v post-processing inside the projection kernel or as its own kernel),
- * "trim=0|1" (prefill above 128 rows: the last layer's queries, attention, O and MLP for the last token of each sequence only),
+ * "trim=0|1" (prefill above 128 rows and from four rows to a sequence on, 16-bit weights, d_model, Hq*hd and ffn_dim multiples of
+ * 128, "o" and "down" not set: the last layer's queries, attention, O and MLP for the last token of each sequence only),
  * "fail_after=N" (error-path tests: the N-th
- * kernel launch of the layer stack from now on is not made and reports a launch failure).  Results stay within
+ * kernel launch of the layer stack from now on is not made and reports a launch failure).  R is taken to what the kernel of the call
+ * has: calls of at most 128 rows 32, 64 or 96 (more: 96); large projections of such calls (gate/up of more than 8,192 columns,
+ * others of more than 64 MB, the LM head from 33 sequences on) 64 or 128, gate/up also 96 and 160; calls of more rows use it only where
+ * they stream.  Results stay within
  * the parity tolerance for every setting; the defaults are the measured best.  "frag" must be set before
  * spiral_model_repack, the others at any time between calls.  Errors: NOT_LOADED, INVALID_ARG. */
 int spiral_model_tune(spiral_model* m, const char* spec);
@@ -171,10 +176,17 @@ int    spiral_kv_free_pages(const spiral_kv_pool* p);
  * dev_tokens_packed: int32 [sum(host_lens)], the sequences' tokens back to back, ids in [0, vocab).
  * dev_logits: fp32 [B, vocab].  dev_ws/ws_bytes: workspace of at least
  * spiral_workspace_bytes(m, sum(host_lens), longest resulting context), 256-byte aligned.
- * Repeating a call repeats its bits.  A sequence's bits are not independent of the rest of its call: above 128 rows the
- * K splits of the projections, and so the order of their fp32 sums, follow from sum(host_lens) (in a decode step the cut of
- * the attention follows from all contexts); logits differ by the rounding of half-precision activations then (0.5e-3 of
- * their standard deviation at most over one layer of a 1024-wide model, 2.2e-3 over four).
+ * Repeating a call repeats its bits.  A sequence's bits are not independent of the rest of its call, but only the sum of
+ * host_lens and B matter, not the other sequences' lengths, contexts or places:
+ *  - above 128 rows the K splits of the projections, and so the order of their fp32 sums, follow from the number of rows;
+ *  - above 128 rows and from four rows to a sequence on (16-bit weights, projections not tuned, see "trim" above) the last layer
+ *    computes its queries, attention, O and MLP for the sequences' last tokens only, on the decode step's kernels;
+ *  - the LM head adds in another order from 33 sequences on.
+ * In a decode step the cut of the attention follows from all contexts of the call; the rules on K splits and on the LM head hold
+ * there as well; 32-bit weights have a form for few sequences (up to 32, fewer where d_model is large).
+ * Logits then differ by the rounding of half-precision activations.  Largest difference seen, in standard deviations of the
+ * logits, after one, two and four layers of a 1024-wide model: 0.7e-3, 1.4e-3 and 2.6e-3 where only the K splits differ, 2.7e-3,
+ * 1.4e-3 and 1.1e-3 where only the last layer does.
  * Errors: INVALID_ARG, OOM_KV (pages, block-table slots or workspace too small), HIP. */
 int spiral_prefill(spiral_model* m, spiral_kv_pool* p, const int32_t* host_seq_ids,
                    const int32_t* host_lens, int B, const int32_t* dev_tokens_packed,
@@ -192,8 +204,8 @@ int spiral_decode_step(spiral_model* m, spiral_kv_pool* p, const int32_t* host_s
 
 /* One decode step fused with the actor's sampler: as spiral_decode_step followed by spiral_sample with generated
  * noise (seed, seq_id = host_seq_ids[i], step = host_steps[i]), bit for bit the same tokens, but the [B, vocab]
- * logits are never written: the LM head keeps the best score of every 128-column tile per row and a small
- * kernel picks the winner.  temperature == 0 is greedy decoding (host_steps may be NULL).  dev_out_tokens:
+ * logits are never written: the LM head keeps the best score of every tile of 64 or 128 columns per row and a
+ * small kernel picks the winner.  temperature == 0 is greedy decoding (host_steps may be NULL).  dev_out_tokens:
  * int32 [B]; it may be the same buffer as dev_in_tokens (free-running generation feeds the samples back).
  * Needs 16-bit weights repacked by spiral_model_repack, d_model % 128 == 0 and vocab % 16 == 0 (SHAPE error
  * otherwise; use the two separate calls then).  Workspace and other errors as spiral_decode_step. */
@@ -292,8 +304,8 @@ int spiral_sample_truncated_ws(const float* dev_logits, int B, int V, float temp
  * ones run untimed).  Errors: INVALID_ARG (unknown class, max_launches < 1, begin while active,
  * end while inactive), HIP. */
 enum spiral_kernel_class {
-    SPIRAL_K_ATTN_DECODE = 0,   /* paged decode attention (without the merge of its partial results) */
-    SPIRAL_K_ATTN_COMBINE,      /* merge of the partial results */
+    SPIRAL_K_ATTN_DECODE = 0,   /* paged decode attention, also of a prefill's last rows (without the merge of its partial results) */
+    SPIRAL_K_ATTN_COMBINE,      /* merge of the partial results, where there are any */
     SPIRAL_K_ATTN_PREFILL,
     SPIRAL_K_GEMM_QKV, SPIRAL_K_GEMM_O, SPIRAL_K_GEMM_GATE_UP, SPIRAL_K_GEMM_DOWN, SPIRAL_K_GEMM_LM_HEAD,
     SPIRAL_K_NORM,              /* embedding / residual-add + RMSNorm kernels */

@@ -165,3 +165,17 @@ def test_output_projection_of_a_prefill_takes_as_long_as_that_of_a_step():
             best[name] = min(best.get(name, 1e9), sb.spiral_profile_end(sess.model)[0])
     sess.close()
     assert best["prefill"] <= 1.35 * best["step"], best
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("key", ["qkv", "o", "down"])
+def test_tuned_rows_and_splits_of_small_calls(key):
+    """spiral_model_tune "key=R:S" up to 128 rows: any R gives the same bits, one and three K splits add in different orders."""
+    from paper_2506_24119_amd import binding as sb
+    w = sb.weights_to_device(si.make_weights(WIDE, seed=75))
+    for B in (5, 100):
+        one = _run(WIDE, w, B, True, tune=f"{key}=32:1")[0]
+        for R in (16, 64, 96, 128, 160):
+            assert np.array_equal(one, _run(WIDE, w, B, True, tune=f"{key}={R}:1")[0]), (B, R)
+        three = _run(WIDE, w, B, True, tune=f"{key}=64:3")[0]
+        assert not np.array_equal(one, three) and np.abs(one - three).max() <= 1e-2 * one.std(), B
