@@ -13,7 +13,9 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("q_heads,kv_heads,head_dim,dtype", [
     (2, 2, 128, si.WEIGHT_BF16), (4, 2, 128, si.WEIGHT_BF16), (6, 2, 64, si.WEIGHT_BF16), (5, 1, 128, si.WEIGHT_BF16),
     (7, 1, 64, si.WEIGHT_BF16), (16, 1, 32, si.WEIGHT_BF16), (9, 3, 32, si.WEIGHT_FP32)])
-def test_ragged_runs_and_histories(q_heads, kv_heads, head_dim, dtype):
+@pytest.mark.parametrize("tune", [None, "trim=0"])
+def test_ragged_runs_and_histories(q_heads, kv_heads, head_dim, dtype, tune):
+    """"trim=0": the last layer's attention goes through the prefill kernel, too, and its output for the last rows to the logits."""
     import torch
     from paper_2506_24119_amd import binding as sb
     g = si.ModelGeometry("attn-edges", 2, 128, q_heads, kv_heads, head_dim, 128, 256, 1e4, qk_norm=head_dim == 128,
@@ -24,7 +26,7 @@ def test_ragged_runs_and_histories(q_heads, kv_heads, head_dim, dtype):
     second = [1, 33, 31, 65, 1, 64, 97, 140]
     seqs = [rng.integers(0, g.vocab, a + b).astype(np.int32) for a, b in zip(first, second)]
     ids = np.arange(len(seqs), dtype=np.int32)
-    sess = sb.Session(g, sb.weights_to_device(w), 160, len(seqs), 24, 1024, 400, page_order=si.make_page_order(160, 2))
+    sess = sb.Session(g, sb.weights_to_device(w), 160, len(seqs), 24, 1024, 400, page_order=si.make_page_order(160, 2), tune=tune)
     got = [sess.prefill(ids, [s[:a] for s, a in zip(seqs, first)]).cpu().numpy()]
     got.append(sess.prefill(ids, [s[a:] for s, a in zip(seqs, first)]).cpu().numpy())
     torch.cuda.synchronize()

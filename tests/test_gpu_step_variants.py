@@ -14,9 +14,9 @@ LOGIT_TOL = 3e-2
 MARGIN = 0.1
 
 G_FUSED = {
-    # 4 query heads per kv head, per-head q/k norm; vocabulary of 16 full 128-column tiles
+    # 4 query heads per kv head, per-head q/k norm; vocabulary of full tiles (64 columns up to 32 rows, 128 above)
     "g4": si.ModelGeometry("g4-qknorm", 2, 256, 8, 2, 128, 640, 2048, 1e6, qk_norm=True),
-    # a vocabulary whose last tile holds 16 of 128 columns, untied head, QKV bias
+    # a vocabulary whose last tile holds 16 of its columns, untied head, QKV bias
     "g2-ragged-vocab": si.ModelGeometry("g2-ragged-vocab", 2, 128, 4, 2, 64, 384, 5008, 1e4, qkv_bias=True, tie_lm_head=False),
 }
 

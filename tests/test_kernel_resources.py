@@ -60,3 +60,12 @@ def test_tiled_projections_keep_their_accumulators_in_registers(tmp_path):
     assert len(tile) == 7, sorted(tile)
     for name, (vgprs, spills) in tile.items():
         assert vgprs <= 512 and spills <= (1 if "ILi3ELi256E" in name else 0), (name, vgprs, spills)
+
+
+def test_projections_of_few_rows_keep_to_the_waves_they_are_built_for(tmp_path):
+    """gemm_decode_kernel is built for one or two waves per SIMD (its last parameter): 512 or 256 registers, nothing spilled."""
+    decode = {k: v for k, v in _resources(tmp_path, "kernels_gemm_decode.hip").items() if "gemm_decode_kernel" in k}
+    assert len(decode) == 49, sorted(decode)                    # 4 row tiles x 3 weight tiles x 2 epilogues x 2 weight orders, and the sampler's
+    for name, (vgprs, spills) in decode.items():
+        waves = int(re.search(r"Li(\d+)EEEvNS", name).group(1))
+        assert vgprs <= 512 // waves and spills == 0, (name, vgprs, spills)
