@@ -620,14 +620,19 @@ static void plan_decode_attention(StepCtx& c, int pages_all, int max_ctx) {
     // once a quarter of the CUs has a pair.  Up to 1,536 once every CU has one and the mean is at least half of
     // the longest: 0.6B, 32 rows of 300..1,480 236 -> 230, 64 323 -> 315, 192 763 -> 758; 4B, 64 rows 470 -> 456, 128 743 -> 735 (of
     // 1,200..1,480 879 -> 865); 7B, 128 788 -> 768.  Beyond: 4B, 128 rows of 400..2,000 859 -> 866, of 1,024..5,120 1471 -> 1510.
-    // Only up to 1,024 where the pairs are just above two to a CU (7B, 144 rows of 300..1,480 1017 -> 1038; 0.6B, 80 of 256..1,250
-    // 354 -> 364; of 200..1,000 965 -> 967 and 331 -> 333), and with fewer than four query heads a pair, whose partial results are
-    // small, up to six (0.6B, 112 rows of 300..1,480 475 -> 485, 128 525 -> 529, 160 644 -> 652; 4B 685 -> 685, 743 -> 735, 919 -> 911).
+    // Only up to 1,024 where the pairs are just above two to a CU, whose third round is nearly empty, and with fewer than four query heads
+    // a pair, whose partial results are small, up to six to a CU.  Step to step of five random batches, rows of 256..1,024 / 512..1,280 /
+    // 736..1,504 tokens: 4B 68 rows (544 pairs) 1.005 / 1.018 / 1.027, 80 0.983 / 0.993 / 0.997, 128 0.977 / 0.985 / 0.989; 7B 144 (576)
+    // 0.995 / 1.002 / 1.006, 176 0.983 / 0.982 / 0.983; 0.6B 72 (576) 1.021 / 1.036 / 1.045, 80 1.001 / 1.012 / 1.018, 112 0.998 / 1.007
+    // / 1.021, 128 0.996 / 1.018 / 1.016, 160 0.991 / 0.996 / 0.999, 184 0.981 / 0.985 / 0.988.  (One batch may be a percent off the mean of
+    // its kind: which pairs share a CU follows from the rows' order.)
     const int pairs = c.rows * m->cfg.n_kv_heads, longest = (max_ctx + kPageTokens - 1) / kPageTokens;
     const bool even = (long)longest * pairs <= 2L * c.total_units;
     const int cus = m->n_cus, group = m->cfg.n_q_heads / m->cfg.n_kv_heads;
-    const bool uneven_rounds = pairs > 2 * cus && (2 * pairs < 5 * cus || (group < 4 && pairs < 6 * cus));
-    if (!m->tune.chunk_set && !m->tune.attn_wgs && longest <= (pairs >= cus && even ? (uneven_rounds ? 64 : 96) : 4 * pairs >= cus ? 32 : 16)) {
+    int most = pairs >= cus && even ? 96 : 4 * pairs >= cus ? 32 : 16;
+    if (pairs > 2 * cus && 2 * pairs < 5 * cus) most = std::min(most, group < 4 ? 32 : 64);
+    else if (pairs > 2 * cus && pairs < 6 * cus && group < 4) most = std::min(most, 64);
+    if (!m->tune.chunk_set && !m->tune.attn_wgs && longest <= most) {
         c.form = DECODE_PAIR;
         return;
     }

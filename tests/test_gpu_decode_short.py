@@ -71,12 +71,13 @@ def test_a_pair_for_every_cu(shortest, longest, direct):
 
 
 @pytest.mark.parametrize("q_heads,kv_heads,rows,longest,direct", [
-    (8, 8, 64, 1100, True), (8, 8, 65, 1023, True), (8, 8, 65, 1024, False), (24, 8, 128, 1100, False), (32, 8, 81, 1100, True), (32, 8, 79, 1100, False),
+    (8, 8, 64, 1100, True), (8, 8, 65, 511, True), (8, 8, 65, 512, False), (24, 8, 128, 1023, True), (32, 8, 65, 1024, False), (32, 8, 65, 1023, True), (24, 8, 128, 1100, False), (32, 8, 81, 1100, True), (32, 8, 79, 1100, False),
     (8, 8, 192, 1100, True)])
 def test_a_pair_to_a_workgroup_in_rounds(q_heads, kv_heads, rows, longest, direct):
-    """Pairs of a little more than two to a CU, and of up to six where a pair has fewer than four query heads: 1,024 tokens; else 1,536."""
+    """Pairs of a little more than two to a CU 1,024 tokens (512 with fewer than four query heads a pair), with fewer than four query heads up
+    to six to a CU 1,024; else 1,536."""
     g = si.ModelGeometry("short", 1, 128, q_heads, kv_heads, 32, 128, 256, 1e4)
-    lens = [700 + (29 * b) % 300 for b in range(rows - 1)] + [longest]
+    lens = [longest - 300 + (29 * b) % 300 for b in range(rows - 1)] + [longest]
     _compare(g, si.make_weights(g, seed=86), lens, direct, (0, rows - 1))
 
 
