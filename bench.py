@@ -114,11 +114,18 @@ def algorithmic_bytes(g, lens_after_append, B, fused):
 def prefill_report(g, prompts, seconds, score):
     """Throughput of a packed causal forward over the prompts against the MFMA peak.  flops = 2 x matmul
     parameters per token (+ the LM head on every row when scoring, on one row per sequence otherwise)
-    + 4 x hd x Hq per (token, visible token, layer) of attention."""
+    + 4 x hd x Hq per (token, visible token, layer) of attention.  Work that is left out is not counted: the last layer of
+    a prefill above 128 rows and from four rows to a sequence on (16-bit weights) has k and v of every token and
+    the rest of one token a sequence."""
     lens = np.array([len(p) for p in prompts], dtype=np.float64)
     tokens = float(lens.sum())
-    flops = 2.0 * g.n_layers * g.params_per_layer() * tokens
-    flops += 4.0 * g.head_dim * g.n_q_heads * g.n_layers * float((lens * (lens + 1) / 2).sum())
+    trimmed = not score and g.weight_dtype == 1 and tokens > 128 and tokens >= 4 * len(prompts)
+    whole = g.n_layers - (1 if trimmed else 0)
+    flops = 2.0 * whole * g.params_per_layer() * tokens
+    flops += 4.0 * g.head_dim * g.n_q_heads * whole * float((lens * (lens + 1) / 2).sum())
+    if trimmed:
+        kv = 2 * g.d_model * g.n_kv_heads * g.head_dim
+        flops += 2.0 * (kv * tokens + (g.params_per_layer() - kv) * len(prompts)) + 4.0 * g.head_dim * g.n_q_heads * tokens
     flops += 2.0 * g.vocab * g.d_model * (tokens if score else len(prompts))
     return {"tokens": int(tokens), "seconds": seconds, "tokens_per_s": tokens / seconds, "tflops": flops / seconds / 1e12,
             "frac_of_mfma_peak": flops / seconds / 1e12 / MFMA_PEAK_TFLOPS}
@@ -343,7 +350,7 @@ def main():
     log(f"[bench] streaming read of {probe_bytes / 1e6:.0f} MB: {stream_gbps:.0f} GB/s")
 
     # ---- dominant kernel: replay the window with HIP events around every decode-attention launch
-    roofline = {"bound": "hbm", "kernel": "attn_stream_kernel (paged decode attention, balanced page stream)", "achieved": None,
+    roofline = {"bound": "hbm", "kernel": "attn_stream_kernel (paged decode attention)", "achieved": None,
                 "peak": HBM_PEAK_GBPS, "unit": "GB/s", "frac": None, "traffic": None}
     if not args.no_kernel_timing:
         rewind()
@@ -353,12 +360,20 @@ def main():
         run_steps(sess, ids, logits, tokens, 1 + P, K, wl.temperature, seed, fused)
         ms, n = sb.spiral_profile_end(sess.model)
         assert n == K * g.n_layers, (n, K * g.n_layers)
+        rewind()                                       # its form: only the balanced stream has partial results to merge
+        sb.spiral_profile_begin(sess.model, sb.KERNEL_CLASSES.index("attn_combine"), g.n_layers)
+        run_steps(sess, ids, logits, tokens, 1 + P - W, 1, wl.temperature, seed, fused)
+        form = "stream" if sb.spiral_profile_end(sess.model)[1] else "pair"
         achieved = attn_bytes / (ms * 1e-3) / 1e9
+        roofline["kernel"] = "attn_stream_kernel (paged decode attention, %s at the start of the window)" % (
+            "balanced page stream" if form == "stream" else "a workgroup to a (row, kv head) pair")
         roofline.update({"achieved": achieved, "frac": achieved / HBM_PEAK_GBPS, "avg_launch_us": 1e3 * ms / n, "launches": n,
                          "algorithmic_bytes_per_launch": attn_bytes / n,
                          "frac_of_measured_stream": achieved / stream_gbps})
         try:
             tj = json.load(open(TRAFFIC_JSON))
+            if tj["form"] != form:
+                raise ValueError(f"counted for the form '{tj['form']}', this run has '{form}'")
             roofline["traffic"] = tj["hbm_bytes_over_algorithmic_bytes"] * attn_bytes / n
             roofline["traffic_source"] = {k: tj[k] for k in ("hbm_bytes_over_algorithmic_bytes", "measured_at_commit", "method", "file")}
         except (OSError, KeyError, ValueError) as e:

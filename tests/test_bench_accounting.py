@@ -43,3 +43,18 @@ def test_more_than_one_gpu_is_refused():
     r = subprocess.run([sys.executable, os.path.join(ROOT, "bench.py"), "--gpus", "2"], stdout=subprocess.PIPE,
                        stderr=subprocess.STDOUT, text=True, timeout=300)
     assert r.returncode != 0 and "single-GPU" in r.stdout
+
+
+def test_prefill_flops_leave_out_what_the_last_layer_does():
+    """Two prompts of 100 and 156 tokens: 35 layers over 256 tokens; in the last, k and v of all and the rest of two."""
+    g = si.WORKLOADS["C3"].geometry
+    prompts = [np.zeros(100, dtype=np.int32), np.zeros(156, dtype=np.int32)]
+    kv, rest = 2560 * 2 * 8 * 128, 2560 * 32 * 128 + 2560 * 4096 + 3 * 2560 * 9728
+    assert kv + rest == g.params_per_layer()
+    want = 2.0 * 35 * g.params_per_layer() * 256 + 2.0 * (kv * 256 + rest * 2) + 2.0 * 151936 * 2560 * 2
+    want += 4.0 * 128 * 32 * (35 * (100 * 101 / 2 + 156 * 157 / 2) + 256)
+    rep = bench.prefill_report(g, prompts, seconds=2.0, score=False)
+    assert abs(rep["tflops"] * 2.0e12 - want) < 1e-6 * want
+    scored = bench.prefill_report(g, prompts, seconds=2.0, score=True)           # a scoring pass computes every row
+    full = 2.0 * 36 * g.params_per_layer() * 256 + 4.0 * 128 * 32 * 36 * (100 * 101 / 2 + 156 * 157 / 2) + 2.0 * 151936 * 2560 * 256
+    assert abs(scored["tflops"] * 2.0e12 - full) < 1e-6 * full
