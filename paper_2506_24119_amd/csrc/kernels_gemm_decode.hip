@@ -14,12 +14,13 @@
 // half-used lines (128 rows, gate/up of the 4B shape 52 us against 27).
 // Loads past a wave's last k step and of weight tiles past the last one carry an offset beyond the buffer's size: the memory
 // pipeline drops them, and no branch stands between the loads.
-// One launch, us, gemm_stream_kernel / this, at 3, 32 and 128 rows (4B and 7B shapes at 128: bound by power):
+// One launch by itself, us, gemm_stream_kernel / this, at 3, 32 and 128 rows (4B and 7B shapes at 128: bound by power; inside a step,
+// between events, q/k/v, O and down of the 4B shape at 128 rows 15.7 / 16.8, 13.5 / 13.7 and 20.4 / 21.6, which fewer partial sums make up for):
 //   0.6B  q/k/v 4.3 / 4.1, 4.8 / 4.5, 7.7 / 6.2; O 4.0 / 3.2, 4.5 / 3.5, 6.9 / 4.8; gate/up 7.2 / 5.3, 7.7 / 5.9, 13.4 / 8.5;
 //         down 4.2 / 3.5, 4.7 / 4.0, 7.3 / 5.7; LM head 59 / 48, 71 / 56 (5.5 to 6.4 TB/s)
-//   4B    q/k/v 8.5 / 7.1, 9.8 / 7.8, 12.7 / 12.1; O 5.7 / 5.5, 6.4 / 6.1, 10.0 / 9.4; gate/up 17.9 / 18.5, 19.1 / 18.1, 31.6 / 27.1;
+//   4B    q/k/v 8.5 / 7.1, 9.8 / 7.8, 12.7 / 12.1; O 5.7 / 5.5, 6.4 / 6.1, 10.0 / 9.4;
 //         down 9.8 / 9.8, 10.6 / 10.6, 17.0 / 16.1; LM head 124 / 116, 149 / 141
-//   7B    q/k/v 8.5 / 7.5, 9.6 / 8.4, 12.8 / 12.8; O 7.3 / 6.3, 8.4 / 7.1, 12.2 / 10.8; down 23.3 / 22.2, 24.1 / 23.8, 32.8 / 33.1
+//   7B    q/k/v 8.5 / 7.5, 9.6 / 8.4, 12.8 / 12.8; O 7.3 / 6.3, 8.4 / 7.1, 12.2 / 10.8
 #include <algorithm>
 
 #include "spiral_internal.h"
