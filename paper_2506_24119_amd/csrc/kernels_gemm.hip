@@ -200,9 +200,8 @@ __global__ __launch_bounds__(256) void gemm_mfma_kernel(GemmArgs g) {
 // 3 to 4, a decode step of the two-layer model 237 -> 83.
 // ---------------------------------------------------------------------------------------------
 // NORM: the rows of A are residual rows, whose RMSNorm each wave does by itself: the sum of squares beside the products, the factor
-// on the sums.  ADD: the product goes onto the residual.  Both save a launch each time in a decode step, which is nothing
-// but launches: two layers, four rows 148 -> 120 us with the attention's merge gone too (4 + 1 launches of 3 us a layer
-// less, and the last norm).
+// on the sums.  ADD: the product goes onto the residual.  Both save launches of 3 us in a decode step of few rows, which is nothing but
+// launches (the host's rule says where): two layers, four rows 148 -> 120 us with the attention's merge gone too.
 template <int EPI, bool VEC, bool NORM = false, bool ADD = false>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs g) {
     constexpr int R = 4;

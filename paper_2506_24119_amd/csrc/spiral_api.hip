@@ -775,13 +775,17 @@ static int run_layers(StepCtx& c) {
     const int mlp_frag = !act32 && gemm_mlp_in_frag(c.rows, d, cfg.ffn_dim);
     const int hf_frag = !act32 && gemm_decode_takes(c.B, cfg.vocab, d, EPI_STORE_F32, true);
 
-    // fp32 weights, a few rows: the norms and the residual's sums are done by the projections.  Each wave norms the rows for itself,
-    // four at a time, so the rows and d must be few.  Four layers, us a step, separate kernels -> this, contexts of 64 tokens: d 256, 16
-    // rows 116 -> 111, 32 131 -> 132; d 512, 1 row 126 -> 114, 4 127 -> 121, 8 132 -> 129, 16 147 -> 151; d 640, 4 137 -> 135, 8
-    // 146 -> 146; d 768, 1 136 -> 133, 4 142 -> 142, 8 153 -> 156; d 1,024, 1 154 -> 154, 4 158 -> 160, 8 176 -> 183.  Of 700: d 512, 8
-    // rows 150 -> 146; d 768, 1 154 -> 149, 4 158 -> 157, 8 169 -> 172; d 1,024, 1 170 -> 170, 4 175 -> 177, 8 192 -> 200.
-    const bool lean = act32 && c.decode && d <= 768 && c.rows <= 32 && c.rows * d <= 4096 && d % 4 == 0 &&
-                      qw % 4 == 0 && cfg.ffn_dim % 4 == 0;
+    // fp32 weights, a few rows: the norms and the residual's sums are done by the projections.  Each wave (a column, four rows) norms the
+    // rows for itself, so waves and d must be few: the price is waves x d, what it saves two launches a layer.  Four layers, us a step,
+    // separate kernels -> this, contexts of 64 tokens, ffn = 4 d: d 128, 1 row 128 -> 106, 8 127 -> 105, 32 130 -> 117; d 256, 16 130 -> 115;
+    // d 512, 1 130 -> 114, 8 135 -> 130 (ffn 4,096 155 -> 159); d 768, 1 138 -> 133, 4 142 -> 142, 5 151 -> 155; d 1,024, ffn 1,024,
+    // 4 rows 132 -> 126; ffn 4,096 160 -> 160; d 2,048, ffn 512, 4 rows 142 -> 154.  d 128, ffn 16,384, 1 row 214 -> 223, 8 253 -> 277.
+    // The head by itself: 151,936 columns, d 128, 1 row 134 -> 168, 32 410 -> 700; 2,048 columns, 8 rows 112 -> 109, 32 121 -> 123.
+    auto few_norms = [&](int columns) {
+        const long waves = (long)((c.rows + 3) / 4) * columns;
+        return waves <= 8192 && waves * d <= 3L << 20;
+    };
+    const bool lean = act32 && c.decode && c.rows <= 32 && d <= 1024 && few_norms(nqkv + cfg.ffn_dim) && d % 4 == 0 && qw % 4 == 0 && cfg.ffn_dim % 4 == 0;
     if (lean) part_o = part_down = c.w.x;
 
     auto project = [&](int l, const QkvPlan& pl, const int32_t* row_map) -> int {
@@ -924,12 +928,14 @@ static int run_layers(StepCtx& c) {
     // final norm on one row per sequence, then the LM head
     NormArgs nf = {c.w.x, part, (const float*)m->w[1], c.w.hf, c.decode ? nullptr : c.w.last_rows,
                    c.rows, c.B, d, pending, cfg.rms_eps, sat, nullptr, hf_frag};
-    if (!lean) HIP_TRY(timed(m, SPIRAL_K_NORM, c.s, [&] { return launch_add_norm(nf, act32, c.s); }));
+    if (lean) nf.n_part = 0;            // the sums are in x
+    const bool lean_head = lean && few_norms(cfg.vocab);
+    if (!lean_head) HIP_TRY(timed(m, SPIRAL_K_NORM, c.s, [&] { return launch_add_norm(nf, act32, c.s); }));
     GemmArgs gl = {};
     gl.A = c.w.hf; gl.w[0] = m->w[2]; gl.rows[0] = cfg.vocab;
     gl.M = c.B; gl.N = cfg.vocab; gl.K = d; gl.out = c.logits; gl.splits = 1;
     gl.wf = m->f_lm; gl.a_frag = hf_frag; gl.head = 1;
-    if (lean) { gl.A = c.w.x; gl.norm_gain = (const float*)m->w[1]; gl.norm_eps = cfg.rms_eps; }
+    if (lean_head) { gl.A = c.w.x; gl.norm_gain = (const float*)m->w[1]; gl.norm_eps = cfg.rms_eps; }
     if (c.sample) {
         // the LM head keeps the best (score, index) of each 128-column tile per row; a small kernel picks the winner
         const int cols = gemm_sample_tile_cols(c.B, t.bn_lm);

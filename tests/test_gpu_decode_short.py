@@ -81,13 +81,15 @@ def test_a_pair_to_a_workgroup_in_rounds(q_heads, kv_heads, rows, longest, direc
     _compare(g, si.make_weights(g, seed=86), lens, direct, (0, rows - 1))
 
 
-@pytest.mark.parametrize("d,ffn,norm,B", [(128, 512, False, 1), (128, 512, False, 4), (128, 512, False, 5), (128, 512, False, 32), (128, 512, False, 33),
-                                          (132, 200, True, 8), (132, 200, True, 31), (132, 200, True, 32), (512, 96, False, 8), (768, 96, False, 5), (1024, 96, False, 8), (1024, 96, False, 9)])
-def test_fp32_projections_that_norm(d, ffn, norm, B):
+@pytest.mark.parametrize("d,ffn,norm,B,vocab", [
+    (128, 512, False, 1, 260), (128, 512, False, 4, 260), (128, 512, False, 5, 260), (128, 512, False, 32, 260), (128, 512, False, 33, 260),
+    (128, 512, False, 32, 1100), (132, 200, True, 8, 260), (132, 200, True, 31, 260), (132, 200, True, 32, 260), (512, 96, False, 8, 260),
+    (512, 1280, False, 16, 260), (768, 96, False, 5, 260), (1024, 96, False, 8, 260), (1024, 512, False, 16, 260), (1028, 96, False, 1, 260)])
+def test_fp32_projections_that_norm(d, ffn, norm, B, vocab):
     """The last batch the rule takes and the first it leaves, remainders of four rows, widths that are and are not multiples of the 256 elements a
     wave reads at once.  Bar: q, k, v and the attention output round to half, 2^-11 each; all four in the same direction in two layers are 4e-3."""
     from paper_2506_24119_amd import binding as sb
-    g = si.ModelGeometry("lean", 2, d, 4, 2, 32, ffn, 260, 1e4, qk_norm=norm, qkv_bias=not norm, weight_dtype=si.WEIGHT_FP32)
+    g = si.ModelGeometry("lean", 2, d, 4, 2, 32, ffn, vocab, 1e4, qk_norm=norm, qkv_bias=not norm, weight_dtype=si.WEIGHT_FP32)
     host = si.make_weights(g, seed=82)
     rng = np.random.Generator(np.random.PCG64(83))
     for lw in host["layers"]:
@@ -100,17 +102,20 @@ def test_fp32_projections_that_norm(d, ffn, norm, B):
         assert np.abs(got[b] - want).max() <= 4e-3 * want.std(), b
 
 
-@pytest.mark.parametrize("d,B,norms", [(128, 32, False), (128, 33, True), (132, 31, False), (132, 32, True), (512, 8, False), (512, 9, True), (768, 1, False),
-                                       (768, 5, False), (768, 6, True), (772, 1, True), (1024, 1, True), (1024, 8, True)])
-def test_which_fp32_steps_keep_their_norms(d, B, norms):
-    """By the launches of a step: wider models and more rows are slower without them (d 1,024, 8 rows 176 -> 183 us, d 768 153 -> 156)."""
+@pytest.mark.parametrize("d,ffn,vocab,B,norms", [
+    (128, 512, 1024, 32, 0), (128, 512, 1024, 33, 4), (128, 512, 1028, 32, 1), (128, 512, 8192, 1, 0), (128, 512, 8196, 1, 1), (128, 512, 151936, 4, 1),
+    (256, 768, 260, 32, 0), (256, 772, 260, 32, 4), (512, 1280, 260, 16, 0), (512, 1284, 260, 16, 4), (512, 1280, 260, 17, 4),
+    (1024, 512, 260, 16, 0), (1028, 96, 260, 1, 4), (132, 200, 260, 32, 0)])
+def test_which_fp32_steps_keep_their_norms(d, ffn, vocab, B, norms):
+    """By the norm launches of a step of two layers: none, the one before the head, all.  Where every wave of a wide projection norms its
+    rows for itself the step is slower (a vocabulary of 151,936, d 128, 32 rows 410 -> 700 us)."""
     import torch
     from paper_2506_24119_amd import binding as sb
-    g = si.ModelGeometry("lean", 2, d, 4, 2, 32, 96, 260, 1e4, weight_dtype=si.WEIGHT_FP32)
+    g = si.ModelGeometry("lean", 2, d, 4, 2, 32, ffn, vocab, 1e4, weight_dtype=si.WEIGHT_FP32)
     ids = np.arange(B, dtype=np.int32)
-    sess = sb.Session(g, sb.weights_to_device(si.make_weights(g, seed=82)), B, B, 1, B, 16)
+    sess = sb.Session(g, si.make_weights_torch(g, 1, "cuda:0"), B, B, 1, B, 16)
     sess.prefill(ids, [np.zeros(1, dtype=np.int32)] * B)
     sb.spiral_profile_begin(sess.model, sb.KERNEL_CLASSES.index("norm"), 16)
     sess.decode_step(ids, torch.zeros(B, dtype=torch.int32, device="cuda"), sess.new_logits(B))
-    assert (sb.spiral_profile_end(sess.model)[1] > 0) == norms
+    assert sb.spiral_profile_end(sess.model)[1] == norms
     sess.close()
