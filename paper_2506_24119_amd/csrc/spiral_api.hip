@@ -675,10 +675,10 @@ bool score_pairs_fit(int vocab, int d, int ffn, int q_width, int kv_width) {
 }
 }  // namespace spiral
 
-// Whether the q/k/v projection of a call with that many rows reads act_frag() order.
-static int qkv_in_frag(const spiral_model* m, int rows) {
+// Whether the projection of so many rows onto q, k and v, or q alone (the last rows of a prefill), reads act_frag() order.
+static int qkv_in_frag(const spiral_model* m, int rows, bool q_alone = false) {
     const spiral_model_config& c = m->cfg;
-    return m->w_bf16 && gemm_decode_takes(rows, c.n_kv_heads * c.head_dim, c.d_model, EPI_STORE_F32, false);
+    return m->w_bf16 && gemm_decode_takes(rows, (c.n_q_heads + (q_alone ? 0 : 2 * c.n_kv_heads)) * c.head_dim, c.d_model, EPI_STORE_F32, false);
 }
 
 static int run_layers(StepCtx& c) {
@@ -769,7 +769,7 @@ static int run_layers(StepCtx& c) {
     int32_t* sat = c.p->d_status;
     // At most 128 rows: activations go from kernel to kernel in the order of the projections' operands where the reader is
     // gemm_decode_kernel.  qkv_in_frag() is what the embedding kernel of the call went by.
-    const int h_frag = qkv_in_frag(m, c.rows);
+    const int h_frag = qkv_in_frag(m, c.rows, c.q_rows != nullptr);
     const int h2_frag = !act32 && gemm_decode_takes(c.rows, cfg.ffn_dim, d, EPI_SWIGLU, false);
     const int o_frag = !act32 && gemm_decode_takes(c.rows, d, qw, EPI_STORE_F32, false);
     const int mlp_frag = !act32 && gemm_mlp_in_frag(c.rows, d, cfg.ffn_dim);
@@ -831,7 +831,7 @@ static int run_layers(StepCtx& c) {
             if (rc) return rc;
             // the last rows: residual to h's memory (h has been read), normed to hf
             NormArgs n = {c.w.x, nullptr, (const float*)m->lw(l, SPIRAL_W_ATTN_NORM), c.w.hf, c.w.last_rows, c.rows, c.B, d, 0, cfg.rms_eps,
-                          nullptr, (float*)c.w.h, qkv_in_frag(m, c.B)};
+                          nullptr, (float*)c.w.h, qkv_in_frag(m, c.B, true)};
             HIP_TRY(timed(m, SPIRAL_K_NORM, c.s, [&] { return launch_add_norm(n, act32, c.s); }));
             std::vector<int32_t> start(c.B + 1, 0);
             int max_ctx = 0;

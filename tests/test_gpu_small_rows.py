@@ -179,3 +179,29 @@ def test_tuned_rows_and_splits_of_small_calls(key):
             assert np.array_equal(one, _run(WIDE, w, B, True, tune=f"{key}={R}:1")[0]), (B, R)
         three = _run(WIDE, w, B, True, tune=f"{key}=64:3")[0]
         assert not np.array_equal(one, three) and np.abs(one - three).max() <= 1e-2 * one.std(), B
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("repack", [True, False])
+def test_widths_on_either_side_of_the_large_projections(repack):
+    """q/k/v (7,168 x 5,120) and down (5,120 x 6,656) of more than 64 MB stay on the streaming kernel, q alone, O and gate/up do not: whoever
+    writes their input has to know.  A decode step, a prefill of few rows and one whose last layer has one row a sequence."""
+    import torch
+    from paper_2506_24119_amd import binding as sb
+    g = si.ModelGeometry("large", 1, 5120, 40, 8, 128, 6656, 512, 1e6)
+    host = si.make_weights(g, seed=76)
+    w = sb.weights_to_device(host)
+    rng = np.random.Generator(np.random.PCG64(77))
+    sess = sb.Session(g, w, 60, 4, 14, 200, 220, page_order=si.make_page_order(60, 3), repack=repack)
+    seqs = [rng.integers(0, g.vocab, n).astype(np.int32) for n in (9, 14)]
+    got = list(sess.prefill(np.arange(2, dtype=np.int32), seqs).cpu().numpy())
+    long = [rng.integers(0, g.vocab, n).astype(np.int32) for n in (60, 75)]
+    got += list(sess.prefill(np.array([2, 3], dtype=np.int32), long).cpu().numpy())
+    step = rng.integers(0, g.vocab, 4).astype(np.int32)
+    got += list(sess.decode_step(np.arange(4, dtype=np.int32), torch.from_numpy(step).cuda(), sess.new_logits(4)).cpu().numpy())
+    sess.close()
+    seqs += long
+    for b, s in enumerate(seqs):
+        want = od.forward_full(g, host, np.concatenate([s, step[b:b + 1]]), logits_at=np.array([len(s) - 1, len(s)]))
+        for k in range(2):
+            assert np.abs(got[4 * k + b] - want[k]).max() <= LOGIT_TOL * want[k].std(), (b, k)
