@@ -13,7 +13,8 @@
 // Decode (attn_stream_kernel): the ordered stream of all (row, kv head, page) units of the batch is cut into equal
 // ranges, one per workgroup; inside a range the four waves take pages round-robin, each with a private online
 // softmax (running max m, sum l, unnormalised O), merged through LDS at the end of every (row, kv head) segment;
-// a second small kernel merges the partial (m, l, O) of a pair that spans workgroups.
+// a second small kernel merges the partial (m, l, O) of a pair that spans workgroups.  Short and even batches give every
+// (row, kv head) pair a workgroup instead, the last rows of a prefill pieces of a fixed number of pages (DecodeForm).
 // Prefill (attn_prefill_kernel): tiles of 32 positions of one head on the 32x32x16 MFMA, four a workgroup, pages in LDS.
 // Softmax is evaluated in base 2: scores are scaled by log2(e)/sqrt(hd) and v_exp_f32 is 2^x.
 #include <type_traits>
