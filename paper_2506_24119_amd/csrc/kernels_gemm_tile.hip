@@ -1,30 +1,29 @@
 // Large-M projection kernel (prefill and the scoring pass): out[m][n] = sum_k A[m][k] * W[n][k] with
 // hundreds or thousands of rows, where the matrix cores, not HBM, are the bound.
 //
-// A workgroup (4 waves, one per SIMD) owns a 256 x 256 output tile and walks K in chunks of 64.  Both
-// operand tiles of a chunk go global -> registers -> LDS (rows padded to 144 B so that operand reads
-// are conflict free; the weights come from the fragment-ordered copies, 1 KB contiguous per wave
-// load, already in the operand type).  Three chunks are in flight: chunk c is multiplied out of one
-// LDS buffer, chunk c + 1 moves from registers into the other buffer, and the global loads of chunk
-// c + 2 are issued; the one barrier of a chunk sits before its last k step, so that the first operand reads of the
-// next chunk are issued under MFMAs like all the others.  Every wave owns a 128 x 128 quarter: per k step of 16 it reads 4 + 4 operand
-// fragments from LDS (one step ahead of their use) for 16 v_mfma_f32_32x32x16 (256 accumulator
-// registers), i.e. 128 flop per byte fetched from L2 against 64 for a 128 x 128 tile; the issue order of
-// a step is pinned (8 LDS reads, then 4 x (4 MFMAs, 1 LDS write, 1 global load)) so that LDS and memory
-// traffic run under the MFMAs: issued as one burst at the start of a chunk the 16 loads of a thread cost a
-// sixth of the kernel, spread over the k steps nothing measurable.  An isolated loop of this shape runs at 71 %
-// of the nominal MFMA rate (a pure MFMA stream at 82 %: the clock under this load is ~2.0 GHz); the kernel delivers
-// 1.0-1.15 PFLOP/s on 16,384 rows, the matrix cores busy 52-57 % of the cycles at 1.9-2.0 GHz (the vendor GEMM:
-// 0.9-1.4 PFLOP/s on these shapes).  The clock follows the operand bits: with all-zero operands the gate/up
-// projection takes 1.09 ms instead of 1.41 (1.50 PFLOP/s; the vendor GEMM 1.3-1.4 -> 1.9-2.0 PFLOP/s).
+// A workgroup of 4 waves owns a tile of 256 or 128 rows x 256 columns, a wave a quarter of it (128 x 128 or 64 x 128, 256 or 128
+// accumulator registers), and walks K in chunks of 64.  Both operands go from memory straight to LDS (buffer loads with an LDS
+// destination): no registers, no LDS writes by the waves, and the 128-row tile, without staging registers and with 80 KB of LDS, fits a
+// compute unit twice, so that one workgroup's first loads, epilogue and barriers run under the other's products.  LDS holds
+// activations as whole 128-byte rows, their eight pieces permuted so that operand reads meet no bank twice, and weights as
+// fragment blocks (frag_block(), already in the operand type), three (two) slots of 64 k of activations and four (three) of 32 k of
+// weights.  What else was tried and measured, gate/up of the 4B shape at 15,272 rows (1412 us with operands staged through registers,
+// 256 rows, one chunk ahead): both operands straight to LDS with two slots of 64 k 1656 to 1706 us (loads one chunk ahead are too
+// late); activations in slots of 32 k, whose loads touch half lines, 1357 (256 rows), 1375 (128); whole lines 1262 to 1290; the
+// reads of a half's second k step as a burst instead of one behind each product +2 %; those behind the barrier spread likewise +1.5 %;
+// s_setprio around the products +3 %; bands of 2048 or 4096 rows +1 and +7 %.
+// The chip's power is the limit: the matrix cores are busy 75 % of the cycles, at 1.4 GHz (62 % at 1.7 before), and with
+// all-zero operands the same launch takes 918 us (1.66 PFLOP/s against 1.20).  A loop of nothing but products with random operands makes
+// 1.70 PFLOP/s, with its operand reads from LDS 1.54.  Times of a launch, us, staged through registers -> now: gate/up 4B shape 15,272 rows
+// 1358 -> 1262, 788 rows 110 -> 97, 0.6B shape 11,206 rows 175 -> 139; O and down 4B 15,272 rows 318 -> 276 and 700 -> 643, 788 rows (3 K splits)
+// 25.9 -> 24.7 and 48 -> 46; down 0.6B 11,206 rows 76 -> 69; q/k/v with its post-processing 4B 517 -> 446, 0.6B 144 -> 108; the
+// scoring LM head, 6,028 rows 4380 -> 3870 (1.21 PFLOP/s).  Same bits throughout.
 // Workgroup ids are dealt round-robin to the 8 XCDs by the hardware; the tile order is arranged so
-// that each XCD (own L2) gets a contiguous run of tiles, ordered in bands of 4 row tiles.
-// A second form has tiles of 128 x 256 (a wave 64 x 128, 128 accumulator registers), and K may be split over workgroups:
-// at 788 rows of the 4B shape 256-row tiles leave O and down 40 workgroups.  A layer's projections there, before (streaming
-// kernel for q/k/v, O and down, 256-row tiles for gate/up) and with the form and the split chosen by estimated time:
-// q/k/v 67 + 17 (its post-processing) -> 50 us, O 51 -> 26, gate/up 133 -> 115, down 113 -> 50.
+// that each XCD (own L2) gets a contiguous run of tiles, ordered in bands of 1024 rows.
+// K may be split over workgroups: at 788 rows of the 4B shape 256-row tiles leave O and down 40 workgroups.
 
 #include <algorithm>
+#include <cmath>
 
 #include "spiral_internal.h"
 #include "mfma_ops.h"
@@ -39,9 +38,27 @@ __device__ __forceinline__ f32x16 mma32t(const u32x4& w, const u32x4& a, const f
     return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, w), __builtin_bit_cast(f16x8, a), c, 0, 0, 0);
 }
 
-constexpr int BN = 256, BK = 64;
-constexpr int ROW = 144;                          // LDS bytes per tile row: 64 k x 2 B + 16 pad
-constexpr int stage_bytes(int bm) { return (bm + BN) * ROW; }      // activation tile, then weight tile
+constexpr int BK = 64;
+constexpr int kAllBytes = 0x7FFFFFFF;
+
+// The operand loads carry a buffer descriptor: one of size zero drops them, so that the steady loop runs to the end of K without a branch.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_upto(const void* p, int bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, bytes, 0x00027000);
+}
+// 64 lanes x 16 bytes straight to 1 KB of LDS at dst (wave-uniform); IMM counts on both sides
+template <int IMM>
+__device__ __forceinline__ void load_to_lds(__amdgpu_buffer_rsrc_t r, char* dst, uint32_t off, int soff) {
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)dst, 16, off, soff, IMM, 0);
+}
+// which of a 128-byte row's eight 16-byte pieces sits where: 8 (and 16) lanes that read one piece of consecutive rows meet no bank twice
+__device__ __forceinline__ int row_swizzle(int r) { return (r & 6) | ((r ^ (r >> 3)) & 1); }
+
+// Slots in LDS: activations of 64 k, weights of 32 k; all 160 KB for the tall tile, half of them for the other, two of which share a compute unit.
+template <int BM> struct Slots {
+    static constexpr int A = BM == 256 ? 3 : 2, W = A + 1;
+    static constexpr int A_BYTES = BM * 128, W_BYTES = 256 * 64, W_BASE = A * A_BYTES;
+    static constexpr int TOTAL = W_BASE + W * W_BYTES;
+};
 
 }  // namespace
 
@@ -54,16 +71,15 @@ constexpr int stage_bytes(int bm) { return (bm + BN) * ROW; }      // activation
 // BM: activation rows of the tile, 256 (a wave's quarter is 128 x 128) or 128 (64 x 128).
 // g.splits > 1 (TEPI 0): K is cut at multiples of 128, split s writes its partial product to out[s], as the streaming kernel does.
 template <int TEPI, int BM>
-__global__ __launch_bounds__(256) void gemm_tile_kernel(GemmArgs g, QkvPostArgs qa) {
+__global__ __launch_bounds__(256, BM == 128 ? 2 : 1) void gemm_tile_kernel(GemmArgs g, QkvPostArgs qa) {
     constexpr bool SWIGLU = TEPI == 1;
     constexpr int J = 4, I = BM / 64;               // 32-row weight tiles and batch tiles per wave
-    constexpr int A_BYTES = BM * ROW;               // activation tile; the weight tile follows it
-    constexpr int STAGE = stage_bytes(BM);
-    constexpr int AU = BM / 32, UNITS = AU + 8, UQ = UNITS / 4;        // 16-byte units of a thread and chunk; a quarter per k step
+    using L = Slots<BM>;
+    constexpr int AU = BM / 32;                     // 8-row blocks of an activation chunk that a wave brings
     constexpr int GROUP_M = 1024 / BM;
     extern __shared__ uint4 lds_raw[];
     char* lds = (char*)lds_raw;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int l32 = lane & 31, lh = lane >> 5;
     const int wm = wave & 1, wn = wave >> 1;        // this wave's quarter
     const int K = g.K;
@@ -88,30 +104,26 @@ __global__ __launch_bounds__(256) void gemm_tile_kernel(GemmArgs g, QkvPostArgs 
     const int ce = TEPI == 0 && g.splits > 1 ? 2 * (int)(((long long)(K >> 7) * (split + 1)) / g.splits) : K / BK;
     const int NC = ce - cb;
 
-    // ---- global -> LDS assignment, AU + 8 16-byte units per thread and chunk.
-    //      Activations (row-major): unit i is row threadIdx.x / 8 + 32 i, 16-byte column threadIdx.x % 8
-    //      (8 lanes read one 128-byte line).  Weights: a wave reads whole 1 KB fragment blocks, unit i is
-    //      block (row tile i, k step threadIdx.x / 64) of the chunk, lane = threadIdx.x % 64.
-    //      Offsets are 32-bit element offsets from the operand's base (the launcher checks that they fit).
-    uint32_t a_off[AU], w_off[8];
-    const int dst0 = (threadIdx.x >> 3) * ROW + (threadIdx.x & 7) * 16;       // unit i lands 32 rows further down
-    const int wdst0 = A_BYTES + l32 * ROW + (threadIdx.x >> 6) * 32 + lh * 16;
-    {
-        const int t_all = SWIGLU ? (g.N + 15) / 16 : (g.N + 31) / 32;
+    // ---- global -> LDS.  Activations (row-major): an instruction brings 8 rows x 128 bytes, block u of a wave is rows 8 (4 u + wave) .. + 7;
+    //      the LDS side of the load is linear, so a lane picks the piece of its row that belongs where it writes.  Weights: an
+    //      instruction brings one fragment block, units 2 i and 2 i + 1 of a wave are the two k steps of row tile wave + 4 i.
+    //      Offsets are bytes from the tile's own first row (the launcher bounds K).
+    const int t_all = SWIGLU ? (g.N + 15) / 16 : (g.N + 31) / 32, tile0 = SWIGLU ? n0 / 16 : n0 / 32;
+    const uint16_t* abase = (const uint16_t*)g.A + (size_t)m0 * K + (size_t)cb * BK;
+    const uint16_t* wbase = (const uint16_t*)g.wf + frag_block(tile0, cb * (BK / 16), K);
+    uint32_t a_off[AU], w_off[2];
 #pragma unroll
-        for (int i = 0; i < AU; ++i) {
-            int m = m0 + (threadIdx.x >> 3) + 32 * i; if (m >= g.M) m = g.M - 1;
-            a_off[i] = (uint32_t)m * (uint32_t)K + (uint32_t)cb * BK + (threadIdx.x & 7) * 8;
-        }
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const int t32 = min((SWIGLU ? n0 / 16 : n0 / 32) + i, t_all - 1);
-            w_off[i] = (uint32_t)frag_block(t32, cb * (BK / 16) + (threadIdx.x >> 6), K) + lane * 8;
-        }
+    for (int u = 0; u < AU; ++u) {
+        const int r = (u * 4 + wave) * 8 + (lane >> 3);
+        a_off[u] = (uint32_t)min(r, g.M - 1 - m0) * (uint32_t)K * 2u + ((lane & 7) ^ row_swizzle(r)) * 16;
     }
+#pragma unroll
+    for (int i = 0; i < 2; ++i) w_off[i] = (uint32_t)min(wave + 4 * i, t_all - 1 - tile0) * (uint32_t)K * 64u + lane * 16;
     // operand fragments: row (wm * BM / 2 + i * 32 + l32 or wn * 128 + j * 32 + l32), k = ks * 16 + lh * 8
-    const int a_frag = (wm * (BM / 2) + l32) * ROW + lh * 16;
-    const int w_frag = A_BYTES + (wn * 128 + l32) * ROW + lh * 16;
+    int a_frag[4];
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) a_frag[ks] = (wm * (BM / 2) + l32) * 128 + ((ks * 2 + lh) ^ row_swizzle(l32)) * 16;
+    const int w_frag = L::W_BASE + wn * 8192 + lane * 16;
 
     f32x16 acc[J][I];                               // [weight tile j][batch tile i]
 #pragma unroll
@@ -121,91 +133,107 @@ __global__ __launch_bounds__(256) void gemm_tile_kernel(GemmArgs g, QkvPostArgs 
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[j][i][r] = 0.f;
 
-    // Two register stages: a chunk's global loads are issued two chunks before it is multiplied and
-    // one chunk before it is parked in LDS, so the staging writes never wait for memory.
-    u32x4 rg[2][UNITS];                             // [stage][AU activation units, 8 weight units]
-    auto load_unit = [&](const int st, const int cc, const int u) {
-        if (u < AU) rg[st][u] = *(const u32x4*)((const uint16_t*)g.A + a_off[u < AU ? u : 0] + (size_t)cc * BK);
-        else rg[st][u] = *(const u32x4*)((const uint16_t*)g.wf + w_off[u < AU ? 0 : u - AU] + (size_t)cc * (BK / 16) * 512);
+    auto load_a = [&](int slot, int c, const int u) {
+        load_to_lds<0>(buffer_upto(abase, c < NC ? kAllBytes : 0), lds + slot * L::A_BYTES + (u * 4 + wave) * 1024, a_off[u], c * 128);
     };
-    auto load = [&](const int st, int c) {
-        const int cc = c < NC ? c : NC - 1;           // past the end: a re-read of the last chunk
+    auto load_w = [&](int slot, int h, const int u) {          // half chunk h
+        const __amdgpu_buffer_rsrc_t r = buffer_upto(wbase, h < 2 * NC ? kAllBytes : 0);
+        char* dst = lds + L::W_BASE + slot * L::W_BYTES + (wave + 4 * (u >> 1)) * 2048;
+        if (u & 1) load_to_lds<1024>(r, dst, w_off[u >> 1], h * 2048);
+        else load_to_lds<0>(r, dst, w_off[u >> 1], h * 2048);
+    };
+    auto frags = [&](int as, int ws, int ks, u32x4* af, u32x4* wf) {
 #pragma unroll
-        for (int u = 0; u < UNITS; ++u) load_unit(st, cc, u);
-    };
-    auto park_unit = [&](char* buf, const int st, const int u) {
-        if (u < AU) *(u32x4*)(buf + dst0 + u * 32 * ROW) = rg[st][u];
-        else *(u32x4*)(buf + wdst0 + (u - AU) * 32 * ROW) = rg[st][u];
-    };
-    auto frags = [&](const char* buf, int ks, u32x4* af, u32x4* wf) {
+        for (int i = 0; i < I; ++i) af[i] = *(const u32x4*)(lds + as * L::A_BYTES + a_frag[ks] + i * 32 * 128);
 #pragma unroll
-        for (int i = 0; i < I; ++i) af[i] = *(const u32x4*)(buf + a_frag + i * 32 * ROW + ks * 32);
-#pragma unroll
-        for (int j = 0; j < J; ++j) wf[j] = *(const u32x4*)(buf + w_frag + j * 32 * ROW + ks * 32);
+        for (int j = 0; j < J; ++j) wf[j] = *(const u32x4*)(lds + ws * L::W_BYTES + w_frag + (j * 2 + (ks & 1)) * 1024);
     };
-    // Chunk c sits in LDS buffer c & 1 and came through register stage c & 1.  The barrier of a chunk sits before
-    // its last k step, not after it: by then every wave has issued (and waited for) its last operand reads of the
-    // chunk and has parked all of chunk c + 1, so the last k step already reads the first fragments of chunk c + 1
-    // and starts parking chunk c + 2 into the buffer that just became free - no operand read is ever exposed
-    // behind a barrier.  Per k step (BM = 256): the 8 operand reads of the next step, four units parked, four units
-    // requested (each unit is requested four k steps before it is parked), 16 MFMAs; issue order pinned to 8 reads, then
-    // 4 x (4 MFMAs, 1 write, 1 global load) (other orders of the same instructions measured within noise).
     u32x4 af[2][I], wf[2][J];
-    auto chunk = [&](int c, const int cu, const int nx) {
-        char* buf = lds + cu * STAGE;                 // cu == c & 1
-        char* other = lds + nx * STAGE;
-        const int c2 = c + 2 < NC ? c + 2 : NC - 1;   // past the end: a re-read of the last chunk
-        const int c3 = c + 3 < NC ? c + 3 : NC - 1;
-        __builtin_amdgcn_sched_barrier(0);
+    auto multiply = [&](const int b) {                         // up and down the batch tiles: one operand stays from one instruction to the next
 #pragma unroll
-        for (int ks = 0; ks < 4; ++ks) {
-            if (ks < 3) {
-                frags(buf, ks + 1, af[(ks + 1) & 1], wf[(ks + 1) & 1]);
+        for (int j = 0; j < J; ++j)
 #pragma unroll
-                for (int u = 0; u < UQ; ++u) park_unit(other, nx, (ks + 1) * UQ + u);
-#pragma unroll
-                for (int u = 0; u < UQ; ++u) load_unit(cu, c2, (ks + 1) * UQ + u);
-            } else {
-                __syncthreads();
-                __builtin_amdgcn_sched_barrier(0);
-                frags(other, 0, af[0], wf[0]);
-#pragma unroll
-                for (int u = 0; u < UQ; ++u) park_unit(buf, cu, u);
-#pragma unroll
-                for (int u = 0; u < UQ; ++u) load_unit(nx, c3, u);
+            for (int x = 0; x < I; ++x) {
+                const int i = (j & 1) ? I - 1 - x : x;
+                acc[j][i] = mma32t(wf[b][j], af[b][i], acc[j][i]);
             }
+    };
+    // The loop runs over halves of a chunk, two k steps each.  In the first the operands of the second are read from LDS; then, when the
+    // wave has its operands and what the next half reads has landed, comes the half's one barrier: the weight slot (after a second
+    // half the activation slot too) is free, the next half's first operands are read and the slot's next loads issued, three
+    // halves (256 rows) or two before they are needed.  The waits count the loads that may still be in flight: per half four of weights
+    // and, 256 rows, four of activations (a chunk's two fours after the barriers of the second half three chunks before and of the first
+    // half two chunks before), or, 128 rows, four of activations after a second half only.
 #pragma unroll
-            for (int j = 0; j < J; ++j)
+    for (int u = 0; u < AU; ++u) load_a(0, 0, u);
 #pragma unroll
-                for (int i = 0; i < I; ++i) acc[j][i] = mma32t(wf[ks & 1][j], af[ks & 1][i], acc[j][i]);
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int u = 0; u < 4; ++u) load_w(h, h, u);
+#pragma unroll
+    for (int u = 0; u < AU; ++u) load_a(1, 1, u);
+#pragma unroll
+    for (int h = 2; h < L::W; ++h)
+#pragma unroll
+        for (int u = 0; u < 4; ++u) load_w(h, h, u);
+    if (BM == 256)
+#pragma unroll
+        for (int u = 0; u < 4; ++u) load_a(2, 2, u);
+    if (BM == 256) asm volatile("s_waitcnt vmcnt(24)" ::: "memory");
+    else asm volatile("s_waitcnt vmcnt(12)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    frags(0, 0, 0, af[0], wf[0]);
+    int as = 0, ws = 0;                                        // the slots being multiplied
+    for (int c = 0; c < NC; ++c) {
+        const int a_next = as == L::A - 1 ? 0 : as + 1, a_last = as == 0 ? L::A - 1 : as - 1;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int w_next = ws == L::W - 1 ? 0 : ws + 1;
+            __builtin_amdgcn_sched_barrier(0);
+            frags(as, ws, 2 * h + 1, af[1], wf[1]);
+            multiply(0);
+#pragma unroll
+            for (int r = 0; r < I + J; ++r) {                  // a read behind each of the first products
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+            }
+            __builtin_amdgcn_sched_group_barrier(0x008, I * J - I - J, 0);
+            __builtin_amdgcn_sched_barrier(0);
+            if (BM == 256) asm volatile("s_waitcnt vmcnt(16) lgkmcnt(0)" ::: "memory");
+            else if (h == 0) asm volatile("s_waitcnt vmcnt(8) lgkmcnt(0)" ::: "memory");
+            else asm volatile("s_waitcnt vmcnt(4) lgkmcnt(0)" ::: "memory");
+            __builtin_amdgcn_s_barrier();
+            asm volatile("" ::: "memory");
+            __builtin_amdgcn_sched_barrier(0);
+            frags(h ? a_next : as, w_next, h ? 0 : 2, af[0], wf[0]);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) load_w(ws, 2 * c + h + L::W, u);
+            if (BM == 256) {
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    if (h) load_a(as, c + 3, u);
+                    else load_a(a_last, c + 2, 4 + u);
+                }
+            } else if (h) {
+#pragma unroll
+                for (int u = 0; u < 4; ++u) load_a(as, c + 2, u);
+            }
+            multiply(1);
             __builtin_amdgcn_sched_group_barrier(0x100, I + J, 0);
 #pragma unroll
-            for (int r = 0; r < UQ; ++r) {
-                __builtin_amdgcn_sched_group_barrier(0x008, I, 0);
-                __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);
-                __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+            for (int r = 0; r < 8; ++r) {
+                __builtin_amdgcn_sched_group_barrier(0x008, I * J / 8, 0);
+                __builtin_amdgcn_sched_group_barrier(0x010, 1, 0);
             }
             __builtin_amdgcn_sched_barrier(0);
+            ws = w_next;
         }
-    };
-
-    load(0, 0);
-    load(1, 1);
-#pragma unroll
-    for (int u = 0; u < UNITS; ++u) park_unit(lds, 0, u);
-#pragma unroll
-    for (int u = 0; u < UQ; ++u) park_unit(lds + STAGE, 1, u);
-#pragma unroll
-    for (int u = 0; u < UQ; ++u) load_unit(0, 2 < NC ? 2 : NC - 1, u);
-    __syncthreads();
-    frags(lds, 0, af[0], wf[0]);
-    int c = 0;
-    for (; c + 2 <= NC; c += 2) {
-        chunk(c, 0, 1);
-        chunk(c + 1, 1, 0);
+        as = a_next;
     }
-    if (c < NC) chunk(c, 0, 1);
-    __syncthreads();                                  // the operand buffers are free for the epilogue
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+    __syncthreads();                                  // the operand slots are free for the epilogue
 
     // ---- epilogue.  In a 32 x 32 tile a lane holds batch row l32 and, in registers 4b..4b+3, weight rows 8b + 4*lh .. +3:
     //      written straight from there a store instruction touches 64 rows x 16 (or 8) bytes.  Each wave therefore
@@ -363,16 +391,17 @@ __global__ __launch_bounds__(256) void gemm_tile_kernel(GemmArgs g, QkvPostArgs 
         for (int i = 0; i < I; ++i) {
             const int m = m0 + wm * (BM / 2) + i * 32 + l32;
             const int tgt = m < g.M ? g.targets[m] : -1;
-            float mx = -INFINITY;
+            const int mine = tgt - c0;                                // its place among this lane's columns, if it is one of them
+            float mx = -INFINITY, found = 0.f;
 #pragma unroll
             for (int j = 0; j < J; ++j)
 #pragma unroll
                 for (int r = 0; r < 16; ++r) {
-                    const int col = c0 + 32 * j + 8 * (r >> 2) + (r & 3);
-                    if (col >= g.N) acc[j][i][r] = -INFINITY;         // padding of the last tile (clamped weight rows)
-                    if (col == tgt) g.tgt_logit[m] = acc[j][i][r];
+                    if (c0 + 32 * j + 8 * (r >> 2) + (r & 3) >= g.N) acc[j][i][r] = -INFINITY;      // padding of the last tile
+                    found = mine == 32 * j + 8 * (r >> 2) + (r & 3) ? acc[j][i][r] : found;
                     mx = fmaxf(mx, acc[j][i][r]);
                 }
+            if (tgt >= 0 && mine >= 0 && mine < 128 && (mine & 4) == 0 && tgt < g.N) g.tgt_logit[m] = found;
             mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
             const float ref = mx > -INFINITY ? mx : 0.f;              // nothing but -inf: all terms are zero
             float sum = 0.f;
@@ -451,7 +480,7 @@ static hipError_t launch_tile_bm(const GemmArgs& a, const QkvPostArgs& qa, hipSt
     const long long total = (long long)m_tiles * n_tiles * (TEPI == 0 ? a.splits : 1);
     if (total > (1ll << 30)) return hipErrorInvalidValue;
     const int per_xcd = (int)((total + 7) / 8);
-    const size_t lds_bytes = (size_t)2 * stage_bytes(BM);
+    const size_t lds_bytes = Slots<BM>::TOTAL;
     hipError_t e = hipFuncSetAttribute((const void*)gemm_tile_kernel<TEPI, BM>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((gemm_tile_kernel<TEPI, BM>), dim3(per_xcd * 8), dim3(256), lds_bytes, s, a, qa);
@@ -463,16 +492,20 @@ static hipError_t launch_tile(const GemmArgs& a, const QkvPostArgs& qa, int bm, 
     return bm == 128 ? launch_tile_bm<TEPI, 128>(a, qa, s) : launch_tile_bm<TEPI, 256>(a, qa, s);
 }
 
-// needs the fragment-ordered weights (a.wf), K % 64 == 0 (% 128 with a split) and operands small enough for 32-bit element offsets
+// needs the fragment-ordered weights (a.wf), K % 64 == 0 (% 128 with a split), operands small enough for 32-bit element offsets and
+// a tile's own rows (256 of activations, 8 x 32 of weights) within a buffer's 2^31 bytes
 bool gemm_tile_usable(const GemmArgs& a) {
     return a.wf != nullptr && a.splits >= 1 && (a.K % (a.splits > 1 ? 128 : BK)) == 0 && a.splits <= std::max(1, a.K >> 7) && (a.N & 3) == 0 &&
-           (long long)a.M * a.K < (1ll << 31) && ((long long)a.N + 32) * 2 * a.K < (1ll << 31);
+           a.K < (1 << 22) && (long long)a.M * a.K < (1ll << 31) && ((long long)a.N + 32) * 2 * a.K < (1ll << 31);
 }
 
-// Estimated microseconds of one launch on 256 x 256 or 128 x 256 tiles (cols: output columns of a tile): rounds over the
-// 256 compute units, one workgroup each, x (fixed part + 64-wide k chunks, which take a third longer on a full chip, where
-// the clock follows the power limit).  Measured, 4B shape (us, one round): O on 40 tiles of 256 rows 84 and down 185
-// (K = 4096, 9728), on 70 tiles of 128 rows 49 and 106; gate/up at 11,200 rows (13 and 26 rounds) 80 and 42.5 a round.
+// What the K splits, the q/k/v projection's form and the line to the streaming kernel go by: estimated microseconds of one launch
+// on 256 x 256 or 128 x 256 tiles (cols: output columns of a tile), rounds over the 256 compute units x (fixed part + 64-wide k
+// chunks, which take a third longer on a full chip).  They describe this kernel as it was with operands staged through
+// registers, and stay because the order of an output's sums follows from them, for row-major weights (on the streaming kernel, as
+// ever) too.  Checked against the kernel as it is, 60 pairs of shape and rows: O and down of the 4B, 0.6B and 7B shapes, 136 to
+// 15,272 rows, launch and partial sums, lose nothing to the best of 1, 2, 3 or 6 splits on 41 of the 47 where the choice is one of these, and 4 to 25 %
+// of 16 to 55 us on the others; fusing q/k/v's post-processing is right at all 15 row counts but 520 (34 us fused, 41 split).
 float gemm_tile_us(int M, int N, int K, int splits, int cols, int bm) {
     const long tiles = (long)((M + bm - 1) / bm) * ((N + cols - 1) / cols) * splits, rounds = (tiles + 255) / 256;
     const float chunk = bm == 256 ? 1.15f : 0.655f, fixed = bm == 256 ? 9.7f : 6.9f;
@@ -487,16 +520,35 @@ float gemm_stream_us(int M, int N, int K, int splits, int bn) {
     return (float)rounds * (bn >= 128 ? 5.8f + 1.41f * chunks : 2.6f + 0.92f * chunks * (1.f + 0.2f * (float)tiles / (256.f * (float)rounds)));
 }
 
-// The tile height for a launch: the cheaper of the two, 0 where the streaming kernel is cheaper still.  All three add
+// Which height is faster goes by estimates of the kernel as it is: a fixed part for each of the n tiles of the busiest compute unit, and
+// per chunk the root of the squares of what that unit needs (n tall tiles one after the other, or pairs of the others and a
+// single one) and of the chip's power for all tiles.  Fitted to 786 launches (the shapes above, gate/up among them, 136 to
+// 15,272 rows): 3 % rms.  The tiles' bits are the same.
+static float tile_us(long tiles, float chunks, bool swiglu, int bm) {
+    const float n = (float)((tiles + 255) / 256), all = (float)tiles / 256.f;
+    const float pairs = floorf(n / 2.f), odd = n - 2.f * pairs;
+    auto hyp = [](float a, float b) { return sqrtf(a * a + b * b); };
+    if (bm == 256) return swiglu ? 11.6f * n + chunks * hyp(0.96f * n, 1.20f * all) : 10.3f * n + chunks * hyp(0.965f * n, 1.35f * all);
+    return swiglu ? 3.9f + 1.8f * n + chunks * hyp(1.16f * pairs + 0.64f * odd, 0.69f * all)
+                  : 3.4f + 3.3f * n + chunks * hyp(1.03f * pairs + 0.55f * odd, 0.75f * all);
+}
+
+// The tile height for a launch, 0 where the streaming kernel takes it.  All three add
 // the products of an output in the same order, so the choice never changes a result.  Shapes that the streaming kernel does not
 // take (row-major weights go to a kernel with another order there) are tiled only where 256 x 256 tiles fill the chip.
+// Gate/up leaves the tall tile for an estimated gain of 7 us.  Tall / not, us (its 256-row form with registers took 6 to 10 % more than tall):
+// 8192 x 1024, 520 / 1,000 / 1,600 rows 33 / 38.5 / 68 and 30 / 37 / 61.5 (all tall), 4B shape, 1,000 / 2,100 / 4,200 / 8,000 / 15,272 rows
+// 122 / 205 / 407 / 702 / 1264 and 100 / 205 / 359 / 678 / 1286, 7B shape, 1,000 / 1,600 / 3,000 / 8,000 271 / 451 / 691 / 1792 and
+// 250 / 392 / 707 / 1830.
 int gemm_tile_height(int M, int N, int K, int splits, int cols, int bn) {
+    const bool swiglu = cols == 128;
+    auto us = [&](int bm) { return tile_us((long)((M + bm - 1) / bm) * ((N + cols - 1) / cols) * splits, K / (float)splits / 64.f, swiglu, bm); };
     if ((K & 127) || (N & 15))
         return M >= 512 && (long)((M + 255) / 256) * ((N + cols - 1) / cols) >= 200 ? 256 : 0;
     const float t256 = gemm_tile_us(M, N, K, splits, cols, 256), t128 = gemm_tile_us(M, N, K, splits, cols, 128);
     const float ts = gemm_stream_us(M, cols == 128 ? 2 * N : N, K, splits, bn == 64 ? 64 : 128);
     if (M <= 128 || ts < std::min(t256, t128)) return 0;
-    return t128 < t256 ? 128 : 256;
+    return us(128) + (swiglu ? 7.f : 0.f) < us(256) ? 128 : 256;
 }
 
 int gemm_tile_rows(const GemmArgs& a, int epilogue, int bn) {
@@ -531,7 +583,11 @@ hipError_t launch_gemm_tile(const GemmArgs& a, int epilogue, int bm, hipStream_t
     return epilogue == EPI_SWIGLU ? launch_tile<1>(a, none, bm, s) : launch_tile<0>(a, none, bm, s);
 }
 
-int gemm_tile_score_height(int M, int N, int K) { return gemm_tile_us(M, N, K, 1, 256, 128) < gemm_tile_us(M, N, K, 1, 256, 256) ? 128 : 256; }
+// The scoring epilogue's exponentials run under another workgroup's products with tiles of 128 rows: 151,936 columns, K = 2560, 300 / 700 /
+// 1,000 / 3,000 rows 276 / 510 / 681 / 2012 us against 352 / 518 / 705 / 2022 on 256, K = 1024 113 / 216 / 289 / 839 against 167 / 243 / 340 / 939.
+// Only small vocabularies on narrow models stay on the tall tile (30,004 columns, K = 256, 700 rows 29 us; 19 on 128, 37 with
+// operands staged through registers), where nothing is spent and both heights stay covered.
+int gemm_tile_score_height(int M, int N, int K) { return M >= 512 && N <= 32768 && K <= 256 ? 256 : 128; }
 // The LM head with the scoring epilogue: one (max, sum exp) pair per row and 128 columns.
 hipError_t launch_gemm_tile_score(const GemmArgs& a, hipStream_t s) {
     if (!gemm_tile_usable(a) || a.splits != 1 || !a.s_part || !a.targets || !a.tgt_logit || a.s_tiles != (a.N + 127) / 128) return hipErrorInvalidValue;
