@@ -516,7 +516,8 @@ __global__ __launch_bounds__(256) void attn_stream_kernel(AttnArgs a) {
     // increase strictly, so r + 1 is the number of entries that satisfy it: the lanes test 64 entries
     // at a time (one round of independent loads instead of a chain of dependent ones).
     int below = 0;
-    if (!STREAM) below = blockIdx.x / Hkv + 1;
+    const int pair_row = blockIdx.x / Hkv;
+    if (!STREAM) below = (FORM == DECODE_PAIR && a.order ? a.order[pair_row] : pair_row) + 1;
     else for (int base = 0; base < a.n_rows; base += 64) {
         const int j = min(base + lane, a.n_rows - 1);
         const bool hit = base + lane < a.n_rows && rps[j] * Hkv <= u;

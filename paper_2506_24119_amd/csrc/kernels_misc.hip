@@ -120,6 +120,16 @@ hipError_t launch_prefill_meta(const int32_t* cu_rows, const int32_t* base_pos, 
 // ---------------------------------------------------------------------------------------------
 // block reduction (256 threads)
 // ---------------------------------------------------------------------------------------------
+// Row r's place among the rows by falling position (equal ones by index), by one wave.
+__device__ __forceinline__ void write_place(const EmbedArgs& a, int r, int pos, int lane) {
+    int before = 0;
+    for (int j0 = 0; j0 < a.n_rows; j0 += 64) {
+        const int j = j0 + lane, other = j < a.n_rows ? a.row_pos[j] : -1;
+        before += __builtin_popcountll(__builtin_amdgcn_ballot_w64(other > pos || (other == pos && j < r)));
+    }
+    if (lane == 0) a.order[before] = r;
+}
+
 __device__ __forceinline__ float block_sum_256(float v, float* red) {
     v = wave_sum(v);
     const int wave = threadIdx.x >> 6;
@@ -143,6 +153,7 @@ __global__ __launch_bounds__(256) void embed_norm_kernel(EmbedArgs a, RopeFreq f
         double ang = (double)pos * f.inv_freq[threadIdx.x];
         a.rope[(size_t)r * a.half_hd + threadIdx.x] = make_float2((float)cos(ang), (float)sin(ang));
     }
+    if (a.order && threadIdx.x < 64) write_place(a, r, pos, threadIdx.x);
     if (threadIdx.x == 255)
         a.row_page[r] = make_int2(a.block_table[(size_t)a.row_seq[r] * a.max_blocks + (pos >> 4)], pos);
     int tok = a.tokens[r];
@@ -193,6 +204,7 @@ __global__ __launch_bounds__(1024) void embed_norm_wide_kernel(EmbedArgs a, Rope
         sincos((double)pos * f.inv_freq[tid], &sn, &cs);
         a.rope[(size_t)r * a.half_hd + tid] = make_float2((float)cs, (float)sn);
     }
+    if (a.order && tid < 64) write_place(a, r, pos, tid);
     if (tid == (int)blockDim.x - 1)
         a.row_page[r] = make_int2(a.block_table[(size_t)a.row_seq[r] * a.max_blocks + (pos >> 4)], pos);
     ss = wave_sum(ss);

@@ -6,6 +6,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <functional>
 #include <new>
 #include <string>
 #include <vector>
@@ -601,39 +602,71 @@ struct StepCtx {
     float temperature = 0.f;
     int32_t* out_tokens = nullptr;
     const int32_t *host_ids = nullptr, *host_pos = nullptr;   // prefill: sequences and the positions of their last tokens
+    int32_t* order = nullptr;                              // DECODE_PAIR: the rows by falling context, from the embedding kernel
     int first_layer = 0;
     const int32_t* q_rows = nullptr;                       // set: first_layer's k and v are in the pages and h is normed; q's rows of the
 };                                                         // rotation table
 
-// Pieces and partial results of the decode attention over c.rows rows; `pages`: the sum of the rows' page counts.
-static void plan_decode_attention(StepCtx& c, int pages_all, int max_ctx) {
+namespace spiral {
+// Whether a workgroup takes a whole (row, kv head) pair, longest pairs first (the kernel that looks up the embeddings ranks the rows), or the
+// batch's pages are cut into equal ranges.  A pair to a workgroup needs no search for its first page, writes no partial results and
+// needs no second launch; its price is the end, when the longest pairs are left and too few workgroups run to draw on the whole
+// memory rate: 7 MB in flight, 212 workgroups of four pages of 8 KB.  The pages that the missing ones would have read in that time are
+// the estimate here, at the rate of the rest, against 8.5 us of the other form (search, merge), plus 6 us where not all pairs
+// start at once, and against 2 us for each segment beyond four that a range may have to hold (a range of short rows
+// merges its waves once a row and kv head).  Below a quarter of the CUs in pairs the pages of one row are the bound: up to 256 tokens only.
+// Three layers and a head of 8,192, one step, us, equal ranges -> pairs longest first: 4B shape, 128 rows of 256..1,280 tokens 540 -> 519 (534
+// in the rows' own order), 400..2,000 637 -> 615, 16..2,000 619 -> 570, 60..4,000 886 -> 845, 1,024..5,120 1114 -> 1122 (stays);
+// 96 of 300..1,200 458 -> 439; 64 of 2,000..3,000 555 -> 536, of 2,000..6,000 722 -> 731 (stays); 36 of 500..3,000 341 -> 369 (stays); 24 of
+// 200..800 238 -> 229; 160 of 1,000..4,000 1182 -> 1154; 7B, 128 rows of 500..2,000 652 -> 638, 27 of 512..2,560 392 -> 420 (stays);
+// 0.6B, 64 of 500..2,000 302 -> 294, 128 of 1,000..4,000 765 -> 773 (stays).
+// All of that with heads of 128.  Narrower ones, whose pages are smaller, keep a line by the longest context: 512 tokens once a quarter of
+// the CUs has a pair, 1,536 once every CU has one and the mean is at least half of the longest (1,024, or 512 with fewer than four query heads a
+// pair, where the pairs are just above two to a CU; 1,024 with fewer than four query heads up to six to a CU).
+// `pages`: the rows' page counts, any order (are sorted); range: pages of a workgroup of the other form.
+bool decode_in_pairs(std::vector<int>& pages, int n_q_heads, int n_kv_heads, int head_dim, int n_cus, int range) {
+    const int rows = (int)pages.size(), pairs = rows * n_kv_heads;
+    std::sort(pages.begin(), pages.end(), std::greater<int>());
+    if (4 * pairs < n_cus) return pages[0] <= 16;
+    if (head_dim != 128) {
+        long all = 0;
+        for (int p : pages) all += p;
+        const int group = n_q_heads / n_kv_heads;
+        int most = pairs >= n_cus && (long)pages[0] * rows <= 2L * all ? 96 : 32;
+        if (pairs > 2 * n_cus && 2 * pairs < 5 * n_cus) most = std::min(most, group < 4 ? 32 : 64);
+        else if (pairs > 2 * n_cus && pairs < 6 * n_cus && group < 4) most = std::min(most, 64);
+        return pages[0] <= most;
+    }
+    // when the place of each row's workgroups runs dry, in pages: rows beyond the places go where the work ends first
+    const int places = std::max(1, std::min(rows, 3 * n_cus / n_kv_heads));
+    std::vector<int> end(pages.rend() - places, pages.rend());             // the longest, rising: a heap whose top is the least
+    for (int i = places; i < rows; ++i) {
+        std::pop_heap(end.begin(), end.end(), std::greater<int>());
+        end.back() += pages[i];
+        std::push_heap(end.begin(), end.end(), std::greater<int>());
+    }
+    std::sort(end.begin(), end.end(), std::greater<int>());
+    constexpr int kFull = 212;
+    long missing = 0;                                                      // workgroups x pages
+    for (int k = 0; k < places && (k + 1) * n_kv_heads < kFull; ++k)
+        missing += (long)(kFull - (k + 1) * n_kv_heads) * (end[k] - (k + 1 < places ? end[k + 1] : 0));
+    const float us = (float)missing * 8192.f / 6.8e6f + (rows > places ? 6.f : 0.f);
+    const float segments = std::min((float)n_kv_heads, (float)range / (float)pages.back());
+    return us < 8.5f + 2.f * std::max(0.f, segments - 4.f);
+}
+}  // namespace spiral
+
+// Pieces and partial results of the decode attention over c.rows rows; `pages`: the rows' page counts (are sorted), pages_all: their sum.
+static void plan_decode_attention(StepCtx& c, std::vector<int>& pages, int pages_all, int max_ctx) {
     const spiral_model* m = c.m;
     const int wgs = m->tune.attn_wgs > 0 ? m->tune.attn_wgs : 3 * m->n_cus;
     c.total_units = pages_all * m->cfg.n_kv_heads;
     c.units_per_wg = std::max(m->tune.chunk_pages, (c.total_units + wgs - 1) / wgs);
     c.n_slots = decode_slots(m, max_ctx);
-    // Short contexts: a workgroup to a pair, which needs no search for its first page, writes no partial results and needs no second
-    // launch.  Its price is that the longest pair is not shared out.  Four layers, us a step, stream -> workgroup to a pair: 0.6B
-    // shape, 1 row of 250 tokens 158 -> 143, of 400 153 -> 157, of 800 159 -> 176; 27 rows of 100 184 -> 160, of 400 205 -> 181, of
-    // 200..1,000 216 -> 207; 128 rows of 250 315 -> 294, of 200..1,000 431 -> 435; 4B, 3 rows of 250 265 -> 251, 8 (64 pairs) of 400
-    // 272 -> 265, of 800 282 -> 283; 128 of 100..400 532 -> 509; 7B, 27 of 400 486 -> 468.  So up to 256 tokens always, up to 512
-    // once a quarter of the CUs has a pair.  Up to 1,536 once every CU has one and the mean is at least half of
-    // the longest: 0.6B, 32 rows of 300..1,480 236 -> 230, 64 323 -> 315, 192 763 -> 758; 4B, 64 rows 470 -> 456, 128 743 -> 735 (of
-    // 1,200..1,480 879 -> 865); 7B, 128 788 -> 768.  Beyond: 4B, 128 rows of 400..2,000 859 -> 866, of 1,024..5,120 1471 -> 1510.
-    // Only up to 1,024 where the pairs are just above two to a CU, whose third round is nearly empty, and with fewer than four query heads
-    // a pair, whose partial results are small, up to six to a CU.  Step to step of five random batches, rows of 256..1,024 / 512..1,280 /
-    // 736..1,504 tokens: 4B 68 rows (544 pairs) 1.005 / 1.018 / 1.027, 80 0.983 / 0.993 / 0.997, 128 0.977 / 0.985 / 0.989; 7B 144 (576)
-    // 0.995 / 1.002 / 1.006, 176 0.983 / 0.982 / 0.983; 0.6B 72 (576) 1.021 / 1.036 / 1.045, 80 1.001 / 1.012 / 1.018, 112 0.998 / 1.007
-    // / 1.021, 128 0.996 / 1.018 / 1.016, 160 0.991 / 0.996 / 0.999, 184 0.981 / 0.985 / 0.988.  (One batch may be a percent off the mean of
-    // its kind: which pairs share a CU follows from the rows' order.)
-    const int pairs = c.rows * m->cfg.n_kv_heads, longest = (max_ctx + kPageTokens - 1) / kPageTokens;
-    const bool even = (long)longest * pairs <= 2L * c.total_units;
-    const int cus = m->n_cus, group = m->cfg.n_q_heads / m->cfg.n_kv_heads;
-    int most = pairs >= cus && even ? 96 : 4 * pairs >= cus ? 32 : 16;
-    if (pairs > 2 * cus && 2 * pairs < 5 * cus) most = std::min(most, group < 4 ? 32 : 64);
-    else if (pairs > 2 * cus && pairs < 6 * cus && group < 4) most = std::min(most, 64);
-    if (!m->tune.chunk_set && !m->tune.attn_wgs && longest <= most) {
+    if (!m->tune.chunk_set && !m->tune.attn_wgs &&
+        decode_in_pairs(pages, m->cfg.n_q_heads, m->cfg.n_kv_heads, m->cfg.head_dim, m->n_cus, c.units_per_wg)) {
         c.form = DECODE_PAIR;
+        c.order = c.w.last_rows;
         return;
     }
     if (!m->tune.chunk_set && c.units_per_wg == m->tune.chunk_pages) {
@@ -641,9 +674,9 @@ static void plan_decode_attention(StepCtx& c, int pages_all, int max_ctx) {
         // is its chain of dependent steps, of which 16 pages are four per wave: one row of 250 tokens, 4B shape, pieces of
         // 16 / 8 / 4 / 2 pages 8.8 / 7.0 / 5.9 / 4.1 us; 1,450 tokens in 16 pieces 5.3 us, in 32 9.4.  The larger
         // number of partial results goes to the q/k/v products' memory, dead by then.
-        const int pages = (max_ctx + kPageTokens - 1) / kPageTokens;
-        const int units = std::max((c.total_units + wgs - 1) / wgs, (pages + kDecodePieces - 1) / kDecodePieces);
-        const int slots = (pages + units - 1) / units + 2;
+        const int longest = (max_ctx + kPageTokens - 1) / kPageTokens;
+        const int units = std::max((c.total_units + wgs - 1) / wgs, (longest + kDecodePieces - 1) / kDecodePieces);
+        const int slots = (longest + units - 1) / units + 2;
         const size_t need = (size_t)c.rows * m->cfg.n_q_heads * slots * (m->cfg.head_dim + 2) * sizeof(float);
         if (units < c.units_per_wg && need <= (size_t)((char*)c.w.q - (char*)c.w.qkv)) {
             c.units_per_wg = units;
@@ -863,7 +896,7 @@ static int run_layers(StepCtx& c) {
         aa.scale_log2e = (float)(1.4426950408889634 / std::sqrt((double)hd));
         if (c.decode) {
             aa.row_page_start = c.w.page_start; aa.units_per_wg = c.units_per_wg; aa.total_units = c.total_units;
-            aa.n_chunks = c.n_slots; aa.out_frag = o_frag; aa.form = c.form;
+            aa.n_chunks = c.n_slots; aa.out_frag = o_frag; aa.form = c.form; aa.order = c.order;
             HIP_TRY(timed(m, SPIRAL_K_ATTN_DECODE, c.s, [&] { return launch_attn_stream(aa, hd, act32, c.s); }));
             if (c.form != DECODE_PAIR) HIP_TRY(timed(m, SPIRAL_K_ATTN_COMBINE, c.s, [&] { return launch_attn_stream_combine(aa, hd, act32, c.s); }));
         } else {
@@ -1104,12 +1137,14 @@ static int decode_impl(spiral_model* m, spiral_kv_pool* p, const int32_t* host_s
         const int32_t* src[4] = {host_seq_ids, pos.data(), start.data(), keys.data()};
         const int cnt[4] = {B, B, B + 1, (int)keys.size()};
         HIP_TRY(launch_upload_multi(dst, src, cnt, keys.empty() ? 3 : 4, s));
+        StepCtx c = {m, p, w, s, B, B, true, 1, decode_chunks(m, max_ctx), dev_logits};
+        std::vector<int> pages(B);
+        for (int i = 0; i < B; ++i) pages[i] = start[i + 1] - start[i];
+        plan_decode_attention(c, pages, start[B], max_ctx);
         EmbedArgs e = {dev_in_tokens, m->w[0], (const float*)m->lw(0, SPIRAL_W_ATTN_NORM), w.x, w.h,
                        w.row_pos, w.rope, B, m->cfg.d_model, m->cfg.head_dim / 2, m->cfg.vocab, m->cfg.rms_eps,
-                       w.row_seq, p->d_block_table, p->max_blocks, w.row_page, qkv_in_frag(m, B)};
+                       w.row_seq, p->d_block_table, p->max_blocks, w.row_page, qkv_in_frag(m, B), c.order};
         HIP_TRY(launch_embed_norm(e, m->freq, m->w_bf16, !m->w_bf16, s));
-        StepCtx c = {m, p, w, s, B, B, true, 1, decode_chunks(m, max_ctx), dev_logits};
-        plan_decode_attention(c, start[B], max_ctx);
         if (sp) { c.sample = true; c.temperature = sp->temperature; c.out_tokens = sp->dev_out_tokens; }
         return run_layers(c);
     };

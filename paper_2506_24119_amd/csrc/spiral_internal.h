@@ -85,6 +85,7 @@ struct AttnArgs {
     float scale_log2e;        // log2(e) / sqrt(hd)
     int32_t out_frag;         // 16-bit out, at most 128 rows: in act_frag() order
     int32_t form;             // decode: DecodeForm
+    const int32_t* order;     // or null: DECODE_PAIR: the rows in the order in which their workgroups start
 };
 
 // Launchers (defined in the kernel translation units).  All enqueue on `s` and return the launch status.
@@ -109,6 +110,7 @@ struct EmbedArgs {
     const int32_t* row_seq; const int32_t* block_table; int32_t max_blocks;
     int2* row_page;           // [rows], written
     int32_t h_frag;           // h in act_frag() order
+    int32_t* order;           // or null: [rows], the rows from the longest context to the shortest, written
 };
 hipError_t launch_embed_norm(const EmbedArgs& a, const RopeFreq& f, bool w_bf16, bool act32, hipStream_t s);
 
