@@ -490,8 +490,9 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(AttnArgs a, Prefil
 // 128 rows of 1,280 tokens, 7 % of a step):
 //   DECODE_PAIR: short contexts (the host's rule): a workgroup has one pair to itself and writes the output: no search, no partial
 //   results, no merging launch.  27 rows of 400 tokens, 0.6B shape: 6 us a layer less of 51.
-//   DECODE_PIECES: the last rows of a prefill: workgroup (x, y) has pages y * U to (y + 1) * U of pair x, if there are any, and writes the
-//   pair's part y.  Where a pair is cut, and with it the order of its sums, follows from its own context, not from the call's others.
+//   DECODE_PIECES: the last rows of a prefill, and small batches: workgroup (x, y) has pages y * U to (y + 1) * U of pair x, if there are any, and
+//   writes the pair's part y: no search, and one pair only.  Where a pair is cut follows from its own pages and U, which a prefill's last rows
+//   leave fixed, so that the order of their sums follows from their own context, not from the call's others.
 template <int HD, bool ACT32, int FORM>
 __global__ __launch_bounds__(256) void attn_stream_kernel(AttnArgs a) {
     constexpr int KS = HD / 32, MT = HD / 16, OSTRIDE = HD + 4;
@@ -507,41 +508,45 @@ __global__ __launch_bounds__(256) void attn_stream_kernel(AttnArgs a) {
     const int li = lane & 15, lg = lane >> 4;
     const int U = a.units_per_wg;
     const int32_t* rps = a.row_page_start;
-    const int T = rps[a.n_rows] * Hkv;
+    const int T = a.total_units;
     int u = blockIdx.x * U;
     if (STREAM && u >= T) return;
     int u_end = min(u + U, T);
 
-    // the row that holds unit u: the largest r with row_page_start[r] * Hkv <= u.  The prefix sums
-    // increase strictly, so r + 1 is the number of entries that satisfy it: the lanes test 64 entries
-    // at a time (one round of independent loads instead of a chain of dependent ones).
-    int below = 0;
-    const int pair_row = blockIdx.x / Hkv;
-    if (!STREAM) below = (FORM == DECODE_PAIR && a.order ? a.order[pair_row] : pair_row) + 1;
-    else for (int base = 0; base < a.n_rows; base += 64) {
-        const int j = min(base + lane, a.n_rows - 1);
-        const bool hit = base + lane < a.n_rows && rps[j] * Hkv <= u;
-        below += __builtin_popcountll(__builtin_amdgcn_ballot_w64(hit));
-    }
-    const int lo = __builtin_amdgcn_readfirstlane(below) - 1;
     struct Seg { int r, kvh, p0, p1, np, rs, pos; const int32_t* bt; };
     Seg cur;
-    cur.r = lo;
-    cur.rs = rps[lo];
-    cur.np = rps[lo + 1] - cur.rs;
     if (STREAM) {
+        // the row that holds unit u: the largest r with row_page_start[r] * Hkv <= u.  The prefix sums
+        // increase strictly, so r + 1 is the number of entries that satisfy it: the lanes test 64 entries
+        // at a time (one round of independent loads instead of a chain of dependent ones).
+        int below = 0;
+        for (int base = 0; base < a.n_rows; base += 64) {
+            const int j = min(base + lane, a.n_rows - 1);
+            const bool hit = base + lane < a.n_rows && rps[j] * Hkv <= u;
+            below += __builtin_popcountll(__builtin_amdgcn_ballot_w64(hit));
+        }
+        cur.r = __builtin_amdgcn_readfirstlane(below) - 1;
+        cur.rs = rps[cur.r];
+        cur.np = rps[cur.r + 1] - cur.rs;
+        cur.pos = a.row_pos[cur.r];
         cur.kvh = (u - cur.rs * Hkv) / cur.np;
         cur.p0 = (u - cur.rs * Hkv) % cur.np;
     } else {
+        // (the row, position and sequence as arguments by value instead: the larger launches cost the host more, 0.3 us each, than the
+        // look-ups cost here; one row of a 0.6B model 938 -> 966 us a step)
+        const int i = blockIdx.x / Hkv;
+        cur.r = FORM == DECODE_PAIR && a.order ? a.order[i] : i;
+        cur.rs = 0;
+        cur.pos = a.row_pos[cur.r];
+        cur.np = cur.pos / kPageTokens + 1;
         cur.kvh = blockIdx.x % Hkv;
         cur.p0 = FORM == DECODE_PIECES ? blockIdx.y * U : 0;
         if (cur.p0 >= cur.np) return;            // the longest pair has more pieces
-        u = cur.rs * Hkv + cur.kvh * cur.np + cur.p0;
+        u = cur.p0;
         u_end = u + (FORM == DECODE_PIECES ? U : cur.np);
     }
     cur.p1 = min(cur.np, cur.p0 + (u_end - u));
-    cur.pos = a.row_pos[lo];
-    cur.bt = a.block_table + (size_t)a.row_seq[lo] * a.max_blocks;
+    cur.bt = a.block_table + (size_t)a.row_seq[cur.r] * a.max_blocks;
 
     const size_t page_elems = (size_t)Hkv * (2 * kPageTokens * HD);
     constexpr int head_elems = 2 * kPageTokens * HD;
@@ -637,8 +642,7 @@ __global__ __launch_bounds__(256) void attn_stream_kernel(AttnArgs a) {
         }
         __syncthreads();
         {
-            const int pair_start = cur.rs * Hkv + cur.kvh * cur.np;
-            const int slot = FORM == DECODE_PIECES ? blockIdx.y : blockIdx.x - pair_start / U;
+            const int slot = STREAM ? blockIdx.x - (cur.rs * Hkv + cur.kvh * cur.np) / U : blockIdx.y;
             float* dst0 = a.part + (((size_t)cur.r * Hkv + cur.kvh) * a.n_chunks + slot) * G * (HD + 2);
             for (int e = threadIdx.x; e < G * HD; e += 256) {
                 const int j = e / HD, i = e % HD;
@@ -737,9 +741,8 @@ static hipError_t stream_impl(const AttnArgs& a, hipStream_t s) {
     const size_t lds = (size_t)(4 * G * (HD + 4) + 128) * sizeof(float);
     const int pairs = a.n_rows * a.n_kv_heads, wgs = (a.total_units + a.units_per_wg - 1) / a.units_per_wg;
     if (a.form == DECODE_PAIR) hipLaunchKernelGGL((attn_stream_kernel<HD, ACT32, DECODE_PAIR>), dim3(pairs), dim3(256), lds, s, a);
-    else if (a.form == DECODE_STREAM) hipLaunchKernelGGL((attn_stream_kernel<HD, ACT32, DECODE_STREAM>), dim3(wgs), dim3(256), lds, s, a);
-    else if constexpr (!ACT32) hipLaunchKernelGGL((attn_stream_kernel<HD, ACT32, DECODE_PIECES>), dim3(pairs, a.n_chunks), dim3(256), lds, s, a);
-    else return hipErrorInvalidValue;            // only prefills with 16-bit weights have such rows
+    else if (a.form == DECODE_PIECES) hipLaunchKernelGGL((attn_stream_kernel<HD, ACT32, DECODE_PIECES>), dim3(pairs, a.n_chunks), dim3(256), lds, s, a);
+    else hipLaunchKernelGGL((attn_stream_kernel<HD, ACT32, DECODE_STREAM>), dim3(wgs), dim3(256), lds, s, a);
     return hipGetLastError();
 }
 

@@ -601,7 +601,7 @@ struct StepCtx {
     bool sample = false;                                   // fused LM head + sampler (no logits written)
     float temperature = 0.f;
     int32_t* out_tokens = nullptr;
-    const int32_t *host_ids = nullptr, *host_pos = nullptr;   // prefill: sequences and the positions of their last tokens
+    const int32_t *host_ids = nullptr, *host_pos = nullptr;   // sequences and the positions of their (last) tokens
     int32_t* order = nullptr;                              // DECODE_PAIR: the rows by falling context, from the embedding kernel
     int first_layer = 0;
     const int32_t* q_rows = nullptr;                       // set: first_layer's k and v are in the pages and h is normed; q's rows of the
@@ -623,10 +623,9 @@ namespace spiral {
 // All of that with heads of 128.  Narrower ones, whose pages are smaller, keep a line by the longest context: 512 tokens once a quarter of
 // the CUs has a pair, 1,536 once every CU has one and the mean is at least half of the longest (1,024, or 512 with fewer than four query heads a
 // pair, where the pairs are just above two to a CU; 1,024 with fewer than four query heads up to six to a CU).
-// `pages`: the rows' page counts, any order (are sorted); range: pages of a workgroup of the other form.
-bool decode_in_pairs(std::vector<int>& pages, int n_q_heads, int n_kv_heads, int head_dim, int n_cus, int range) {
+// `pages`: the rows' page counts, falling; range: pages of a workgroup of the other form.
+bool decode_in_pairs(const std::vector<int>& pages, int n_q_heads, int n_kv_heads, int head_dim, int n_cus, int range) {
     const int rows = (int)pages.size(), pairs = rows * n_kv_heads;
-    std::sort(pages.begin(), pages.end(), std::greater<int>());
     if (4 * pairs < n_cus) return pages[0] <= 16;
     if (head_dim != 128) {
         long all = 0;
@@ -656,26 +655,49 @@ bool decode_in_pairs(std::vector<int>& pages, int n_q_heads, int n_kv_heads, int
 }
 }  // namespace spiral
 
-// Pieces and partial results of the decode attention over c.rows rows; `pages`: the rows' page counts (are sorted), pages_all: their sum.
-static void plan_decode_attention(StepCtx& c, std::vector<int>& pages, int pages_all, int max_ctx) {
+// Form, pieces and partial results of the decode attention over c.rows rows; pages_all: the sum of their page counts.
+static void plan_decode_attention(StepCtx& c, int pages_all, int max_ctx) {
     const spiral_model* m = c.m;
-    const int wgs = m->tune.attn_wgs > 0 ? m->tune.attn_wgs : 3 * m->n_cus;
-    c.total_units = pages_all * m->cfg.n_kv_heads;
+    const int wgs = m->tune.attn_wgs > 0 ? m->tune.attn_wgs : 3 * m->n_cus, kv = m->cfg.n_kv_heads;
+    c.total_units = pages_all * kv;
     c.units_per_wg = std::max(m->tune.chunk_pages, (c.total_units + wgs - 1) / wgs);
     c.n_slots = decode_slots(m, max_ctx);
-    if (!m->tune.chunk_set && !m->tune.attn_wgs &&
-        decode_in_pairs(pages, m->cfg.n_q_heads, m->cfg.n_kv_heads, m->cfg.head_dim, m->n_cus, c.units_per_wg)) {
-        c.form = DECODE_PAIR;
-        c.order = c.w.last_rows;
-        return;
+    if (m->tune.chunk_set) return;
+    const bool few = c.units_per_wg == m->tune.chunk_pages;
+    const int longest = (max_ctx + kPageTokens - 1) / kPageTokens;
+    int units = std::max((c.total_units + wgs - 1) / wgs, (longest + kDecodePieces - 1) / kDecodePieces);
+    if (!m->tune.attn_wgs) {
+        std::vector<int> pages(c.rows);
+        for (int i = 0; i < c.rows; ++i) pages[i] = c.host_pos[i] / kPageTokens + 1;
+        std::sort(pages.begin(), pages.end(), std::greater<int>());
+        if (decode_in_pairs(pages, m->cfg.n_q_heads, kv, m->cfg.head_dim, m->n_cus, c.units_per_wg)) {
+            c.form = DECODE_PAIR;
+            c.order = c.w.last_rows;
+            return;
+        }
+        // Few units (a small batch): up to 16 pieces to a pair, counted from its first page, as short as the places hold all of
+        // them at once.  Against equal ranges of the whole batch (below) a workgroup has one pair and looks for nothing.  One step, us, ranges -> pieces: a
+        // 0.6B model, 1 row of 400 tokens 954 -> 938, of 1,450 1025 -> 975, 3 of 200..1,500 1092 -> 1058; four 4B layers, 5 of 200..1,500
+        // 275 -> 267; three 7B layers, 9 of 300..2,000 348 -> 342, 27 of 512..2,560 392.5 -> 390.
+        auto pieces = [&](int u) { int n = 0; for (int p : pages) n += (p + u - 1) / u; return n * kv; };
+        int u = units;
+        while (u <= c.units_per_wg && pieces(u) > wgs) ++u;
+        const int slots = (longest + u - 1) / u;
+        const size_t need = (size_t)c.rows * m->cfg.n_q_heads * slots * (m->cfg.head_dim + 2) * sizeof(float);
+        const bool borrow = slots > c.n_slots;               // the q/k/v products' memory, dead by then
+        if (few && u <= c.units_per_wg && (!borrow || need <= (size_t)((char*)c.w.q - (char*)c.w.qkv))) {
+            c.form = DECODE_PIECES;
+            c.units_per_wg = u;
+            c.n_slots = slots;
+            if (borrow) c.w.attn_part = c.w.qkv;
+            return;
+        }
     }
-    if (!m->tune.chunk_set && c.units_per_wg == m->tune.chunk_pages) {
-        // Few units (a small batch): as many workgroups as there are pages, up to 16 pieces to a pair.  A workgroup's time
+    if (few) {
+        // Equal ranges as short as there are pages, up to 16 to a pair.  A workgroup's time
         // is its chain of dependent steps, of which 16 pages are four per wave: one row of 250 tokens, 4B shape, pieces of
         // 16 / 8 / 4 / 2 pages 8.8 / 7.0 / 5.9 / 4.1 us; 1,450 tokens in 16 pieces 5.3 us, in 32 9.4.  The larger
         // number of partial results goes to the q/k/v products' memory, dead by then.
-        const int longest = (max_ctx + kPageTokens - 1) / kPageTokens;
-        const int units = std::max((c.total_units + wgs - 1) / wgs, (longest + kDecodePieces - 1) / kDecodePieces);
         const int slots = (longest + units - 1) / units + 2;
         const size_t need = (size_t)c.rows * m->cfg.n_q_heads * slots * (m->cfg.head_dim + 2) * sizeof(float);
         if (units < c.units_per_wg && need <= (size_t)((char*)c.w.q - (char*)c.w.qkv)) {
@@ -1138,9 +1160,8 @@ static int decode_impl(spiral_model* m, spiral_kv_pool* p, const int32_t* host_s
         const int cnt[4] = {B, B, B + 1, (int)keys.size()};
         HIP_TRY(launch_upload_multi(dst, src, cnt, keys.empty() ? 3 : 4, s));
         StepCtx c = {m, p, w, s, B, B, true, 1, decode_chunks(m, max_ctx), dev_logits};
-        std::vector<int> pages(B);
-        for (int i = 0; i < B; ++i) pages[i] = start[i + 1] - start[i];
-        plan_decode_attention(c, pages, start[B], max_ctx);
+        c.host_ids = host_seq_ids; c.host_pos = pos.data();
+        plan_decode_attention(c, start[B], max_ctx);
         EmbedArgs e = {dev_in_tokens, m->w[0], (const float*)m->lw(0, SPIRAL_W_ATTN_NORM), w.x, w.h,
                        w.row_pos, w.rope, B, m->cfg.d_model, m->cfg.head_dim / 2, m->cfg.vocab, m->cfg.rms_eps,
                        w.row_seq, p->d_block_table, p->max_blocks, w.row_page, qkv_in_frag(m, B), c.order};
