@@ -208,11 +208,12 @@ __global__ __launch_bounds__(256, WAVES) void gemm_decode_kernel(GemmArgs g) {
                     const float T = g.s_temperature;
                     const uint64_t key = (T > 0.f && m < g.M) ? g.s_keys[m] : 0ull;
                     const float x[4] = {v.x, v.y, v.z, v.w};
+                    const uint64_t at = noise_at(key, c);
                     float bv = -INFINITY;
                     int bi = 0x7FFFFFFF;
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
-                        const float sc = T > 0.f ? x[e] / T + gumbel_noise(key, c + e) : x[e];
+                        const float sc = T > 0.f ? x[e] / T + gumbel_noise(at + (uint64_t)e * kNoiseStep) : x[e];
                         if (c + e < g.N && better(sc, c + e, bv, bi)) { bv = sc; bi = c + e; }
                     }
 #pragma unroll

@@ -175,6 +175,7 @@ __global__ __launch_bounds__(256) void gemm_stream_kernel(GemmArgs g) {
             const int row = (wm * MW + t) * 32 + l32;
             const int m = m0 + row;
             const uint64_t key = (T > 0.f && m < g.M) ? g.s_keys[m] : 0ull;
+            const uint64_t at = noise_at(key, n_first + 4 * lh);
             float bv = -INFINITY;
             int bi = 0x7FFFFFFF;
 #pragma unroll
@@ -183,7 +184,7 @@ __global__ __launch_bounds__(256) void gemm_stream_kernel(GemmArgs g) {
                 for (int i = 0; i < 4; ++i) {
                     const int n = n_first + 8 * b + 4 * lh + i;
                     float sc = acc[t][4 * b + i];
-                    if (T > 0.f) sc = sc / T + gumbel_noise(key, n);
+                    if (T > 0.f) sc = sc / T + gumbel_noise(at + (uint64_t)(8 * b + i) * kNoiseStep);
                     if (n < g.N && better(sc, n, bv, bi)) { bv = sc; bi = n; }
                 }
             const float ov = __shfl_xor(bv, 32, 64);

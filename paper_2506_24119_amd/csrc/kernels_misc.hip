@@ -3,6 +3,8 @@
 // sampler, and the by-value uploads that keep the library free of device allocations.
 #include <algorithm>
 
+#include <type_traits>
+
 #include "spiral_internal.h"
 #include "mfma_ops.h"
 
@@ -500,10 +502,11 @@ hipError_t launch_repack(const void* src0, const void* src1, const void* src2, i
 // can be computed again from the index, so the slices compete for out[row] by compare-and-swap on the index.  The order (score,
 // then index) is total, so the result does not depend on who comes first; out[row] starts as 0, which a NaN at index 0 does
 // not defend.
-// Bound by the generator's 64-bit arithmetic.  In a long slice most entries cannot win and are told apart without a logarithm
-// (noise_may_win, with the best score any thread has found so far; the product with 1/T stands for the division there).
-// Measured with 151,936 entries against a workgroup per row and two logarithms per entry: 128 rows, T = 1 77 -> 34 us, greedy
-// 30 -> 19; 16 rows 75 -> 18 and 27 -> 14; one row 74 -> 14 and 27 -> 14.
+// Bound by the generator's 64-bit arithmetic (vector units busy three quarters of the time): six integer multiplications an entry, the counter
+// moving by known steps and only the upper half of the last product made.  In a long slice most entries cannot win and are told apart
+// without a logarithm.  Measured with 151,936 entries, us, a workgroup per row and two logarithms per entry / nine multiplications and an exponential in
+// the screen, four-byte loads that each step waited for / now: 128 rows, T = 1 77 / 33.4 / 27.6, T = 0.6 (200 rows) - / 67 / 57, greedy 30 / 18.5 / 17.3;
+// 16 rows 75 / 17.5 / 17.1; one row 74 / 13.4 / 13.4 (two launches from the host).  128 rows of 20,000 13.0 -> 11.6.
 // ---------------------------------------------------------------------------------------------
 // Where a row is cut: the launch that sets out[row] costs 3 us.  One workgroup per row against slices (us, one and 128 rows; a
 // call does not get below 11 from the host): greedy 65,536 entries 10.6 / 10.3 against 13.3 / 13.3, 98,304 13.2 / 15.2
@@ -532,10 +535,12 @@ __global__ void sample_begin_kernel(int32_t* out, int n) {
     if (i < n) out[i] = 0;
 }
 
-template <int MODE, bool SCREEN>
+// VEC: neighbouring entries a thread loads at once, 4 where the rows are 16-byte aligned and their length is a multiple.
+template <int MODE, bool SCREEN, int VEC>
 __global__ __launch_bounds__(kSampleThreads) void sample_kernel(const float* logits, int V, float temperature, int per_slice,
                                                                 KeyChunk keys, const float* noise, int32_t* out) {
-    constexpr int NT = kSampleThreads, U = 8;
+    constexpr int NT = kSampleThreads, LOADS = VEC == 4 ? 2 : 8, STEP = LOADS * NT * VEC;
+    typedef __attribute__((ext_vector_type(VEC))) float vec;
     __shared__ float s_v[NT / 64];
     __shared__ int s_i[NT / 64];
     __shared__ int s_best;                       // largest score any thread has found, as an ordered integer
@@ -547,7 +552,6 @@ __global__ __launch_bounds__(kSampleThreads) void sample_kernel(const float* log
     float bv = -INFINITY;
     int bi = 0x7FFFFFFF;
     float bound = -INFINITY, pass = -INFINITY;   // a score of the row that an entry has to beat, and that less its slack
-    const float inv_t = 1.0f / temperature;
     if (SCREEN) {
         if (tid == 0) s_best = ordered_bits(__float_as_int(-INFINITY));
         __syncthreads();
@@ -558,34 +562,61 @@ __global__ __launch_bounds__(kSampleThreads) void sample_kernel(const float* log
         }
         __syncthreads();
     }
-    // eight loads in flight per thread (past the end they re-read the last entry: a branch around a load makes
-    // every load wait)
-    for (int base = lo + tid; base < hi; base += NT * U) {
-        float l[U];
+    // The screen, an entry's logit l against the best score so far: g > best - z needs w = 1 - u < -ln u < e^(z - best).  In units of 2^-23
+    // of a binary logarithm: the bits of a positive float, as an integer, are at most its logarithm (127 added) in these units, so an entry is out where the
+    // bits of a lower bound of w are no less than (z - best) in them, one product and sum with z = l / T.  Its rounding matters only for z within
+    // about 20 of best (beyond, no noise makes up for it, or any does), and is with that of the rest (2^-17 each) below the 1e-3 + 2e-6 |best| that
+    // `pass` takes off the bound.  Infinite and undefined values pass, and all do where the scale is not finite.
+    const float c = 1.4426950408889634f * 8388608.f / temperature;
+    const float scale = c < INFINITY ? c : NAN;
+    auto may_win = [&](uint64_t at, float l) {
+        const uint32_t r = mix64_upper(at);
+        const float w = fmaf((float)r, -2.3283064365386963e-10f, 1.f - 2.384185791015625e-07f);      // 1 - r 2^-32 - 2^-22 <= 1 - u
+        return !((float)__float_as_int(w) >= fmaf(l, scale, -pass));
+    };
+    auto visit = [&](int v, uint64_t at, float l, float n) {
+        float sc = l;
+        if (MODE != 0) sc = sc / temperature + (MODE == 2 ? n : gumbel_noise(at));
+        if (better(sc, v, bv, bi)) {
+            bv = sc; bi = v;
+            if (SCREEN && sc > bound) atomicMax(&s_best, ordered_bits(__float_as_int(sc)));
+        }
+    };
+    // The next step's loads are in flight while this one's entries are visited (past the end they re-read the last entries: a branch
+    // around a load makes every load wait).
+    vec l[LOADS], l_next[LOADS], nz[LOADS], nz_next[LOADS];
+    auto load = [&](int base) {
 #pragma unroll
-        for (int u = 0; u < U; ++u) l[u] = lr[min(base + u * NT, hi - 1)];
+        for (int u = 0; u < LOADS; ++u) {
+            const int v = min(base + u * NT * VEC, hi - VEC);
+            l_next[u] = *(const vec*)(lr + v);
+            if (MODE == 2) nz_next[u] = *(const vec*)(nr + v);
+        }
+    };
+    int base = lo + tid * VEC;
+    if (base < hi) load(base);
+    for (; base < hi; base += STEP) {
+#pragma unroll
+        for (int u = 0; u < LOADS; ++u) { l[u] = l_next[u]; if (MODE == 2) nz[u] = nz_next[u]; }
+        load(base + STEP);
+        const uint64_t at = noise_at(key, base);
+        bool in[LOADS * VEC], any = !SCREEN;
         if (SCREEN) {
             bound = __int_as_float(ordered_bits(*(volatile int*)&s_best));
-            pass = noise_pass(bound);
-        }
+            pass = (bound - 1e-3f - 2e-6f * fabsf(bound)) * (1.4426950408889634f * 8388608.f) - 127.f * 8388608.f;
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int v = base + u * NT;
-            if (v >= hi) continue;
-            if (SCREEN) {
-                if (noise_may_win(key, v, l[u] * inv_t, pass)) {
-                    const float sc = l[u] / temperature + gumbel_noise(key, v);
-                    if (better(sc, v, bv, bi)) {
-                        bv = sc; bi = v;
-                        if (sc > bound) atomicMax(&s_best, ordered_bits(__float_as_int(sc)));
-                    }
-                }
-            } else {
-                float sc = l[u];
-                if (MODE != 0) sc = sc / temperature + (MODE == 2 ? nr[v] : gumbel_noise(key, v));
-                if (better(sc, v, bv, bi)) { bv = sc; bi = v; }
-            }
+            for (int u = 0; u < LOADS; ++u)
+#pragma unroll
+                for (int e = 0; e < VEC; ++e) any |= in[u * VEC + e] = may_win(at + (uint64_t)(u * NT * VEC + e) * kNoiseStep, l[u][e]);
         }
+        if (any)
+#pragma unroll
+            for (int u = 0; u < LOADS; ++u)
+                if (base + u * NT * VEC < hi)
+#pragma unroll
+                    for (int e = 0; e < VEC; ++e)
+                        if (!SCREEN || in[u * VEC + e])
+                            visit(base + u * NT * VEC + e, at + (uint64_t)(u * NT * VEC + e) * kNoiseStep, l[u][e], MODE == 2 ? nz[u][e] : 0.f);
     }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) {
@@ -621,15 +652,22 @@ hipError_t launch_sample(const float* logits, int B, int V, float temperature, c
         const int m = B - off < 128 ? B - off : 128;
         for (int i = 0; i < m; ++i) k.key[i] = host_keys ? host_keys[off + i] : 0;
         const int slices = sample_slices(m, V, mode);
-        const int per = (V + slices - 1) / slices;
-        const dim3 g((V + per - 1) / per, m), b(kSampleThreads);
         const float* lg = logits + (size_t)off * V;
         const float* nz = noise ? noise + (size_t)off * V : nullptr;
+        const bool wide = (V & 3) == 0 && (((uintptr_t)lg | (uintptr_t)(mode == 2 ? nz : lg)) & 15) == 0;
+        int per = (V + slices - 1) / slices;
+        if (wide) per = (per + 3) & ~3;
+        const dim3 g((V + per - 1) / per, m), b(kSampleThreads);
         if (g.x > 1) hipLaunchKernelGGL(sample_begin_kernel, dim3((m + 255) / 256), dim3(256), 0, s, out + off, m);
-        if (mode == 0) hipLaunchKernelGGL((sample_kernel<0, false>), g, b, 0, s, lg, V, temperature, per, k, nz, out + off);
-        else if (mode == 2) hipLaunchKernelGGL((sample_kernel<2, false>), g, b, 0, s, lg, V, temperature, per, k, nz, out + off);
-        else if (sample_screens(per)) hipLaunchKernelGGL((sample_kernel<1, true>), g, b, 0, s, lg, V, temperature, per, k, nz, out + off);
-        else hipLaunchKernelGGL((sample_kernel<1, false>), g, b, 0, s, lg, V, temperature, per, k, nz, out + off);
+        auto go = [&](auto vec) {
+            constexpr int VEC = decltype(vec)::value;
+            if (mode == 0) hipLaunchKernelGGL((sample_kernel<0, false, VEC>), g, b, 0, s, lg, V, temperature, per, k, nz, out + off);
+            else if (mode == 2) hipLaunchKernelGGL((sample_kernel<2, false, VEC>), g, b, 0, s, lg, V, temperature, per, k, nz, out + off);
+            else if (sample_screens(per)) hipLaunchKernelGGL((sample_kernel<1, true, VEC>), g, b, 0, s, lg, V, temperature, per, k, nz, out + off);
+            else hipLaunchKernelGGL((sample_kernel<1, false, VEC>), g, b, 0, s, lg, V, temperature, per, k, nz, out + off);
+        };
+        if (wide) go(std::integral_constant<int, 4>());
+        else go(std::integral_constant<int, 1>());
         e = hipGetLastError();
         if (e != hipSuccess) return e;
     }

@@ -473,8 +473,9 @@ __global__ __launch_bounds__(kThreads) void trunc_select_kernel(const float* log
         const int b = bin_of(z, r.zmax);
         if (b < r.cand_lo) {
             const float bound = __int_as_float(ordered_bits(*(volatile int*)&s_best));
-            if (!nr && !noise_may_win(key64, v, z, noise_pass(bound))) return;
-            const float sc = z + (nr ? nr[v] : gumbel_noise(key64, v));
+            const uint64_t at = noise_at(key64, v);
+            if (!nr && !noise_may_win(at, z, noise_pass(bound))) return;
+            const float sc = z + (nr ? nr[v] : gumbel_noise(at));
             if (better(sc, v, bv, bi)) {
                 bv = sc; bi = v;
                 if (sc > bound) atomicMax(&s_best, ordered_bits(__float_as_int(sc)));

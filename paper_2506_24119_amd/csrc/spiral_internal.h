@@ -271,24 +271,35 @@ template <> struct ActStore<false> {
 };
 
 // ---- the sampler's counter generator (same stream in every kernel that draws noise)
-__device__ __forceinline__ uint64_t mix64(uint64_t z) {
-    z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
-    z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
-    return z ^ (z >> 31);
+// z ^ (z >> s), s < 32, in 32-bit steps
+__device__ __forceinline__ uint64_t xor_shifted(uint64_t z, int s) {
+    const uint32_t lo = (uint32_t)z, hi = (uint32_t)(z >> 32);
+    return ((uint64_t)(hi ^ (hi >> s)) << 32) | (lo ^ __builtin_amdgcn_alignbit(hi, lo, s));
 }
-// standard Gumbel noise of vocabulary entry v under a row key: u = ((r >> 9) + 0.5) * 2^-23, g = -ln(-ln u)
-__device__ __forceinline__ float gumbel_noise(uint64_t key, int v) {
-    const uint32_t r = (uint32_t)(mix64(key + (uint64_t)v * 0x9E3779B97F4A7C15ull) >> 32);
+// the upper half of the mixed counter but for its lowest bit, which nothing reads: of the last product its upper half alone
+__device__ __forceinline__ uint32_t mix64_upper(uint64_t z) {
+    z = xor_shifted(xor_shifted(z, 30) * 0xBF58476D1CE4E5B9ull, 27);
+    const uint32_t lo = (uint32_t)z, hi = (uint32_t)(z >> 32);
+    return __umulhi(lo, 0x133111EBu) + lo * 0x94D049BBu + hi * 0x133111EBu;
+}
+// The generator's counter for vocabulary entry v (>= 0) under a row key.  Neighbouring entries are kNoiseStep apart: code that visits many adds multiples
+// of it that the compiler knows, as the product here is three of an entry's nine integer multiplications, which run at a quarter of the rate.
+constexpr uint64_t kNoiseStep = 0x9E3779B97F4A7C15ull;
+__device__ __forceinline__ uint64_t noise_at(uint64_t key, int v) { return key + (uint64_t)(uint32_t)v * kNoiseStep; }
+// standard Gumbel noise there: u = ((r >> 9) + 0.5) * 2^-23, g = -ln(-ln u)
+__device__ __forceinline__ float gumbel_noise(uint64_t at) {
+    const uint32_t r = mix64_upper(at);
     const float u = ((float)(r >> 9) + 0.5f) * 1.1920928955078125e-07f;   // 2^-23
     return -logf(-logf(u));
 }
+__device__ __forceinline__ float gumbel_noise(uint64_t key, int v) { return gumbel_noise(noise_at(key, v)); }
 // Tells apart, without a logarithm, entries that cannot win: g > t needs 1 - u < -ln u < e^-t, so where some score `best` of
 // the row is known an entry with 1 - u >= e^(z - best) is out.  noise_pass(best) takes 1e-3 and 1e-6 of the magnitude off
 // the bound, noise_may_win 1e-6 of |z|: the rounding of z, of z + g and of the fast exponential stays below that, so ties are still
 // decided on the exact scores.  True when in doubt (infinities, NaN).
 __device__ __forceinline__ float noise_pass(float best) { return best - 1e-3f - 1e-6f * fabsf(best); }
-__device__ __forceinline__ bool noise_may_win(uint64_t key, int v, float z, float pass) {
-    const uint32_t r = (uint32_t)(mix64(key + (uint64_t)v * 0x9E3779B97F4A7C15ull) >> 32) >> 9;
+__device__ __forceinline__ bool noise_may_win(uint64_t at, float z, float pass) {
+    const uint32_t r = mix64_upper(at) >> 9;
     const float w = ((float)(0x7FFFFFu - r) + 0.5f) * 1.1920928955078125e-07f;      // 1 - u, exact
     return !(w >= __builtin_amdgcn_exp2f((fmaf(fabsf(z), 1e-6f, z) - pass) * 1.4426950408889634f));
 }
