@@ -320,6 +320,7 @@ hipError_t launch_gemm(const GemmArgs& a, int epilogue, bool w_bf16, int bn, hip
     if (gemm_decode_takes(a.M, a.N, a.K, epilogue, a.head != 0))
         return launch_gemm_decode(a, epilogue, a.head || bn == 0 ? 0 : std::max(1, std::min(bn / 32, 3)), s);
     if (a.a_frag || (a.out_frag && (a.M > 128 || (a.K & 127) || (a.N & 15)))) return hipErrorInvalidValue;      // the streaming kernels write that order, too
+    if (bn >= 128 && gemm_head_tile_takes(a, epilogue)) return launch_gemm_head_tile(a, epilogue, s);
     // more rows than one tile of the streaming kernel: the LDS-tiled kernel where it is the faster one
     if (a.M > 128 && bn != 1 && epilogue != EPI_SAMPLE) {
         const int bm = gemm_tile_rows(a, epilogue, bn);

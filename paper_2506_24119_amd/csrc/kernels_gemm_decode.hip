@@ -274,13 +274,15 @@ static hipError_t launch_tiles(const GemmArgs& a, int nt, hipStream_t s) {
 // The others stay there from 64 MB of weights on: the 7B shape's down (136 MB) row-major 31.8 -> 47.4, 35.1 -> 49.8, 44.0 -> 58.0, repacked 27.0
 // -> 26.2, 28.8 -> 28, 37.0 -> 37; 2,560 x 12,288 (63 MB) row-major 19.8 -> 20.9, 21.0 -> 21.9, 26.4 -> 30.8, repacked 16.1 -> 14.9,
 // 18.6 -> 16.2, 23.4 -> 24.7.
-// The LM head does up to 32 rows (above, 128 rows: 186 us against 180 on the 4B shape, 85 and 83 on the 0.6B); its sums are rounded by
-// nothing that follows.  One layer and a row-major head, 1, 16 and 32 rows: 0.6B 119 -> 107, 129 -> 115, 136 -> 122; 4B 252 -> 229,
+// The LM head does up to 32 rows, with logits as a small head (2^25 weights) up to 128: its sums are rounded by nothing that follows.  Streaming kernel
+// -> this, us, 8,192 columns at 33, 64 and 128 rows: K = 1024 8.7 -> 5.2, 9.0 -> 5.6, 13.5 -> 7.9; 2560 17 -> 9.6, 19 -> 10.2, 30.5 -> 15.1; 3584 23 -> 12.4,
+// 25 -> 14.3, 41 -> 21.4.  One layer and a row-major head of 151,936, 1, 16 and 32 rows: 0.6B 119 -> 107, 129 -> 115, 136 -> 122; 4B 252 -> 229,
 // 267 -> 264, 283 -> 287; 7B 337 -> 333, 364 -> 370, 382 -> 402.
 bool gemm_decode_takes(int M, int N, int K, int epilogue, bool head) {
-    if (M < 1 || M > (head ? 32 : 128) || (K & 127) || (N & 15)) return false;
+    if (M < 1 || M > 128 || (K & 127) || (N & 15)) return false;
     if (epilogue == EPI_SWIGLU) return (N + 15) / 16 <= 512;
-    return head || (long long)N * K <= 1 << 25;
+    if (head && M <= 32) return true;
+    return epilogue != EPI_SAMPLE && (long long)N * K <= 1 << 25;
 }
 
 // Whether the down projection reads act_frag() order: whenever it comes here, as gate/up (d columns in, ffn out) writes that order from
@@ -322,11 +324,11 @@ int gemm_decode_tiles(int M, int N, int K, int epilogue, int splits) {
 
 hipError_t launch_gemm_decode(const GemmArgs& a, int epilogue, int nt, hipStream_t s) {
     if (!gemm_decode_takes(a.M, a.N, a.K, epilogue, a.head != 0) || a.splits < 1 || a.splits > (a.K >> 7)) return hipErrorInvalidValue;
-    // the head: two tiles a workgroup (1 / 2 / 3 / 4 tiles, 4B shape: 111 / 116 / 119 / 117 us at 3 rows, 156 / 142 / 141 / 138 at 32;
-    // the winners' array has room for 64 columns each)
+    // a large head: two tiles a workgroup (the winners' array has room for 64 columns each), one for logits of a few rows and a long K (151,936
+    // columns, 1 / 2 / 3 tiles, us, K = 2560: 3 rows 110 / 116 / 119, 16 123 / 125 / 129, 24 140 / 132 / 135; K = 1024: 3 rows 48 / 47 / 47, 16 56 / 51 / 52; row-major weights, of whose lines a load has 32 bytes, lose 10 % of the step)
     if (epilogue == EPI_SAMPLE) return launch_one<1, 2, EPI_SAMPLE, 6, 2>(a, s);
     if (epilogue == EPI_SWIGLU && a.splits != 1) return hipErrorInvalidValue;
-    if (nt == 0) nt = a.head ? 2 : gemm_decode_tiles(a.M, a.N, a.K, epilogue, a.splits);
+    if (nt == 0) nt = a.head && (long long)a.N * a.K > 1 << 25 ? (a.wf && a.M <= 16 && a.K >= 2048 ? 1 : 2) : gemm_decode_tiles(a.M, a.N, a.K, epilogue, a.splits);
     if (epilogue == EPI_SWIGLU)
         return a.M <= 32 ? launch_tiles<EPI_SWIGLU, 1>(a, nt, s) : a.M <= 64 ? launch_tiles<EPI_SWIGLU, 2>(a, nt, s)
              : a.M <= 96 ? launch_tiles<EPI_SWIGLU, 3>(a, nt, s) : launch_tiles<EPI_SWIGLU, 4>(a, nt, s);

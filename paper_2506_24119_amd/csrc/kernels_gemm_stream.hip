@@ -1,4 +1,4 @@
-// Weight-streaming projection kernel for row tiles of 128 (K a multiple of 128): the LM head above 32 rows, gate/up of more than
+// Weight-streaming projection kernel for row tiles of 128 (K a multiple of 128): LM heads above 32 rows that are neither small nor tiled, gate/up of more than
 // 8,192 ffn columns, projections of more than 64 MB of weights, and above 128 rows row-major weights and what gemm_tile_kernel does not take.
 //
 // out[m][n] = sum_k A[m][k] * W[n][k], M <= 128 rows per tile.  Every weight byte is used once, so

@@ -46,9 +46,9 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_upto(const void* p, int
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, bytes, 0x00027000);
 }
 // 64 lanes x 16 bytes straight to 1 KB of LDS at dst (wave-uniform); IMM counts on both sides
-template <int IMM>
+template <int IMM, int AUX = 0>
 __device__ __forceinline__ void load_to_lds(__amdgpu_buffer_rsrc_t r, char* dst, uint32_t off, int soff) {
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)dst, 16, off, soff, IMM, 0);
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)dst, 16, off, soff, IMM, AUX);
 }
 // which of a 128-byte row's eight 16-byte pieces sits where: 8 (and 16) lanes that read one piece of consecutive rows meet no bank twice
 __device__ __forceinline__ int row_swizzle(int r) { return (r & 6) | ((r ^ (r >> 3)) & 1); }
@@ -70,8 +70,9 @@ template <int BM> struct Slots {
 // exponentials over each 128 columns, and the target column's product; no product reaches memory).
 // BM: activation rows of the tile, 256 (a wave's quarter is 128 x 128) or 128 (64 x 128).
 // g.splits > 1 (TEPI 0): K is cut at multiples of 128, split s writes its partial product to out[s], as the streaming kernel does.
-template <int TEPI, int BM>
-__global__ __launch_bounds__(256, BM == 128 ? 2 : 1) void gemm_tile_kernel(GemmArgs g, QkvPostArgs qa) {
+// NT: weights are read once, by non-temporal loads.
+template <int TEPI, int BM, bool NT>
+__device__ __forceinline__ void tile_body(const GemmArgs& g, const QkvPostArgs& qa) {
     constexpr bool SWIGLU = TEPI == 1;
     constexpr int J = 4, I = BM / 64;               // 32-row weight tiles and batch tiles per wave
     using L = Slots<BM>;
@@ -139,8 +140,8 @@ __global__ __launch_bounds__(256, BM == 128 ? 2 : 1) void gemm_tile_kernel(GemmA
     auto load_w = [&](int slot, int h, const int u) {          // half chunk h
         const __amdgpu_buffer_rsrc_t r = buffer_upto(wbase, h < 2 * NC ? kAllBytes : 0);
         char* dst = lds + L::W_BASE + slot * L::W_BYTES + (wave + 4 * (u >> 1)) * 2048;
-        if (u & 1) load_to_lds<1024>(r, dst, w_off[u >> 1], h * 2048);
-        else load_to_lds<0>(r, dst, w_off[u >> 1], h * 2048);
+        if (u & 1) load_to_lds<1024, NT ? 2 : 0>(r, dst, w_off[u >> 1], h * 2048);
+        else load_to_lds<0, NT ? 2 : 0>(r, dst, w_off[u >> 1], h * 2048);
     };
     auto frags = [&](int as, int ws, int ks, u32x4* af, u32x4* wf) {
 #pragma unroll
@@ -415,6 +416,31 @@ __global__ __launch_bounds__(256, BM == 128 ? 2 : 1) void gemm_tile_kernel(GemmA
             sum += __shfl_xor(sum, 32, 64);
             if (lh == 0 && m < g.M && pair < g.s_tiles) g.s_part[(size_t)pair * g.M + m] = make_float2(mx, sum);
         }
+    } else if (TEPI == 4) {
+        // score = logit / T + noise (the sampler's own expression); the best of the wave's 128 columns per row, a second kernel picks
+        const int c0 = n0 + wn * 128 + 4 * lh, part = tile_n * 2 + wn;
+        const float T = g.s_temperature;
+#pragma unroll
+        for (int i = 0; i < I; ++i) {
+            const int m = m0 + wm * (BM / 2) + i * 32 + l32;
+            const uint64_t key = (T > 0.f && m < g.M) ? g.s_keys[m] : 0ull;
+            const uint64_t at = noise_at(key, c0);
+            float bv = -INFINITY;
+            int bi = 0x7FFFFFFF;
+#pragma unroll
+            for (int j = 0; j < J; ++j)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const int n = c0 + 32 * j + 8 * (r >> 2) + (r & 3);
+                    float sc = acc[j][i][r];
+                    if (T > 0.f) sc = sc / T + gumbel_noise(at + (uint64_t)(32 * j + 8 * (r >> 2) + (r & 3)) * kNoiseStep);
+                    if (n < g.N && better(sc, n, bv, bi)) { bv = sc; bi = n; }
+                }
+            const float ov = __shfl_xor(bv, 32, 64);
+            const int oi = __shfl_xor(bi, 32, 64);
+            if (better(ov, oi, bv, bi)) { bv = ov; bi = oi; }
+            if (lh == 0 && m < g.M && part < g.s_tiles) g.s_part[(size_t)m * g.s_tiles + part] = make_float2(bv, __int_as_float(bi));
+        }
     } else if (!SWIGLU) {
         float* out = (float*)g.out + (size_t)split * g.M * g.N;
         constexpr int TROW = 128 * 4 + 16;              // staged row: 128 floats + pad
@@ -471,6 +497,13 @@ __global__ __launch_bounds__(256, BM == 128 ? 2 : 1) void gemm_tile_kernel(GemmA
         report_saturation(g.sat_count, bad);
     }
 }
+
+template <int TEPI, int BM>
+__global__ __launch_bounds__(256, BM == 128 ? 2 : 1) void gemm_tile_kernel(GemmArgs g, QkvPostArgs qa) { tile_body<TEPI, BM, false>(g, qa); }
+
+// The LM head of a decode step: logits, or with SAMPLE the winners of each 128 columns.  NT: one tile of rows.
+template <bool SAMPLE, bool NT>
+__global__ __launch_bounds__(256, 2) void head_tile_kernel(GemmArgs g) { tile_body<SAMPLE ? 4 : 0, 128, NT>(g, QkvPostArgs{}); }
 
 template <int TEPI, int BM>
 static hipError_t launch_tile_bm(const GemmArgs& a, const QkvPostArgs& qa, hipStream_t s) {
@@ -581,6 +614,32 @@ hipError_t launch_gemm_tile(const GemmArgs& a, int epilogue, int bm, hipStream_t
         return hipErrorInvalidValue;
     const QkvPostArgs none = {};
     return epilogue == EPI_SWIGLU ? launch_tile<1>(a, none, bm, s) : launch_tile<0>(a, none, bm, s);
+}
+
+// The LM head of a decode step of more than 64 rows and at least 65,536 columns on tiles of 128 rows (two workgroups a compute unit), with
+// logits or the sampler's winners.  Bound by the weights' way into the compute units, 4.8 TB/s with non-temporal loads (without, as on the
+// streaming kernel, 4.2; zeros for operands change nothing).  Streaming kernel -> this, us, 151,936 columns: logits, K = 2560, 65 / 96 / 128 rows 164 / 173 / 180 ->
+// 147 / 154 / 160, K = 1024 74 / 78 / 84 -> 64 / 67 / 71; 65,536 columns, K = 1024 30 / 33 / 35 -> 28 / 31 / 29.  Winners, whose noise keeps the
+// vector units busy where nothing else runs: 128 rows, K = 2560 190 -> 180, 3584 244 -> 229, but 1024 101 -> 110, so from K = 2048 on; two row tiles (160 rows), for which the
+// streaming kernel reads the weights twice, 1024 / 2560 / 3584 179 / 346 / 464 -> 157 / 259 / 331.  (Logits of more than 128 rows go by gemm_tile_rows().)
+// 8,192 columns are too few tiles (160 rows 46 -> 60).
+bool gemm_head_tile_takes(const GemmArgs& a, int epilogue) {
+    if (!a.head || epilogue == EPI_SWIGLU || a.splits != 1 || a.N < 65536 || a.M <= 64 || !gemm_tile_usable(a)) return false;
+    return epilogue == EPI_SAMPLE ? a.M > 128 || a.K >= 2048 : a.M <= 128;
+}
+template <bool SAMPLE, bool NT>
+static hipError_t launch_head_tile_nt(const GemmArgs& a, hipStream_t s) {
+    const int tiles = ((a.M + 127) / 128) * ((a.N + 255) / 256);
+    const hipError_t e = hipFuncSetAttribute((const void*)head_tile_kernel<SAMPLE, NT>, hipFuncAttributeMaxDynamicSharedMemorySize, Slots<128>::TOTAL);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((head_tile_kernel<SAMPLE, NT>), dim3((tiles + 7) / 8 * 8), dim3(256), Slots<128>::TOTAL, s, a);
+    return hipGetLastError();
+}
+hipError_t launch_gemm_head_tile(const GemmArgs& a, int epilogue, hipStream_t s) {
+    if (!gemm_head_tile_takes(a, epilogue)) return hipErrorInvalidValue;
+    if (epilogue == EPI_STORE_F32) return launch_head_tile_nt<false, true>(a, s);
+    if (!a.s_part || a.s_tiles != (a.N + 127) / 128 || (a.s_temperature > 0.f && !a.s_keys)) return hipErrorInvalidValue;
+    return a.M <= 128 ? launch_head_tile_nt<true, true>(a, s) : launch_head_tile_nt<true, false>(a, s);
 }
 
 // The scoring epilogue's exponentials run under another workgroup's products with tiles of 128 rows: 151,936 columns, K = 2560, 300 / 700 /

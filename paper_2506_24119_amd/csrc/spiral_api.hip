@@ -829,7 +829,7 @@ static int run_layers(StepCtx& c) {
     const int h2_frag = !act32 && gemm_decode_takes(c.rows, cfg.ffn_dim, d, EPI_SWIGLU, false);
     const int o_frag = !act32 && gemm_decode_takes(c.rows, d, qw, EPI_STORE_F32, false);
     const int mlp_frag = !act32 && gemm_mlp_in_frag(c.rows, d, cfg.ffn_dim);
-    const int hf_frag = !act32 && gemm_decode_takes(c.B, cfg.vocab, d, EPI_STORE_F32, true);
+    const int hf_frag = !act32 && gemm_decode_takes(c.B, cfg.vocab, d, c.sample ? EPI_SAMPLE : EPI_STORE_F32, true);
 
     // fp32 weights, a few rows: the norms and the residual's sums are done by the projections.  Each wave (a column, four rows) norms the
     // rows for itself, so waves and d must be few: the price is waves x d, what it saves two launches a layer.  Four layers, us a step,

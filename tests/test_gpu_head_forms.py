@@ -1,0 +1,45 @@
+"""The LM head of a decode step by rows and vocabulary: gemm_decode_kernel (at most 32 rows, or a small head up to 128), the streaming
+kernel, tiles of 128 rows (from 65 rows and 65,536 columns on).  Repacked weights give the bits of row-major ones, whose head is never
+tiled, and the fused step's tokens are those of the sampler on the stored logits."""
+import numpy as np
+import pytest
+
+from paper_2506_24119_amd import inputs as si
+
+pytestmark = pytest.mark.gpu
+
+
+def _step(g, w, rows, repack, T):
+    import torch
+    from paper_2506_24119_amd import binding as sb
+    ids = np.arange(rows, dtype=np.int32)
+    rng = np.random.Generator(np.random.PCG64(rows))
+    tok = torch.from_numpy(rng.integers(0, g.vocab, rows).astype(np.int32)).cuda()
+    steps = (np.arange(rows, dtype=np.int32) * 5 + 2).astype(np.int32)
+    sess = sb.Session(g, w, rows, rows, 1, 5 * rows, 16, repack=repack)
+    sess.prefill(ids, [rng.integers(0, g.vocab, 1 + b % 5).astype(np.int32) for b in range(rows)])
+    lens = np.array([1 + b % 5 for b in range(rows)], dtype=np.int32)
+    logits = sess.decode_step(ids, tok, sess.new_logits(rows))
+    stored, fused = (torch.full((rows,), -1, dtype=torch.int32, device="cuda") for _ in range(2))
+    sb.spiral_sample(logits, rows, g.vocab, T, 9, ids, steps, None, stored)
+    if repack:
+        sb.spiral_seq_truncate(sess.pool, ids, lens)
+        sess.decode_sample_step(ids, tok, T, 9, steps, fused)
+    out = logits.cpu().numpy(), stored.cpu().numpy(), fused.cpu().numpy()
+    sess.close()
+    return out
+
+
+@pytest.mark.parametrize("d,vocab,rows", [
+    (128, 1008, 33), (128, 1008, 128), (2560, 8192, 65), (2560, 13120, 128), (128, 65520, 65),         # small heads: up to 2^25 weights
+    (640, 65536, 64), (640, 65536, 65), (640, 65552, 128), (640, 65536, 129),                          # more: the streaming kernel, then tiles
+    (2048, 65552, 65), (2048, 65536, 100), (128, 70000, 257)])                                         # tiles with winners, one and three rows of them
+def test_forms_of_the_head_agree(d, vocab, rows):
+    g = si.ModelGeometry("head", 1, d, 4, 2, 64, 256, vocab, 1e6, qk_norm=True)
+    w = si.make_weights_torch(g, 5, "cuda:0")
+    tiled, stored, fused = _step(g, w, rows, True, 1.0)
+    plain, other, _ = _step(g, w, rows, False, 1.0)
+    assert np.array_equal(tiled, plain) and np.array_equal(stored, other)
+    assert np.array_equal(fused, stored) and len(set(fused)) > rows // 8
+    logits, greedy, fused = _step(g, w, rows, True, 0.0)
+    assert np.array_equal(greedy, logits.argmax(1)) and np.array_equal(fused, greedy)
