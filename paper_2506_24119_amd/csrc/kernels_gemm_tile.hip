@@ -24,6 +24,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 
 #include "spiral_internal.h"
 #include "mfma_ops.h"
@@ -88,16 +89,32 @@ __device__ __forceinline__ void tile_body(const GemmArgs& g, const QkvPostArgs& 
     // ---- tile of this workgroup
     const int n_cols = SWIGLU ? 128 : 256;          // output columns per workgroup
     const int m_tiles = (g.M + BM - 1) / BM, n_tiles = (g.N + n_cols - 1) / n_cols;
-    const int per_split = m_tiles * n_tiles, total = per_split * (TEPI == 0 ? g.splits : 1);
-    const int per_xcd = (total + 7) / 8;
-    int t = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
-    if ((int)(blockIdx.x >> 3) >= per_xcd || t >= total) return;
-    const int split = TEPI == 0 ? t / per_split : 0;
-    t -= split * per_split;
-    const int band = t / (GROUP_M * n_tiles);
-    const int band_rows = min(GROUP_M, m_tiles - band * GROUP_M);
-    const int tile_m = band * GROUP_M + (t % (GROUP_M * n_tiles)) % band_rows;
-    const int tile_n = (t % (GROUP_M * n_tiles)) / band_rows;
+    const int splits = TEPI == 0 ? g.splits : 1;
+    // A last row tile at most half full is light work.  Its workgroups come last on every XCD, where they fill what the whole tiles leave (one after
+    // the other with them, the last whole ones started when a light one ended), unless its second walk over the weights would be over
+    // memory: the memory-side cache holds 256 MB.  us, all tiles alike / light ones multiplying what there is / and last: gate/up of the 4B shape,
+    // 400 rows 60.6 / 57.5 / 53.5, 788 96 / 88 / 84, 1,300 134 / 134 / 128, q/k/v 1,300 68 / 65 / 58; scoring LM head 300 rows 286 / 268 / 329.
+    const bool light = BM == 128 && TEPI <= 2 && m_tiles > 1 && g.M - (m_tiles - 1) * BM <= BM / 2 && (long long)g.N * K <= (SWIGLU ? 1 << 25 : 1 << 26);
+    const int whole_m = m_tiles - light;             // row tiles of the first part
+    const int per_split = whole_m * n_tiles, total = per_split * splits;
+    const int per_xcd = (total + 7) / 8, xcd = blockIdx.x & 7, at = blockIdx.x >> 3;
+    int split, tile_m, tile_n;
+    if (at < per_xcd) {
+        int t = xcd * per_xcd + at;
+        if (t >= total) return;
+        split = TEPI == 0 ? t / per_split : 0;
+        t -= split * per_split;
+        const int band = t / (GROUP_M * n_tiles);
+        const int band_rows = min(GROUP_M, whole_m - band * GROUP_M);
+        tile_m = band * GROUP_M + (t % (GROUP_M * n_tiles)) % band_rows;
+        tile_n = (t % (GROUP_M * n_tiles)) / band_rows;
+    } else {
+        const int rest = light ? n_tiles * splits : 0, per_rest = (rest + 7) / 8, t = xcd * per_rest + at - per_xcd;
+        if (at - per_xcd >= per_rest || t >= rest) return;
+        split = TEPI == 0 ? t / n_tiles : 0;
+        tile_m = whole_m;
+        tile_n = t - split * n_tiles;
+    }
     const int m0 = tile_m * BM, n0 = tile_n * n_cols;
 
     // ---- chunks of this workgroup's share of K
@@ -143,19 +160,22 @@ __device__ __forceinline__ void tile_body(const GemmArgs& g, const QkvPostArgs& 
         if (u & 1) load_to_lds<1024, NT ? 2 : 0>(r, dst, w_off[u >> 1], h * 2048);
         else load_to_lds<0, NT ? 2 : 0>(r, dst, w_off[u >> 1], h * 2048);
     };
-    auto frags = [&](int as, int ws, int ks, u32x4* af, u32x4* wf) {
+    auto frags = [&](auto ni, int as, int ws, int ks, u32x4* af, u32x4* wf) {
+        constexpr int NI = decltype(ni)::value;
+        if (NI == 0) return;
 #pragma unroll
-        for (int i = 0; i < I; ++i) af[i] = *(const u32x4*)(lds + as * L::A_BYTES + a_frag[ks] + i * 32 * 128);
+        for (int i = 0; i < NI; ++i) af[i] = *(const u32x4*)(lds + as * L::A_BYTES + a_frag[ks] + i * 32 * 128);
 #pragma unroll
         for (int j = 0; j < J; ++j) wf[j] = *(const u32x4*)(lds + ws * L::W_BYTES + w_frag + (j * 2 + (ks & 1)) * 1024);
     };
     u32x4 af[2][I], wf[2][J];
-    auto multiply = [&](const int b) {                         // up and down the batch tiles: one operand stays from one instruction to the next
+    auto multiply = [&](auto ni, const int b) {                // up and down the batch tiles: one operand stays from one instruction to the next
+        constexpr int NI = decltype(ni)::value;
 #pragma unroll
         for (int j = 0; j < J; ++j)
 #pragma unroll
-            for (int x = 0; x < I; ++x) {
-                const int i = (j & 1) ? I - 1 - x : x;
+            for (int x = 0; x < NI; ++x) {
+                const int i = (j & 1) ? NI - 1 - x : x;
                 acc[j][i] = mma32t(wf[b][j], af[b][i], acc[j][i]);
             }
     };
@@ -185,56 +205,66 @@ __device__ __forceinline__ void tile_body(const GemmArgs& g, const QkvPostArgs& 
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
     __builtin_amdgcn_sched_barrier(0);
-    frags(0, 0, 0, af[0], wf[0]);
-    int as = 0, ws = 0;                                        // the slots being multiplied
-    for (int c = 0; c < NC; ++c) {
-        const int a_next = as == L::A - 1 ? 0 : as + 1, a_last = as == 0 ? L::A - 1 : as - 1;
+    // Waves of a last row tile that is partly empty multiply the 32-row blocks that there are.
+    auto walk = [&](auto ni) {
+        constexpr int NI = decltype(ni)::value;
+        frags(ni, 0, 0, 0, af[0], wf[0]);
+        int as = 0, ws = 0;                                        // the slots being multiplied
+        for (int c = 0; c < NC; ++c) {
+            const int a_next = as == L::A - 1 ? 0 : as + 1, a_last = as == 0 ? L::A - 1 : as - 1;
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const int w_next = ws == L::W - 1 ? 0 : ws + 1;
-            __builtin_amdgcn_sched_barrier(0);
-            frags(as, ws, 2 * h + 1, af[1], wf[1]);
-            multiply(0);
+            for (int h = 0; h < 2; ++h) {
+                const int w_next = ws == L::W - 1 ? 0 : ws + 1;
+                __builtin_amdgcn_sched_barrier(0);
+                frags(ni, as, ws, 2 * h + 1, af[1], wf[1]);
+                multiply(ni, 0);
 #pragma unroll
-            for (int r = 0; r < I + J; ++r) {                  // a read behind each of the first products
-                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-            }
-            __builtin_amdgcn_sched_group_barrier(0x008, I * J - I - J, 0);
-            __builtin_amdgcn_sched_barrier(0);
-            if (BM == 256) asm volatile("s_waitcnt vmcnt(16) lgkmcnt(0)" ::: "memory");
-            else if (h == 0) asm volatile("s_waitcnt vmcnt(8) lgkmcnt(0)" ::: "memory");
-            else asm volatile("s_waitcnt vmcnt(4) lgkmcnt(0)" ::: "memory");
-            __builtin_amdgcn_s_barrier();
-            asm volatile("" ::: "memory");
-            __builtin_amdgcn_sched_barrier(0);
-            frags(h ? a_next : as, w_next, h ? 0 : 2, af[0], wf[0]);
-#pragma unroll
-            for (int u = 0; u < 4; ++u) load_w(ws, 2 * c + h + L::W, u);
-            if (BM == 256) {
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    if (h) load_a(as, c + 3, u);
-                    else load_a(a_last, c + 2, 4 + u);
+                for (int r = 0; NI > 0 && r < NI + J; ++r) {                  // a read behind each of the first products
+                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                    __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
                 }
-            } else if (h) {
+                __builtin_amdgcn_sched_group_barrier(0x008, NI == I ? I * J - I - J : 16, 0);
+                __builtin_amdgcn_sched_barrier(0);
+                if (BM == 256) asm volatile("s_waitcnt vmcnt(16) lgkmcnt(0)" ::: "memory");
+                else if (h == 0) asm volatile("s_waitcnt vmcnt(8) lgkmcnt(0)" ::: "memory");
+                else asm volatile("s_waitcnt vmcnt(4) lgkmcnt(0)" ::: "memory");
+                __builtin_amdgcn_s_barrier();
+                asm volatile("" ::: "memory");
+                __builtin_amdgcn_sched_barrier(0);
+                frags(ni, h ? a_next : as, w_next, h ? 0 : 2, af[0], wf[0]);
 #pragma unroll
-                for (int u = 0; u < 4; ++u) load_a(as, c + 2, u);
-            }
-            multiply(1);
-            __builtin_amdgcn_sched_group_barrier(0x100, I + J, 0);
+                for (int u = 0; u < 4; ++u) load_w(ws, 2 * c + h + L::W, u);
+                if (BM == 256) {
 #pragma unroll
-            for (int r = 0; r < 8; ++r) {
-                __builtin_amdgcn_sched_group_barrier(0x008, I * J / 8, 0);
-                __builtin_amdgcn_sched_group_barrier(0x010, 1, 0);
+                    for (int u = 0; u < 4; ++u) {
+                        if (h) load_a(as, c + 3, u);
+                        else load_a(a_last, c + 2, 4 + u);
+                    }
+                } else if (h) {
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) load_a(as, c + 2, u);
+                }
+                multiply(ni, 1);
+                __builtin_amdgcn_sched_group_barrier(0x100, NI + J, 0);
+#pragma unroll
+                for (int r = 0; r < 8; ++r) {
+                    __builtin_amdgcn_sched_group_barrier(0x008, NI == I ? I * J / 8 : 1, 0);
+                    __builtin_amdgcn_sched_group_barrier(0x010, 1, 0);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+                ws = w_next;
             }
-            __builtin_amdgcn_sched_barrier(0);
-            ws = w_next;
+            as = a_next;
         }
-        as = a_next;
-    }
+    };
+    const int blocks = max(0, min(I, (g.M - m0 - wm * (BM / 2) + 31) >> 5));
+    static_assert(BM == 256 || I == 2, "the wave's blocks are two, one or none");
+    if (BM == 256 || blocks == I) walk(std::integral_constant<int, I>());
+    else if (blocks == 1) walk(std::integral_constant<int, 1>());
+    else walk(std::integral_constant<int, 0>());
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
     __syncthreads();                                  // the operand slots are free for the epilogue
+    if (BM == 128 && blocks == 0) return;
 
     // ---- epilogue.  In a 32 x 32 tile a lane holds batch row l32 and, in registers 4b..4b+3, weight rows 8b + 4*lh .. +3:
     //      written straight from there a store instruction touches 64 rows x 16 (or 8) bytes.  Each wave therefore
@@ -512,7 +542,7 @@ static hipError_t launch_tile_bm(const GemmArgs& a, const QkvPostArgs& qa, hipSt
     const int n_tiles = (a.N + cols - 1) / cols;
     const long long total = (long long)m_tiles * n_tiles * (TEPI == 0 ? a.splits : 1);
     if (total > (1ll << 30)) return hipErrorInvalidValue;
-    const int per_xcd = (int)((total + 7) / 8);
+    const int per_xcd = (int)((total + 7) / 8) + 1;          // the two parts of the grid are rounded up by themselves
     const size_t lds_bytes = Slots<BM>::TOTAL;
     hipError_t e = hipFuncSetAttribute((const void*)gemm_tile_kernel<TEPI, BM>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
     if (e != hipSuccess) return e;
