@@ -562,18 +562,7 @@ __global__ __launch_bounds__(kSampleThreads) void sample_kernel(const float* log
         }
         __syncthreads();
     }
-    // The screen, an entry's logit l against the best score so far: g > best - z needs w = 1 - u < -ln u < e^(z - best).  In units of 2^-23
-    // of a binary logarithm: the bits of a positive float, as an integer, are at most its logarithm (127 added) in these units, so an entry is out where the
-    // bits of a lower bound of w are no less than (z - best) in them, one product and sum with z = l / T.  Its rounding matters only for z within
-    // about 20 of best (beyond, no noise makes up for it, or any does), and is with that of the rest (2^-17 each) below the 1e-3 + 2e-6 |best| that
-    // `pass` takes off the bound.  Infinite and undefined values pass, and all do where the scale is not finite.
-    const float c = 1.4426950408889634f * 8388608.f / temperature;
-    const float scale = c < INFINITY ? c : NAN;
-    auto may_win = [&](uint64_t at, float l) {
-        const uint32_t r = mix64_upper(at);
-        const float w = fmaf((float)r, -2.3283064365386963e-10f, 1.f - 2.384185791015625e-07f);      // 1 - r 2^-32 - 2^-22 <= 1 - u
-        return !((float)__float_as_int(w) >= fmaf(l, scale, -pass));
-    };
+    const float scale = screen_scale(temperature);
     auto visit = [&](int v, uint64_t at, float l, float n) {
         float sc = l;
         if (MODE != 0) sc = sc / temperature + (MODE == 2 ? n : gumbel_noise(at));
@@ -603,11 +592,11 @@ __global__ __launch_bounds__(kSampleThreads) void sample_kernel(const float* log
         bool in[LOADS * VEC], any = !SCREEN;
         if (SCREEN) {
             bound = __int_as_float(ordered_bits(*(volatile int*)&s_best));
-            pass = (bound - 1e-3f - 2e-6f * fabsf(bound)) * (1.4426950408889634f * 8388608.f) - 127.f * 8388608.f;
+            pass = screen_pass(bound);
 #pragma unroll
             for (int u = 0; u < LOADS; ++u)
 #pragma unroll
-                for (int e = 0; e < VEC; ++e) any |= in[u * VEC + e] = may_win(at + (uint64_t)(u * NT * VEC + e) * kNoiseStep, l[u][e]);
+                for (int e = 0; e < VEC; ++e) any |= in[u * VEC + e] = screen_may_win(at + (uint64_t)(u * NT * VEC + e) * kNoiseStep, l[u][e], scale, pass);
         }
         if (any)
 #pragma unroll

@@ -11,19 +11,22 @@
 // One block of 1024 threads per row; each wave fills its own histogram copy in LDS.
 //
 // With a workspace the same thresholds are found in three sweeps of the row instead of up to nine, and by several
-// workgroups per row: (1) row maximum; (2) one histogram of count and mass over 4096 bins that are linear in
-// zmax - z (width 1/128; the last bin takes everything 32 or more below the maximum, whose mass is zero in the
-// 2^45 fixed point), with sums over every 64 bins; (3) one sweep whose workgroups first find the bin that holds the cut (an
-// integer prefix sum over the 64 sums, then over the 64 bins below one of them), then score the tokens in the bins above
-// it for the Gumbel-max and copy the tokens of the cut bin (a few hundred to a few thousand) to the row's candidate list, on
-// which the radix descent then runs in LDS, in a last kernel of a workgroup per row.  Bin order follows key order and the
-// masses are the same integers, so the threshold is the one the single-kernel path finds, bit for bit; a row whose cut bin
-// holds more candidates than the list (many equal scores) is done by that path's code in the last kernel.
-// Bound by the fixed-point exponentials of the histogram and the generator's integer arithmetic of the sweep.  Measured
-// against six launches (a plan kernel that read every bin, the single path's kernel launched behind for flagged rows) and at
-// most 8 slices a row, 151,936 entries, T = 0.6, top-p 0.95: one row 59 -> 35 us, 16 rows 55 -> 34, 128 rows of flat logits
-// 130 -> 111 (a call; 117 traced); 64 rows, top-k 50 54 -> 42.
+// workgroups per row: (1) row maximum; (2) one histogram over 4096 bins that are linear in zmax - z (width 1/128; the last bin takes
+// everything 32 or more below the maximum, whose mass is zero in the 2^45 fixed point), with sums over every 64 bins: of counts where there is a
+// top-k, by which the cut then goes (top-p is a share of the survivors' mass, which the last kernel finds), else of mass; (3) one sweep whose
+// workgroups first find the bin that holds the cut (an integer prefix sum over the 64 sums, then over the 64 bins below one of them) and the least
+// logits that lie in it and above it, then score the tokens above for the Gumbel-max and copy the tokens of the cut bin (one to a few
+// hundred) to the row's candidate list, on which the radix descent then runs in LDS, in a last kernel of a workgroup per row.  Bin order
+// follows key order and the masses are the same integers, so the threshold is the one the single-kernel path finds, bit for bit; a
+// row whose cut bin holds more candidates than the list (many equal scores) is done by that path's code in the last kernel.
+// Many rows: bound by the fixed-point exponentials of the histogram and the generator's integer arithmetic of the sweep; few: by four dependent
+// launches, each a chain of a few loads, barriers and reductions.  151,936 entries, T = 0.6, top-p 0.95, us a call, with six launches and at most 8 slices a
+// row / with both histograms, a division and a bin an entry in the sweep, one wave adding up the slices, four digits always and thread 0 comparing
+// the waves' results / now: one row 59 / 30.7 / 22.4, 16 rows 55 / 35.0 / 27.4, 64 - / 57.6 / 47.8, 128 - / 94.8 / 72.3, of flat logits
+// 130 / 111 / 86; 16 rows, top-k 50 - / 29.4 / 22.3, top-k 20 with top-p 0.9 - / 36.9 / 26.9.  (16 rows, traced: maximum 4.0 -> 3.4,
+// histogram 11.9 -> 9.0, sweep 12.1 -> 10.0, last kernel 8.0 -> 6.1.)
 #include <algorithm>
+#include <type_traits>
 
 #include "spiral_internal.h"
 
@@ -59,6 +62,40 @@ __device__ __forceinline__ void sweep(const float* lr, int lo, int hi, int tid, 
     }
 }
 
+// The same by threads that hold VEC neighbouring entries a load (4: rows of a multiple of four entries, 16-byte aligned, lo and hi multiples of
+// four).  The first step's loads are issued by the constructor, so that what comes before run() hides them, every other step's under the step before.
+template <int VEC>
+struct Sweep {
+    static constexpr int U = VEC == 4 ? 3 : 8, STEP = kThreads * VEC * U;
+    typedef __attribute__((ext_vector_type(VEC))) float vec;
+    const float* lr;
+    int base, hi;
+    vec next[U];
+    __device__ __forceinline__ Sweep(const float* lr_, int lo, int hi_, int tid) : lr(lr_), base(lo + tid * VEC), hi(hi_) {
+        if (base < hi) load(base);
+    }
+    __device__ __forceinline__ void load(int at) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) next[u] = *(const vec*)(lr + min(at + u * kThreads * VEC, hi - VEC));
+    }
+    // step() before every step's entries, f(logit, v) for each
+    template <class S, class F>
+    __device__ __forceinline__ void run(S&& step, F&& f) {
+        for (; base < hi; base += STEP) {
+            vec l[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) l[u] = next[u];
+            load(base + STEP);
+            step();
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (base + u * kThreads * VEC < hi)
+#pragma unroll
+                    for (int e = 0; e < VEC; ++e) f(l[u][e], base + u * kThreads * VEC + e);
+        }
+    }
+};
+
 __device__ __forceinline__ uint64_t shfl_down_u64(uint64_t v, int d) {
     const uint32_t lo = __shfl_down((uint32_t)v, d, 64), hi = __shfl_down((uint32_t)(v >> 32), d, 64);
     return ((uint64_t)hi << 32) | lo;
@@ -78,7 +115,8 @@ __device__ const double kExp2Tab[32] = {
 // floor(exp(z - zmax) * 2^45) for z <= zmax; zero from 32 below the maximum on (exp(-32) * 2^45 < 1) and for
 // z = -inf.  exp(x) = 2^(k/32) * exp(r) with k = round(32 x / ln 2): the table gives 2^((k mod 32)/32), the Taylor
 // series to the 6th power exp(r) for |r| <= ln 2 / 64 (remainder 4e-18), ldexp the rest; 4e-16 of exp() at worst.
-__device__ __forceinline__ uint64_t mass45(float z, float zmax) {
+// `tab`: the table, or a copy of it in LDS.
+__device__ __forceinline__ uint64_t mass45(float z, float zmax, const double* tab = kExp2Tab) {
     const double x = (double)z - (double)zmax;
     if (!(x > -32.0)) return 0;
     const double k = rint(x * 46.16624130844683);
@@ -92,22 +130,24 @@ __device__ __forceinline__ uint64_t mass45(float z, float zmax) {
     p = fma(p, r, 1.0);
     p = fma(p, r, 1.0);
     const int ki = (int)k;                              // <= 0
-    return (uint64_t)ldexp(kExp2Tab[ki & 31] * p, (ki >> 5) + 45);
+    // to an integer: below 2^52, floor(x) + 2^52 has it in its lower bits (the general conversion is several times that)
+    const double m = floor(ldexp(tab[ki & 31] * p, (ki >> 5) + 45)) + 4503599627370496.0;
+    return (uint64_t)__double_as_longlong(m) & 0xFFFFFFFFFFFFFull;
 }
 
 constexpr int kBins = 4096;           // linear in zmax - z, 1/128 wide; the last one is everything >= 32 below the maximum
 constexpr int kCap = 8192;            // candidates of a row that the in-LDS resolution takes
 constexpr int kCoarse = 64;           // sums of 64 bins each
 constexpr int kMaxSlices = 16;        // workgroups per row
+static_assert(kMaxSlices <= kWaves, "a wave of the last sweep reads one slice's sums");
 
 // What the prefix sum over a row's histogram decides (one per row, in the workspace).
 struct TruncRow {
     float zmax;
     int cand_lo, cand_hi;             // tokens in bins [cand_lo, cand_hi] go to the candidate list; bins below cand_lo are kept
-    int fallback;                     // more candidates than the list holds: the single-kernel path does this row
+    int fallback;                     // no cut found, or (top-k) more candidates than the list holds: the single-kernel path does this row
     uint64_t need_mass;               // top-p alone: fixed-point mass still to be covered inside the candidate bin
     uint32_t need_count;              // top-k: how many of the candidates, from the largest, are kept
-    int n_cand;
 };
 
 __device__ __forceinline__ int bin_of(float z, float zmax) {
@@ -285,74 +325,85 @@ __global__ __launch_bounds__(kThreads) void sample_truncated_kernel(const float*
 
 // ---- the multi-workgroup path (needs a workspace) ---------------------------------------------------------------
 
-// vocabulary range of slice blockIdx.x of gridDim.x
-__device__ __forceinline__ void slice_range(int V, int& lo, int& hi) {
-    const int per = (V + (int)gridDim.x - 1) / (int)gridDim.x;
-    lo = (int)blockIdx.x * per;
-    hi = min(V, lo + per);
+// The best of the waves' (score, index) pairs, in every lane of the wave that calls this.
+__device__ __forceinline__ void best_of_waves(const float* s_red, const int* s_idx, int lane, float& bv, int& bi) {
+    bv = s_red[lane & (kWaves - 1)];
+    bi = s_idx[lane & (kWaves - 1)];
+#pragma unroll
+    for (int o = kWaves / 2; o > 0; o >>= 1) {
+        const float ov = __shfl_xor(bv, o, 64);
+        const int oi = __shfl_xor(bi, o, 64);
+        if (better(ov, oi, bv, bi)) { bv = ov; bi = oi; }
+    }
 }
 
-__global__ __launch_bounds__(kThreads) void trunc_max_kernel(const float* logits, int V, float* lmax_part, int* cand_n) {
+// `per`: entries of a slice, blockIdx.x; a multiple of VEC.
+template <int VEC>
+__global__ __launch_bounds__(kThreads) void trunc_max_kernel(const float* logits, int V, int per, float* lmax_part, int* cand_n) {
     __shared__ float s_red[kWaves];
     const int row = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const float* lr = logits + (size_t)row * V;
-    int lo, hi;
-    slice_range(V, lo, hi);
+    const int lo = (int)blockIdx.x * per;
+    Sweep<VEC> sw(logits + (size_t)row * V, lo, min(V, lo + per), tid);
     float m = -INFINITY;
-    sweep<8>(lr, lo, hi, tid, [&](float l, int) { m = fmaxf(m, l); });
+    sw.run([] {}, [&](float l, int) { m = fmaxf(m, l); });
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
     if (lane == 0) s_red[wave] = m;
     __syncthreads();
-    if (tid == 0) {
-        for (int w = 1; w < kWaves; ++w) m = fmaxf(m, s_red[w]);
+    if (wave != 0) return;
+    m = s_red[lane & (kWaves - 1)];
+#pragma unroll
+    for (int o = kWaves / 2; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
+    if (lane == 0) {
         lmax_part[row * kMaxSlices + blockIdx.x] = m;
         if (blockIdx.x == 0) cand_n[row] = 0;
     }
 }
 
-// the row maximum of z: division by T > 0 is monotone, so max(l / T) = max(l) / T
-__device__ __forceinline__ float row_zmax(const float* lmax_part, int row, int slices, float temperature) {
-    float m = lmax_part[row * kMaxSlices];
-    for (int i = 1; i < slices; ++i) m = fmaxf(m, lmax_part[row * kMaxSlices + i]);
-    return m / temperature;
+// the row's largest logit, by a wave; z's maximum is that / T, as division by T > 0 is monotone
+__device__ __forceinline__ float row_lmax(const float* lmax_part, int row, int slices, int lane) {
+    float m = lane < slices ? lmax_part[row * kMaxSlices + lane] : -INFINITY;
+#pragma unroll
+    for (int o = 8; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
+    return __shfl(m, 0, 64);
 }
 
-__global__ __launch_bounds__(kThreads) void trunc_hist_kernel(const float* logits, int V, float temperature, const float* lmax_part,
-                                                              int want_mass, uint64_t* hist_mass, uint32_t* hist_cnt,
-                                                              uint64_t* sum_mass, uint32_t* sum_cnt) {
-    __shared__ uint64_t hm[kBins];
-    __shared__ uint32_t hc[kBins];
+__device__ __forceinline__ uint64_t shfl_down_any(uint64_t v, int d) { return shfl_down_u64(v, d); }
+__device__ __forceinline__ uint32_t shfl_down_any(uint32_t v, int d) { return __shfl_down(v, d, 64); }
+
+// H: uint64_t, the mass of every bin, or uint32_t, the number of its tokens (with top-k, which the cut then goes by).
+template <int VEC, class H>
+__global__ __launch_bounds__(kThreads) void trunc_hist_kernel(const float* logits, int V, int per, float temperature, const float* lmax_part,
+                                                              H* hist, H* sums) {
+    constexpr bool MASS = sizeof(H) == 8;
+    __shared__ H h[kBins];
+    __shared__ double s_exp2[32];
     const int row = blockIdx.y, tid = threadIdx.x;
-    const float* lr = logits + (size_t)row * V;
-    for (int i = tid; i < kBins; i += kThreads) { hm[i] = 0; hc[i] = 0; }
-    const float zmax = row_zmax(lmax_part, row, gridDim.x, temperature);
+    const int lo = (int)blockIdx.x * per;
+    const float zmax = row_lmax(lmax_part, row, gridDim.x, tid & 63) / temperature;
+    Sweep<VEC> sw(logits + (size_t)row * V, lo, min(V, lo + per), tid);
+    if (MASS && tid < 32) s_exp2[tid] = kExp2Tab[tid];
+    for (int i = tid; i < kBins; i += kThreads) h[i] = 0;
     __syncthreads();
-    int lo, hi;
-    slice_range(V, lo, hi);
-    sweep<8>(lr, lo, hi, tid, [&](float l, int) {
+    sw.run([] {}, [&](float l, int) {
         const float z = l / temperature;
         const int b = bin_of(z, zmax);
-        atomicAdd(&hc[b], 1u);
-        if (want_mass) {
-            const uint64_t m = mass45(z, zmax);
-            if (m) atomicAdd((unsigned long long*)&hm[b], (unsigned long long)m);
+        if constexpr (MASS) {
+            const uint64_t m = mass45(z, zmax, s_exp2);
+            if (m) atomicAdd((unsigned long long*)&h[b], (unsigned long long)m);
+        } else {
+            atomicAdd(&h[b], 1u);
         }
     });
     __syncthreads();
-    const size_t base = ((size_t)row * gridDim.x + blockIdx.x) * kBins;
-    for (int i = tid; i < kBins; i += kThreads) { hist_mass[base + i] = hm[i]; hist_cnt[base + i] = hc[i]; }
-    uint64_t m = 0;
-    uint32_t c = 0;
+    const size_t seg = (size_t)row * gridDim.x + blockIdx.x;
+    for (int i = tid; i < kBins; i += kThreads) hist[seg * kBins + i] = h[i];
+    H sum = 0;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) { m += hm[tid * 4 + i]; c += hc[tid * 4 + i]; }       // 16 threads to a sum
+    for (int i = 0; i < 4; ++i) sum += h[tid * 4 + i];       // 16 threads to a sum
 #pragma unroll
-    for (int d = 8; d > 0; d >>= 1) { m += shfl_down_u64(m, d); c += __shfl_down(c, d, 64); }
-    if ((tid & 15) == 0) {
-        const size_t at = ((size_t)row * gridDim.x + blockIdx.x) * kCoarse + (tid >> 4);
-        sum_mass[at] = m;
-        sum_cnt[at] = c;
-    }
+    for (int d = 8; d > 0; d >>= 1) sum += shfl_down_any(sum, d);
+    if ((tid & 15) == 0) sums[seg * kCoarse + (tid >> 4)] = sum;
 }
 
 __device__ __forceinline__ uint64_t shfl_up_u64(uint64_t v, int d) {
@@ -360,129 +411,161 @@ __device__ __forceinline__ uint64_t shfl_up_u64(uint64_t v, int d) {
     return ((uint64_t)hi << 32) | lo;
 }
 
-// Prefix sums over the bins of a row (bin 0 = the largest z) and the bin in which the cut falls; by one wave, two levels
-// of 64.  Every lane of the wave returns with the plan.
-__device__ __forceinline__ TruncRow trunc_plan(int row, int V, float temperature, int top_k, float top_p, int slices, const float* lmax_part,
-                                               const uint64_t* hist_mass, const uint32_t* hist_cnt, const uint64_t* sum_mass,
-                                               const uint32_t* sum_cnt, int lane) {
+// Prefix sums over the bins of a row (bin 0 = the largest z) and the bin in which the cut falls, two levels of 64, by a
+// workgroup: wave s brings the entries of slice s, all at once, the first wave adds and searches them.  (One wave that read four slices at a
+// time waited eight times for memory.)  coarse: the sum of slice `wave` at `lane`; s_sum: LDS, [kMaxSlices][64].
+// The first wave returns with the plan.
+__device__ __forceinline__ TruncRow trunc_plan(int row, int V, float zmax, int top_k, float top_p, int slices,
+                                               const uint64_t* hist_mass, const uint32_t* hist_cnt, uint64_t coarse, uint64_t* s_sum) {
+    __shared__ int s_first;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     TruncRow r = {};
-    r.zmax = row_zmax(lmax_part, row, slices, temperature);
+    r.zmax = zmax;
     const bool by_count = top_k > 0 && top_k < V;
     const bool by_mass = top_p < 1.0f;
-    uint64_t target = 0, base_m = 0;
-    uint32_t base_c = 0;
+    uint64_t target = (uint64_t)top_k, base = 0;              // of tokens, or of mass
     int first = 0;                                           // the 64 entries of the level start here
 #pragma unroll
     for (int level = 0; level < 2; ++level) {
-        uint64_t m = 0;
-        uint32_t c = 0;
-#pragma unroll 4
-        for (int s = 0; s < slices; ++s) {
-            const size_t seg = (size_t)row * slices + s;
-            m += level == 0 ? sum_mass[seg * kCoarse + lane] : hist_mass[seg * kBins + first + lane];
-            c += level == 0 ? sum_cnt[seg * kCoarse + lane] : hist_cnt[seg * kBins + first + lane];
+        if (level == 1) {
+            if (threadIdx.x == 0) s_first = first;
+            __syncthreads();
+            first = s_first;
         }
-        uint64_t im = m;
-        uint32_t ic = c;
+        if (first < 0) continue;                             // no bin qualifies (every thread of the workgroup knows)
+        if (wave < slices) {
+            const size_t bin = ((size_t)row * slices + wave) * kBins + first + lane;
+            s_sum[wave * 64 + lane] = level == 0 ? coarse : by_count ? (uint64_t)hist_cnt[bin] : hist_mass[bin];
+        }
+        __syncthreads();
+        if (wave != 0) continue;
+        uint64_t own = 0;
+        for (int s = 0; s < slices; ++s) own += s_sum[s * 64 + lane];
+        uint64_t sum = own;
 #pragma unroll
         for (int d = 1; d < 64; d <<= 1) {
-            const uint64_t om = shfl_up_u64(im, d);
-            const uint32_t oc = __shfl_up(ic, d, 64);
-            if (lane >= d) { im += om; ic += oc; }
+            const uint64_t o = shfl_up_u64(sum, d);
+            if (lane >= d) sum += o;
         }
         if (level == 0 && !by_count) {
-            const uint64_t total = ((uint64_t)__shfl((uint32_t)(im >> 32), 63, 64) << 32) | __shfl((uint32_t)im, 63, 64);
+            const uint64_t total = ((uint64_t)__shfl((uint32_t)(sum >> 32), 63, 64) << 32) | __shfl((uint32_t)sum, 63, 64);
             target = (uint64_t)ceil((double)top_p * (double)total);
             if (target < 1) target = 1;
             if (target > total) target = total;
         }
-        const uint64_t before_m = base_m + im - m;
-        const uint32_t before_c = base_c + ic - c;
-        const bool here = by_count ? (before_c < (uint32_t)top_k && (uint32_t)top_k <= before_c + c)
-                                   : (before_m < target && target <= before_m + m);
+        const uint64_t before = base + sum - own;
+        const bool here = before < target && target <= before + own;
         const uint64_t where = __builtin_amdgcn_ballot_w64(here);
-        if (where == 0) { r.fallback = 1; return r; }        // no bin qualifies (a row of NaN): the single path's business
+        if (where == 0) { r.fallback = 1; first = -1; continue; }        // no bin qualifies (a row of NaN): the single path's business
         const int at = __builtin_ctzll(where);               // exactly one
-        base_m = ((uint64_t)__shfl((uint32_t)(before_m >> 32), at, 64) << 32) | __shfl((uint32_t)before_m, at, 64);
-        base_c = __shfl(before_c, at, 64);
+        base = ((uint64_t)__shfl((uint32_t)(before >> 32), at, 64) << 32) | __shfl((uint32_t)before, at, 64);
         if (level == 0) {
             first = at * (kBins / kCoarse);
         } else {
-            const uint32_t bin_c = __shfl(c, at, 64);
             r.cand_hi = first + at;
-            if (by_count && by_mass) {                       // top-p needs the mass of the top-k survivors: resolve both on the list
-                r.cand_lo = 0;
-                r.need_count = (uint32_t)top_k;
-                r.n_cand = (int)(base_c + bin_c);
+            if (by_count) {                                  // too many for the list: known here; by mass, when they have been listed
+                const uint64_t through = base + (uint64_t)__shfl((uint32_t)own, at, 64);
+                // top-p needs the mass of the top-k survivors: resolve both on the list
+                r.cand_lo = by_mass ? 0 : r.cand_hi;
+                r.need_count = (uint32_t)(by_mass ? target : target - base);
+                r.fallback = (by_mass ? through : through - base) > kCap ? 1 : 0;
             } else {
                 r.cand_lo = r.cand_hi;
-                r.need_count = by_count ? (uint32_t)top_k - base_c : 0u;
-                r.need_mass = by_count ? 0ull : target - base_m;
-                r.n_cand = (int)bin_c;
+                r.need_mass = target - base;
             }
-            r.fallback = r.n_cand > kCap ? 1 : 0;
         }
     }
     return r;
 }
 
+// The least logit whose bin is at most `most`, NaN (which no logit reaches) where there is none, in both halves of a wave with a `most` each.  Division by
+// T > 0 and the binning are monotone, so entries can be told apart by this one comparison instead of a division and the arithmetic of the bin
+// each.  Five bits of the logit's order-preserving key at a time: lane i of a half tries the last key of the i-th range.  Undefined
+// and -inf logits lie in the last bin, which is not asked for here (most < kBins - 1); keys above the row's maximum count as it.
+__device__ __forceinline__ float bin_threshold(int most, float zmax, float lmax, float temperature, int lane) {
+    const uint32_t top = order_key(lmax), bottom = order_key(-INFINITY);
+    const int i = lane & 31;
+    auto reaches = [&](uint32_t key) { return key > bottom && bin_of((key < top ? key_value(key) : lmax) / temperature, zmax) <= most; };
+    uint32_t at = 0;
+#pragma unroll
+    for (int shift = 30; shift >= 0; shift -= 5) {
+        const uint32_t last = at + ((uint32_t)(shift == 30 ? i & 3 : i) << shift) + ((1u << shift) - 1u);
+        const uint64_t hit = __builtin_amdgcn_ballot_w64(reaches(last));
+        const uint32_t mine = (uint32_t)(hit >> (lane & 32));
+        // a range whose last key reaches it exists, or (first step: the row's maximum does not) there is none at all
+        at += (mine ? (uint32_t)__builtin_ctz(mine) : 0u) << shift;
+    }
+    return reaches(at) ? key_value(at) : NAN;
+}
+
 // One sweep: tokens above the candidate bins compete for the Gumbel-max right away, tokens in them are listed.
-__global__ __launch_bounds__(kThreads) void trunc_select_kernel(const float* logits, int V, float temperature, int top_k, float top_p,
+template <int VEC>
+__global__ __launch_bounds__(kThreads) void trunc_select_kernel(const float* logits, int V, int per, float temperature, int top_k, float top_p,
                                                                 const float* lmax_part, const uint64_t* hist_mass, const uint32_t* hist_cnt,
                                                                 const uint64_t* sum_mass, const uint32_t* sum_cnt, TruncRow* rows,
                                                                 int use_noise_buffer, KeyChunk keys, const float* noise,
                                                                 uint2* cand, int* cand_n, float2* part) {
     extern __shared__ uint4 lds_raw[];
-    uint2* list = (uint2*)lds_raw;                            // [kCap]: this slice's candidates
-    __shared__ TruncRow s_row;
+    uint2* list = (uint2*)lds_raw;                            // [kCap]: this slice's candidates; before, the plan's sums
+    __shared__ int s_fallback;
+    __shared__ float s_keep, s_list;                          // logits from s_keep on are kept, below it those from s_list on are listed
     __shared__ int s_n, s_at;
     __shared__ int s_best;                                    // best score of the slice's kept tokens so far, as an ordered int
     __shared__ float s_red[kWaves];
     __shared__ int s_idx[kWaves];
     const int row = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int lo = (int)blockIdx.x * per, hi = min(V, lo + per);
+    const float lmax = row_lmax(lmax_part, row, gridDim.x, lane);
+    // (loads return in order: the plan's before the first logits)
+    const size_t seg = (size_t)row * gridDim.x + blockIdx.x, seg_wave = (size_t)row * gridDim.x + min(wave, (int)gridDim.x - 1);
+    const uint64_t coarse = top_k > 0 && top_k < V ? (uint64_t)sum_cnt[seg_wave * kCoarse + lane] : sum_mass[seg_wave * kCoarse + lane];
+    Sweep<VEC> sw(logits + (size_t)row * V, lo, hi, tid);
+    const TruncRow p = trunc_plan(row, V, lmax / temperature, top_k, top_p, gridDim.x, hist_mass, hist_cnt, coarse, (uint64_t*)lds_raw);
     if (wave == 0) {
-        const TruncRow p = trunc_plan(row, V, temperature, top_k, top_p, gridDim.x, lmax_part, hist_mass, hist_cnt, sum_mass, sum_cnt, lane);
+        const int most = lane < 32 ? p.cand_lo - 1 : p.cand_hi;
+        float t = bin_threshold(most, p.zmax, lmax, temperature, lane);
+        if (most < 0) t = NAN;
+        if (lane == 32) s_list = p.cand_hi == kBins - 1 ? -INFINITY : t;
         if (lane == 0) {
-            s_row = p;
+            s_keep = t;
+            s_fallback = p.fallback;
             s_n = 0;
             s_best = ordered_bits(__float_as_int(-INFINITY));
             if (blockIdx.x == 0) rows[row] = p;
         }
     }
     __syncthreads();
-    const TruncRow r = s_row;
-    if (r.fallback) return;
-    const float* lr = logits + (size_t)row * V;
+    if (s_fallback) return;
+    const float keep = s_keep, from = s_list;
+    const bool all = from == -INFINITY;                       // undefined logits too
     const float* nr = use_noise_buffer ? noise + (size_t)row * V : nullptr;
     const uint64_t key64 = keys.key[row];
-    const size_t seg = (size_t)row * gridDim.x + blockIdx.x;
-    int lo, hi;
-    slice_range(V, lo, hi);
     float bv = -INFINITY;
     int bi = 0x7FFFFFFF;
-    if (!nr && lo + tid < hi) {                               // a first bound for noise_may_win: one kept token a thread
-        const float z = lr[lo + tid] / temperature;
-        if (bin_of(z, r.zmax) < r.cand_lo) {
-            const float sc = z + gumbel_noise(key64, lo + tid);
-            if (sc > -INFINITY) atomicMax(&s_best, ordered_bits(__float_as_int(sc)));
-        }
+    if (!nr && sw.base < hi && sw.next[0][0] >= keep) {       // a first bound for the screen: one kept token a thread
+        const float sc = sw.next[0][0] / temperature + gumbel_noise(key64, sw.base);
+        if (sc > -INFINITY) atomicMax(&s_best, ordered_bits(__float_as_int(sc)));
     }
     __syncthreads();
-    sweep<8>(lr, lo, hi, tid, [&](float l, int v) {
-        const float z = l / temperature;
-        const int b = bin_of(z, r.zmax);
-        if (b < r.cand_lo) {
-            const float bound = __int_as_float(ordered_bits(*(volatile int*)&s_best));
+    const float scale = screen_scale(temperature);
+    float bound = -INFINITY, pass = -INFINITY;
+    bool full = false;                                        // more candidates than the list holds: the last kernel does the row
+    sw.run([&] {
+        bound = __int_as_float(ordered_bits(*(volatile int*)&s_best));
+        pass = screen_pass(bound);
+        full = *(volatile int*)&s_n > kCap;
+    }, [&](float l, int v) {
+        if (l >= keep) {
             const uint64_t at = noise_at(key64, v);
-            if (!nr && !noise_may_win(at, z, noise_pass(bound))) return;
-            const float sc = z + (nr ? nr[v] : gumbel_noise(at));
+            if (!nr && !screen_may_win(at, l, scale, pass)) return;
+            const float sc = l / temperature + (nr ? nr[v] : gumbel_noise(at));
             if (better(sc, v, bv, bi)) {
                 bv = sc; bi = v;
                 if (sc > bound) atomicMax(&s_best, ordered_bits(__float_as_int(sc)));
             }
-        } else if (b <= r.cand_hi) {
+        } else if ((l >= from || all) && !full) {
             const int slot = atomicAdd(&s_n, 1);
-            if (slot < kCap) list[slot] = make_uint2(order_key(z), (uint32_t)v);      // n_cand <= kCap in all
+            if (slot < kCap) list[slot] = make_uint2(order_key(l / temperature), (uint32_t)v);
         }
     });
 #pragma unroll
@@ -493,9 +576,8 @@ __global__ __launch_bounds__(kThreads) void trunc_select_kernel(const float* log
     }
     if (lane == 0) { s_red[wave] = bv; s_idx[wave] = bi; }
     __syncthreads();
+    if (wave == 0) best_of_waves(s_red, s_idx, lane, bv, bi);
     if (tid == 0) {
-        for (int w = 1; w < kWaves; ++w)
-            if (better(s_red[w], s_idx[w], bv, bi)) { bv = s_red[w]; bi = s_idx[w]; }
         part[seg] = make_float2(bv, __int_as_float(bi));
         s_at = s_n > 0 ? atomicAdd(&cand_n[row], s_n) : 0;    // this slice's place in the row's list
     }
@@ -505,7 +587,8 @@ __global__ __launch_bounds__(kThreads) void trunc_select_kernel(const float* log
 }
 
 // The radix descent of the single-kernel path on the candidate list (in LDS), then the Gumbel-max over the kept
-// candidates and the slices' winners among the tokens above the cut bin.  The list is short: one histogram for all waves.
+// candidates and the slices' winners among the tokens above the cut bin.  The list is short: one histogram for all waves.  Its keys mostly come
+// from one bin and share their upper bits: the descent starts at the first digit in which any two differ.
 __global__ __launch_bounds__(kThreads) void trunc_resolve_kernel(const float* logits, int V, float temperature, int top_k, float top_p, int slices,
                                                                  const TruncRow* rows, int use_noise_buffer, KeyChunk keys, const float* noise,
                                                                  const uint2* cand, const int* cand_n, const float2* part,
@@ -514,18 +597,38 @@ __global__ __launch_bounds__(kThreads) void trunc_resolve_kernel(const float* lo
     uint2* list = (uint2*)lds_raw;                            // [kCap]
     __shared__ uint64_t hist[256];
     __shared__ Select sel;
+    __shared__ uint32_t s_diff;
+    __shared__ double s_exp2[32];
     __shared__ float s_red[kWaves];
     __shared__ int s_idx[kWaves];
     const int row = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int n_listed = cand_n[row];
+    const uint2 c0 = cand[(size_t)row * kCap], c_tid = cand[(size_t)row * kCap + tid];        // asked for before n is known, used below it
     const TruncRow r = rows[row];
-    if (r.fallback) {                                         // too many candidates, or none: all sweeps by this workgroup
+    if (r.fallback || n_listed > kCap) {                      // too many candidates, or none: all sweeps by this workgroup
         truncated_row((uint64_t*)lds_raw, logits, row, V, temperature, top_k, top_p, use_noise_buffer, keys.key[row], noise, out, tau_out);
         return;
     }
     uint64_t* my_hist = hist;
-    const int n = min(cand_n[row], kCap);
-    for (int i = tid; i < n; i += kThreads) list[i] = cand[(size_t)row * kCap + i];
+    const int n = n_listed;
+    if (tid == 0) s_diff = 0;
+    if (tid < 32) s_exp2[tid] = kExp2Tab[tid];
     __syncthreads();
+    uint32_t diff = 0;
+    if (tid < n) { list[tid] = c_tid; diff = c_tid.x ^ c0.x; }
+    for (int i = tid + kThreads; i < n; i += kThreads) {
+        const uint2 e = cand[(size_t)row * kCap + i];
+        list[i] = e;
+        diff |= e.x ^ c0.x;
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) diff |= __shfl_xor(diff, o, 64);
+    if (lane == 0 && diff) atomicOr(&s_diff, diff);
+    __syncthreads();
+    // digits below which all keys agree; the digits above are the first key's
+    const uint32_t any = s_diff;
+    const int first_shift = any >> 24 ? 24 : any >> 16 ? 16 : any >> 8 ? 8 : 0;
+    const uint32_t shared_bits = n > 0 && first_shift < 24 ? c0.x & ~((256u << first_shift) - 1u) : 0u;
 
     auto clear_hist = [&] {
         if (tid < 256) hist[tid] = 0;
@@ -536,14 +639,13 @@ __global__ __launch_bounds__(kThreads) void trunc_resolve_kernel(const float* lo
     uint32_t floor_key = 0;
 
     if (by_count) {
-        if (tid == 0) { sel.prefix = 0; sel.remaining = (uint64_t)r.need_count; }
-        for (int pass = 0; pass < 4; ++pass) {
-            const int shift = 24 - 8 * pass;
+        if (tid == 0) { sel.prefix = shared_bits; sel.remaining = (uint64_t)r.need_count; }
+        for (int shift = first_shift; shift >= 0; shift -= 8) {
             clear_hist();
             const uint32_t prefix = sel.prefix;
             for (int i = tid; i < n; i += kThreads) {
                 const uint32_t key = list[i].x;
-                if (pass == 0 || (key >> (shift + 8)) == (prefix >> (shift + 8)))
+                if (shift == first_shift || (key >> (shift + 8)) == (prefix >> (shift + 8)))
                     atomicAdd((unsigned long long*)&my_hist[(key >> shift) & 255u], 1ull);
             }
             __syncthreads();
@@ -554,22 +656,21 @@ __global__ __launch_bounds__(kThreads) void trunc_resolve_kernel(const float* lo
         __syncthreads();
     }
     if (by_mass) {
-        if (tid == 0) { sel.prefix = 0; sel.remaining = r.need_mass; }
-        for (int pass = 0; pass < 4; ++pass) {
-            const int shift = 24 - 8 * pass;
+        if (tid == 0) { sel.prefix = shared_bits; sel.remaining = r.need_mass; }
+        for (int shift = first_shift; shift >= 0; shift -= 8) {
             clear_hist();
             const uint32_t prefix = sel.prefix;
             for (int i = tid; i < n; i += kThreads) {
                 const uint32_t key = list[i].x;
-                if (key >= floor_key && (pass == 0 || (key >> (shift + 8)) == (prefix >> (shift + 8)))) {
-                    const uint64_t mass = mass45(key_value(key), r.zmax);
+                if (key >= floor_key && (shift == first_shift || (key >> (shift + 8)) == (prefix >> (shift + 8)))) {
+                    const uint64_t mass = mass45(key_value(key), r.zmax, s_exp2);
                     atomicAdd((unsigned long long*)&my_hist[(key >> shift) & 255u], (unsigned long long)mass);
                 }
             }
             __syncthreads();
-            if (pass == 0) {
+            if (by_count && shift == first_shift) {
                 // with top-k in front the target is a share of the survivors' mass, known only now; alone it came with
-                // the row (and cannot exceed the list's mass: the same integers were summed for the histogram)
+                // the row (and is 1 at least and no more than the list's mass: the same integers were summed for the histogram)
                 if (wave == 0) {
                     uint64_t mine = 0;
                     for (int i = 0; i < 4; ++i) mine += hist[lane * 4 + i];
@@ -580,7 +681,7 @@ __global__ __launch_bounds__(kThreads) void trunc_resolve_kernel(const float* lo
                     }
                     if (lane == 0) {
                         const uint64_t Z = mine;
-                        uint64_t target = by_count ? (uint64_t)ceil((double)top_p * (double)Z) : sel.remaining;
+                        uint64_t target = (uint64_t)ceil((double)top_p * (double)Z);
                         if (target < 1) target = 1;
                         if (target > Z) target = Z;
                         sel.remaining = target;
@@ -619,9 +720,8 @@ __global__ __launch_bounds__(kThreads) void trunc_resolve_kernel(const float* lo
     }
     if (lane == 0) { s_red[wave] = bv; s_idx[wave] = bi; }
     __syncthreads();
+    if (wave == 0) best_of_waves(s_red, s_idx, lane, bv, bi);
     if (tid == 0) {
-        for (int w = 1; w < kWaves; ++w)
-            if (better(s_red[w], s_idx[w], bv, bi)) { bv = s_red[w]; bi = s_idx[w]; }
         out[row] = bi == 0x7FFFFFFF ? 0 : bi;
         if (tau_out) tau_out[row] = floor_key == 0 ? -INFINITY : key_value(floor_key);
     }
@@ -685,7 +785,10 @@ hipError_t launch_sample_truncated_ws(const float* logits, int B, int V, float t
     int* cand_n = (int*)(ws + L.cand_n);
     float2* part = (float2*)(ws + L.part);
     const size_t list_lds = (size_t)kCap * sizeof(uint2);
-    hipError_t e = hipFuncSetAttribute((const void*)trunc_select_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)list_lds);
+    const bool wide = (V & 3) == 0 && ((uintptr_t)logits & 15) == 0;
+    int per = (V + slices - 1) / slices;
+    if (wide) per = (per + 3) & ~3;
+    hipError_t e = hipFuncSetAttribute(wide ? (const void*)trunc_select_kernel<4> : (const void*)trunc_select_kernel<1>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)list_lds);
     if (e != hipSuccess) return e;
     e = hipFuncSetAttribute((const void*)trunc_resolve_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)list_lds);
     if (e != hipSuccess) return e;
@@ -695,11 +798,17 @@ hipError_t launch_sample_truncated_ws(const float* logits, int B, int V, float t
         for (int i = 0; i < m; ++i) k.key[i] = host_keys ? host_keys[off + i] : 0;
         const float* lg = logits + (size_t)off * V;
         const float* nz = noise ? noise + (size_t)off * V : nullptr;
-        hipLaunchKernelGGL(trunc_max_kernel, dim3(slices, m), dim3(kThreads), 0, s, lg, V, lmax, cand_n);
-        hipLaunchKernelGGL(trunc_hist_kernel, dim3(slices, m), dim3(kThreads), 0, s, lg, V, temperature, lmax,
-                           top_p < 1.0f ? 1 : 0, hist_mass, hist_cnt, sum_mass, sum_cnt);
-        hipLaunchKernelGGL(trunc_select_kernel, dim3(slices, m), dim3(kThreads), list_lds, s, lg, V, temperature, top_k, top_p, lmax,
-                           hist_mass, hist_cnt, sum_mass, sum_cnt, rows, noise ? 1 : 0, k, nz, cand, cand_n, part);
+        auto sweeps = [&](auto vec) {
+            constexpr int VEC = decltype(vec)::value;
+            const dim3 g(slices, m), b(kThreads);
+            hipLaunchKernelGGL(trunc_max_kernel<VEC>, g, b, 0, s, lg, V, per, lmax, cand_n);
+            if (top_k > 0 && top_k < V) hipLaunchKernelGGL((trunc_hist_kernel<VEC, uint32_t>), g, b, 0, s, lg, V, per, temperature, lmax, hist_cnt, sum_cnt);
+            else hipLaunchKernelGGL((trunc_hist_kernel<VEC, uint64_t>), g, b, 0, s, lg, V, per, temperature, lmax, hist_mass, sum_mass);
+            hipLaunchKernelGGL(trunc_select_kernel<VEC>, g, b, list_lds, s, lg, V, per, temperature, top_k, top_p, lmax, hist_mass, hist_cnt,
+                               sum_mass, sum_cnt, rows, noise ? 1 : 0, k, nz, cand, cand_n, part);
+        };
+        if (wide) sweeps(std::integral_constant<int, 4>());
+        else sweeps(std::integral_constant<int, 1>());
         hipLaunchKernelGGL(trunc_resolve_kernel, dim3(m), dim3(kThreads), list_lds, s, lg, V, temperature, top_k, top_p, slices, rows,
                            noise ? 1 : 0, k, nz, cand, cand_n, part, out + off, tau_out ? tau_out + off : nullptr);
         e = hipGetLastError();

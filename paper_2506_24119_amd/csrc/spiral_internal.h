@@ -295,15 +295,23 @@ __device__ __forceinline__ float gumbel_noise(uint64_t at) {
     return -logf(-logf(u));
 }
 __device__ __forceinline__ float gumbel_noise(uint64_t key, int v) { return gumbel_noise(noise_at(key, v)); }
-// Tells apart, without a logarithm, entries that cannot win: g > t needs 1 - u < -ln u < e^-t, so where some score `best` of
-// the row is known an entry with 1 - u >= e^(z - best) is out.  noise_pass(best) takes 1e-3 and 1e-6 of the magnitude off
-// the bound, noise_may_win 1e-6 of |z|: the rounding of z, of z + g and of the fast exponential stays below that, so ties are still
-// decided on the exact scores.  True when in doubt (infinities, NaN).
-__device__ __forceinline__ float noise_pass(float best) { return best - 1e-3f - 1e-6f * fabsf(best); }
-__device__ __forceinline__ bool noise_may_win(uint64_t at, float z, float pass) {
-    const uint32_t r = mix64_upper(at) >> 9;
-    const float w = ((float)(0x7FFFFFu - r) + 0.5f) * 1.1920928955078125e-07f;      // 1 - u, exact
-    return !(w >= __builtin_amdgcn_exp2f((fmaf(fabsf(z), 1e-6f, z) - pass) * 1.4426950408889634f));
+// Tells apart, without a logarithm or a division, entries that cannot win.  For a logit l and the best score known so far: g > best - z needs
+// w = 1 - u < -ln u < e^(z - best).  In units of 2^-23 of a binary logarithm: the bits of a positive float, as an integer, are at most its logarithm
+// (127 added) in these units, so an entry is out where the bits of a lower bound of w are no less than (z - best) in them, one product and sum with
+// z = l / T.  Its rounding matters only for z within about 20 of best (beyond, no noise makes up for it, or any does), and is with
+// that of the rest (2^-17 each) below the 1e-3 + 2e-6 |best| that screen_pass takes off the bound.  Infinite and undefined values
+// pass, and all do where the scale is not finite.
+__device__ __forceinline__ float screen_scale(float temperature) {
+    const float c = 1.4426950408889634f * 8388608.f / temperature;
+    return c < INFINITY ? c : NAN;
+}
+__device__ __forceinline__ float screen_pass(float best) {
+    return (best - 1e-3f - 2e-6f * fabsf(best)) * (1.4426950408889634f * 8388608.f) - 127.f * 8388608.f;
+}
+__device__ __forceinline__ bool screen_may_win(uint64_t at, float l, float scale, float pass) {
+    const uint32_t r = mix64_upper(at);
+    const float w = fmaf((float)r, -2.3283064365386963e-10f, 1.f - 2.384185791015625e-07f);      // 1 - r 2^-32 - 2^-22 <= 1 - u
+    return !((float)__float_as_int(w) >= fmaf(l, scale, -pass));
 }
 // an order-preserving int of a float (not NaN), for integer maxima; its own inverse
 __device__ __forceinline__ int ordered_bits(int i) { return i ^ ((i >> 31) & 0x7FFFFFFF); }
