@@ -350,63 +350,81 @@ __device__ __forceinline__ void tile_body(const GemmArgs& g, const QkvPostArgs& 
                             }
                         }
                 }
-                if (is_q || is_k) {
-                    __builtin_amdgcn_wave_barrier();     // the rotation rows have been read
+                __builtin_amdgcn_wave_barrier();         // the rotation rows have been read
 #pragma unroll
-                    for (int j = 0; j < J; ++j)
+                for (int j = 0; j < J; ++j)
 #pragma unroll
-                        for (int b = 0; b < 4; ++b) {
-                            bool out_of_range = false;
-                            ushort4 o;
-                            o.x = f32_to_act16_noting(acc[j][i][4 * b], out_of_range);
-                            o.y = f32_to_act16_noting(acc[j][i][4 * b + 1], out_of_range);
-                            o.z = f32_to_act16_noting(acc[j][i][4 * b + 2], out_of_range);
-                            o.w = f32_to_act16_noting(acc[j][i][4 * b + 3], out_of_range);
-                            bad = bad || (out_of_range && m < g.M);
-                            *(ushort4*)(tb + l32 * OROW + (32 * j + 8 * b + 4 * lh) * 2) = o;
+                    for (int b = 0; b < 4; ++b) {
+                        bool out_of_range = false;
+                        ushort4 o;
+                        o.x = f32_to_act16_noting(acc[j][i][4 * b], out_of_range);
+                        o.y = f32_to_act16_noting(acc[j][i][4 * b + 1], out_of_range);
+                        o.z = f32_to_act16_noting(acc[j][i][4 * b + 2], out_of_range);
+                        o.w = f32_to_act16_noting(acc[j][i][4 * b + 3], out_of_range);
+                        bad = bad || (out_of_range && m < g.M);
+                        *(ushort4*)(tb + l32 * OROW + (32 * j + 8 * b + 4 * lh) * 2) = o;
+                    }
+                __builtin_amdgcn_wave_barrier();
+                if (is_q) {                          // 16 lanes a row of 256 bytes
+                    const int c16 = lane & 15;
+#pragma unroll
+                    for (int ps = 0; ps < 8; ++ps) {
+                        const int row = 4 * ps + (lane >> 4);
+                        const u32x4 v = *(const u32x4*)(tb + row * OROW + c16 * 16);
+                        if (mb + row < g.M) *(u32x4*)(qa.q + ((size_t)(mb + row) * qa.n_q_heads + head) * 128 + c16 * 8) = v;
+                    }
+                } else if (is_k) {                       // 16 rows x 4 groups of 8 d: tokens of a page are neighbours
+                    const int r16 = lane & 15;
+#pragma unroll
+                    for (int half = 0; half < 2; ++half) {
+                        const int row = half * 16 + r16;
+                        const int2 pp = qa.row_page[min(mb + row, g.M - 1)];
+                        uint16_t* dst = qa.pages + ((size_t)pp.x * qa.n_kv_heads + kvh) * (size_t)(2 * kPageTokens * 128);
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) {
+                            // K element (token, d) sits at (d/32)*512 + (((d%32)/8)*16 + token)*8 + d%8; this lane's d/8 is 4 j + lane/16
+                            const int b = lane >> 4;
+                            const u32x4 v = *(const u32x4*)(tb + row * OROW + (4 * j + b) * 16);
+                            if (mb + row < g.M) *(u32x4*)(dst + j * 512 + ((b * 16 + (pp.y & (kPageTokens - 1))) << 3)) = v;
                         }
-                    __builtin_amdgcn_wave_barrier();
-                    if (is_q) {                          // 16 lanes a row of 256 bytes
-                        const int c16 = lane & 15;
+                    }
+                } else {
+                    // V element (d, token) sits at (d/32)*512 + ((token/4)*16 + d%16)*8 + ((d/16)%2)*4 + token%4: four tokens from a multiple of four on, at d
+                    // and d + 16, are 16 neighbouring bytes, a lane's here (its d is 32 (lane/16) + lane%16).  Such runs start anywhere in
+                    // the tile, as sequences do; the runs cut off at its ends or a sequence's go row by row.  (Two bytes a store, straight from the
+                    // accumulators, was 64 stores of 16 pieces each for 32 rows.  us a launch, that -> this: 0.6B shape, 11,206 rows 147 -> 119, the last
+                    // layer's k and v alone 84 -> 65; 4B, 788 rows 53 -> 46 and 51 -> 43, 15,272 rows 497 -> 484 and 191 -> 166.)
+                    const int rows = min(32, g.M - mb);
+                    const int2 mine = qa.row_page[min(m, g.M - 1)];
+                    const int page_before = __shfl_up(mine.x, 1, 64), run_before = __shfl_up(mine.y >> 2, 1, 64);
+                    const bool first = l32 == 0 || mine.x != page_before || (mine.y >> 2) != run_before;
+                    uint32_t left = (uint32_t)__builtin_amdgcn_ballot_w64(first && l32 < rows);
+                    const char* src = tb + (32 * (lane >> 4) + (lane & 15)) * 2;
+                    while (left) {
+                        const int r0 = __builtin_ctz(left);
+                        left &= left - 1;
+                        const int r1 = left ? __builtin_ctz(left) : rows;
+                        const int page = __builtin_amdgcn_readlane(mine.x, r0), pos = __builtin_amdgcn_readlane(mine.y, r0);
+                        uint16_t* dst = qa.pages + ((size_t)page * qa.n_kv_heads + kvh) * (size_t)(2 * kPageTokens * 128) + kPageTokens * 128 +
+                                        (lane >> 4) * 512 + (((((pos & (kPageTokens - 1)) >> 2) * 16) + (lane & 15)) << 3);
+                        if (r1 - r0 == 4) {
+                            uint32_t x[8];
 #pragma unroll
-                        for (int ps = 0; ps < 8; ++ps) {
-                            const int row = 4 * ps + (lane >> 4);
-                            const u32x4 v = *(const u32x4*)(tb + row * OROW + c16 * 16);
-                            if (mb + row < g.M) *(u32x4*)(qa.q + ((size_t)(mb + row) * qa.n_q_heads + head) * 128 + c16 * 8) = v;
-                        }
-                    } else {                             // 16 rows x 4 groups of 8 d: tokens of a page are neighbours
-                        const int r16 = lane & 15;
-#pragma unroll
-                        for (int half = 0; half < 2; ++half) {
-                            const int row = half * 16 + r16;
-                            const int2 pp = qa.row_page[min(mb + row, g.M - 1)];
-                            uint16_t* dst = qa.pages + ((size_t)pp.x * qa.n_kv_heads + kvh) * (size_t)(2 * kPageTokens * 128);
-#pragma unroll
-                            for (int j = 0; j < 4; ++j) {
-                                // K element (token, d) sits at (d/32)*512 + (((d%32)/8)*16 + token)*8 + d%8; this lane's d/8 is 4 j + lane/16
-                                const int b = lane >> 4;
-                                const u32x4 v = *(const u32x4*)(tb + row * OROW + (4 * j + b) * 16);
-                                if (mb + row < g.M) *(u32x4*)(dst + j * 512 + ((b * 16 + (pp.y & (kPageTokens - 1))) << 3)) = v;
+                            for (int t = 0; t < 4; ++t) {
+                                x[t] = *(const uint16_t*)(src + (r0 + t) * OROW);
+                                x[4 + t] = *(const uint16_t*)(src + (r0 + t) * OROW + 32);
+                            }
+                            *(u32x4*)dst = u32x4{x[0] | x[1] << 16, x[2] | x[3] << 16, x[4] | x[5] << 16, x[6] | x[7] << 16};
+                        } else {
+                            for (int r = r0; r < r1; ++r) {
+                                const int slot = __builtin_amdgcn_readlane(mine.y, r) & 3;
+                                dst[slot] = *(const uint16_t*)(src + r * OROW);
+                                dst[4 + slot] = *(const uint16_t*)(src + r * OROW + 32);
                             }
                         }
                     }
-                    __builtin_amdgcn_wave_barrier();
-                } else if (m < g.M) {
-                    const int2 pp = qa.row_page[m];
-                    const int slot = pp.y & (kPageTokens - 1);
-                    uint16_t* dst = qa.pages + ((size_t)pp.x * qa.n_kv_heads + kvh) * (size_t)(2 * kPageTokens * 128) + kPageTokens * 128;
-#pragma unroll
-                    for (int j = 0; j < J; ++j)
-#pragma unroll
-                        for (int b = 0; b < 4; ++b) {
-                            // V element (d, token) sits at (d/32)*512 + ((token/4)*16 + d%16)*8 + ((d/16)%2)*4 + token%4
-                            uint16_t* vb = dst + j * 512 + (((slot >> 2) * 16 + 8 * (b & 1) + 4 * lh) << 3) + ((b >> 1) << 2) + (slot & 3);
-                            vb[0] = f32_to_act16_noting(acc[j][i][4 * b], bad);
-                            vb[8] = f32_to_act16_noting(acc[j][i][4 * b + 1], bad);
-                            vb[16] = f32_to_act16_noting(acc[j][i][4 * b + 2], bad);
-                            vb[24] = f32_to_act16_noting(acc[j][i][4 * b + 3], bad);
-                        }
                 }
+                __builtin_amdgcn_wave_barrier();
             }
         }
         report_saturation(qa.sat_count, bad);
