@@ -181,7 +181,7 @@ int    spiral_kv_free_pages(const spiral_kv_pool* p);
  *  - above 128 rows the K splits of the projections, and so the order of their fp32 sums, follow from the number of rows;
  *  - above 128 rows and from four rows to a sequence on (16-bit weights, projections not tuned, see "trim" above) the last layer
  *    computes its queries, attention, O and MLP for the sequences' last tokens only, on the decode step's kernels;
- *  - the LM head adds in another order from 33 sequences on.
+ *  - the LM head adds in another order from 33 sequences on, one of at most 2^25 weights and 8 d_model columns from 129 on.
  * In a decode step the cut of the attention follows from all contexts of the call; the rules on K splits and on the LM head hold
  * there as well; 32-bit weights have a form for few sequences (up to 32, fewer where d_model is large).
  * Logits then differ by the rounding of half-precision activations.  Largest difference seen, in standard deviations of the

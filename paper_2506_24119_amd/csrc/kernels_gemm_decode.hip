@@ -47,10 +47,9 @@ __global__ __launch_bounds__(256, WAVES) void gemm_decode_kernel(GemmArgs g) {
     constexpr int GROUP = UNITS < 4 ? UNITS : 4;     // tiles that meet in LDS at a time
     constexpr int PASSES = (UNITS + 3) / 4;
     constexpr int BUF = 4 * GROUP * TILE;
-    static_assert(EPI != EPI_SAMPLE || M32 == 1, "the sampling epilogue has one row tile");
     __shared__ __attribute__((aligned(16))) char lds[(PASSES > 1 ? 2 : 1) * BUF];
-    __shared__ float s_val[EPI == EPI_SAMPLE ? NT * 32 : 1];
-    __shared__ int s_idx[EPI == EPI_SAMPLE ? NT * 32 : 1];
+    __shared__ float s_val[EPI == EPI_SAMPLE ? NT * M32 * 32 : 1];
+    __shared__ int s_idx[EPI == EPI_SAMPLE ? NT * M32 * 32 : 1];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int l32 = lane & 31, lh = lane >> 5;
     const int K = g.K, tile0 = blockIdx.x * NT, split = blockIdx.y;
@@ -222,7 +221,7 @@ __global__ __launch_bounds__(256, WAVES) void gemm_decode_kernel(GemmArgs g) {
                         const int oi = __shfl_xor(bi, s, 64);
                         if (better(ov, oi, bv, bi)) { bv = ov; bi = oi; }
                     }
-                    if (cg == 0) { s_val[j * 32 + m] = bv; s_idx[j * 32 + m] = bi; }
+                    if (cg == 0) { s_val[j * M32 * 32 + m] = bv; s_idx[j * M32 * 32 + m] = bi; }
                 }
             }
         }
@@ -236,7 +235,7 @@ __global__ __launch_bounds__(256, WAVES) void gemm_decode_kernel(GemmArgs g) {
             int bi = s_idx[m];
 #pragma unroll
             for (int j = 1; j < NT; ++j)
-                if (better(s_val[j * 32 + m], s_idx[j * 32 + m], bv, bi)) { bv = s_val[j * 32 + m]; bi = s_idx[j * 32 + m]; }
+                if (better(s_val[j * M32 * 32 + m], s_idx[j * M32 * 32 + m], bv, bi)) { bv = s_val[j * M32 * 32 + m]; bi = s_idx[j * M32 * 32 + m]; }
             g.s_part[(size_t)m * g.s_tiles + blockIdx.x] = make_float2(bv, __int_as_float(bi));
         }
     }
@@ -274,15 +273,18 @@ static hipError_t launch_tiles(const GemmArgs& a, int nt, hipStream_t s) {
 // The others stay there from 64 MB of weights on: the 7B shape's down (136 MB) row-major 31.8 -> 47.4, 35.1 -> 49.8, 44.0 -> 58.0, repacked 27.0
 // -> 26.2, 28.8 -> 28, 37.0 -> 37; 2,560 x 12,288 (63 MB) row-major 19.8 -> 20.9, 21.0 -> 21.9, 26.4 -> 30.8, repacked 16.1 -> 14.9,
 // 18.6 -> 16.2, 23.4 -> 24.7.
-// The LM head does up to 32 rows, with logits as a small head (2^25 weights) up to 128: its sums are rounded by nothing that follows.  Streaming kernel
+// The LM head does up to 32 rows, a small one (2^25 weights) up to 128, with logits and with the sampler's winners alike, as both have to
+// come from the same sums: they are rounded by nothing that follows.  Up to eight columns to a k: the noise of the winners, one wave a SIMD above 64
+// rows, outweighs the rest beyond (one layer and head, sampled, streaming kernel -> this, 128 rows: 8,192 x 1024 72 -> 63, x 2560 100 -> 84,
+// x 3584 120 -> 101, 40 rows x 2560 68 -> 62, but 32,768 x 1024 76 -> 83, 65,536 x 128 60 -> 90).  Streaming kernel
 // -> this, us, 8,192 columns at 33, 64 and 128 rows: K = 1024 8.7 -> 5.2, 9.0 -> 5.6, 13.5 -> 7.9; 2560 17 -> 9.6, 19 -> 10.2, 30.5 -> 15.1; 3584 23 -> 12.4,
 // 25 -> 14.3, 41 -> 21.4.  One layer and a row-major head of 151,936, 1, 16 and 32 rows: 0.6B 119 -> 107, 129 -> 115, 136 -> 122; 4B 252 -> 229,
 // 267 -> 264, 283 -> 287; 7B 337 -> 333, 364 -> 370, 382 -> 402.
 bool gemm_decode_takes(int M, int N, int K, int epilogue, bool head) {
     if (M < 1 || M > 128 || (K & 127) || (N & 15)) return false;
     if (epilogue == EPI_SWIGLU) return (N + 15) / 16 <= 512;
-    if (head && M <= 32) return true;
-    return epilogue != EPI_SAMPLE && (long long)N * K <= 1 << 25;
+    if (head) return M <= 32 || (N <= 8LL * K && (long long)N * K <= 1 << 25);
+    return (long long)N * K <= 1 << 25;
 }
 
 // Whether the down projection reads act_frag() order: whenever it comes here, as gate/up (d columns in, ffn out) writes that order from
@@ -326,7 +328,9 @@ hipError_t launch_gemm_decode(const GemmArgs& a, int epilogue, int nt, hipStream
     if (!gemm_decode_takes(a.M, a.N, a.K, epilogue, a.head != 0) || a.splits < 1 || a.splits > (a.K >> 7)) return hipErrorInvalidValue;
     // a large head: two tiles a workgroup (the winners' array has room for 64 columns each), one for logits of a few rows and a long K (151,936
     // columns, 1 / 2 / 3 tiles, us, K = 2560: 3 rows 110 / 116 / 119, 16 123 / 125 / 129, 24 140 / 132 / 135; K = 1024: 3 rows 48 / 47 / 47, 16 56 / 51 / 52; row-major weights, of whose lines a load has 32 bytes, lose 10 % of the step)
-    if (epilogue == EPI_SAMPLE) return launch_one<1, 2, EPI_SAMPLE, 6, 2>(a, s);
+    if (epilogue == EPI_SAMPLE)
+        return a.M <= 32 ? launch_one<1, 2, EPI_SAMPLE, 6, 2>(a, s) : a.M <= 64 ? launch_one<2, 2, EPI_SAMPLE, 6, 2>(a, s)
+             : a.M <= 96 ? launch_one<3, 2, EPI_SAMPLE, 3, 1>(a, s) : launch_one<4, 2, EPI_SAMPLE, 3, 1>(a, s);
     if (epilogue == EPI_SWIGLU && a.splits != 1) return hipErrorInvalidValue;
     if (nt == 0) nt = a.head && (long long)a.N * a.K > 1 << 25 ? (a.wf && a.M <= 16 && a.K >= 2048 ? 1 : 2) : gemm_decode_tiles(a.M, a.N, a.K, epilogue, a.splits);
     if (epilogue == EPI_SWIGLU)

@@ -443,7 +443,7 @@ static hipError_t launch_shape(const GemmArgs& a, int bn, hipStream_t s, bool sa
 
 // columns of the LM head that one workgroup of the sampling epilogue covers (host code sizes s_part with it): up to 32 rows two
 // tiles of gemm_decode_kernel
-int gemm_sample_tile_cols(int M, int bn) { return (M <= 32 || bn < 128) ? 64 : 128; }
+int gemm_sample_tile_cols(int M, int N, int K, int bn) { return bn < 128 || gemm_decode_takes(M, N, K, EPI_SAMPLE, true) ? 64 : 128; }
 
 hipError_t launch_gemm_stream(const GemmArgs& a, int epilogue, int bn, hipStream_t s) {
     if ((a.K & 127) || (a.N & 15) || a.splits < 1 || a.splits > (a.K >> 7)) return hipErrorInvalidValue;

@@ -170,7 +170,7 @@ hipError_t launch_attn_prefill(const AttnArgs& a, int hd, int B, int max_new, bo
 
 hipError_t launch_stream_read(const void* p, size_t bytes, int workgroups, hipStream_t s);
 hipError_t launch_sample_pick(const float2* part, int B, int n_tiles, int32_t* out, hipStream_t s);
-int gemm_sample_tile_cols(int M, int bn);     // LM-head columns per workgroup of the sampling epilogue
+int gemm_sample_tile_cols(int M, int N, int K, int bn);     // LM-head columns per workgroup of the sampling epilogue
 int sample_slices(int rows, int V, int mode);       // workgroups per row; mode 0: greedy, 1: generated noise, 2: noise buffer
 bool sample_screens(int per_slice);                 // entries that cannot win are told apart first (generated noise)
 hipError_t launch_sample(const float* logits, int B, int V, float temperature, const uint64_t* host_keys,

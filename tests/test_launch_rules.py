@@ -43,3 +43,15 @@ def test_scoring_pairs_of_narrow_head_models_fit(lib):
     fit = rule(lib, "_ZN6spiral15score_pairs_fitEiiiii", C.c_bool, *[C.c_int] * 5)
     assert fit(151936, 1536, 8960, 12 * 128, 2 * 128) and fit(151936, 896, 4864, 14 * 64, 2 * 64)
     assert fit(30000, 256, 384, 128, 128) and not fit(70000, 256, 384, 128, 128)
+
+
+def test_both_forms_of_the_head_add_in_the_same_order(lib):
+    """A step with the sampler inside draws the tokens of the sampler on that step's logits, bit for bit: the LM head of either comes
+    from gemm_decode_kernel, whose order of sums is its own, or of neither."""
+    takes = rule(lib, "_ZN6spiral17gemm_decode_takesEiiiib", C.c_bool, *[C.c_int] * 4, C.c_bool)
+    STORE, SAMPLE = 0, 2
+    for rows in (1, 32, 33, 64, 65, 96, 97, 128, 129, 500):
+        for d in (128, 640, 1024, 2560, 3584):
+            for vocab in (1008, 8192, 13120, 65520, 65536, 151936):
+                assert takes(rows, vocab, d, STORE, True) == takes(rows, vocab, d, SAMPLE, True), (rows, d, vocab)
+    assert takes(128, 8192, 2560, SAMPLE, True) and not takes(33, 151936, 1024, SAMPLE, True)
