@@ -490,9 +490,10 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(AttnArgs a, Prefil
 // 128 rows of 1,280 tokens, 7 % of a step):
 //   DECODE_PAIR: short contexts (the host's rule): a workgroup has one pair to itself and writes the output: no search, no partial
 //   results, no merging launch.  27 rows of 400 tokens, 0.6B shape: 6 us a layer less of 51.
-//   DECODE_PIECES: the last rows of a prefill, and small batches: workgroup (x, y) has pages y * U to (y + 1) * U of pair x, if there are any, and
-//   writes the pair's part y: no search, and one pair only.  Where a pair is cut follows from its own pages and U, which a prefill's last rows
-//   leave fixed, so that the order of their sums follows from their own context, not from the call's others.
+//   DECODE_PIECES: the last rows of a prefill, and small batches: workgroup (x, y) has the y-th piece of pair x, if there is one, and
+//   writes the pair's part y: no search, and one pair only.  Small batches are cut where the equal ranges cut them (a workgroup that would have
+//   crossed from one pair to the next is two here), so that the two forms give the same bits.  A prefill's last rows (own_cut) are cut from each
+//   pair's first page on: there the order of the sums follows from their own context, not from the call's others.
 template <int HD, bool ACT32, int FORM>
 __global__ __launch_bounds__(256) void attn_stream_kernel(AttnArgs a) {
     constexpr int KS = HD / 32, MT = HD / 16, OSTRIDE = HD + 4;
@@ -540,10 +541,16 @@ __global__ __launch_bounds__(256) void attn_stream_kernel(AttnArgs a) {
         cur.pos = a.row_pos[cur.r];
         cur.np = cur.pos / kPageTokens + 1;
         cur.kvh = blockIdx.x % Hkv;
-        cur.p0 = FORM == DECODE_PIECES ? blockIdx.y * U : 0;
-        if (cur.p0 >= cur.np) return;            // the longest pair has more pieces
+        cur.p0 = 0;
+        u_end = cur.np;
+        if (FORM == DECODE_PIECES) {
+            const int start = a.own_cut ? 0 : rps[cur.r] * Hkv + cur.kvh * cur.np;
+            const int from = (start / U + (int)blockIdx.y) * U - start;
+            cur.p0 = max(from, 0);
+            u_end = from + U;
+            if (cur.p0 >= cur.np) return;        // the longest pair has more pieces
+        }
         u = cur.p0;
-        u_end = u + (FORM == DECODE_PIECES ? U : cur.np);
     }
     cur.p1 = min(cur.np, cur.p0 + (u_end - u));
     cur.bt = a.block_table + (size_t)a.row_seq[cur.r] * a.max_blocks;
@@ -684,7 +691,7 @@ __global__ __launch_bounds__(64) void attn_stream_combine_kernel(AttnArgs a) {
     const int G = a.n_q_heads / a.n_kv_heads, Hkv = a.n_kv_heads;
     const int kvh = h / G, j = h % G;
     const int rs = a.row_page_start[r], np = a.row_page_start[r + 1] - rs;
-    const int start = a.form == DECODE_PIECES ? 0 : rs * Hkv + kvh * np;           // pieces are counted from the pair's own start
+    const int start = a.own_cut ? 0 : rs * Hkv + kvh * np;
     const int first = start / a.units_per_wg;
     const int last = (start + np - 1) / a.units_per_wg;
     const int n_parts = last - first + 1;
@@ -741,7 +748,8 @@ static hipError_t stream_impl(const AttnArgs& a, hipStream_t s) {
     const size_t lds = (size_t)(4 * G * (HD + 4) + 128) * sizeof(float);
     const int pairs = a.n_rows * a.n_kv_heads, wgs = (a.total_units + a.units_per_wg - 1) / a.units_per_wg;
     if (a.form == DECODE_PAIR) hipLaunchKernelGGL((attn_stream_kernel<HD, ACT32, DECODE_PAIR>), dim3(pairs), dim3(256), lds, s, a);
-    else if (a.form == DECODE_PIECES) hipLaunchKernelGGL((attn_stream_kernel<HD, ACT32, DECODE_PIECES>), dim3(pairs, a.n_chunks), dim3(256), lds, s, a);
+    else if (a.form == DECODE_PIECES)            // a pair that starts inside a piece has one more: of the two spare slots one is enough
+        hipLaunchKernelGGL((attn_stream_kernel<HD, ACT32, DECODE_PIECES>), dim3(pairs, a.own_cut ? a.n_chunks : a.n_chunks - 1), dim3(256), lds, s, a);
     else hipLaunchKernelGGL((attn_stream_kernel<HD, ACT32, DECODE_STREAM>), dim3(wgs), dim3(256), lds, s, a);
     return hipGetLastError();
 }

@@ -602,6 +602,7 @@ struct StepCtx {
     float temperature = 0.f;
     int32_t* out_tokens = nullptr;
     const int32_t *host_ids = nullptr, *host_pos = nullptr;   // sequences and the positions of their (last) tokens
+    bool own_cut = false;                                  // DECODE_PIECES: counted from each pair's first page
     int32_t* order = nullptr;                              // DECODE_PAIR: the rows by falling context, from the embedding kernel
     int first_layer = 0;
     const int32_t* q_rows = nullptr;                       // set: first_layer's k and v are in the pages and h is normed; q's rows of the
@@ -654,6 +655,14 @@ bool decode_in_pairs(const std::vector<int>& pages, int n_q_heads, int n_kv_head
     const float segments = std::min((float)n_kv_heads, (float)range / (float)pages.back());
     return us < 8.5f + 2.f * std::max(0.f, segments - 4.f);
 }
+
+// Whether each piece of a pair gets a workgroup to itself, which looks for nothing and has one pair only, instead of each of the equal ranges
+// of the whole batch: where the places hold all pieces at once, one more than ranges for every pair.  The cuts, and so the bits, are the same.
+// One step, us, ranges -> pieces: a 0.6B model, 1 row of 1,450 tokens 1027 -> 971, 3 of 200..1,500 1074 -> 1047, 6 of 200..2,500 1192 -> 1172; four 4B
+// layers, 5 of 200..1,500 272.5 -> 265, 1 of 3,500 272 -> 262; three 7B layers, 9 of 300..2,000 348 -> 341, 20 of 500..1,500 364 -> 360.  Where the pieces
+// are too many: four 0.6B layers, 16 of 300..2,000 202.5 -> 209, three 7B layers, 24 of 512..2,560 379.4 -> 383.5 (27: the same).  (Cut from each
+// pair's first page instead the first three take 964, 1039 and 1153, and the results then round otherwise than the ranges' do.)
+bool decode_in_pieces(int units, int units_per_wg, int pairs, int places) { return (units + units_per_wg - 1) / units_per_wg + pairs <= places; }
 }  // namespace spiral
 
 // Form, pieces and partial results of the decode attention over c.rows rows; pages_all: the sum of their page counts.
@@ -664,9 +673,7 @@ static void plan_decode_attention(StepCtx& c, int pages_all, int max_ctx) {
     c.units_per_wg = std::max(m->tune.chunk_pages, (c.total_units + wgs - 1) / wgs);
     c.n_slots = decode_slots(m, max_ctx);
     if (m->tune.chunk_set) return;
-    const bool few = c.units_per_wg == m->tune.chunk_pages;
     const int longest = (max_ctx + kPageTokens - 1) / kPageTokens;
-    int units = std::max((c.total_units + wgs - 1) / wgs, (longest + kDecodePieces - 1) / kDecodePieces);
     if (!m->tune.attn_wgs) {
         std::vector<int> pages(c.rows);
         for (int i = 0; i < c.rows; ++i) pages[i] = c.host_pos[i] / kPageTokens + 1;
@@ -676,37 +683,21 @@ static void plan_decode_attention(StepCtx& c, int pages_all, int max_ctx) {
             c.order = c.w.last_rows;
             return;
         }
-        // Few units (a small batch): up to 16 pieces to a pair, counted from its first page, as short as the places hold all of
-        // them at once.  Against equal ranges of the whole batch (below) a workgroup has one pair and looks for nothing.  One step, us, ranges -> pieces: a
-        // 0.6B model, 1 row of 400 tokens 954 -> 938, of 1,450 1025 -> 975, 3 of 200..1,500 1092 -> 1058; four 4B layers, 5 of 200..1,500
-        // 275 -> 267; three 7B layers, 9 of 300..2,000 348 -> 342, 27 of 512..2,560 392.5 -> 390.
-        auto pieces = [&](int u) { int n = 0; for (int p : pages) n += (p + u - 1) / u; return n * kv; };
-        int u = units;
-        while (u <= c.units_per_wg && pieces(u) > wgs) ++u;
-        const int slots = (longest + u - 1) / u;
-        const size_t need = (size_t)c.rows * m->cfg.n_q_heads * slots * (m->cfg.head_dim + 2) * sizeof(float);
-        const bool borrow = slots > c.n_slots;               // the q/k/v products' memory, dead by then
-        if (few && u <= c.units_per_wg && (!borrow || need <= (size_t)((char*)c.w.q - (char*)c.w.qkv))) {
-            c.form = DECODE_PIECES;
-            c.units_per_wg = u;
-            c.n_slots = slots;
-            if (borrow) c.w.attn_part = c.w.qkv;
-            return;
-        }
     }
-    if (few) {
-        // Equal ranges as short as there are pages, up to 16 to a pair.  A workgroup's time
-        // is its chain of dependent steps, of which 16 pages are four per wave: one row of 250 tokens, 4B shape, pieces of
-        // 16 / 8 / 4 / 2 pages 8.8 / 7.0 / 5.9 / 4.1 us; 1,450 tokens in 16 pieces 5.3 us, in 32 9.4.  The larger
-        // number of partial results goes to the q/k/v products' memory, dead by then.
-        const int slots = (longest + units - 1) / units + 2;
-        const size_t need = (size_t)c.rows * m->cfg.n_q_heads * slots * (m->cfg.head_dim + 2) * sizeof(float);
-        if (units < c.units_per_wg && need <= (size_t)((char*)c.w.q - (char*)c.w.qkv)) {
-            c.units_per_wg = units;
-            c.n_slots = slots;
-            c.w.attn_part = c.w.qkv;
-        }
+    if (c.units_per_wg != m->tune.chunk_pages) return;
+    // Few units (a small batch): ranges as short as there are pages, up to 16 to a pair.  A workgroup's time
+    // is its chain of dependent steps, of which 16 pages are four per wave: one row of 250 tokens, 4B shape, pieces of
+    // 16 / 8 / 4 / 2 pages 8.8 / 7.0 / 5.9 / 4.1 us; 1,450 tokens in 16 pieces 5.3 us, in 32 9.4.  The larger
+    // number of partial results goes to the q/k/v products' memory, dead by then.
+    const int units = std::max((c.total_units + wgs - 1) / wgs, (longest + kDecodePieces - 1) / kDecodePieces);
+    const int slots = (longest + units - 1) / units + 2;
+    const size_t need = (size_t)c.rows * m->cfg.n_q_heads * slots * (m->cfg.head_dim + 2) * sizeof(float);
+    if (units < c.units_per_wg && need <= (size_t)((char*)c.w.q - (char*)c.w.qkv)) {
+        c.units_per_wg = units;
+        c.n_slots = slots;
+        c.w.attn_part = c.w.qkv;
     }
+    if (!m->tune.attn_wgs && decode_in_pieces(c.total_units, c.units_per_wg, c.rows * kv, wgs)) c.form = DECODE_PIECES;
 }
 
 // The same for the last rows of a prefill: pieces of a fixed number of pages from each pair's first on, so that a sequence's sums do not
@@ -720,6 +711,7 @@ static void plan_last_rows_attention(StepCtx& c, int pages_all, int max_ctx) {
     const int longest = (max_ctx + kPageTokens - 1) / kPageTokens;
     c.n_slots = (longest + c.units_per_wg - 1) / c.units_per_wg;
     c.form = c.n_slots == 1 ? DECODE_PAIR : DECODE_PIECES;
+    c.own_cut = true;
 }
 
 namespace spiral {
@@ -919,7 +911,7 @@ static int run_layers(StepCtx& c) {
         aa.scale_log2e = (float)(1.4426950408889634 / std::sqrt((double)hd));
         if (c.decode) {
             aa.row_page_start = c.w.page_start; aa.units_per_wg = c.units_per_wg; aa.total_units = c.total_units;
-            aa.n_chunks = c.n_slots; aa.out_frag = o_frag; aa.form = c.form; aa.order = c.order;
+            aa.n_chunks = c.n_slots; aa.out_frag = o_frag; aa.form = c.form; aa.order = c.order; aa.own_cut = c.own_cut;
             HIP_TRY(timed(m, SPIRAL_K_ATTN_DECODE, c.s, [&] { return launch_attn_stream(aa, hd, act32, c.s); }));
             if (c.form != DECODE_PAIR) HIP_TRY(timed(m, SPIRAL_K_ATTN_COMBINE, c.s, [&] { return launch_attn_stream_combine(aa, hd, act32, c.s); }));
         } else {

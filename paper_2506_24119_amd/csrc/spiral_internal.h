@@ -65,7 +65,7 @@ struct GemmArgs {
 };
 
 // How the decode attention shares out its pages: the whole batch in equal ranges, a workgroup to a (row, kv head) pair, which writes `out`
-// (no partial results), or pieces of units_per_wg pages counted from each pair's first (n_chunks: as many as the longest pair has).
+// (no partial results), or a workgroup to each piece of a pair: cut where the equal ranges are, or own_cut (n_chunks: as many as the longest pair has).
 enum DecodeForm { DECODE_STREAM = 0, DECODE_PAIR = 1, DECODE_PIECES = 2 };
 
 struct AttnArgs {
@@ -86,6 +86,7 @@ struct AttnArgs {
     int32_t out_frag;         // 16-bit out, at most 128 rows: in act_frag() order
     int32_t form;             // decode: DecodeForm
     const int32_t* order;     // or null: DECODE_PAIR: the rows in the order in which their workgroups start
+    int32_t own_cut;          // DECODE_PIECES: counted from each pair's first page, not from the batch's
 };
 
 // Launchers (defined in the kernel translation units).  All enqueue on `s` and return the launch status.

@@ -42,3 +42,35 @@ def test_pieces_match_the_coarse_cut_and_the_oracle(lens, dtype):
             for form in (0, 2):
                 assert np.abs(got[form][k][b] - want[k]).max() <= 3e-2 * std, (b, k)
                 assert np.abs(got[form][k][b] - got[1][k][b]).max() <= 1e-2 * std, (b, k)
+
+
+@pytest.mark.parametrize("q_heads,kv_heads,head_dim,dtype", [(8, 2, 128, si.WEIGHT_BF16), (6, 3, 64, si.WEIGHT_BF16), (4, 4, 32, si.WEIGHT_FP32)])
+@pytest.mark.parametrize("lens", [[257], [700, 3, 16, 129, 250], [15, 16, 17, 512, 513], [300 + 25 * i for i in range(16)], [4200, 100]])
+def test_pieces_are_cut_where_the_equal_ranges_are(lens, q_heads, kv_heads, head_dim, dtype):
+    """A workgroup to each piece and the equal ranges of the whole batch (which setting "wgs" to its default keeps) add the same partial sums in
+    the same order: the same bits, whichever form a batch's size takes.  One row and ragged ones, pairs that start anywhere in a range, pieces of one
+    page to 16, and contexts so long that the pieces are not shortened (4,200 tokens)."""
+    import ctypes as C
+    import torch
+    from paper_2506_24119_amd import binding as sb
+    g = si.ModelGeometry("pieces", 2, 256, q_heads, kv_heads, head_dim, 256, 512, 1e6, qk_norm=True, weight_dtype=dtype)
+    w = sb.weights_to_device(si.make_weights(g, seed=22))
+    rng = np.random.Generator(np.random.PCG64(sum(lens)))
+    B, blocks = len(lens), max(lens) // 16 + 2
+    n_pages = sum(n // 16 + 2 for n in lens)
+    rule = sb.load_library()["_ZN6spiral16decode_in_piecesEiiii"]
+    rule.restype, rule.argtypes = C.c_bool, [C.c_int] * 4
+    pages = [(n + 1 + 15) // 16 for n in lens]
+    per = min(16, max((sum(pages) * kv_heads + 767) // 768, (max(pages) + 15) // 16))
+    assert rule(sum(pages) * kv_heads, per, B * kv_heads, 768)
+    seqs = [rng.integers(0, g.vocab, n).astype(np.int32) for n in lens]
+    tok = torch.from_numpy(rng.integers(0, g.vocab, B).astype(np.int32)).cuda()
+    ids, got = np.arange(B, dtype=np.int32), []
+    for tune in (None, "wgs=768"):
+        sess = sb.Session(g, w, n_pages, B, blocks, sum(lens), max(lens) + 4, page_order=si.make_page_order(n_pages, 3), tune=tune)
+        sess.prefill(ids, seqs)
+        sb.spiral_profile_begin(sess.model, sb.KERNEL_CLASSES.index("attn_combine"), 8)
+        got.append(sess.decode_step(ids, tok, sess.new_logits(B)).cpu().numpy())
+        assert sb.spiral_profile_end(sess.model)[1] == g.n_layers                # partial results in both
+        sess.close()
+    assert np.isfinite(got[0]).all() and np.array_equal(got[0], got[1])
