@@ -671,9 +671,14 @@ hipError_t launch_gemm_tile(const GemmArgs& a, int epilogue, int bm, hipStream_t
 // vector units busy where nothing else runs: 128 rows, K = 2560 190 -> 180, 3584 244 -> 229, but 1024 101 -> 110, so from K = 2048 on; two row tiles (160 rows), for which the
 // streaming kernel reads the weights twice, 1024 / 2560 / 3584 179 / 346 / 464 -> 157 / 259 / 331.  (Logits of more than 128 rows go by gemm_tile_rows().)
 // 8,192 columns are too few tiles (160 rows 46 -> 60).
+// Only the shapes that the streaming kernel takes: its sums are in the tiles' order, those of gemm_mfma_kernel, which row-major weights of the
+// others go to, are not, and repacked weights have to give the same bits.
+bool gemm_head_tiled(int M, int N, int K, int epilogue) {
+    if (epilogue == EPI_SWIGLU || (K & 127) || (N & 15) || N < 65536 || M <= 64) return false;
+    return epilogue == EPI_SAMPLE ? M > 128 || K >= 2048 : M <= 128;
+}
 bool gemm_head_tile_takes(const GemmArgs& a, int epilogue) {
-    if (!a.head || epilogue == EPI_SWIGLU || a.splits != 1 || a.N < 65536 || a.M <= 64 || !gemm_tile_usable(a)) return false;
-    return epilogue == EPI_SAMPLE ? a.M > 128 || a.K >= 2048 : a.M <= 128;
+    return a.head && a.splits == 1 && gemm_head_tiled(a.M, a.N, a.K, epilogue) && gemm_tile_usable(a);
 }
 template <bool SAMPLE, bool NT>
 static hipError_t launch_head_tile_nt(const GemmArgs& a, hipStream_t s) {

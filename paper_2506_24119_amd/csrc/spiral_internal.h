@@ -157,6 +157,7 @@ bool gemm_tile_qkv_fits(int N, int K, const QkvPostArgs& qa);                   
 bool gemm_tile_qkv_fills(int M, int N);                                                    // for K % 128 == 64
 float gemm_tile_qkv_us(int M, int N, int K);
 hipError_t launch_gemm_tile_qkv(const GemmArgs& a, const QkvPostArgs& qa, hipStream_t s);  // q/k/v projection + qkv_post in one kernel
+bool gemm_head_tiled(int M, int N, int K, int epilogue);
 bool gemm_head_tile_takes(const GemmArgs& a, int epilogue);                                // the LM head of a decode step
 hipError_t launch_gemm_head_tile(const GemmArgs& a, int epilogue, hipStream_t s);
 hipError_t launch_gemm_stream(const GemmArgs& a, int epilogue, int bn, hipStream_t s);   // K % 128 == 0, N % 16 == 0

@@ -43,3 +43,24 @@ def test_forms_of_the_head_agree(d, vocab, rows):
     assert np.array_equal(fused, stored) and len(set(fused)) > rows // 8
     logits, greedy, fused = _step(g, w, rows, True, 0.0)
     assert np.array_equal(greedy, logits.argmax(1)) and np.array_equal(fused, greedy)
+
+
+@pytest.mark.parametrize("d,vocab", [(576, 65536), (640, 65540), (96, 70004)])
+@pytest.mark.parametrize("rows", [64, 65, 100, 128, 129])
+def test_large_heads_of_other_widths_agree(d, vocab, rows):
+    """d_model not a multiple of 128, or a vocabulary not one of 16: neither the streaming kernel nor tiles, with either weights."""
+    import torch
+    from paper_2506_24119_amd import binding as sb
+    g = si.ModelGeometry("head", 1, d, 4, 2, 64, 256, vocab, 1e6, qk_norm=True)
+    w = si.make_weights_torch(g, 5, "cuda:0")
+    ids = np.arange(rows, dtype=np.int32)
+    rng = np.random.Generator(np.random.PCG64(rows))
+    seqs = [rng.integers(0, vocab, 1 + b % 5).astype(np.int32) for b in range(rows)]
+    tok = torch.from_numpy(rng.integers(0, vocab, rows).astype(np.int32)).cuda()
+    got = []
+    for repack in (True, False):
+        sess = sb.Session(g, w, rows, rows, 1, 5 * rows, 16, repack=repack)
+        got.append([sess.prefill(ids, seqs).cpu().numpy(), sess.decode_step(ids, tok, sess.new_logits(rows)).cpu().numpy()])
+        sess.close()
+    for a, b in zip(*got):
+        assert np.isfinite(a).all() and np.array_equal(a, b)

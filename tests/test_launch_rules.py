@@ -55,3 +55,14 @@ def test_both_forms_of_the_head_add_in_the_same_order(lib):
             for vocab in (1008, 8192, 13120, 65520, 65536, 151936):
                 assert takes(rows, vocab, d, STORE, True) == takes(rows, vocab, d, SAMPLE, True), (rows, d, vocab)
     assert takes(128, 8192, 2560, SAMPLE, True) and not takes(33, 151936, 1024, SAMPLE, True)
+
+
+def test_tiles_of_the_head_keep_to_the_streaming_kernels_shapes(lib):
+    """Repacked heads may be tiled only where row-major ones go to the streaming kernel, which adds in the tiles' order: d_model a multiple of
+    128 and a vocabulary of 16.  (Others go to a kernel that splits d_model over four waves.)"""
+    tiled = rule(lib, "_ZN6spiral15gemm_head_tiledEiiii", C.c_bool, *[C.c_int] * 4)
+    STORE, SAMPLE = 0, 2
+    for rows in (64, 65, 100, 128, 129):
+        for vocab, d in ((65536, 1088), (65540, 2560), (151944, 1024), (65536, 64), (151936, 2080)):
+            assert not tiled(rows, vocab, d, STORE) and not tiled(rows, vocab, d, SAMPLE), (rows, vocab, d)
+        assert tiled(rows, 151936, 2560, STORE) == (65 <= rows <= 128) and tiled(rows, 151936, 2560, SAMPLE) == (rows >= 65)
