@@ -548,16 +548,16 @@ __global__ __launch_bounds__(kSampleThreads) void sample_kernel(const float* log
     const float* lr = logits + (size_t)row * V;
     const float* nr = MODE == 2 ? noise + (size_t)row * V : nullptr;
     const uint64_t key = keys.key[row];
-    const int lo = blockIdx.x * per_slice, hi = min(V, lo + per_slice);
+    const int lo = blockIdx.x * per_slice, hi = (int)min((uint32_t)V, (uint32_t)lo + per_slice);
     float bv = -INFINITY;
     int bi = 0x7FFFFFFF;
     float bound = -INFINITY, pass = -INFINITY;   // a score of the row that an entry has to beat, and that less its slack
     if (SCREEN) {
         if (tid == 0) s_best = ordered_bits(__float_as_int(-INFINITY));
         __syncthreads();
-        const int v = lo + tid;                  // one entry a thread in full: a first bound (they are visited again below)
-        if (v < hi) {
-            const float sc = lr[v] / temperature + gumbel_noise(key, v);
+        const uint32_t v = lo + tid;             // one entry a thread in full: a first bound (they are visited again below)
+        if (v < (uint32_t)hi) {
+            const float sc = lr[v] / temperature + gumbel_noise(key, (int)v);
             if (sc > -INFINITY) atomicMax(&s_best, ordered_bits(__float_as_int(sc)));
         }
         __syncthreads();
@@ -572,23 +572,24 @@ __global__ __launch_bounds__(kSampleThreads) void sample_kernel(const float* log
         }
     };
     // The next step's loads are in flight while this one's entries are visited (past the end they re-read the last entries: a branch
-    // around a load makes every load wait).
+    // around a load makes every load wait).  Unsigned, as the indices run ahead of a row that may have 2^31 - 1 entries.
     vec l[LOADS], l_next[LOADS], nz[LOADS], nz_next[LOADS];
-    auto load = [&](int base) {
+    const uint32_t end = hi;
+    auto load = [&](uint32_t base) {
 #pragma unroll
         for (int u = 0; u < LOADS; ++u) {
-            const int v = min(base + u * NT * VEC, hi - VEC);
+            const uint32_t v = min(base + u * NT * VEC, end - VEC);
             l_next[u] = *(const vec*)(lr + v);
             if (MODE == 2) nz_next[u] = *(const vec*)(nr + v);
         }
     };
-    int base = lo + tid * VEC;
-    if (base < hi) load(base);
-    for (; base < hi; base += STEP) {
+    uint32_t base = lo + tid * VEC;
+    if (base < end) load(base);
+    for (; base < end; base += STEP) {
 #pragma unroll
         for (int u = 0; u < LOADS; ++u) { l[u] = l_next[u]; if (MODE == 2) nz[u] = nz_next[u]; }
         load(base + STEP);
-        const uint64_t at = noise_at(key, base);
+        const uint64_t at = noise_at(key, (int)base);
         bool in[LOADS * VEC], any = !SCREEN;
         if (SCREEN) {
             bound = __int_as_float(ordered_bits(*(volatile int*)&s_best));
@@ -601,11 +602,11 @@ __global__ __launch_bounds__(kSampleThreads) void sample_kernel(const float* log
         if (any)
 #pragma unroll
             for (int u = 0; u < LOADS; ++u)
-                if (base + u * NT * VEC < hi)
+                if (base + u * NT * VEC < end)
 #pragma unroll
                     for (int e = 0; e < VEC; ++e)
                         if (!SCREEN || in[u * VEC + e])
-                            visit(base + u * NT * VEC + e, at + (uint64_t)(u * NT * VEC + e) * kNoiseStep, l[u][e], MODE == 2 ? nz[u][e] : 0.f);
+                            visit((int)(base + u * NT * VEC + e), at + (uint64_t)(u * NT * VEC + e) * kNoiseStep, l[u][e], MODE == 2 ? nz[u][e] : 0.f);
     }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) {
@@ -644,9 +645,9 @@ hipError_t launch_sample(const float* logits, int B, int V, float temperature, c
         const float* lg = logits + (size_t)off * V;
         const float* nz = noise ? noise + (size_t)off * V : nullptr;
         const bool wide = (V & 3) == 0 && (((uintptr_t)lg | (uintptr_t)(mode == 2 ? nz : lg)) & 15) == 0;
-        int per = (V + slices - 1) / slices;
+        int per = (int)(((long long)V + slices - 1) / slices);
         if (wide) per = (per + 3) & ~3;
-        const dim3 g((V + per - 1) / per, m), b(kSampleThreads);
+        const dim3 g((unsigned)(((long long)V + per - 1) / per), m), b(kSampleThreads);
         if (g.x > 1) hipLaunchKernelGGL(sample_begin_kernel, dim3((m + 255) / 256), dim3(256), 0, s, out + off, m);
         auto go = [&](auto vec) {
             constexpr int VEC = decltype(vec)::value;

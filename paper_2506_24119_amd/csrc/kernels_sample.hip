@@ -47,17 +47,18 @@ __device__ __forceinline__ float key_value(uint32_t k) {
 }
 
 // f(logit, v) for v = lo + tid, lo + tid + kThreads, ... < hi, with U loads in flight per thread (issued before the
-// first use; past the end they re-read the last entry, a branch around a load would make every load wait)
+// first use; past the end they re-read the last entry, a branch around a load would make every load wait).  Indices are unsigned: they
+// run ahead of a row that may have 2^31 - 1 entries.
 template <int U, class F>
-__device__ __forceinline__ void sweep(const float* lr, int lo, int hi, int tid, F&& f) {
-    for (int base = lo + tid; base < hi; base += kThreads * U) {
+__device__ __forceinline__ void sweep(const float* lr, uint32_t lo, uint32_t hi, int tid, F&& f) {
+    for (uint32_t base = lo + tid; base < hi; base += kThreads * U) {
         float l[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) l[u] = lr[min(base + u * kThreads, hi - 1)];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int v = base + u * kThreads;
-            if (v < hi) f(l[u], v);
+            const uint32_t v = base + u * kThreads;
+            if (v < hi) f(l[u], (int)v);
         }
     }
 }
@@ -69,12 +70,12 @@ struct Sweep {
     static constexpr int U = VEC == 4 ? 3 : 8, STEP = kThreads * VEC * U;
     typedef __attribute__((ext_vector_type(VEC))) float vec;
     const float* lr;
-    int base, hi;
+    uint32_t base, hi;
     vec next[U];
-    __device__ __forceinline__ Sweep(const float* lr_, int lo, int hi_, int tid) : lr(lr_), base(lo + tid * VEC), hi(hi_) {
+    __device__ __forceinline__ Sweep(const float* lr_, uint32_t lo, uint32_t hi_, int tid) : lr(lr_), base(lo + tid * VEC), hi(hi_) {
         if (base < hi) load(base);
     }
-    __device__ __forceinline__ void load(int at) {
+    __device__ __forceinline__ void load(uint32_t at) {
 #pragma unroll
         for (int u = 0; u < U; ++u) next[u] = *(const vec*)(lr + min(at + u * kThreads * VEC, hi - VEC));
     }
@@ -91,7 +92,7 @@ struct Sweep {
             for (int u = 0; u < U; ++u)
                 if (base + u * kThreads * VEC < hi)
 #pragma unroll
-                    for (int e = 0; e < VEC; ++e) f(l[u][e], base + u * kThreads * VEC + e);
+                    for (int e = 0; e < VEC; ++e) f(l[u][e], (int)(base + u * kThreads * VEC + e));
         }
     }
 };
@@ -343,7 +344,7 @@ __global__ __launch_bounds__(kThreads) void trunc_max_kernel(const float* logits
     __shared__ float s_red[kWaves];
     const int row = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int lo = (int)blockIdx.x * per;
-    Sweep<VEC> sw(logits + (size_t)row * V, lo, min(V, lo + per), tid);
+    Sweep<VEC> sw(logits + (size_t)row * V, lo, min((uint32_t)V, (uint32_t)lo + per), tid);
     float m = -INFINITY;
     sw.run([] {}, [&](float l, int) { m = fmaxf(m, l); });
 #pragma unroll
@@ -381,7 +382,7 @@ __global__ __launch_bounds__(kThreads) void trunc_hist_kernel(const float* logit
     const int row = blockIdx.y, tid = threadIdx.x;
     const int lo = (int)blockIdx.x * per;
     const float zmax = row_lmax(lmax_part, row, gridDim.x, tid & 63) / temperature;
-    Sweep<VEC> sw(logits + (size_t)row * V, lo, min(V, lo + per), tid);
+    Sweep<VEC> sw(logits + (size_t)row * V, lo, min((uint32_t)V, (uint32_t)lo + per), tid);
     if (MASS && tid < 32) s_exp2[tid] = kExp2Tab[tid];
     for (int i = tid; i < kBins; i += kThreads) h[i] = 0;
     __syncthreads();
@@ -514,7 +515,7 @@ __global__ __launch_bounds__(kThreads) void trunc_select_kernel(const float* log
     __shared__ float s_red[kWaves];
     __shared__ int s_idx[kWaves];
     const int row = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int lo = (int)blockIdx.x * per, hi = min(V, lo + per);
+    const int lo = (int)blockIdx.x * per, hi = (int)min((uint32_t)V, (uint32_t)lo + per);
     const float lmax = row_lmax(lmax_part, row, gridDim.x, lane);
     // (loads return in order: the plan's before the first logits)
     const size_t seg = (size_t)row * gridDim.x + blockIdx.x, seg_wave = (size_t)row * gridDim.x + min(wave, (int)gridDim.x - 1);
@@ -542,8 +543,8 @@ __global__ __launch_bounds__(kThreads) void trunc_select_kernel(const float* log
     const uint64_t key64 = keys.key[row];
     float bv = -INFINITY;
     int bi = 0x7FFFFFFF;
-    if (!nr && sw.base < hi && sw.next[0][0] >= keep) {       // a first bound for the screen: one kept token a thread
-        const float sc = sw.next[0][0] / temperature + gumbel_noise(key64, sw.base);
+    if (!nr && sw.base < (uint32_t)hi && sw.next[0][0] >= keep) {       // a first bound for the screen: one kept token a thread
+        const float sc = sw.next[0][0] / temperature + gumbel_noise(key64, (int)sw.base);
         if (sc > -INFINITY) atomicMax(&s_best, ordered_bits(__float_as_int(sc)));
     }
     __syncthreads();
@@ -786,7 +787,7 @@ hipError_t launch_sample_truncated_ws(const float* logits, int B, int V, float t
     float2* part = (float2*)(ws + L.part);
     const size_t list_lds = (size_t)kCap * sizeof(uint2);
     const bool wide = (V & 3) == 0 && ((uintptr_t)logits & 15) == 0;
-    int per = (V + slices - 1) / slices;
+    int per = (int)(((long long)V + slices - 1) / slices);
     if (wide) per = (per + 3) & ~3;
     hipError_t e = hipFuncSetAttribute(wide ? (const void*)trunc_select_kernel<4> : (const void*)trunc_select_kernel<1>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)list_lds);
     if (e != hipSuccess) return e;

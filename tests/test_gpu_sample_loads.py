@@ -41,3 +41,36 @@ def test_temperatures_at_the_ends(T, scale):
         logits[1] = -logits[1].abs()                       # scores of one sign, most of them beyond the range
         a, b = _both(logits, T, 4)
         assert np.array_equal(a, b), (V, a, b)
+
+
+@pytest.mark.parametrize("V", [2 ** 31 - 1, 2 ** 31 - 4])
+def test_the_longest_rows(V):
+    """The loads of the sampler and of the truncated one run a step ahead: past the end of a row whose length is the largest that the entry
+    points take, in loads of one entry and of four.  All but the last 20,000 entries are -inf, whose noise never counts."""
+    import torch
+    from oracle import sampling as osp
+    from oracle import truncated as otr
+    from paper_2506_24119_amd import binding as sb
+    n = 20000
+    rng = np.random.Generator(np.random.PCG64(V % 1000))
+    tail = rng.standard_normal(n).astype(np.float32)
+    logits = torch.full((1, V), -float("inf"), dtype=torch.float32, device="cuda")
+    logits[0, V - n:] = torch.from_numpy(tail).cuda()
+    ids, steps = np.array([3], dtype=np.int32), np.array([8], dtype=np.int32)
+    with np.errstate(over="ignore"):
+        key = osp._mix(osp._mix(np.uint64(5) ^ osp._GOLD) + ((np.uint64(3) << np.uint64(32)) | np.uint64(8)))
+        r = (osp._mix(key + np.arange(V - n, V, dtype=np.uint64) * osp._GOLD) >> np.uint64(32)).astype(np.uint32)
+    noise = -np.log(-np.log(osp.uniform_from_bits(r), dtype=np.float32), dtype=np.float32)
+    out = torch.full((1,), -1, dtype=torch.int32, device="cuda")
+    sb.spiral_sample(logits, 1, V, 0.0, 5, ids, steps, None, out)
+    assert int(out) == V - n + int(tail.argmax())
+    sb.spiral_sample(logits, 1, V, 1.0, 5, ids, steps, None, out)
+    tok, margin = osp.sample_row(tail, 1.0, noise)
+    assert margin > 1e-5 and int(out) == V - n + tok
+    need = sb.spiral_sample_truncated_workspace_bytes(1, V)
+    work = torch.empty(need, dtype=torch.uint8, device="cuda")
+    for top_k, top_p in ((0, 0.9), (50, 1.0), (20, 0.9)):
+        out.fill_(-1)
+        sb.spiral_sample_truncated_ws(logits, 1, V, 1.0, top_k, top_p, 5, ids, steps, None, out, None, work, need)
+        tok, margin, _, slack = otr.sample_row(tail, 1.0, top_k, top_p, noise)
+        assert margin > 1e-5 and slack > 1e-6 and int(out) == V - n + tok, (top_k, top_p)
