@@ -695,16 +695,14 @@ hipError_t launch_gemm_head_tile(const GemmArgs& a, int epilogue, hipStream_t s)
     return a.M <= 128 ? launch_head_tile_nt<true, true>(a, s) : launch_head_tile_nt<true, false>(a, s);
 }
 
-// The scoring epilogue's exponentials run under another workgroup's products with tiles of 128 rows: 151,936 columns, K = 2560, 300 / 700 /
-// 1,000 / 3,000 rows 276 / 510 / 681 / 2012 us against 352 / 518 / 705 / 2022 on 256, K = 1024 113 / 216 / 289 / 839 against 167 / 243 / 340 / 939.
-// Only small vocabularies on narrow models stay on the tall tile (30,004 columns, K = 256, 700 rows 29 us; 19 on 128, 37 with
-// operands staged through registers), where nothing is spent and both heights stay covered.
-int gemm_tile_score_height(int M, int N, int K) { return M >= 512 && N <= 32768 && K <= 256 ? 256 : 128; }
 // The LM head with the scoring epilogue: one (max, sum exp) pair per row and 128 columns.
+// Tiles of 128 rows: the exponentials run under another workgroup's products.  151,936 columns, K = 2560, 300 / 700 / 1,000 / 3,000
+// rows 276 / 510 / 681 / 2012 us against 352 / 518 / 705 / 2022 on 256, K = 1024 113 / 216 / 289 / 839 against 167 / 243 / 340 / 939; 30,004
+// columns, K = 256, 700 rows 19 against 29.
 hipError_t launch_gemm_tile_score(const GemmArgs& a, hipStream_t s) {
     if (!gemm_tile_usable(a) || a.splits != 1 || !a.s_part || !a.targets || !a.tgt_logit || a.s_tiles != (a.N + 127) / 128) return hipErrorInvalidValue;
     const QkvPostArgs none = {};
-    return launch_tile<3>(a, none, gemm_tile_score_height(a.M, a.N, a.K), s);
+    return launch_tile_bm<3, 128>(a, none, s);
 }
 
 // The q/k/v projection with the work of qkv_post_kernel in its epilogue (qa.qkv and qa.n_part are not used).

@@ -152,7 +152,6 @@ float gemm_tile_us(int M, int N, int K, int splits, int cols, int bm);          
 float gemm_stream_us(int M, int N, int K, int splits, int bn);
 int gemm_tile_height(int M, int N, int K, int splits, int cols, int bn);                   // the rule of gemm_tile_rows
 float gemm_wide_shape(int M, int N, int K, int most, int& bn, int& splits);                // K splits above 128 rows
-int gemm_tile_score_height(int M, int N, int K);                                           // tile height of the scoring LM head
 bool gemm_tile_qkv_fits(int N, int K, const QkvPostArgs& qa);                              // head_dim 128, whole heads per tile
 bool gemm_tile_qkv_fills(int M, int N);                                                    // for K % 128 == 64
 float gemm_tile_qkv_us(int M, int N, int K);

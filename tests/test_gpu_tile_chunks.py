@@ -1,6 +1,8 @@
 """Tiled projections over one to eight chunks of 64 k, around the number of LDS slots that their loads run ahead by, on both tile heights,
-against the float64 oracle: the scoring LM head, whose logits are seen through log-probabilities (tolerance twice the logit bar of 3e-2 x
-per-row logit std, as in the other scoring tests), and a single chunk in a prefill (the logit bar)."""
+against the float64 oracle: the scoring LM head (128 rows), whose logits are seen through log-probabilities (tolerance twice the logit bar of
+3e-2 x per-row logit std, as in the other scoring tests), and gate/up in a prefill (256 rows; the logit bar)."""
+import ctypes as C
+
 import numpy as np
 import pytest
 
@@ -11,7 +13,7 @@ from paper_2506_24119_amd import inputs as si
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("rows", [1, 130, 600])                 # 600: the tall tile up to K = 256
+@pytest.mark.parametrize("rows", [1, 130, 600])
 @pytest.mark.parametrize("d", [128, 256, 384, 512])
 def test_few_chunks_of_k(d, rows):
     import torch
@@ -40,21 +42,29 @@ def test_few_chunks_of_k(d, rows):
         off += len(s)
 
 
-def test_a_single_chunk_of_k():
-    """d = 64 and rows enough that the tall tiles of gate/up fill the chip, which is where such widths leave the general kernel."""
-    import ctypes as C
+def _tall_gate_up(d, ffn, n_seqs):
+    """Rows enough that the tall tiles of gate/up fill the chip, which is where a d that is no multiple of 128 leaves the general kernel."""
     from paper_2506_24119_amd import binding as sb
     rule = sb.load_library()["_ZN6spiral16gemm_tile_heightEiiiiii"]
     rule.restype, rule.argtypes = C.c_int, [C.c_int] * 6
-    g = si.ModelGeometry("one chunk", 2, 64, 2, 1, 64, 2048, 500, 1e6, qk_norm=True)
+    g = si.ModelGeometry("chunks", 2, d, 2, 1, 64, ffn, 500, 1e6, qk_norm=True)
     host = si.make_weights(g, seed=3)
-    seqs = si.make_prompts(g.vocab, 44, 74, 78, seed=4)
+    seqs = si.make_prompts(g.vocab, n_seqs, 74, 78, seed=4)
     rows = sum(len(s) for s in seqs)
-    assert rule(rows, g.ffn_dim, 64, 1, 128, 128) == 256 and rows % 256
-    ids = np.arange(44, dtype=np.int32)
-    sess = sb.Session(g, sb.weights_to_device(host), 44 * 8, 44, 8, rows, 128, page_order=si.make_page_order(44 * 8, 4))
+    assert rule(rows, g.ffn_dim, d, 1, 128, 128) == 256 and rows % 256
+    ids = np.arange(n_seqs, dtype=np.int32)
+    sess = sb.Session(g, sb.weights_to_device(host), n_seqs * 8, n_seqs, 8, rows, 128, page_order=si.make_page_order(n_seqs * 8, 4))
     got = sess.prefill(ids, seqs).cpu().numpy()
     sess.close()
-    for b in (0, 21, 43):
+    for b in (0, n_seqs // 2 - 1, n_seqs - 1):
         want = od.forward_full(g, host, seqs[b], logits_at=np.array([len(seqs[b]) - 1]))[0]
-        assert np.abs(got[b] - want).max() <= 3e-2 * want.std(), b
+        assert np.abs(got[b] - want).max() <= 3e-2 * want.std(), (d, b)
+
+
+def test_a_single_chunk_of_k():
+    _tall_gate_up(64, 2048, 44)
+
+
+@pytest.mark.parametrize("d,n_seqs", [(128, 12), (192, 15), (256, 12), (320, 15), (384, 12), (512, 12)])
+def test_few_chunks_on_the_tall_tile(d, n_seqs):
+    _tall_gate_up(d, 6144, n_seqs)
