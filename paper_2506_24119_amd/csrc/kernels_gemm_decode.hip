@@ -39,8 +39,8 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void* p) {
 
 // M32: batch tiles of 32 rows; NT: 32-row weight tiles of a workgroup; P: k steps of 16 whose operands a wave holds or waits for;
 // WAVES: waves per SIMD that the registers are bounded for.  FRAG: weights in fragment order (already halves), else rows as given.
-template <int M32, int NT, int EPI, bool FRAG, int P>
-__device__ __forceinline__ void decode_body(const GemmArgs& g) {
+template <int M32, int NT, int EPI, bool FRAG, int P, int WAVES>
+__global__ __launch_bounds__(256, WAVES) void gemm_decode_kernel(GemmArgs g) {
     constexpr int TROW = 144;                        // bytes of a staged row: 32 floats + 16 pad
     constexpr int TILE = 32 * TROW;
     constexpr int UNITS = M32 * NT;                  // 32 x 32 tiles of the product
@@ -241,21 +241,10 @@ __device__ __forceinline__ void decode_body(const GemmArgs& g) {
     }
 }
 
-template <int M32, int NT, int EPI, bool FRAG, int P, int WAVES>
-__global__ __launch_bounds__(256, WAVES) void gemm_decode_kernel(GemmArgs g) { decode_body<M32, NT, EPI, FRAG, P>(g); }
-
-// the winners of a small head of 33 to 128 rows
-template <int M32, int NT, int P, int WAVES>
-__global__ __launch_bounds__(256, WAVES) void head_winners_kernel(GemmArgs g) { decode_body<M32, NT, EPI_SAMPLE, true, P>(g); }
-
 template <int M32, int NT, int EPI, int P, int WAVES>
 static hipError_t launch_one(const GemmArgs& a, hipStream_t s) {
     const int tiles = EPI == EPI_SWIGLU ? (a.N + 15) / 16 : (a.N + 31) / 32, wgs = (tiles + NT - 1) / NT;
     if (EPI == EPI_SAMPLE && (!a.wf || !a.s_part || a.splits != 1 || a.s_tiles != wgs)) return hipErrorInvalidValue;
-    if constexpr (EPI == EPI_SAMPLE && M32 > 1) {
-        hipLaunchKernelGGL((head_winners_kernel<M32, NT, P, WAVES>), dim3(wgs, a.splits), dim3(256), 0, s, a);
-        return hipGetLastError();
-    } else
     if (a.wf) hipLaunchKernelGGL((gemm_decode_kernel<M32, NT, EPI, true, P, WAVES>), dim3(wgs, a.splits), dim3(256), 0, s, a);
     else hipLaunchKernelGGL((gemm_decode_kernel<M32, NT, EPI, EPI == EPI_SAMPLE, P, WAVES>), dim3(wgs, a.splits), dim3(256), 0, s, a);
     return hipGetLastError();

@@ -54,17 +54,21 @@ def test_prefill_attention_fits_two_waves_per_simd(tmp_path):
 
 
 def test_tiled_projections_keep_their_accumulators_in_registers(tmp_path):
-    """One wave per SIMD has 512 registers, a 256-row tile's accumulators take half of them; nothing spills."""
-    tile = {k: v for k, v in _resources(tmp_path, "kernels_gemm_tile.hip").items() if "gemm_tile_kernel" in k}
-    assert len(tile) == 6, sorted(tile)                         # plain and SwiGLU of both heights, the fused q/k/v and the scoring head of 128 rows
+    """One wave per SIMD has 512 registers, a 256-row tile's accumulators take half of them.  Tiles of 128 rows share a compute unit by two,
+    which holds only up to 256.  Nothing spills.  Every kernel of the file is one of these, whatever it is called."""
+    tile = _resources(tmp_path, "kernels_gemm_tile.hip")
+    assert len([k for k in tile if "gemm_tile_kernel" in k]) == 6, sorted(tile)      # plain and SwiGLU of both heights, the fused q/k/v and the scoring head
+    assert len([k for k in tile if "head_tile_kernel" in k]) == 3 and len(tile) == 9, sorted(tile)      # logits; winners of one row tile and of more
     for name, (vgprs, spills) in tile.items():
-        assert vgprs <= 512 and spills == 0, (name, vgprs, spills)
+        tall = re.search(r"gemm_tile_kernelILi\d+ELi256E", name)
+        assert vgprs <= (512 if tall else 256) and spills == 0, (name, vgprs, spills)
 
 
 def test_projections_of_few_rows_keep_to_the_waves_they_are_built_for(tmp_path):
     """gemm_decode_kernel is built for one or two waves per SIMD (its last parameter): 512 or 256 registers, nothing spilled."""
-    decode = {k: v for k, v in _resources(tmp_path, "kernels_gemm_decode.hip").items() if "gemm_decode_kernel" in k}
-    assert len(decode) == 49, sorted(decode)                    # 4 row tiles x 3 weight tiles x 2 epilogues x 2 weight orders, and the sampler's
+    decode = _resources(tmp_path, "kernels_gemm_decode.hip")
+    assert all("gemm_decode_kernel" in k for k in decode) and len(decode) == 52, sorted(decode)
+    # 4 row tiles x 3 weight tiles x 2 epilogues x 2 weight orders, and the sampler's 4 row tiles
     for name, (vgprs, spills) in decode.items():
         waves = int(re.search(r"Li(\d+)EEEvNS", name).group(1))
         assert vgprs <= 512 // waves and spills == 0, (name, vgprs, spills)
