@@ -1,5 +1,5 @@
 """The LM head of a decode step by rows and vocabulary: gemm_decode_kernel (at most 32 rows, or a small head up to 128), the streaming
-kernel, tiles of 128 rows (from 65 rows and 65,536 columns on).  Repacked weights give the bits of row-major ones, whose head is never
+kernel, tiles of 128 rows (from 65 rows and 65,536 columns on; the sampler's winners of up to 128 rows only from a d_model of 2,048 on).  Repacked weights give the bits of row-major ones, whose head is never
 tiled, and the fused step's tokens are those of the sampler on the stored logits."""
 import numpy as np
 import pytest
@@ -43,6 +43,22 @@ def test_forms_of_the_head_agree(d, vocab, rows):
     assert np.array_equal(fused, stored) and len(set(fused)) > rows // 8
     logits, greedy, fused = _step(g, w, rows, True, 0.0)
     assert np.array_equal(greedy, logits.argmax(1)) and np.array_equal(fused, greedy)
+
+
+@pytest.mark.parametrize("d,vocab,rows", [(1024, 65536, 65), (1920, 65552, 128)])
+def test_tiled_logits_and_streamed_winners_agree(d, vocab, rows):
+    """Up to 128 rows and d_model below 2,048 the logits come from tiles, the sampler's winners from the streaming kernel."""
+    import ctypes as C
+    from paper_2506_24119_amd import binding as sb
+    tiled = sb.load_library()["_ZN6spiral15gemm_head_tiledEiiii"]
+    tiled.restype, tiled.argtypes = C.c_bool, [C.c_int] * 4
+    assert tiled(rows, vocab, d, 0) and not tiled(rows, vocab, d, 2)
+    g = si.ModelGeometry("head", 1, d, 4, 2, 64, 256, vocab, 1e6, qk_norm=True)
+    w = si.make_weights_torch(g, 5, "cuda:0")
+    for T in (1.0, 0.0):
+        logits, stored, fused = _step(g, w, rows, True, T)
+        assert np.array_equal(fused, stored) and len(set(fused)) > rows // 8
+    assert np.array_equal(fused, logits.argmax(1))
 
 
 @pytest.mark.parametrize("d,vocab", [(576, 65536), (640, 65540), (96, 70004)])

@@ -47,14 +47,22 @@ def test_scoring_pairs_of_narrow_head_models_fit(lib):
 
 def test_both_forms_of_the_head_add_in_the_same_order(lib):
     """A step with the sampler inside draws the tokens of the sampler on that step's logits, bit for bit: the LM head of either comes
-    from gemm_decode_kernel, whose order of sums is its own, or of neither."""
+    from gemm_decode_kernel, whose order of sums is its own, or of neither.  The rule may not look at the epilogue; that the other kernels (of
+    which the two forms may take different ones) add in one order is seen on the GPU.  Its lines: 32 rows, for small heads 128; those have at most
+    2^25 weights and eight columns to a k."""
     takes = rule(lib, "_ZN6spiral17gemm_decode_takesEiiiib", C.c_bool, *[C.c_int] * 4, C.c_bool)
     STORE, SAMPLE = 0, 2
     for rows in (1, 32, 33, 64, 65, 96, 97, 128, 129, 500):
         for d in (128, 640, 1024, 2560, 3584):
             for vocab in (1008, 8192, 13120, 65520, 65536, 151936):
                 assert takes(rows, vocab, d, STORE, True) == takes(rows, vocab, d, SAMPLE, True), (rows, d, vocab)
-    assert takes(128, 8192, 2560, SAMPLE, True) and not takes(33, 151936, 1024, SAMPLE, True)
+    for epilogue in (STORE, SAMPLE):
+        head = lambda rows, vocab, d: takes(rows, vocab, d, epilogue, True)
+        assert head(32, 151936, 1024) and not head(33, 151936, 1024) and not head(128, 151936, 2560)
+        assert head(128, 8192, 2560) and not head(129, 8192, 2560) and not head(129, 1008, 128)
+        assert head(128, 8192, 1024) and not head(33, 8208, 1024)                # eight columns to a k
+        assert head(128, 16384, 2048) and not head(33, 16400, 2048) and head(128, 13104, 2560) and not head(33, 13120, 2560)      # 2^25 weights
+        assert not head(32, 8192, 1088) and not head(32, 8196, 1024)             # widths that it does not take
 
 
 def test_tiles_of_the_head_keep_to_the_streaming_kernels_shapes(lib):
