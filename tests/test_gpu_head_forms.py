@@ -31,8 +31,9 @@ def _step(g, w, rows, repack, T):
 
 
 @pytest.mark.parametrize("d,vocab,rows", [
-    (128, 1008, 33), (128, 1008, 128), (2560, 8192, 65), (2560, 13120, 128), (128, 65520, 65),         # small heads: up to 2^25 weights
-    (640, 65536, 64), (640, 65536, 65), (640, 65552, 128), (640, 65536, 129),                          # more: the streaming kernel, then tiles
+    (128, 1008, 33), (128, 1008, 128), (2560, 8192, 65), (2560, 13104, 96),                            # small heads: up to 2^25 weights, eight columns to a k
+    (2560, 13120, 128), (128, 65520, 65), (640, 65536, 64),                                            # more weights, more columns: the streaming kernel
+    (640, 65536, 65), (640, 65552, 128), (640, 65536, 129),                                            # tiles of the logits, up to 128 rows; winners streamed up to there
     (2048, 65552, 65), (2048, 65536, 100), (128, 70000, 257)])                                         # tiles with winners, one and three rows of them
 def test_forms_of_the_head_agree(d, vocab, rows):
     g = si.ModelGeometry("head", 1, d, 4, 2, 64, 256, vocab, 1e6, qk_norm=True)
