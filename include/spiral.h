@@ -109,14 +109,16 @@ void spiral_model_free(spiral_model* m);
  * spiral_model_repack_bytes(m) bytes (0: this geometry cannot be repacked), 256-byte aligned, which
  * must stay valid as long as the model; the original weights must stay valid too (embedding rows,
  * norms and biases are read from them).  The copies are enqueued on `stream`; calls that follow on the
- * same stream use them.  Same results bit for bit.  Errors: NOT_LOADED, SHAPE, INVALID_ARG, HIP. */
+ * same stream use them.  Same results bit for bit, but for prefills of at least 512 rows (an LM head of as many sequences) whose d_model,
+ * Hq*hd or ffn_dim is no multiple of 128, or vocab none of 16: there the fp32 sums may be added in another order.
+ * Errors: NOT_LOADED, SHAPE, INVALID_ARG, HIP. */
 size_t spiral_model_repack_bytes(const spiral_model* m);
 int spiral_model_repack(spiral_model* m, void* dev_buffer, size_t bytes, void* stream);
 
 /* Measurement / test hook: overrides the launch decomposition the library would choose from the geometry.
  * spec is a comma-separated list of key=value items (unknown keys are ignored): "qkv=R:S", "o=R:S", "down=R:S"
  * (weight rows per workgroup : K splits of that projection; above 128 rows as many splits as the workspace holds,
- * one where S is not given), "gu=R", "lm=R" (from 33 sequences on), "chunk=P" (least pages per decode-attention workgroup, from 16 on
+ * one where S is not given), "gu=R", "lm=R" (from 33 sequences on, small heads, see below, from 129 on), "chunk=P" (least pages per decode-attention workgroup, from 16 on
  * also of a prefill's last rows), "wgs=N" (workgroups of the decode attention; with either of the two set, no (row, kv head) pair gets
  * a workgroup to itself), "frag=0|1" (use the repacked weights),
  * "fuse_qkv=0|1" (large row counts: q/k/v post-processing inside the projection kernel or as its own kernel),
@@ -125,7 +127,8 @@ int spiral_model_repack(spiral_model* m, void* dev_buffer, size_t bytes, void* s
  * "fail_after=N" (error-path tests: the N-th
  * kernel launch of the layer stack from now on is not made and reports a launch failure).  R is taken to what the kernel of the call
  * has: calls of at most 128 rows 32, 64 or 96 (more: 96); large projections of such calls (gate/up of more than 8,192 columns,
- * others of more than 64 MB, the LM head from 33 sequences on) 64 or 128, gate/up also 96 and 160; calls of more rows use it only where
+ * others of more than 64 MB, the LM head from 33 sequences on unless it is small: at most 2^25 weights and 8 d_model columns) 64 or 128 (the
+ * LM head's 64 also keeps it off the tiles that it has above 64 sequences), gate/up also 96 and 160; calls of more rows use it only where
  * they stream.  Results stay within
  * the parity tolerance for every setting; the defaults are the measured best.  "frag" must be set before
  * spiral_model_repack, the others at any time between calls.  Errors: NOT_LOADED, INVALID_ARG. */
@@ -181,7 +184,8 @@ int    spiral_kv_free_pages(const spiral_kv_pool* p);
  *  - above 128 rows the K splits of the projections, and so the order of their fp32 sums, follow from the number of rows;
  *  - above 128 rows and from four rows to a sequence on (16-bit weights, projections not tuned, see "trim" above) the last layer
  *    computes its queries, attention, O and MLP for the sequences' last tokens only, on the decode step's kernels;
- *  - the LM head adds in another order from 33 sequences on, one of at most 2^25 weights and 8 d_model columns from 129 on.
+ *  - the LM head adds in another order from 33 sequences on, one of at most 2^25 weights and 8 d_model columns from 129 on (where d_model is
+ *    no multiple of 128 or vocab none of 16: repacked ones from 512 on).
  * In a decode step the cut of the attention follows from all contexts of the call; the rules on K splits and on the LM head hold
  * there as well; 32-bit weights have a form for few sequences (up to 32, fewer where d_model is large).
  * Logits then differ by the rounding of half-precision activations.  Largest difference seen, in standard deviations of the

@@ -13,8 +13,9 @@
 // Decode (attn_stream_kernel): the ordered stream of all (row, kv head, page) units of the batch is cut into equal
 // ranges, one per workgroup; inside a range the four waves take pages round-robin, each with a private online
 // softmax (running max m, sum l, unnormalised O), merged through LDS at the end of every (row, kv head) segment;
-// a second small kernel merges the partial (m, l, O) of a pair that spans workgroups.  Short and even batches give every
-// (row, kv head) pair a workgroup instead, the last rows of a prefill pieces of a fixed number of pages (DecodeForm).
+// a second small kernel merges the partial (m, l, O) of a pair that spans workgroups.  Batches whose longest pairs do not end much later than
+// the rest give every (row, kv head) pair a workgroup instead, small ones every piece of a pair; the last rows of a prefill have pieces of
+// a fixed number of pages (DecodeForm).
 // Prefill (attn_prefill_kernel): tiles of 32 positions of one head on the 32x32x16 MFMA, four a workgroup, pages in LDS.
 // Softmax is evaluated in base 2: scores are scaled by log2(e)/sqrt(hd) and v_exp_f32 is 2^x.
 #include <type_traits>
@@ -488,8 +489,9 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(AttnArgs a, Prefil
 // ---------------------------------------------------------------------------------------------
 // FORM (a parameter of the template, since the test at run time costs the stream 8 registers and with them a workgroup of three a CU:
 // 128 rows of 1,280 tokens, 7 % of a step):
-//   DECODE_PAIR: short contexts (the host's rule): a workgroup has one pair to itself and writes the output: no search, no partial
-//   results, no merging launch.  27 rows of 400 tokens, 0.6B shape: 6 us a layer less of 51.
+//   DECODE_PAIR: a workgroup has one pair to itself and writes the output: no search, no partial results, no merging launch; the longest
+//   pairs start first.  For contexts of up to 512 tokens (256 with few pairs) and, with heads of 128, thousands, wherever the estimated
+//   end, when too few workgroups are left, costs less than that (decode_in_pairs()).  27 rows of 400 tokens, 0.6B shape: 6 us a layer less of 51.
 //   DECODE_PIECES: the last rows of a prefill, and small batches: workgroup (x, y) has the y-th piece of pair x, if there is one, and
 //   writes the pair's part y: no search, and one pair only.  Small batches are cut where the equal ranges cut them (a workgroup that would have
 //   crossed from one pair to the next is two here), so that the two forms give the same bits.  A prefill's last rows (own_cut) are cut from each

@@ -274,9 +274,11 @@ static hipError_t launch_tiles(const GemmArgs& a, int nt, hipStream_t s) {
 // -> 26.2, 28.8 -> 28, 37.0 -> 37; 2,560 x 12,288 (63 MB) row-major 19.8 -> 20.9, 21.0 -> 21.9, 26.4 -> 30.8, repacked 16.1 -> 14.9,
 // 18.6 -> 16.2, 23.4 -> 24.7.
 // The LM head does up to 32 rows, a small one (2^25 weights) up to 128, with logits and with the sampler's winners alike, as both have to
-// come from the same sums: they are rounded by nothing that follows.  Up to eight columns to a k: the noise of the winners, one wave a SIMD above 64
-// rows, outweighs the rest beyond (one layer and head, sampled, streaming kernel -> this, 128 rows: 8,192 x 1024 72 -> 63, x 2560 100 -> 84,
-// x 3584 120 -> 101, 40 rows x 2560 68 -> 62, but 32,768 x 1024 76 -> 83, 65,536 x 128 60 -> 90).  Streaming kernel
+// come from the same sums: they are rounded by nothing that follows.  Its limit is the second round of workgroups: above 64 rows they have one wave
+// a SIMD, whose noise runs under nothing else, so 256 of 64 columns (16,384) are one round.  One layer and head, sampled, streaming kernel -> this, 128 rows:
+// 8,192 x 1024 72 -> 63, x 2560 100 -> 84, x 3584 120 -> 101, 40 rows x 2560 68 -> 62, but 32,768 x 1024 76 -> 83, 65,536 x 128 60 -> 90.  The line at
+// eight columns to a k is short of that: heads of 10,240 to 16,384 columns at K = 1024, 8,192 and 16,384 at 512, which stay on the streaming kernel,
+// would gain as well (winners of 128 rows 31 -> 22 and 26 -> 19 us, logits 18 -> 13..15 and 12..13 -> 8..11; 24,576 at 1024 32 -> 40 and 20 -> 18).  Streaming kernel
 // -> this, us, 8,192 columns at 33, 64 and 128 rows: K = 1024 8.7 -> 5.2, 9.0 -> 5.6, 13.5 -> 7.9; 2560 17 -> 9.6, 19 -> 10.2, 30.5 -> 15.1; 3584 23 -> 12.4,
 // 25 -> 14.3, 41 -> 21.4.  One layer and a row-major head of 151,936, 1, 16 and 32 rows: 0.6B 119 -> 107, 129 -> 115, 136 -> 122; 4B 252 -> 229,
 // 267 -> 264, 283 -> 287; 7B 337 -> 333, 364 -> 370, 382 -> 402.

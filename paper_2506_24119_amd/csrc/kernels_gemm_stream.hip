@@ -441,8 +441,8 @@ static hipError_t launch_shape(const GemmArgs& a, int bn, hipStream_t s, bool sa
     return bn >= 128 ? launch_one<4, 4, SWIGLU, STREAM_PD>(a, s, sample) : launch_one<4, 2, SWIGLU, 3>(a, s, sample);
 }
 
-// columns of the LM head that one workgroup of the sampling epilogue covers (host code sizes s_part with it): up to 32 rows two
-// tiles of gemm_decode_kernel
+// columns of the LM head that one workgroup of the sampling epilogue covers (host code sizes s_part with it): two tiles of
+// gemm_decode_kernel wherever that takes the head, 64 where the streaming kernel is asked for narrow workgroups, else 128
 int gemm_sample_tile_cols(int M, int N, int K, int bn) { return bn < 128 || gemm_decode_takes(M, N, K, EPI_SAMPLE, true) ? 64 : 128; }
 
 hipError_t launch_gemm_stream(const GemmArgs& a, int epilogue, int bn, hipStream_t s) {

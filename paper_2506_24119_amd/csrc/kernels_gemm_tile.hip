@@ -7,17 +7,17 @@
 // compute unit twice, so that one workgroup's first loads, epilogue and barriers run under the other's products.  LDS holds
 // activations as whole 128-byte rows, their eight pieces permuted so that operand reads meet no bank twice, and weights as
 // fragment blocks (frag_block(), already in the operand type), three (two) slots of 64 k of activations and four (three) of 32 k of
-// weights.  What else was tried and measured, gate/up of the 4B shape at 15,272 rows (1412 us with operands staged through registers,
-// 256 rows, one chunk ahead): both operands straight to LDS with two slots of 64 k 1656 to 1706 us (loads one chunk ahead are too
+// weights.  What else was tried and measured, gate/up of the 4B shape at 15,272 rows (us in one session, in which the kernel that staged operands
+// through registers, 256 rows, one chunk ahead, took 1412): both operands straight to LDS with two slots of 64 k 1656 to 1706 (loads one chunk ahead are too
 // late); activations in slots of 32 k, whose loads touch half lines, 1357 (256 rows), 1375 (128); whole lines 1262 to 1290; the
 // reads of a half's second k step as a burst instead of one behind each product +2 %; those behind the barrier spread likewise +1.5 %;
 // s_setprio around the products +3 %; bands of 2048 or 4096 rows +1 and +7 %.
-// The chip's power is the limit: the matrix cores are busy 75 % of the cycles, at 1.4 GHz (62 % at 1.7 before), and with
-// all-zero operands the same launch takes 918 us (1.66 PFLOP/s against 1.20).  A loop of nothing but products with random operands makes
-// 1.70 PFLOP/s, with its operand reads from LDS 1.54.  Times of a launch, us, staged through registers -> now: gate/up 4B shape 15,272 rows
-// 1358 -> 1262, 788 rows 110 -> 97, 0.6B shape 11,206 rows 175 -> 139; O and down 4B 15,272 rows 318 -> 276 and 700 -> 643, 788 rows (3 K splits)
-// 25.9 -> 24.7 and 48 -> 46; down 0.6B 11,206 rows 76 -> 69; q/k/v with its post-processing 4B 517 -> 446, 0.6B 144 -> 108; the
-// scoring LM head, 6,028 rows 4380 -> 3870 (1.21 PFLOP/s).  Same bits throughout.
+// The chip's power is the limit.  Counters of that launch, staged through registers -> now: matrix cores busy 58 -> 64 % of the cycles, clock 1.79 -> 1.73 GHz;
+// traced with all-zero operands it takes 981 us instead of 1369 (1.55 PFLOP/s against 1.11).  A loop of nothing but products with random operands makes
+// 1.70 PFLOP/s, with its operand reads from LDS 1.54.  Times of a launch, us between events, staged through registers -> now: gate/up 4B shape 15,272 rows
+// 1399 -> 1309, 788 rows 115 -> 94, 0.6B shape 11,206 rows 184 -> 146; O and down 4B 15,272 rows 330 -> 291 and 700 -> 662, 788 rows (3 K splits)
+// 29.0 -> 28.9 and 52.6 -> 51.2 (traced with the rest of a prefill 27.8 -> 28.1 and 51.9 -> 54.3); down 0.6B 11,206 rows 83 -> 75; q/k/v with its
+// post-processing 4B 549 -> 465, 0.6B 161 -> 115; the scoring LM head, 6,028 rows 4527 -> 4160 (3780 by itself, 1.24 PFLOP/s).  Same bits throughout.
 // Workgroup ids are dealt round-robin to the 8 XCDs by the hardware; the tile order is arranged so
 // that each XCD (own L2) gets a contiguous run of tiles, ordered in bands of 1024 rows.
 // K may be split over workgroups: at 788 rows of the 4B shape 256-row tiles leave O and down 40 workgroups.
@@ -392,8 +392,8 @@ __device__ __forceinline__ void tile_body(const GemmArgs& g, const QkvPostArgs& 
                     // V element (d, token) sits at (d/32)*512 + ((token/4)*16 + d%16)*8 + ((d/16)%2)*4 + token%4: four tokens from a multiple of four on, at d
                     // and d + 16, are 16 neighbouring bytes, a lane's here (its d is 32 (lane/16) + lane%16).  Such runs start anywhere in
                     // the tile, as sequences do; the runs cut off at its ends or a sequence's go row by row.  (Two bytes a store, straight from the
-                    // accumulators, was 64 stores of 16 pieces each for 32 rows.  us a launch, that -> this: 0.6B shape, 11,206 rows 147 -> 119, the last
-                    // layer's k and v alone 84 -> 65; 4B, 788 rows 53 -> 46 and 51 -> 43, 15,272 rows 497 -> 484 and 191 -> 166.)
+                    // accumulators, was 64 stores of 16 pieces each for 32 rows.  us a launch, that -> this: 0.6B shape, 11,206 rows 140 -> 115; 4B, 788 rows 52.6 -> 46.7,
+                    // 6,028 rows 217 -> 198, 15,272 rows 480 -> 465; traced, the last layer's k and v alone: 0.6B 83 -> 63, 4B 50 -> 44.5 and 193 -> 164.)
                     const int rows = min(32, g.M - mb);
                     const int2 mine = qa.row_page[min(m, g.M - 1)];
                     const int page_before = __shfl_up(mine.x, 1, 64), run_before = __shfl_up(mine.y >> 2, 1, 64);
@@ -431,9 +431,9 @@ __device__ __forceinline__ void tile_body(const GemmArgs& g, const QkvPostArgs& 
     } else if (TEPI == 3) {
         // A lane holds 64 of the 128 columns of four rows: it folds them, column tile by column tile, and the lane halves
         // merge theirs: one (max, sum exp) pair per row and 128 columns.  The streaming kernel folds in the same order, so
-        // that repacked and row-major weights give the same bits.  The exponentials (256 a lane) are 5 % of the tile's
-        // matrix time at K = 2560.  Bound by the matrix cores: 6,028 rows x 151,936 columns x 2560 take 4.4 ms
-        // (1.09 PFLOP/s); the streaming kernel with 128-row tiles, which fetches twice the bytes per product from L2 and
+        // that repacked and row-major weights give the same bits.  The exponentials (128 a lane) are 5 % of the tile's
+        // matrix time at K = 2560.  Bound by the matrix cores' power: 6,028 rows x 151,936 columns x 2560 take 3.8 to 4.2 ms
+        // (1.24 to 1.13 PFLOP/s); the streaming kernel, which fetches twice the bytes per product from L2 and
         // reads twice the LDS per MFMA, took 6.5.
         const int c0 = n0 + wn * 128 + 4 * lh, pair = tile_n * 2 + wn;
 #pragma unroll

@@ -985,7 +985,7 @@ static int run_layers(StepCtx& c) {
     gl.wf = m->f_lm; gl.a_frag = hf_frag; gl.head = 1;
     if (lean_head) { gl.A = c.w.x; gl.norm_gain = (const float*)m->w[1]; gl.norm_eps = cfg.rms_eps; }
     if (c.sample) {
-        // the LM head keeps the best (score, index) of each 128-column tile per row; a small kernel picks the winner
+        // the LM head keeps the best (score, index) of each tile of 64 or 128 columns per row; a small kernel picks the winner
         const int cols = gemm_sample_tile_cols(c.B, cfg.vocab, d, t.bn_lm);
         gl.out = nullptr; gl.s_keys = c.w.s_keys; gl.s_part = c.w.s_part; gl.s_temperature = c.temperature;
         gl.s_tiles = (cfg.vocab + cols - 1) / cols;

@@ -34,7 +34,7 @@ struct RopeFreq { double inv_freq[64]; };   // theta^(-2j/hd), j < hd/2 <= 64
 
 // GEMM: out[m][n] = sum_k A[m][k] * W[n][k]; W is up to three row blocks stacked along n
 // (q|k|v) or, for the SwiGLU epilogue, the gate and up matrices addressed by the same row.
-// EPI_SAMPLE (LM head only): no logits are written; every workgroup reduces its 128 vocabulary columns to the
+// EPI_SAMPLE (LM head only): no logits are written; every 64 or 128 vocabulary columns (gemm_sample_tile_cols()) are reduced to the
 // best (score, index) per batch row, score = logit / T + Gumbel noise (or the logit itself when greedy).
 enum GemmEpilogue { EPI_STORE_F32 = 0, EPI_SWIGLU = 1, EPI_SAMPLE = 2 };
 

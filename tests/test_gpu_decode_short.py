@@ -1,4 +1,5 @@
-"""Decode steps on short contexts: a workgroup to a (row, kv head) pair up to 16, 32 or 96 pages, against the balanced stream (forced by
+"""Decode steps on short contexts: a workgroup to a (row, kv head) pair up to 16, 32 or 96 pages (heads narrower than 128; those of 128
+go by an estimate beyond 32 pages, see the tests of the rows' order), against the balanced stream (forced by
 spiral_model_tune "chunk=") on either side of the rule, and the fp32 step of a few rows whose projections do the norms and the
 residual's sums, against the oracle and at the edges of its rows."""
 import numpy as np
